@@ -58,13 +58,9 @@ PREC = {"fp64": 0, "fp32": 1, "bf16": 2}
 DTYPE = {"fp64": "f64", "fp32": "f64+f32", "bf16": "f64+bf16"}
 # kernel kinds of the context's launch profile
 KERNELS = {0: ("gemm_kernel<double> (FP64 MFMA contraction)", "mfma"),
-           1: ("gram_kernel (Jacobi pair Gram of a split's first round, FP64 MFMA)", "hbm"),
-           2: ("inner_kernel (Jacobi pair sweeps in LDS -- FP32 vector arithmetic far from convergence, FP64 "
-               "near it -- with FP64 MFMA Newton-Schulz steps and the FP64 MFMA identity-part rotation on the "
-               "other compute units; bound by the latency of the sweep's barrier chain; priced at the FP64 peak, "
-               "the dtype of most of its counted flops)", "alu"),
-           3: ("rotate_gram_kernel (Jacobi row rotation fused with the next round's pair Gram, FP64 MFMA; "
-               "rotate_kernel for 16-row blocks and the last identity-part rotation)", "mfma")}
+           1: ("bidiagonalisation (bd_left_kernel, bd_right_kernel: Householder reflectors of a split's block)", "hbm"),
+           2: ("divide and conquer (dc_*_kernel: merges of a split's bidiagonal SVD, FP64 MFMA products)", "mfma"),
+           3: ("wy_apply_kernel (reflectors applied to a split's kept singular vectors, FP64 MFMA)", "mfma")}
 
 
 def log(msg):
@@ -692,7 +688,7 @@ def run_sample(ite, torch, args, nsamples=1024):
 
 
 def run_split(ite, torch, args, reps=3):
-    """The Jacobi bond split of one full-size block (theta 2048 x 2048, seeded
+    """The bond split of one full-size block (theta 2048 x 2048, seeded
     Gaussian, left-to-right: A1 = U, A2 = S V^T, chi 1024, cutoff 0), timed,
     then a plain device copy of 256 MiB: the reference kernel for scaling the
     HBM traffic counters (its algorithmic traffic is 256 MiB read and 256 MiB

@@ -155,7 +155,7 @@ const char* ite_last_error(const ite_ctx* ctx);
 const char* ite_version(void);
 
 /* Launch profiler (observability, used by the benchmark): with enable = 1
- * the context brackets FP64 contraction launches (all) and Jacobi launches
+ * the context brackets FP64 contraction launches (all) and split launches
  * (a sample) with HIP events on its stream and counts their algorithmic work;
  * enabling resets the totals, enable = 0 stops recording.
  * ite_ctx_profile_read synchronises the stream and returns, for the FP64
@@ -164,11 +164,12 @@ const char* ite_version(void);
 int ite_ctx_profile(ite_ctx* ctx, int enable);
 int ite_ctx_profile_read(ite_ctx* ctx, long long* launches, double* ms, double* flops);
 /* Per-kernel launch profile since the last enable, by kind: 0 FP64
- * contraction GEMMs (every launch timed), 1 Jacobi Gram, 2 Jacobi inner
- * sweep, 3 Jacobi rotation (every 32nd launch of a kind timed).  launches: all
+ * contraction GEMMs (every launch timed); of the splits, 1 bidiagonalisation,
+ * 2 divide and conquer, 3 application of the reflectors to the kept vectors
+ * (every 32nd launch of a kind timed).  launches: all
  * launches; timed, ms_timed: the timed ones and their summed device time;
- * flops, bytes: the algorithmic work of all launches (Jacobi: of the pairs
- * and column chunks the kernels actually processed). */
+ * flops, bytes: the algorithmic work of all launches (divide and conquer:
+ * without deflation). */
 int ite_ctx_profile_kernel(ite_ctx* ctx, int kind, long long* launches, long long* timed,
                            double* ms_timed, double* flops, double* bytes);
 
@@ -404,7 +405,7 @@ int ite_evolve_grid(ite_mps* psi, const ite_mpo* H, const double* taus, int n_ta
  * end, at each site, the tensor T_j of O_j psi_j contracted with what is
  * already kept to its right, its reduced density matrix rho_j = T^T F_j T
  * (over the site index and the kept right index), and the eigenvectors of
- * rho_j's largest eigenvalues (one-sided Jacobi, FP64) as the new
+ * rho_j's largest eigenvalues (from the split's FP64 SVD) as the new
  * right-orthonormal site tensor; the kept count follows the split's rule
  * (cutoff, tie_rel) on the square roots of the eigenvalues, at most
  * min(chi_max, the bond's largest possible rank); site 1 keeps the rest
@@ -581,7 +582,8 @@ int ite_debug_env_update(ite_ctx* ctx, int dir, int Dxa, int Dya, int Dxb, int D
                          const double* Y, double* Eout);
 
 /* Truncated SVD split of theta [Dl][d1][d2][Dr] seen as an (Dl d1) x (d2 Dr)
- * matrix, by one-sided Jacobi: dir = 0 gives A1 = U, A2 = S V^T; dir = 1 gives
+ * matrix, by Householder bidiagonalisation and divide and conquer (one-sided
+ * Jacobi up to 32 x 32): dir = 0 gives A1 = U, A2 = S V^T; dir = 1 gives
  * A1 = U S, A2 = V^T.  A1 [Dl][d1][k], A2 [k][d2][Dr] (device, capacity
  * min(rows, cols, chi_max) columns).  sigma_out (host, nullable, capacity
  * min(rows, cols)) receives all singular values in descending order; *k_out

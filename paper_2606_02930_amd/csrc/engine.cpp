@@ -11,7 +11,7 @@
 //       (trapezoid): the right-hand side projected into x's basis through the
 //       mixed environments;
 //     GMRES on (1 - h s) v + h H_eff v = b from x_j x_(j+1);
-//     SVD split (one-sided Jacobi) with truncation, environment updates;
+//     SVD split with truncation, environment updates;
 //   normalise, energy <x|H|x>, psi <- x.
 #include "engine.h"
 
@@ -138,13 +138,13 @@ void prof_collect(ite_ctx* c) {
 namespace {
 
 // The context's LaunchProbe: counts launches, times every launch of an FP64
-// GEMM and every jac_period-th launch of each Jacobi kernel.
+// GEMM and every split_period-th launch of each kind of the split.
 struct CtxProbe final : LaunchProbe {
     ite_ctx* c;
     explicit CtxProbe(ite_ctx* cc) : c(cc) {}
     bool begin(int kind, hipStream_t s) override {
         const long long n = c->prof_launches[kind]++;
-        if (kind != PK_GEMM && n % c->jac_period != 0) return false;
+        if (kind != PK_GEMM && n % c->split_period != 0) return false;
         if (c->prof_kind.size() >= 4096) prof_collect(c);
         HIP_CHECK(hipEventRecord(prof_event(c), s));
         return true;
@@ -394,7 +394,7 @@ double dot(ite_ctx* c, const double* x, const double* y, size_t n) {
 }
 
 // ---------------------------------------------------------------------------
-// Truncated split by one-sided Jacobi
+// Truncated split
 // ---------------------------------------------------------------------------
 
 int truncation_rank(const std::vector<double>& s, double cutoff, int chi_max, double tie_rel) {
@@ -417,50 +417,79 @@ int truncation_rank(const std::vector<double>& s, double cutoff, int chi_max, do
     return k;
 }
 
-SplitResult split(ite_ctx* c, int dir, int Dl, int d1, int d2, int Dr, const double* theta, int chi_max,
-                  double cutoff, double tie_rel, double* A1, double* A2, std::vector<double>* sigma) {
-    const int m = Dl * d1, n = d2 * Dr;
-    const int p = dir == 0 ? m : n, q = dir == 0 ? n : m, ld = p + q;
-    double* Z = slot_t<double>(c, SL_Z, (size_t)p * ld);
-    size_t ngram = 0, nrot = 0, noff = 0;
-    jacobi_workspace(p, q, &ngram, &nrot, &noff);
-    double* gram = slot_t<double>(c, SL_GRAM, ngram);
-    double* rot = slot_t<double>(c, SL_ROT, nrot);
-    double* off = slot_t<double>(c, SL_OFF, noff);
-    double* norms = slot_t<double>(c, SL_NORM, (size_t)p + 16);
-    int* perm = slot_t<int>(c, SL_PERM, (size_t)p + 16);
-    jacobi_input(theta, m, n, dir, Z, c->stream);
-    // Householder preconditioning: the Jacobi then works on the rows of R,
-    // of which only the first min(p, q) can be non-zero
-    int pj = p;
-    if (householder_applies(p, q)) {
-        double* qws = slot_t<double>(c, SL_QR, householder_workspace(p, q, ld));
-        householder_rows(Z, p, q, ld, qws, c->stream);
-        pj = std::min(p, q);
-    }
-    double* host = pinned(c, (size_t)p + 64);
-    const double tol = 8.0 * std::sqrt((double)std::max(q, 1)) * 2.220446049250313e-16;
-    CtxProbe probe(c);
-    JacobiResult jr = jacobi_rows(Z, pj, q, ld, tol, 60, gram, rot, off, host, c->stream,
-                                  c->prof_on ? &probe : nullptr);
-    row_norms(Z, p, q, ld, norms, c->stream);
-    d2h(c, host, norms, p);
-    sync(c);
-    std::vector<int> idx(p);
+// Truncation of the singular values nv (any order): idx their order from the
+// largest down, the kept count and the discarded weight.
+static SplitResult truncate(const std::vector<double>& nv, int r, double cutoff, int chi_max, double tie_rel,
+                            std::vector<int>& idx, std::vector<double>* sigma) {
+    idx.resize(nv.size());
     std::iota(idx.begin(), idx.end(), 0);
-    std::vector<double> nv(host, host + p);
     std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return nv[a] > nv[b]; });
-    const int r = std::min(m, n);
     std::vector<double> s(r);
     for (int i = 0; i < r; ++i) s[i] = nv[idx[i]];
     SplitResult res;
     res.k = truncation_rank(s, cutoff, chi_max, tie_rel);
-    double total = 0.0, kept = 0.0;
+    double total = 0.0, dropped = 0.0;
     for (int i = 0; i < r; ++i) total += s[i] * s[i];
-    for (int i = res.k; i < r; ++i) kept += s[i] * s[i];
-    res.disc = total > 0.0 ? kept / total : 0.0;
-    res.sweeps = jr.sweeps;
+    for (int i = res.k; i < r; ++i) dropped += s[i] * s[i];
+    res.disc = total > 0.0 ? dropped / total : 0.0;
     if (sigma) *sigma = s;
+    return res;
+}
+
+// The split by bidiagonalisation and divide and conquer: the singular values
+// come to the host for the truncation, then only the kept vectors are
+// transformed back, straight into the two site tensors.
+static SplitResult split_dc(ite_ctx* c, int dir, int m, int n, const double* theta, int chi_max, double cutoff,
+                            double tie_rel, double* A1, double* A2, std::vector<double>* sigma) {
+    const bool tr = m < n;
+    const int P = std::max(m, n), N = std::min(m, n);
+    CtxProbe probe(c);
+    LaunchProbe* pr = c->prof_on ? &probe : nullptr;
+    const BdWork bd = bd_carve(slot_t<double>(c, SL_Z, bd_workspace(P, N)), P, N);
+    const DcWork dc = dc_carve(slot_t<double>(c, SL_DC, dc_workspace(N)), N, bd.d, bd.e);
+    int* perm = slot_t<int>(c, SL_PERM, (size_t)N + 16);
+    bidiagonalise(bd, theta, tr, c->stream, pr);
+    const int w = bidiagonal_svd(dc, c->stream, pr);
+    double* host = pinned(c, (size_t)N + 64);
+    d2h(c, host, dc.sg[w], N);
+    d2h(c, host + N, dc.scale, 1);
+    sync(c);
+    std::vector<double> nv(host, host + N);
+    for (double& v : nv) v *= host[N];
+    std::vector<int> idx;
+    const SplitResult res = truncate(nv, N, cutoff, chi_max, tie_rel, idx, sigma);
+    int* hp = reinterpret_cast<int*>(host);
+    std::memcpy(hp, idx.data(), sizeof(int) * res.k);
+    h2d(c, perm, hp, sizeof(int) * res.k);
+    const size_t nt = bd_vectors_tmp(P, N, res.k);
+    double* tmp = nt ? slot_t<double>(c, SL_VECS, nt) : nullptr;
+    // U to A1 [m][k], V^T to A2 [k][n]; the singular values go to the factor
+    // that is not orthonormal
+    const BdOut u{A1, 1, dir == 1}, v{A2, 0, dir == 0};
+    bd_vectors(bd, dc.UT[w], dc.VT[w], perm, res.k, dc.sg[w], dc.scale, tr ? v : u, tr ? u : v, tmp, c->stream, pr);
+    sync(c);   // the pinned staging buffer is reused by the next call
+    return res;
+}
+
+SplitResult split(ite_ctx* c, int dir, int Dl, int d1, int d2, int Dr, const double* theta, int chi_max,
+                  double cutoff, double tie_rel, double* A1, double* A2, std::vector<double>* sigma) {
+    const int m = Dl * d1, n = d2 * Dr;
+    if (std::max(m, n) > 32) return split_dc(c, dir, m, n, theta, chi_max, cutoff, tie_rel, A1, A2, sigma);
+    const int p = dir == 0 ? m : n, q = dir == 0 ? n : m, ld = p + q;
+    double* Z = slot_t<double>(c, SL_Z, (size_t)p * ld);
+    double* norms = slot_t<double>(c, SL_NORM, (size_t)p + 16);
+    int* perm = slot_t<int>(c, SL_PERM, (size_t)p + 16);
+    jacobi_input(theta, m, n, dir, Z, c->stream);
+    double* host = pinned(c, (size_t)p + 64);
+    const double tol = 8.0 * std::sqrt((double)std::max(q, 1)) * 2.220446049250313e-16;
+    CtxProbe probe(c);
+    jacobi_rows(Z, p, q, ld, tol, 60, norms + p, c->stream, c->prof_on ? &probe : nullptr);
+    row_norms(Z, p, q, ld, norms, c->stream);
+    d2h(c, host, norms, p);
+    sync(c);
+    const std::vector<double> nv(host, host + p);
+    std::vector<int> idx;
+    const SplitResult res = truncate(nv, std::min(m, n), cutoff, chi_max, tie_rel, idx, sigma);
     int* hp = reinterpret_cast<int*>(host);
     std::memcpy(hp, idx.data(), sizeof(int) * res.k);
     h2d(c, perm, hp, sizeof(int) * res.k);

@@ -1,6 +1,6 @@
 // Host-side objects of the library: context, MPO and MPS handles, and the
 // operations of one implicit step (effective-Hamiltonian product,
-// environment updates, GMRES local solve, Jacobi split, sweep).
+// environment updates, GMRES local solve, split, sweep).
 #pragma once
 
 #include "internal.h"
@@ -15,7 +15,7 @@ enum SlotId {
     SL_TPSI, SL_B, SL_TH,          // theta_psi, right-hand side, solution
     SL_V, SL_W,                    // Krylov basis, work vector
     SL_PART, SL_SMALL,             // reduction partials, small device scalars
-    SL_Z, SL_GRAM, SL_ROT, SL_OFF, SL_NORM, SL_PERM,   // Jacobi split
+    SL_Z, SL_DC, SL_VECS, SL_NORM, SL_PERM,   // split: block, divide and conquer, long vectors
     SL_QR,                         // Householder preconditioning
     SL_TMPA, SL_TMPB,              // scratch environments (overlap, energy)
     SL_LO_L, SL_LO_R, SL_LO_T, SL_LO_X,   // low-precision shadows (mixed precision)
@@ -43,9 +43,9 @@ struct ite_ctx {
     std::vector<hipEvent_t> events;
     size_t events_used = 0;
     // launch profiler (observability): FP64 GEMM launches are all timed,
-    // Jacobi launches every `jac_period`-th of a kind; see LaunchProbe
+    // split launches every `split_period`-th of a kind; see LaunchProbe
     bool prof_on = false;
-    int jac_period = 32;
+    int split_period = 32;
     std::vector<hipEvent_t> prof_events;
     size_t prof_used = 0;
     std::vector<int> prof_kind;                 // kind of each recorded event pair
@@ -168,7 +168,6 @@ void two_site(ite_ctx* c, int Dl, int d1, int Dm, int d2, int Dr, const double* 
 struct SplitResult {
     int k = 0;
     double disc = 0.0;
-    int sweeps = 0;
 };
 SplitResult split(ite_ctx* c, int dir, int Dl, int d1, int d2, int Dr, const double* theta, int chi_max,
                   double cutoff, double tie_rel, double* A1, double* A2, std::vector<double>* sigma);

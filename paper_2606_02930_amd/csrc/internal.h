@@ -229,7 +229,7 @@ constexpr int BATCH_STAGE_SC = 128;
 // Observability of kernel launches: every launch of a kind is counted, some
 // are bracketed by events (begin returns true for those), and the
 // algorithmic work actually done is added once it is known.
-enum ProbeKind { PK_GEMM = 0, PK_GRAM = 1, PK_INNER = 2, PK_ROTATE = 3, PK_COUNT = 4 };
+enum ProbeKind { PK_GEMM = 0, PK_BIDIAG = 1, PK_MERGE = 2, PK_VECTORS = 3, PK_COUNT = 4 };
 struct LaunchProbe {
     virtual ~LaunchProbe() = default;
     virtual bool begin(int kind, hipStream_t s) = 0;
@@ -237,18 +237,14 @@ struct LaunchProbe {
     virtual void work(int kind, double flops, double bytes) = 0;
 };
 
-// One-sided Jacobi on the rows of Z[p][ld] (the first q columns are the
-// matrix whose rows are orthogonalised; all ld columns are rotated).  probe
-// may be null.
-struct JacobiResult { int sweeps = 0; double last_off = 0.0; };
-JacobiResult jacobi_rows(double* Z, int p, int q, int ld, double tol, int max_sweeps,
-                         double* gram_ws, double* rot_ws, double* off_ws, double* host_off,
-                         hipStream_t s, LaunchProbe* probe = nullptr);
+// One-sided Jacobi on the p <= 32 rows of Z[p][ld] (the first q columns are the
+// matrix whose rows are orthogonalised; all ld columns are rotated).  res (two
+// doubles, device): the last measure and the number of sweeps.
+void jacobi_rows(double* Z, int p, int q, int ld, double tol, int max_sweeps, double* res, hipStream_t s,
+                 LaunchProbe* probe = nullptr);
 // Build the Jacobi work matrix [theta | I_m] (dir 0) or [theta^T | I_n]
 // (dir 1) for theta m x n; leading dimension m + n.
 void jacobi_input(const double* theta, int m, int n, int dir, double* Z, hipStream_t s);
-// Workspace sizes (doubles) of jacobi_rows for p rows of length q.
-void jacobi_workspace(int p, int q, size_t* gram, size_t* rot, size_t* off);
 // norms[i] = || Z[i][0:q] ||
 void row_norms(const double* Z, int p, int q, int ld, double* norms, hipStream_t s);
 // Gather kept rows: for t < k, r = perm[t]:
@@ -257,13 +253,48 @@ void row_norms(const double* Z, int p, int q, int ld, double* norms, hipStream_t
 void gather_split(const double* Z, int ld, const int* perm, int k, int roff, int nr,
                   double* rowdst, int coff, int nc, double* coldst, hipStream_t s);
 
-// Householder QR preconditioning of the Jacobi work matrix: Z <- Q^T Z with
-// X = Q R the QR of the first q columns (p rows, leading dimension ld); the
-// rows q..p-1 of the first part become zero when p > q.  Applies to
-// 256 <= p <= 2048 and q >= 16; ws holds householder_workspace doubles.
-bool householder_applies(int p, int q);
+// Householder QR of the first q columns of Z (p <= 2048 rows, leading dimension
+// ld): Z <- Q^T Z, the rows q..p-1 of the first part zero when p > q; ws holds
+// householder_workspace doubles.
 size_t householder_workspace(int p, int q, int ld);
 void householder_rows(double* Z, int p, int q, int ld, double* ws, hipStream_t s);
+
+// Bidiagonalisation A = Q B Z^T of a block (bidiag.hip).
+struct BdWork {
+    int P, N;                 // rows >= columns
+    double *A, *VQ, *VP, *TQ, *TP, *col, *row, *tauq, *taup;
+    double *d, *e;            // B: diagonal and superdiagonal
+};
+size_t bd_workspace(int P, int N);            // doubles
+BdWork bd_carve(double* ws, int P, int N);
+// theta is P x N, or N x P when tr (its transpose is taken).
+void bidiagonalise(const BdWork& w, const double* theta, bool tr, hipStream_t s, LaunchProbe* probe = nullptr);
+// The k singular vectors of the block from rows perm[0..k) of those of B (XQ
+// left, XP right, [N][N]); each side to out [k][len], or transposed to
+// [len][k], times the singular values sg[perm[t]] *scale when scaled.  tmp:
+// bd_vectors_tmp doubles.
+struct BdOut {
+    double* out;
+    int transposed, scaled;
+};
+size_t bd_vectors_tmp(int P, int N, int k);
+void bd_vectors(const BdWork& w, const double* XQ, const double* XP, const int* perm, int k, const double* sg,
+                const double* scale, const BdOut& q, const BdOut& p, double* tmp, hipStream_t s,
+                LaunchProbe* probe = nullptr);
+
+// SVD of the bidiagonal matrix by divide and conquer (dcsvd.hip).  Returns the
+// index i of the result: singular values sg[i] (times *scale, in no order),
+// vectors the rows of UT[i], VT[i].
+struct DcWork {
+    int n;
+    const double *d, *e;
+    double *UT[2], *VT[2], *GU, *GV;
+    double *sg[2], *dd, *zz, *zh, *x, *dc, *cr, *sr, *t0, *t1, *t2, *cs, *scale, *inv;
+    int *ord, *act, *dst, *nxt, *i0, *i1, *K;
+};
+size_t dc_workspace(int n);                   // doubles
+DcWork dc_carve(double* ws, int n, const double* d, const double* e);
+int bidiagonal_svd(const DcWork& w, hipStream_t s, LaunchProbe* probe = nullptr);
 
 // MFMA lane-layout probe (tests only).
 void mfma_probe_f64(double* out, hipStream_t s);

@@ -34,7 +34,7 @@
 // The eigenvectors of rho_j's largest eigenvalues (their square roots are
 // phi's singular values at bond j) are the rows of the new site tensor and
 // C_j = T_j V; site 1 keeps T_1 whole.  Every contraction is an FP64 GEMM or
-// a sparse MPO stage; the eigenvectors come from the one-sided Jacobi split
+// a sparse MPO stage; the eigenvectors come from the split
 // of rho_j (for a symmetric positive semi-definite matrix the right singular
 // vectors are eigenvectors and the singular values the eigenvalues).
 #include "engine.h"
