@@ -4,15 +4,18 @@
 // A (P x N, P >= N, row-major) becomes B = Q^T A Z, upper bidiagonal (Golub
 // and Kahan): in step c a reflector on the rows from c on clears column c
 // below the diagonal, one on the columns from c + 1 on clears row c right of
-// the superdiagonal.  One launch applies the left reflector (workgroups own
-// 16-column strips: the products v^T A of a strip need no other workgroup),
-// the next the right one (a wavefront owns a row).  Each launch leaves the row
-// or column that the next reflector is formed from in a contiguous buffer,
-// and every workgroup forms that reflector for itself, in the same order, so
-// that two launches a step are all the synchronisation there is.
+// the superdiagonal.  While more than 192 rows are left a step is one pass over
+// the trailing block (bd_step_kernel: both reflectors applied to a row while it
+// is in a wavefront's registers, and its share of the next step's column
+// products taken) and one sum over the workgroups (bd_sum_kernel); the rest is
+// done by one workgroup in its registers (bd_tail_kernel).  Bound by the
+// latency of a step: about 7 us with two launches at 200 to 512 columns,
+// 18 us at 2048 (38 MB read and written by it on average there), 1.3 to 1.9 us
+// inside one workgroup.  Two launches a step that each read and wrote the
+// block (columns, then rows) took 9 us and 31 us.
 //
-// The reflectors are kept as rows (VQ [N][P], VP [N][N]; zero before the
-// first entry, which is one).  bd_vectors applies them in blocks of 16 in the
+// The reflectors are kept as rows of VQ and VP (zero before the first entry,
+// which is one), both sizes padded with zeros to multiples of 16.  bd_vectors applies them in blocks of 16 in the
 // compact WY form (Schreiber and Van Loan) to the kept singular vectors: a
 // workgroup holds 16 vectors in the accumulator registers of its wavefronts
 // for all blocks, since the FP64 MFMA accumulator layout (element r of lane
@@ -28,43 +31,46 @@ namespace {
 typedef double d4_t __attribute__((ext_vector_type(4)));
 
 constexpr int WYB = 16;      // reflectors per block
+__host__ __device__ inline int pad16(int n) { return (n + 15) & ~15; }
 
 // The reflector of x[0..len) (LAPACK's convention: beta = -sign(alpha) ||x||,
 // tau = (beta - alpha) / beta, v = x / (alpha - beta) with v_0 = 1; tau = 0
-// when x_1.. = 0).  Every thread of the workgroup gets it; sh: one double per
-// wavefront.
+// when x_1.. = 0) from alpha = x_0 and sg = x_1^2 + ...
 struct Refl {
     double beta, tau, scale;
 };
 __device__ inline Refl reflector(double alpha, double sg) {
     Refl r{alpha, 0.0, 0.0};
     if (sg > 0.0) {
-        const double nrm = sqrt(alpha * alpha + sg);
-        r.beta = alpha >= 0.0 ? -nrm : nrm;
-        r.tau = (r.beta - alpha) / r.beta;
-        r.scale = 1.0 / (alpha - r.beta);
+        const double s2 = alpha * alpha + sg;
+        if (s2 > 1e-280 && s2 < 1e280) {
+            // the two reciprocals side by side instead of a square root and
+            // two divisions in a chain
+            const double y = recip_sqrt(s2), nrm = s2 * y;
+            r.beta = alpha >= 0.0 ? -nrm : nrm;
+            r.tau = 1.0 + fabs(alpha) * y;
+            r.scale = recip(alpha - r.beta);
+        } else {
+            const double nrm = sqrt(s2);
+            r.beta = alpha >= 0.0 ? -nrm : nrm;
+            r.tau = (r.beta - alpha) / r.beta;
+            r.scale = 1.0 / (alpha - r.beta);
+        }
     } else if (!(sg == 0.0)) {
         r.beta = r.tau = sg;     // NaN stays visible in the result
     }
     return r;
 }
-template <int NT>
-__device__ inline Refl block_reflector(const double* __restrict__ x, int len, double* sh) {
-    double sg = 0.0;
-    for (int i = 1 + threadIdx.x; i < len; i += NT) sg += x[i] * x[i];
-    sg = wave_sum(sg);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = sg;
-    __syncthreads();
-    sg = sh[0];
-#pragma unroll
-    for (int w = 1; w < NT / 64; ++w) sg += sh[w];
-    return reflector(x[0], sg);
-}
-
-// A <- theta (P x N), or theta^T when tr (theta then N x P); col <- column 0.
+// A <- theta (P x N), or theta^T when tr (theta then N x P).
 __global__ __launch_bounds__(256) void bd_load_kernel(const double* __restrict__ theta, int P, int N, int tr,
-                                                      double* __restrict__ A, double* __restrict__ col) {
+                                                      double* __restrict__ A, double* __restrict__ VQ,
+                                                      double* __restrict__ VP) {
     __shared__ double tile[32][33];
+    // the rows past the last reflector of either side
+    const long id = ((long)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
+    const long all = (long)gridDim.x * gridDim.y * 256;
+    for (long i = (long)N * pad16(P) + id; i < (long)pad16(N) * pad16(P); i += all) VQ[i] = 0.0;
+    for (long i = (long)(N - 1) * pad16(N) + id; i < (long)pad16(N) * pad16(N); i += all) VP[i] = 0.0;
     const int x = threadIdx.x & 31, y0 = threadIdx.x >> 5;
     const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;      // of A
     if (tr) {
@@ -75,147 +81,351 @@ __global__ __launch_bounds__(256) void bd_load_kernel(const double* __restrict__
     for (int y = y0; y < 32; y += 8) {
         const int r = r0 + y, c = c0 + x;
         if (r >= P || c >= N) continue;
-        const double v = tr ? tile[y][x] : theta[(long)r * N + c];
-        A[(long)r * N + c] = v;
-        if (c == 0) col[r] = v;
+        A[(long)r * N + c] = tr ? tile[y][x] : theta[(long)r * N + c];
     }
 }
 
-// Left reflector of step c from col[c..P), applied to the columns c + 1..;
-// row[j] <- A[c][j].  16 columns a workgroup; thread (tx, ty) keeps the rows
-// c + ty, c + ty + NT / 16, ... of its column in registers when there are at
-// most RPT of them, so A is read and written once.
-template <int NT, int RPT>
-__global__ __launch_bounds__(NT) void bd_left_kernel(double* __restrict__ A, int P, int N, int c,
-                                                     const double* __restrict__ col, double* __restrict__ row,
-                                                     double* __restrict__ VQ, double* __restrict__ tauq,
-                                                     double* __restrict__ d) {
-    constexpr int RG = NT / 16, NW = NT / 64;
-    __shared__ double sh[NW];
-    __shared__ double part[NW][16];
-    const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
-    const int len = P - c;
-    const int j = c + 1 + blockIdx.x * 16 + tx;
-    const bool in = j < N;
-    const bool keep = len <= RG * RPT;
-    double a[RPT];
-    double* Aj = A + (long)c * N + j;
-    if (keep) {
-#pragma unroll
-        for (int u = 0; u < RPT; ++u) {
-            const int i = ty + RG * u;
-            a[u] = (in && i < len) ? Aj[(long)i * N] : 0.0;
-        }
-    }
-    const double* x = col + c;
-    const Refl h = block_reflector<NT>(x, len, sh);
-    if (blockIdx.x == 0) {
-        double* v = VQ + (long)c * P;
-        for (int i = t; i < P; i += NT) v[i] = i < c ? 0.0 : (i == c ? 1.0 : col[i] * h.scale);
-        if (t == 0) {
-            tauq[c] = h.tau;
-            d[c] = h.beta;
-        }
-    }
-    double z = 0.0;
-    if (keep) {
-#pragma unroll
-        for (int u = 0; u < RPT; ++u) {
-            const int i = ty + RG * u;
-            if (i < len) z += (i == 0 ? 1.0 : x[i] * h.scale) * a[u];
-        }
-    } else if (in) {
-        for (int i = ty; i < len; i += RG) z += (i == 0 ? 1.0 : x[i] * h.scale) * Aj[(long)i * N];
-    }
-    z += __shfl_xor(z, 16, 64);
-    z += __shfl_xor(z, 32, 64);
-    if ((t & 63) < 16) part[t >> 6][tx] = z;
-    __syncthreads();
-    z = part[0][tx];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) z += part[w][tx];
-    z *= h.tau;
-    if (!in) return;
-    if (keep) {
-#pragma unroll
-        for (int u = 0; u < RPT; ++u) {
-            const int i = ty + RG * u;
-            if (i >= len) continue;
-            const double v = a[u] - (i == 0 ? 1.0 : x[i] * h.scale) * z;
-            if (i == 0) row[j] = v;
-            else Aj[(long)i * N] = v;
-        }
-    } else {
-        for (int i = ty; i < len; i += RG) {
-            const double v = Aj[(long)i * N] - (i == 0 ? 1.0 : x[i] * h.scale) * z;
-            if (i == 0) row[j] = v;
-            else Aj[(long)i * N] = v;
-        }
-    }
-}
-
-// Right reflector of step c from row[c + 1..N), applied to the rows c + 1..P;
-// col[i] <- A[i][c + 1].  A wavefront owns a row and keeps it in registers
-// when it has at most 64 CPL columns left.
+// Step c in one pass over the rows below it, a wavefront a row (in registers,
+// 64 CPL columns at most).  p[j] = sum_(i > c) A[i][c] A[i][j] (j >= c) is all
+// that is needed from the other rows: with it every workgroup has the left
+// reflector and the updated row c, and from that the right reflector.  Each row
+// takes both reflectors, and its share of the next step's p follows while it
+// is in registers: part[workgroup][j], summed by bd_sum_kernel.  start: no
+// step, only the products for the first column (c = -1).  CPL = 0: rows of any
+// length, in memory, with z and u formed again where they are used.
+constexpr int BS_NW = 8;            // rows (wavefronts) a workgroup
+constexpr int BS_CH = 512;          // columns of a row of products in LDS
 template <int CPL>
-__global__ __launch_bounds__(256) void bd_right_kernel(double* __restrict__ A, int P, int N, int c,
-                                                       double* __restrict__ col, const double* __restrict__ row,
-                                                       double* __restrict__ VP, double* __restrict__ taup,
-                                                       double* __restrict__ e) {
-    __shared__ double sh[4];
-    const int t = threadIdx.x, lane = t & 63;
-    const int c1 = c + 1, len = N - c1;
-    const int i = c1 + blockIdx.x * 4 + (t >> 6);
-    const bool in = i < P;
-    const bool keep = len <= 64 * CPL;
-    double* Ai = A + (long)i * N + c1;
-    double a[CPL];
-    if (keep) {
+__global__ __launch_bounds__(64 * BS_NW) void bd_step_kernel(BdWork b, int c, bool start) {
+    constexpr int NT = 64 * BS_NW;
+    extern __shared__ double zu[];                  // z and u, the columns from c + 1 on
+    __shared__ double buf[BS_NW][BS_CH];
+    __shared__ double sh[BS_NW];
+    const int P = b.P, N = b.N, c1 = c + 1, len = N - c1;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    // a row has the same workgroup number in every step; the first ones finish
+    const int blk0 = c1 / BS_NW, i = blockIdx.x * BS_NW + w;
+    if ((int)blockIdx.x < blk0) return;
+    const bool in = i >= c1 && i < P;
+    double* z = zu;
+    double* u = zu + len;
+    double* Ai = b.A + (long)i * N + c1;
+    constexpr int CR = CPL > 0 ? CPL : 1;
+    double a[CR];
+    if (CPL > 0) {
 #pragma unroll
-        for (int u = 0; u < CPL; ++u) a[u] = (in && lane + 64 * u < len) ? Ai[lane + 64 * u] : 0.0;
+        for (int q = 0; q < CR; ++q) a[q] = (in && lane + 64 * q < len) ? Ai[lane + 64 * q] : 0.0;
     }
-    const double* x = row + c1;
-    const Refl h = block_reflector<256>(x, len, sh);
-    if (blockIdx.x == 0) {
-        double* v = VP + (long)c * N;
-        for (int k = t; k < N; k += 256) v[k] = k < c1 ? 0.0 : (k == c1 ? 1.0 : row[k] * h.scale);
-        if (t == 0) {
-            taup[c] = h.tau;
-            e[c] = h.beta;
+    double xn;       // the row's entry in the next step's column
+    if (!start) {
+        const double* rowc = b.A + (long)c * N;
+        const double x = in ? Ai[-1] : 0.0;
+        const Refl h = reflector(rowc[c], b.p[c]);
+        auto left = [&](int j) { return h.tau * (rowc[c1 + j] + h.scale * b.p[c1 + j]); };
+        double n2 = 0.0;
+        for (int j = t; j < len; j += NT) {
+            const double zj = left(j), r = rowc[c1 + j] - zj;
+            if (CPL > 0) {
+                z[j] = zj;
+                u[j] = r;
+            }
+            if (j > 0) n2 += r * r;
         }
-    }
-    if (!in) return;
-    double w = 0.0;
-    if (keep) {
-        double v[CPL];
+        n2 = wave_sum(n2);
+        if (lane == 0) sh[w] = n2;
+        __syncthreads();
+        n2 = sh[0];
 #pragma unroll
-        for (int u = 0; u < CPL; ++u) {
-            const int k = lane + 64 * u;
-            v[u] = k < len ? (k == 0 ? 1.0 : x[k] * h.scale) : 0.0;
-            w += v[u] * a[u];
+        for (int q = 1; q < BS_NW; ++q) n2 += sh[q];
+        const Refl k = reflector(len > 0 ? rowc[c1] - left(0) : 0.0, n2);
+        if (CPL > 0) {
+            for (int j = t; j < len; j += NT) u[j] = j == 0 ? 1.0 : u[j] * k.scale;
+            __syncthreads();
         }
-        w = h.tau * wave_sum(w);
+        auto uat = [&](int j) {
+            if (CPL > 0) return u[j];
+            return j == 0 ? 1.0 : (rowc[c1 + j] - left(j)) * k.scale;
+        };
+        const int ldq = pad16(P), ldp = pad16(N);
+        if ((int)blockIdx.x == blk0) {
+            double* vq = b.VQ + (long)c * ldq;
+            for (int q = t; q <= c; q += NT) vq[q] = q == c ? 1.0 : 0.0;
+            for (int q = P + t; q < ldq; q += NT) vq[q] = 0.0;
+            if (len > 0) {
+                double* vp = b.VP + (long)c * ldp;
+                for (int q = t; q < ldp; q += NT) vp[q] = q < c1 || q >= N ? 0.0 : uat(q - c1);
+            }
+            if (t == 0) {
+                b.tauq[c] = h.tau;
+                b.d[c] = h.beta;
+                b.taup[c] = k.tau;
+                b.e[c] = k.beta;
+            }
+        }
+        const double v = x * h.scale;
+        if (in && lane == 0) b.VQ[(long)c * ldq + i] = v;
+        if (len == 0) return;
+        double d = 0.0;
+        if (CPL > 0) {
 #pragma unroll
-        for (int u = 0; u < CPL; ++u) {
-            const int k = lane + 64 * u;
-            const double r = a[u] - w * v[u];
-            if (k < len) Ai[k] = r;
-            if (k == 0) col[i] = r;
+            for (int q = 0; q < CR; ++q) {
+                const int j = lane + 64 * q;
+                if (j < len) {
+                    a[q] -= v * z[j];
+                    d += a[q] * u[j];
+                }
+            }
+            d = k.tau * wave_sum(d);
+#pragma unroll
+            for (int q = 0; q < CR; ++q) {
+                const int j = lane + 64 * q;
+                if (j < len) {
+                    a[q] -= d * u[j];
+                    if (in) Ai[j] = a[q];
+                }
+            }
+            xn = lane_value(a[0], 0);
+        } else {
+            for (int j = lane; in && j < len; j += 64) d += (Ai[j] - v * left(j)) * uat(j);
+            d = k.tau * wave_sum(d);
+            double first = 0.0;
+            for (int j = lane; in && j < len; j += 64) {
+                const double r = Ai[j] - v * left(j) - d * uat(j);
+                Ai[j] = r;
+                if (j == 0) first = r;
+            }
+            xn = lane_value(first, 0);
         }
     } else {
-        for (int k = lane; k < len; k += 64) w += (k == 0 ? 1.0 : x[k] * h.scale) * Ai[k];
-        w = h.tau * wave_sum(w);
-        for (int k = lane; k < len; k += 64) {
-            const double r = Ai[k] - w * (k == 0 ? 1.0 : x[k] * h.scale);
-            Ai[k] = r;
-            if (k == 0) col[i] = r;
+        xn = in ? Ai[0] : 0.0;
+    }
+    // the next step's column products: rows below its own row
+    if (i == c1 || !in) xn = 0.0;
+    double* part = b.part + (long)blockIdx.x * N + c1;
+    for (int c0 = 0; c0 < len; c0 += BS_CH) {
+        if (c0 > 0) __syncthreads();
+        if (CPL > 0) {
+#pragma unroll
+            for (int q = 0; q < CR; ++q) {
+                const int j = lane + 64 * q - c0;
+                if (j >= 0 && j < BS_CH) buf[w][j] = xn * a[q];
+            }
+        } else {
+            for (int j = lane; j < BS_CH; j += 64) buf[w][j] = (in && c0 + j < len) ? xn * Ai[c0 + j] : 0.0;
+        }
+        __syncthreads();
+        for (int j = t; j < BS_CH && c0 + j < len; j += NT) {
+            double s = buf[0][j];
+#pragma unroll
+            for (int q = 1; q < BS_NW; ++q) s += buf[q][j];
+            part[c0 + j] = s;
         }
     }
 }
 
-// The triangular factors T [WYB][WYB] of the reflector blocks:
-// H_0 ... H_15 = I - V T V^T, T_jj = tau_j,
-// T[0:j, j] = -tau_j T[0:j, 0:j] (V^T v_j).  Grid: block x side (0: VQ, 1: VP).
+// p[j] = the sum over the products of workgroups q0 .. np - 1, j >= c.
+__global__ __launch_bounds__(1024) void bd_sum_kernel(BdWork b, int c, int q0, int np) {
+    __shared__ double sh[16][17];
+    const int N = b.N, t = threadIdx.x, tx = t & 15, ty = t >> 4, j = c + blockIdx.x * 16 + tx;
+    double s = 0.0;
+    if (j < N)
+        for (int q = q0 + ty; q < np; q += 64) s += b.part[(long)q * N + j];
+    s += __shfl_xor(s, 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    if ((ty & 3) == 0) sh[t >> 6][tx] = s;
+    __syncthreads();
+    if (t < 16 && j < N) {
+        s = sh[0][tx];
+#pragma unroll
+        for (int q = 1; q < 16; ++q) s += sh[q][tx];
+        b.p[j] = s;
+    }
+}
+
+// The sum over the four 16-lane rows of the wavefront for four values at a
+// time, scattered: row g ends with the sum of v[{0, 2, 1, 3}[g]] (the swaps
+// pair the halves and then the rows of two values, so an addition serves both).
+__device__ inline double swap_add32(double a, double b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+__device__ inline double swap_add16(double a, double b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+__device__ inline double rows_sum4(double v0, double v1, double v2, double v3) {
+    return swap_add16(swap_add32(v0, v1), swap_add32(v2, v3));
+}
+// The sum over the 16 lanes of each row, returned to all of them.
+__device__ inline double row_sum(double v) {
+    v += dpp_move<0xB1, 0xf>(v);
+    v += dpp_move<0x4E, 0xf>(v);
+    v += dpp_move<0x141, 0xf>(v);
+    v += dpp_move<0x140, 0xf>(v);
+    return v;
+}
+
+// The rest of the bidiagonalisation from column c0 on by one workgroup, the
+// trailing block (at most 4 NW RS rows, 16 CS columns) in its registers: lane
+// (g, cx) of wavefront w holds the rows 4 w + g + 4 NW s and the columns
+// cx + 16 u.  A step costs two barriers: the products of column c with every
+// column (with itself: its norm) are summed over the wavefronts in LDS, and
+// row c goes with them, so that after them every lane has its part of the
+// updated row c, from which the right reflector follows without another
+// exchange (the sums along a row stay inside 16 lanes).
+template <int NW, int RS, int CS>
+struct TailLDS {
+    double part[NW][16 * CS], psum[16 * CS], rowc[2][16 * CS], colc[2][4 * NW * RS];
+};
+
+// Columns 16 U0 .. 16 U0 + 15 of it; true when the block is finished.
+template <int NW, int RS, int CS, int U0>
+__device__ __forceinline__ bool bd_tail_columns(const BdWork& b, int c0, double (&a)[RS][CS],
+                                                TailLDS<NW, RS, CS>& L) {
+    constexpr int RW = 4 * NW, NC = 16 * CS;         // rows and columns a register slot covers in all
+    constexpr int s0 = U0 * 16 / RW;                 // row slots before it are finished
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, cx = lane & 15, g = lane >> 4, ry = 4 * w + g;
+    const int P = b.P, N = b.N, C = N - c0;
+    const int sel = ((g & 1) << 1) | (g >> 1);       // the slot of four whose sum this row of lanes gets
+    for (int cc = 0; cc < 16; ++cc) {
+        const int c = 16 * U0 + cc;
+        if (c >= C) return true;
+        double* rowc = L.rowc[c & 1];
+        double* colc = L.colc[c & 1];
+        // column c below row c, to every lane of a row (and to LDS)
+        double x[RS];
+#pragma unroll
+        for (int s = s0; s < RS; ++s) {
+            const double v = __shfl(a[s][U0], cc, 16);
+            x[s] = ry + RW * s > c ? v : 0.0;
+        }
+        if (cx == cc) {
+#pragma unroll
+            for (int s = s0; s < RS; ++s) colc[ry + RW * s] = x[s];
+        }
+        if (ry == c % RW) {
+#pragma unroll
+            for (int u = U0; u < CS; ++u) rowc[cx + 16 * u] = a[s0][u];
+        }
+        // the products of column c with the columns from c on
+#pragma unroll
+        for (int u = U0 & ~3; u < CS; u += 4) {
+            double v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                v[q] = 0.0;
+                if (u + q >= U0) {
+#pragma unroll
+                    for (int s = s0; s < RS; ++s) v[q] += x[s] * a[s][u + q];
+                }
+            }
+            L.part[w][16 * (u + sel) + cx] = rows_sum4(v[0], v[1], v[2], v[3]);
+        }
+        __syncthreads();
+        if (t < NC) {
+            double p = L.part[0][t];
+#pragma unroll
+            for (int q = 1; q < NW; ++q) p += L.part[q][t];
+            L.psum[t] = p;
+        }
+        double sg = L.part[0][c];
+#pragma unroll
+        for (int q = 1; q < NW; ++q) sg += L.part[q][c];
+        const Refl h = reflector(rowc[c], sg);
+        __syncthreads();
+        double r[CS];
+#pragma unroll
+        for (int s = s0; s < RS; ++s) x[s] *= h.scale;
+#pragma unroll
+        for (int u = U0; u < CS; ++u) {
+            const int j = cx + 16 * u;
+            const double rc = rowc[j], z = h.tau * (rc + h.scale * L.psum[j]);
+            r[u] = rc - z;
+#pragma unroll
+            for (int s = s0; s < RS; ++s) a[s][u] -= x[s] * z;
+        }
+        // the reflector's row of VQ, a value a thread
+        const int ldq = pad16(P), ldp = pad16(N);
+        for (int i = t; i < ldq; i += 64 * NW) {
+            const int l = i - c0;
+            b.VQ[(long)(c0 + c) * ldq + i] = l < c || i >= P ? 0.0 : (l == c ? 1.0 : h.scale * colc[l]);
+        }
+        if (t == 0) {
+            b.tauq[c0 + c] = h.tau;
+            b.d[c0 + c] = h.beta;
+        }
+        if (c + 1 >= C) return true;
+        // right reflector from the updated row c
+        double n2 = 0.0;
+#pragma unroll
+        for (int u = U0; u < CS; ++u) n2 += cx + 16 * u > c + 1 ? r[u] * r[u] : 0.0;
+        n2 = row_sum(n2);
+        const double alpha = __shfl(cc < 15 ? r[U0] : r[U0 + 1 < CS ? U0 + 1 : U0], (c + 1) & 15, 16);
+        const Refl k = reflector(alpha, n2);
+#pragma unroll
+        for (int u = U0; u < CS; ++u) {
+            const int j = cx + 16 * u;
+            r[u] = j > c + 1 ? r[u] * k.scale : (j == c + 1 ? 1.0 : 0.0);
+        }
+        // (rows up to c are finished: their registers are not read again)
+#pragma unroll
+        for (int s = s0; s < RS; ++s) {
+            double q = 0.0;
+#pragma unroll
+            for (int u = U0; u < CS; ++u) q += a[s][u] * r[u];
+            q = k.tau * row_sum(q);
+#pragma unroll
+            for (int u = U0; u < CS; ++u) a[s][u] -= q * r[u];
+        }
+        for (int j = t; j < ldp; j += 64 * NW) {
+            const int l = j - c0;
+            double v = l == c + 1 ? 1.0 : 0.0;
+            if (l > c + 1 && j < N) {
+                const double rc = rowc[l];
+                v = k.scale * (rc - h.tau * (rc + h.scale * L.psum[l]));
+            }
+            b.VP[(long)(c0 + c) * ldp + j] = v;
+        }
+        if (t == 0) {
+            b.taup[c0 + c] = k.tau;
+            b.e[c0 + c] = k.beta;
+        }
+    }
+    return false;
+}
+
+template <int NW, int RS, int CS, int U0>
+__device__ __forceinline__ void bd_tail_from(const BdWork& b, int c0, double (&a)[RS][CS], TailLDS<NW, RS, CS>& L) {
+    if constexpr (U0 < CS) {
+        if (bd_tail_columns<NW, RS, CS, U0>(b, c0, a, L)) return;
+        bd_tail_from<NW, RS, CS, U0 + 1>(b, c0, a, L);
+    }
+}
+
+template <int NW, int RS, int CS>
+__global__ __launch_bounds__(64 * NW) void bd_tail_kernel(BdWork b, int c0) {
+    constexpr int RW = 4 * NW;
+    static_assert(RW % 16 == 0 && CS % 4 == 0 && 16 * CS <= 64 * NW, "slots");
+    __shared__ TailLDS<NW, RS, CS> L;
+    const int t = threadIdx.x, lane = t & 63, cx = lane & 15, ry = 4 * (t >> 6) + (lane >> 4);
+    const int R = b.P - c0, C = b.N - c0;
+    double a[RS][CS];
+#pragma unroll
+    for (int s = 0; s < RS; ++s)
+#pragma unroll
+        for (int u = 0; u < CS; ++u) {
+            const int i = ry + RW * s, j = cx + 16 * u;
+            a[s][u] = (i < R && j < C) ? b.A[(long)(c0 + i) * b.N + c0 + j] : 0.0;
+        }
+    bd_tail_from<NW, RS, CS, 0>(b, c0, a, L);
+}
+
+// The triangular factors of the reflector blocks: H_0 ... H_15 = I - V T V^T,
+// T_jj = tau_j, T[0:j, j] = -tau_j T[0:j, 0:j] (V^T v_j); stored as -T.  Grid: block x side (0: VQ, 1: VP).
 __global__ __launch_bounds__(256) void wy_t_kernel(const double* __restrict__ VQ, int P, const double* __restrict__ VP,
                                                    int N, const double* __restrict__ tauq,
                                                    const double* __restrict__ taup, double* __restrict__ TQ,
@@ -223,15 +433,14 @@ __global__ __launch_bounds__(256) void wy_t_kernel(const double* __restrict__ VQ
     __shared__ double Sp[4][WYB][WYB + 1];
     __shared__ double S[WYB][WYB + 1];
     const int side = blockIdx.y, b0 = blockIdx.x * WYB;
-    const int len = side ? N : P, nr = side ? N - 1 : N;
+    const int len = pad16(side ? N : P), nr = side ? N - 1 : N;
     const double* V = side ? VP : VQ;
     const double* tau = side ? taup : tauq;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, l16 = lane & 15, kg = lane >> 4;
-    const bool live = b0 + l16 < nr;
     const double* v = V + (long)(b0 + l16) * len;
     d4_t acc = {0, 0, 0, 0};
-    for (int k0 = (b0 & ~3) + 4 * w; k0 < len; k0 += 16) {
-        const double x = (live && k0 + kg < len) ? v[k0 + kg] : 0.0;
+    for (int k0 = b0 + 4 * w; k0 < len; k0 += 16) {
+        const double x = v[k0 + kg];
         acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x, x, acc, 0, 0, 0);
     }
 #pragma unroll
@@ -252,21 +461,22 @@ __global__ __launch_bounds__(256) void wy_t_kernel(const double* __restrict__ VQ
 #pragma unroll
             for (int k = 0; k < j; ++k) s += trow[k] * S[k][j];
             trow[j] = t < j ? -tj * s : (t == j ? tj : 0.0);
-            T[j] = trow[j];
+            T[j] = -trow[j];
         }
     }
 }
 
-// Vector t < k of a side: H_0 H_1 ... (the reflectors V [nr][len]) applied
-// to row perm[t] of X [n][n] (zero-extended to len), times sg[perm[t]] *scale
+// Vector t < k of a side: H_0 H_1 ... (the reflectors V, nblk blocks of 16
+// with rows of pad16(len)) applied to row perm[t] of X [n][n] (zero-extended
+// to len), times sg[perm[t]] *scale
 // when scaled; written to out[t][len], or transposed to out[len][k].
 struct WySide {
     const double* X;
     const double* V;
-    const double* T;
-    int len, nr;
+    const double* T;       // -T of the blocks
+    int len, nblk;
     double* out;
-    double* tmp;      // [16 ceil(k / 16)][len], only for len > the register limit
+    double* tmp;      // [pad16(k)][pad16(len)], only for len > the register limit
     int transposed, scaled;
 };
 
@@ -287,59 +497,106 @@ __global__ __launch_bounds__(64 * NW) void wy_apply_kernel(WySide s0, WySide s1,
     const int l16 = lane & 15, kg = lane >> 4;
     const int vec = blockIdx.x * WYB + l16;       // this lane's vector
     const int row = vec < k ? perm[vec] : -1;
-    const int ntile = (s.len + WYB - 1) / WYB;
-    double* tmp = TPW > 0 ? nullptr : s.tmp + (long)vec * s.len;
+    const int ld = pad16(s.len), ntile = ld / WYB, nblk = s.nblk;
+    double* tmp = TPW > 0 ? nullptr : s.tmp + (long)vec * ld;
     d4_t acc[TR];
-    if (TPW > 0) {
-#pragma unroll
-        for (int u = 0; u < TR; ++u)
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const int c = (w + NW * u) * WYB + 4 * rr + kg;
-                acc[u][rr] = (row >= 0 && c < n) ? s.X[(long)row * n + c] : 0.0;
-            }
-    } else {
-        for (int c = w * WYB; c < s.len; c += NW * WYB)
-            for (int rr = 0; rr < 4; ++rr) {
-                const int cc = c + 4 * rr + kg;
-                if (cc < s.len) tmp[cc] = (row >= 0 && cc < n) ? s.X[(long)row * n + cc] : 0.0;
-            }
-    }
-    auto load = [&](int tile, d4_t& x) {
+    auto first = [&](int tile, d4_t& x) {
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
-            const int cc = tile * WYB + 4 * rr + kg;
-            x[rr] = cc < s.len ? tmp[cc] : 0.0;
+            const int c = tile * WYB + 4 * rr + kg;
+            x[rr] = (row >= 0 && c < n) ? s.X[(long)row * n + c] : 0.0;
         }
     };
-    for (int b = (s.nr + WYB - 1) / WYB - 1; b >= 0; --b) {
-        const int b0 = b * WYB;
-        const double* V = s.V + (long)b0 * s.len;
-        const bool live = b0 + l16 < s.nr;
+    auto load = [&](int tile, d4_t& x) {
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) x[rr] = tmp[tile * WYB + 4 * rr + kg];
+    };
+    auto store = [&](int tile, const d4_t& x) {
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) tmp[tile * WYB + 4 * rr + kg] = x[rr];
+    };
+    // Operands of a block: its reflectors as rows (W) and as columns (the
+    // update), and T.
+    auto load_dot = [&](int b, int tile, double (&a)[4]) {
+        const double* v = s.V + (long)(b * WYB + l16) * ld + tile * WYB + kg;
+#pragma unroll
+        for (int st = 0; st < 4; ++st) a[st] = v[4 * st];
+    };
+    auto load_upd = [&](int b, int tile, double (&a)[4]) {
+        const double* v = s.V + (long)(b * WYB + kg) * ld + tile * WYB + l16;
+#pragma unroll
+        for (int st = 0; st < 4; ++st) a[st] = v[(long)(4 * st) * ld];
+    };
+    auto load_t = [&](int b, double (&a)[4]) {
+#pragma unroll
+        for (int st = 0; st < 4; ++st) a[st] = s.T[(long)b * WYB * WYB + l16 * WYB + 4 * st + kg];
+    };
+    auto mma4 = [](const double (&a)[4], const d4_t& x, d4_t c) {
+#pragma unroll
+        for (int st = 0; st < 4; ++st) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[st], x[st], c, 0, 0, 0);
+        return c;
+    };
+    // Up to 512 entries the operands are fetched as soon as the block before has
+    // used its own, across the barriers, and every tile takes
+    // part in every block (it meets zeros before a block's first reflector).
+    constexpr bool PF = TPW > 0 && NW * TPW <= 32;
+    int tl[TR];
+#pragma unroll
+    for (int u = 0; u < TR; ++u) tl[u] = PF ? min(w + NW * u, ntile - 1) : w + NW * u;
+    double vd[PF ? TR : 1][4], vu[PF ? TR : 1][4], tt[4];
+    if (TPW > 0) {
+#pragma unroll
+        for (int u = 0; u < TR; ++u) {
+            acc[u] = d4_t{0, 0, 0, 0};
+            if (w + NW * u < ntile) first(w + NW * u, acc[u]);
+        }
+    } else {
+        for (int tile = w; tile < ntile; tile += NW) {
+            d4_t x;
+            first(tile, x);
+            store(tile, x);
+        }
+    }
+    if (PF) {
+        // the reflectors into this XCD's L2 first, one load a cache line with
+        // many in flight, so that a block waits for L2 and not for memory
+        double warm = 0.0;
+        const int lines = nblk * ld;      // 16 ld values a block, 16 a line
+        for (int e = t; e < lines; e += 64 * NW) warm += s.V[(long)e * 16];
+        asm volatile("" ::"v"(warm));
+#pragma unroll
+        for (int u = 0; u < (PF ? TR : 0); ++u) {
+            load_dot(nblk - 1, tl[u], vd[u]);
+            load_upd(nblk - 1, tl[u], vu[u]);
+        }
+        load_t(nblk - 1, tt);
+    }
+    for (int b = nblk - 1; b >= 0; --b) {
+        const int bn = max(b - 1, 0);
         // W = V^T x over this wavefront's tiles
         d4_t wp = {0, 0, 0, 0};
-        auto dot_tile = [&](int tile, const d4_t& x) {
-            double a[4];
+        if (PF) {
 #pragma unroll
-            for (int st = 0; st < 4; ++st) {
-                const int cc = tile * WYB + 4 * st + kg;
-                a[st] = (live && cc < s.len) ? V[(long)l16 * s.len + cc] : 0.0;
+            for (int u = 0; u < (PF ? TR : 0); ++u) {
+                wp = mma4(vd[u], acc[u], wp);
+                load_dot(bn, tl[u], vd[u]);
             }
-#pragma unroll
-            for (int st = 0; st < 4; ++st) wp = __builtin_amdgcn_mfma_f64_16x16x4f64(a[st], x[st], wp, 0, 0, 0);
-        };
-        if (TPW > 0) {
+        } else if (TPW > 0) {
 #pragma unroll
             for (int u = 0; u < TR; ++u) {
-                const int tile = w + NW * u;
-                if (tile >= b && tile < ntile) dot_tile(tile, acc[u]);
+                if (tl[u] < b || tl[u] >= ntile) continue;
+                double a[4];
+                load_dot(b, tl[u], a);
+                wp = mma4(a, acc[u], wp);
             }
         } else {
             for (int tile = w; tile < ntile; tile += NW) {
                 if (tile < b) continue;
                 d4_t x;
+                double a[4];
                 load(tile, x);
-                dot_tile(tile, x);
+                load_dot(b, tile, a);
+                wp = mma4(a, x, wp);
             }
         }
 #pragma unroll
@@ -354,37 +611,34 @@ __global__ __launch_bounds__(64 * NW) void wy_apply_kernel(WySide s0, WySide s1,
             Ws[i][v] = sum;
         }
         __syncthreads();
-        d4_t w2 = {0, 0, 0, 0};
-        const double* T = s.T + (long)b * WYB * WYB;
+        if (!PF) load_t(b, tt);
+        d4_t ws, w2 = {0, 0, 0, 0};
 #pragma unroll
-        for (int st = 0; st < 4; ++st)
-            w2 = __builtin_amdgcn_mfma_f64_16x16x4f64(-T[l16 * WYB + 4 * st + kg], Ws[4 * st + kg][l16], w2, 0, 0, 0);
-        auto update_tile = [&](int tile, d4_t& x) {
-            const int cc = tile * WYB + l16;
-            double a[4];
+        for (int st = 0; st < 4; ++st) ws[st] = Ws[4 * st + kg][l16];
+        w2 = mma4(tt, ws, w2);
+        if (PF) {
+            load_t(bn, tt);
 #pragma unroll
-            for (int st = 0; st < 4; ++st)
-                a[st] = (b0 + 4 * st + kg < s.nr && cc < s.len) ? V[(long)(4 * st + kg) * s.len + cc] : 0.0;
-#pragma unroll
-            for (int st = 0; st < 4; ++st) x = __builtin_amdgcn_mfma_f64_16x16x4f64(a[st], w2[st], x, 0, 0, 0);
-        };
-        if (TPW > 0) {
+            for (int u = 0; u < (PF ? TR : 0); ++u) {
+                if (w + NW * u < ntile) acc[u] = mma4(vu[u], w2, acc[u]);
+                load_upd(bn, tl[u], vu[u]);
+            }
+        } else if (TPW > 0) {
 #pragma unroll
             for (int u = 0; u < TR; ++u) {
-                const int tile = w + NW * u;
-                if (tile >= b && tile < ntile) update_tile(tile, acc[u]);
+                if (tl[u] < b || tl[u] >= ntile) continue;
+                double a[4];
+                load_upd(b, tl[u], a);
+                acc[u] = mma4(a, w2, acc[u]);
             }
         } else {
             for (int tile = w; tile < ntile; tile += NW) {
                 if (tile < b) continue;
                 d4_t x;
+                double a[4];
                 load(tile, x);
-                update_tile(tile, x);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const int cc = tile * WYB + 4 * rr + kg;
-                    if (cc < s.len) tmp[cc] = x[rr];
-                }
+                load_upd(b, tile, a);
+                store(tile, mma4(a, w2, x));
             }
         }
     }
@@ -412,14 +666,15 @@ __global__ __launch_bounds__(64 * NW) void wy_apply_kernel(WySide s0, WySide s1,
     }
 }
 
-constexpr int WY_NW = 16;
-constexpr int WY_MAX = WY_NW * WYB * 8;     // longest vector held in registers
+constexpr int BD_TAIL = 192;                // rows of the block that one workgroup finishes
+constexpr int WY_MAX = 8 * WYB * 16;     // longest vector held in registers
 
 }  // namespace
 
 size_t bd_workspace(int P, int N) {
-    const size_t nb = (size_t)(N + WYB - 1) / WYB;
-    return (size_t)P * N + (size_t)N * P + (size_t)N * N + 2 * nb * WYB * WYB + 2 * (size_t)P + 6 * (size_t)N + 64;
+    const size_t nb = (size_t)(N + WYB - 1) / WYB, np = pad16(N);
+    return (size_t)P * N + np * pad16(P) + np * np + 2 * nb * WYB * WYB +
+           (size_t)((P + BS_NW - 1) / BS_NW) * N + 5 * (size_t)N + 64;
 }
 
 BdWork bd_carve(double* ws, int P, int N) {
@@ -429,12 +684,12 @@ BdWork bd_carve(double* ws, int P, int N) {
     w.N = N;
     w.A = ws;
     w.VQ = w.A + (size_t)P * N;
-    w.VP = w.VQ + (size_t)N * P;
-    w.TQ = w.VP + (size_t)N * N;
+    w.VP = w.VQ + (size_t)pad16(N) * pad16(P);
+    w.TQ = w.VP + (size_t)pad16(N) * pad16(N);
     w.TP = w.TQ + nb * WYB * WYB;
-    w.col = w.TP + nb * WYB * WYB;
-    w.row = w.col + P;
-    w.tauq = w.row + N;
+    w.part = w.TP + nb * WYB * WYB;
+    w.p = w.part + (size_t)((P + BS_NW - 1) / BS_NW) * N;
+    w.tauq = w.p + N;
     w.taup = w.tauq + N;
     w.d = w.taup + N;
     w.e = w.d + N;
@@ -444,35 +699,33 @@ BdWork bd_carve(double* ws, int P, int N) {
 void bidiagonalise(const BdWork& w, const double* theta, bool tr, hipStream_t s, LaunchProbe* probe) {
     const int P = w.P, N = w.N;
     hipLaunchKernelGGL(bd_load_kernel, dim3((N + 31) / 32, (P + 31) / 32), dim3(256), 0, s, theta, P, N, (int)tr, w.A,
-                       w.col);
+                       w.VQ, w.VP);
+    auto step = [&](int c, bool start) {
+        const bool timed = probe && probe->begin(PK_BIDIAG, s);
+        const int len = N - c - 1, g = (P + BS_NW - 1) / BS_NW;
+        const size_t lds = start || len > 2048 ? 0 : 2 * sizeof(double) * (size_t)std::max(len, 1);
+        if (len <= 256) hipLaunchKernelGGL((bd_step_kernel<4>), dim3(g), dim3(64 * BS_NW), lds, s, w, c, start);
+        else if (len <= 512) hipLaunchKernelGGL((bd_step_kernel<8>), dim3(g), dim3(64 * BS_NW), lds, s, w, c, start);
+        else if (len <= 1024) hipLaunchKernelGGL((bd_step_kernel<16>), dim3(g), dim3(64 * BS_NW), lds, s, w, c, start);
+        else if (len <= 2048) hipLaunchKernelGGL((bd_step_kernel<32>), dim3(g), dim3(64 * BS_NW), lds, s, w, c, start);
+        else hipLaunchKernelGGL((bd_step_kernel<0>), dim3(g), dim3(64 * BS_NW), lds, s, w, c, start);
+        if (len > 0) hipLaunchKernelGGL(bd_sum_kernel, dim3((len + 15) / 16), dim3(1024), 0, s, w, c + 1,
+                                        (c + 1) / BS_NW, g);
+        if (timed) probe->end(PK_BIDIAG, s);
+    };
+    if (P > BD_TAIL) step(-1, true);
     for (int c = 0; c < N; ++c) {
-        bool timed = probe && probe->begin(PK_BIDIAG, s);
         const int len = P - c;
-        const dim3 gl(std::max(1, (N - c - 1 + 15) / 16));
-        if (len > 512)
-            hipLaunchKernelGGL((bd_left_kernel<1024, 32>), gl, dim3(1024), 0, s, w.A, P, N, c, w.col, w.row, w.VQ,
-                               w.tauq, w.d);
-        else if (len > 128)
-            hipLaunchKernelGGL((bd_left_kernel<512, 16>), gl, dim3(512), 0, s, w.A, P, N, c, w.col, w.row, w.VQ,
-                               w.tauq, w.d);
-        else
-            hipLaunchKernelGGL((bd_left_kernel<256, 8>), gl, dim3(256), 0, s, w.A, P, N, c, w.col, w.row, w.VQ,
-                               w.tauq, w.d);
+        if (len > BD_TAIL) {
+            step(c, false);
+            continue;
+        }
+        const bool timed = probe && probe->begin(PK_BIDIAG, s);
+        if (len <= 64) hipLaunchKernelGGL((bd_tail_kernel<4, 4, 4>), dim3(1), dim3(256), 0, s, w, c);
+        else if (len <= 128) hipLaunchKernelGGL((bd_tail_kernel<4, 8, 8>), dim3(1), dim3(256), 0, s, w, c);
+        else hipLaunchKernelGGL((bd_tail_kernel<8, 6, 12>), dim3(1), dim3(512), 0, s, w, c);
         if (timed) probe->end(PK_BIDIAG, s);
-        if (c + 1 >= N) break;
-        timed = probe && probe->begin(PK_BIDIAG, s);
-        const dim3 gr((P - c - 1 + 3) / 4);
-        const int cl = N - c - 1;
-        if (cl > 512)
-            hipLaunchKernelGGL((bd_right_kernel<32>), gr, dim3(256), 0, s, w.A, P, N, c, w.col, w.row, w.VP, w.taup,
-                               w.e);
-        else if (cl > 128)
-            hipLaunchKernelGGL((bd_right_kernel<8>), gr, dim3(256), 0, s, w.A, P, N, c, w.col, w.row, w.VP, w.taup,
-                               w.e);
-        else
-            hipLaunchKernelGGL((bd_right_kernel<2>), gr, dim3(256), 0, s, w.A, P, N, c, w.col, w.row, w.VP, w.taup,
-                               w.e);
-        if (timed) probe->end(PK_BIDIAG, s);
+        break;
     }
     hipLaunchKernelGGL(wy_t_kernel, dim3((N + WYB - 1) / WYB, 2), dim3(256), 0, s, w.VQ, P, w.VP, N, w.tauq, w.taup,
                        w.TQ, w.TP);
@@ -488,21 +741,22 @@ void bd_vectors(const BdWork& w, const double* XQ, const double* XP, const int* 
                 const double* scale, const BdOut& q, const BdOut& p, double* tmp, hipStream_t s, LaunchProbe* probe) {
     if (k <= 0) return;
     const int N = w.N;
-    const int kr = (k + WYB - 1) / WYB * WYB;
-    WySide sq{XQ, w.VQ, w.TQ, w.P, N, q.out, tmp, q.transposed, q.scaled};
-    WySide sp{XP, w.VP, w.TP, N, N - 1, p.out, tmp ? tmp + (size_t)kr * w.P : nullptr, p.transposed, p.scaled};
+    const int kr = pad16(k);
+    const int nblk = (N + WYB - 1) / WYB;
+    WySide sq{XQ, w.VQ, w.TQ, w.P, nblk, q.out, tmp, q.transposed, q.scaled};
+    WySide sp{XP, w.VP, w.TP, N, nblk, p.out, tmp ? tmp + (size_t)kr * pad16(w.P) : nullptr, p.transposed, p.scaled};
     const dim3 grid(kr / WYB, 2);
     const bool timed = probe && probe->begin(PK_VECTORS, s);
     const int tiles = (w.P + WYB - 1) / WYB;
 #define ITE_WY(NW, TPW) \
     hipLaunchKernelGGL((wy_apply_kernel<NW, TPW>), grid, dim3(64 * NW), 0, s, sq, sp, N, perm, k, sg, scale)
     if (tiles <= 4) ITE_WY(4, 1);
-    else if (tiles <= 8) ITE_WY(8, 1);
-    else if (tiles <= 16) ITE_WY(16, 1);
-    else if (tiles <= 32) ITE_WY(16, 2);
+    else if (tiles <= 8) ITE_WY(4, 2);
+    else if (tiles <= 16) ITE_WY(4, 4);
+    else if (tiles <= 32) ITE_WY(8, 4);
     else if (tiles <= 64) ITE_WY(16, 4);
-    else if (tiles <= WY_MAX / WYB) ITE_WY(16, 8);
-    else ITE_WY(16, 0);
+    else if (tiles <= WY_MAX / WYB) ITE_WY(8, 16);
+    else ITE_WY(8, 0);
 #undef ITE_WY
     if (timed) probe->end(PK_VECTORS, s);
     HIP_CHECK(hipGetLastError());
@@ -515,7 +769,7 @@ void bd_vectors(const BdWork& w, const double* XQ, const double* XP, const int* 
 
 size_t bd_vectors_tmp(int P, int N, int k) {
     if (P <= WY_MAX) return 0;
-    return (size_t)((k + WYB - 1) / WYB * WYB) * ((size_t)P + N);
+    return (size_t)pad16(k) * ((size_t)pad16(P) + pad16(N));
 }
 
 }  // namespace ite

@@ -74,13 +74,6 @@ __device__ inline Node node_of(int n, int depth, int g, int& q) {
 
 __device__ inline double clean(double v) { return v == v ? v : 0.0; }
 
-// 1 / x to rounding (x normal).
-__device__ inline double recip(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(fma(-x, r, 1.0), r, r);
-    return fma(fma(-x, r, 1.0), r, r);
-}
-
 // One update of a root of f(x) = 1 + psi(x) + phi(x): psi (the poles up to
 // da = pole - x) and phi (those from db on) are replaced by r + s / (pole - x)
 // with their values and slopes at x (Bunch, Nielsen and Sorensen); kept inside
@@ -120,15 +113,24 @@ __device__ inline double sigma_of(double dc, double x) {
 // Subtrees in LDS
 // ---------------------------------------------------------------------------
 
+// A level of a subtree in three steps: a wavefront a node sorts and deflates;
+// then 32 lanes a row find the roots, recompute z and form the vectors (a pole
+// each: a subtree has at most 32 rows, so the workgroup holds every row of
+// the level whatever its nodes are); then a thread an entry of the products.
+constexpr int LNT = LEAF * 32;
+constexpr int LNW = LNT / 64;
+
 struct LeafLDS {
     double U[2][LEAF][LEAF + 1], V[2][LEAF + 1][LEAF + 2];
     double Us[LEAF][LEAF + 1], Vs[LEAF][LEAF + 1];
     double sg[2][LEAF + 1], d[LEAF], e[LEAF];
-    double key[4][LEAF], sd[4][LEAF], sz[4][LEAF], cr[4][LEAF], sr[4][LEAF], dd[4][LEAF], zz[4][LEAF], zh[4][LEAF];
-    int srow[4][LEAF], act[4][LEAF];
-    int und[LEAF];                                            // gathered source row of pole i of the node at a: und[a + i]
-    int kind[LEAF + 1], src[LEAF + 1], na[LEAF + 1], nb[LEAF + 1], nk[LEAF + 1];
-    double red[4];
+    // a node's entries from its first row on: the order (scratch of its
+    // wavefront), then poles, z and z recomputed
+    double key[LEAF], sd[LEAF], sz[LEAF], cr[LEAF], sr[LEAF], dd[LEAF], zz[LEAF], zh[LEAF], x[LEAF], dc[LEAF];
+    int srow[LEAF], prev[LEAF];
+    int und[LEAF];                 // source row of the node's pole i: und[a + i]
+    int kind[LEAF + 1], src[LEAF + 1], na[LEAF + 1], nb[LEAF + 1], nk[LEAF];
+    double red[LNW];
 };
 enum { ROW_PRODUCT = 0, ROW_COPY = 1, ROW_NULL = 2 };
 
@@ -137,9 +139,9 @@ __device__ inline void wave_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// One node of a subtree by one wavefront (local rows, at most 32).  `null`:
-// column b exists.
-__device__ void leaf_merge(LeafLDS& L, int cur, int a, int m, int b, bool null, int wv, int lane) {
+// Sort and deflation of one node of a subtree by one wavefront (local rows, at
+// most 32).  `null`: column b exists.
+__device__ __forceinline__ void leaf_deflate(LeafLDS& L, int cur, int a, int m, int b, bool null, int lane) {
     const int N = b - a;
     auto& U = L.U[cur];
     auto& V = L.V[cur];
@@ -156,6 +158,8 @@ __device__ void leaf_merge(LeafLDS& L, int cur, int a, int m, int b, bool null, 
     if (lane < N) {
         L.na[a + lane] = a;
         L.nb[a + lane] = b;
+        L.kind[a + lane] = ROW_COPY;
+        L.nk[a + lane] = 0;
     }
     const double alpha = L.d[m], beta = L.e[m];
     if (N == 1) {
@@ -175,7 +179,6 @@ __device__ void leaf_merge(LeafLDS& L, int cur, int a, int m, int b, bool null, 
                 V[b][b] = c;
             }
             L.sg[cur ^ 1][a] = clean(r);
-            L.kind[a] = ROW_COPY;
             L.src[a] = a;
         }
         return;
@@ -202,9 +205,13 @@ __device__ void leaf_merge(LeafLDS& L, int cur, int a, int m, int b, bool null, 
         V[m][c] = c0 * w1 + s0 * w2;
         V[b][c] = c0 * w2 - s0 * w1;
     }
+    double* key = L.key + a;
+    double* sd = L.sd + a;
+    double* sz = L.sz + a;
+    int* srow = L.srow + a;
     if (lane < N) {
         U[m][a + lane] = a + lane == m ? 1.0 : 0.0;
-        L.key[wv][lane] = dv;
+        key[lane] = dv;
     }
     const double nrm = fmax(wave_max_nonneg(dv), fmax(fabs(clean(alpha)), fabs(clean(beta))));
     const double tol = DEFLATE * nrm;
@@ -213,20 +220,20 @@ __device__ void leaf_merge(LeafLDS& L, int cur, int a, int m, int b, bool null, 
     if (lane < N) {
         int rank = lane == lm ? 0 : 1;
         for (int t = 0; t < N; ++t) {
-            const double k = L.key[wv][t];
+            const double k = key[t];
             if (lane != lm && t != lm) rank += k < dv || (k == dv && t < lane);
         }
-        L.sd[wv][rank] = dv;
-        L.sz[wv][rank] = zv;
-        L.srow[wv][rank] = a + lane;
+        sd[rank] = dv;
+        sz[rank] = zv;
+        srow[rank] = a + lane;
     }
     wave_fence();
     double ds = 0.0, zs = 0.0;
     int act = 1, row = 0;
     if (lane < N) {
-        ds = L.sd[wv][lane];
-        zs = L.sz[wv][lane];
-        row = L.srow[wv][lane];
+        ds = sd[lane];
+        zs = sz[lane];
+        row = srow[lane];
         if (lane == 0 && !(fabs(zs) > tol)) zs = zs < 0.0 ? -tol : tol;
     }
     const bool surv = lane > 0 && lane < N && fabs(zs) > tol;
@@ -237,7 +244,7 @@ __device__ void leaf_merge(LeafLDS& L, int cur, int a, int m, int b, bool null, 
     if (surv && !tiny) {
         const unsigned long long q = ms & below;
         pv = q ? 63 - __clzll(q) : -1;
-        act = pv >= 0 && ds - L.sd[wv][pv] <= tol ? 2 : 0;
+        act = pv >= 0 && ds - sd[pv] <= tol ? 2 : 0;
     } else if (tiny) {
         act = 3;
     } else if (lane == 0) {
@@ -248,7 +255,7 @@ __device__ void leaf_merge(LeafLDS& L, int cur, int a, int m, int b, bool null, 
     const int K = __popcll(m0);
     const int slot = __popcll(m0 & below);
     if (in) {
-        L.sz[wv][lane] = zs;
+        sz[lane] = zs;
         if (act == 0) {
             // the chain that starts here: its rows rotate into one
             double z = zs, dl = ds;
@@ -256,41 +263,41 @@ __device__ void leaf_merge(LeafLDS& L, int cur, int a, int m, int b, bool null, 
             if (lane == 0) {
                 for (unsigned long long q = m3; q; q &= q - 1) {
                     const int t = __ffsll((long long)q) - 1;
-                    const double zt = L.sz[wv][t], tau = hypot(z, zt);
-                    L.cr[wv][t] = z / tau;
-                    L.sr[wv][t] = zt / tau;
+                    const double zt = sz[t], tau = hypot(z, zt);
+                    L.cr[a + t] = z / tau;
+                    L.sr[a + t] = zt / tau;
                     z = tau;
                 }
-            } else {
+            } else if (m2) {
                 const unsigned long long later = ms & ~below & ~(1ull << lane);
                 for (unsigned long long q = later; q; q &= q - 1) {
                     const int t = __ffsll((long long)q) - 1;
                     if (!((m2 >> t) & 1)) break;
-                    const double zt = L.sz[wv][t], tau = hypot(z, zt);
-                    L.cr[wv][t] = zt / tau;
-                    L.sr[wv][t] = z / tau;
+                    const double zt = sz[t], tau = hypot(z, zt);
+                    L.cr[a + t] = zt / tau;
+                    L.sr[a + t] = z / tau;
                     z = tau;
-                    dl = L.sd[wv][t];
-                    last = L.srow[wv][t];
+                    dl = sd[t];
+                    last = srow[t];
                 }
             }
-            L.dd[wv][slot] = dl;
-            L.zz[wv][slot] = z;
+            L.dd[a + slot] = dl;
+            L.zz[a + slot] = z;
             L.und[a + slot] = last;
+            L.kind[a + slot] = ROW_PRODUCT;
         } else {
             const int o = a + K + (lane - slot);      // lane - slot deflated entries before this one
-            L.kind[o] = ROW_COPY;
-            L.src[o] = act == 2 ? L.srow[wv][pv] : row;
-            L.sg[cur ^ 1][o] = act == 2 ? L.sd[wv][pv] : (act == 3 ? 0.0 : ds);
+            L.src[o] = act == 2 ? srow[pv] : row;
+            L.sg[cur ^ 1][o] = act == 2 ? sd[pv] : (act == 3 ? 0.0 : ds);
         }
-        L.act[wv][lane] = pv;
+        L.prev[a + lane] = pv;
         L.nk[a + lane] = K;
     }
     wave_fence();
     for (unsigned long long q = m2 | m3; q; q &= q - 1) {
         const int t = __ffsll((long long)q) - 1;
-        const double c = L.cr[wv][t], s = L.sr[wv][t];
-        const int rt = L.srow[wv][t];
+        const double c = L.cr[a + t], s = L.sr[a + t];
+        const int rt = srow[t];
         if ((m3 >> t) & 1) {
             if (lane <= N) {
                 const double x = V[m][a + lane], y = V[rt][a + lane];
@@ -298,7 +305,7 @@ __device__ void leaf_merge(LeafLDS& L, int cur, int a, int m, int b, bool null, 
                 V[rt][a + lane] = c * y - s * x;
             }
         } else {
-            const int rp = L.srow[wv][L.act[wv][t]];
+            const int rp = srow[L.prev[a + t]];
             if (lane <= N) {
                 const double x = V[rp][a + lane], y = V[rt][a + lane];
                 V[rp][a + lane] = c * x - s * y;
@@ -312,94 +319,22 @@ __device__ void leaf_merge(LeafLDS& L, int cur, int a, int m, int b, bool null, 
         }
         wave_fence();
     }
-    // roots: one lane each
-    const double* dd = L.dd[wv];
-    const double* zz = L.zz[wv];
-    if (K == 1) {
-        if (lane == 0) {
-            L.sg[cur ^ 1][a] = fabs(zz[0]);
-            L.Us[a][0] = 1.0;
-            L.Vs[a][0] = zz[0] < 0.0 ? -1.0 : 1.0;
-            L.kind[a] = ROW_PRODUCT;
-            L.src[a] = a;
-        }
-        return;
-    }
-    double x = 0.0, dc = 0.0;
-    const int i = lane;
-    if (i < K) {
-        const bool last = i == K - 1;
-        double lo = 0.0, hi;
-        int c = i;
-        if (last) {
-            double tot = 0.0;
-            for (int j = 0; j < K; ++j) tot += zz[j] * zz[j];
-            hi = tot * (1.0 + 8.0 * EPS);
-            x = 0.5 * hi;
-        } else {
-            const double mid = 0.5 * (dd[i + 1] - dd[i]) * (dd[i + 1] + dd[i]);
-            double f = 1.0;
-            for (int j = 0; j < K; ++j) f += zz[j] * zz[j] * recip((dd[j] - dd[i]) * (dd[j] + dd[i]) - mid);
-            hi = mid;
-            if (!(f >= 0.0)) {
-                c = i + 1;
-                lo = -mid;
-                hi = 0.0;
-            }
-            x = f >= 0.0 ? mid : -mid;
-        }
-        dc = dd[c];
-        for (int it = 0; it < ROOT_ITERS; ++it) {
-            double psi = 0.0, dpsi = 0.0, phi = 0.0, dphi = 0.0;
-            for (int j = 0; j < K; ++j) {
-                const double r = recip((dd[j] - dc) * (dd[j] + dc) - x), tt = zz[j] * zz[j] * r;
-                if (j <= i) {
-                    psi += tt;
-                    dpsi += tt * r;
-                } else {
-                    phi += tt;
-                    dphi += tt * r;
-                }
-            }
-            const double da = (dd[i] - dc) * (dd[i] + dc) - x;
-            const double db = last ? 0.0 : (dd[i + 1] - dc) * (dd[i + 1] + dc) - x;
-            if (root_step(x, lo, hi, psi, dpsi, phi, dphi, da, db, last)) break;
-        }
-        L.sg[cur ^ 1][a + i] = sigma_of(dc, x);
-        L.cr[wv][i] = x;
-        L.sr[wv][i] = dc;
-        L.kind[a + i] = ROW_PRODUCT;
-        L.src[a + i] = i;
-    }
-    wave_fence();
-    if (i < K) {
-        // z recomputed: pole i against every root
-        const double di = dd[i];
-        auto diff = [&](int k) { return (di - L.sr[wv][k]) * (di + L.sr[wv][k]) - L.cr[wv][k]; };
-        double p = -diff(K - 1);
-        for (int k = 0; k < i; ++k) p *= -diff(k) * recip((dd[k] - di) * (dd[k] + di));
-        for (int k = i; k < K - 1; ++k) p *= -diff(k) * recip((dd[k + 1] - di) * (dd[k + 1] + di));
-        const double zh = sqrt(fabs(p));
-        L.zh[wv][i] = zz[i] < 0.0 ? -zh : zh;
-    }
-    wave_fence();
-    if (i < K) {
-        double nu = 0.0, nv = 0.0;
-        for (int j = 0; j < K; ++j) {
-            const double v = L.zh[wv][j] * recip((dd[j] - dc) * (dd[j] + dc) - x);
-            const double u = j == 0 ? -1.0 : dd[j] * v;
-            L.Vs[a + i][j] = v;
-            L.Us[a + i][j] = u;
-            nu += u * u;
-            nv += v * v;
-        }
-        nu = 1.0 / sqrt(nu);
-        nv = 1.0 / sqrt(nv);
-        for (int j = 0; j < K; ++j) {
-            L.Vs[a + i][j] *= nv;
-            L.Us[a + i][j] *= nu;
-        }
-    }
+}
+
+// Sums and products over the 32 lanes of a half wavefront, to all of them.
+__device__ inline double half_sum(double v) {
+    v += dpp_move<0xB1, 0xf>(v);
+    v += dpp_move<0x4E, 0xf>(v);
+    v += dpp_move<0x141, 0xf>(v);
+    v += dpp_move<0x140, 0xf>(v);
+    return v + __shfl_xor(v, 16, 32);
+}
+__device__ inline double half_product(double v) {
+    v *= dpp_move<0xB1, 0xf>(v);
+    v *= dpp_move<0x4E, 0xf>(v);
+    v *= dpp_move<0x141, 0xf>(v);
+    v *= dpp_move<0x140, 0xf>(v);
+    return v * __shfl_xor(v, 16, 32);
 }
 
 // A power of two near the largest |d|, |e|.
@@ -410,15 +345,16 @@ __device__ inline double pow2_scale(double mx, bool inverse) {
     return ldexp(1.0, inverse ? -ex : ex);
 }
 
-__global__ __launch_bounds__(256) void dc_leaf_kernel(DcWork w, int depth) {
+__global__ __launch_bounds__(LNT) void dc_leaf_kernel(DcWork w, int depth) {
     __shared__ LeafLDS L;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6, n = w.n;
     double mx = 0.0;
-    for (int i = t; i < n; i += 256) mx = fmax(mx, fmax(fabs(w.d[i]), i + 1 < n ? fabs(w.e[i]) : 0.0));
+    for (int i = t; i < n; i += LNT) mx = fmax(mx, fmax(fabs(w.d[i]), i + 1 < n ? fabs(w.e[i]) : 0.0));
     mx = wave_max_nonneg(mx);
     if (lane == 0) L.red[wv] = mx;
     __syncthreads();
-    mx = fmax(fmax(L.red[0], L.red[1]), fmax(L.red[2], L.red[3]));
+    mx = L.red[0];
+    for (int q = 1; q < LNW; ++q) mx = fmax(mx, L.red[q]);
     const double inv = pow2_scale(mx, true);
     if (blockIdx.x == 0 && t == 0) {
         *w.scale = pow2_scale(mx, false);
@@ -430,47 +366,119 @@ __global__ __launch_bounds__(256) void dc_leaf_kernel(DcWork w, int depth) {
         L.d[t] = w.d[a0 + t] * inv;
         L.e[t] = a0 + t + 1 < n ? w.e[a0 + t] * inv : 0.0;
     }
-    for (int x = t; x < 2 * LEAF * (LEAF + 1); x += 256) (&L.U[0][0][0])[x] = 0.0;
-    for (int x = t; x < 2 * (LEAF + 1) * (LEAF + 2); x += 256) (&L.V[0][0][0])[x] = 0.0;
+    for (int x = t; x < 2 * LEAF * (LEAF + 1); x += LNT) (&L.U[0][0][0])[x] = 0.0;
+    for (int x = t; x < 2 * (LEAF + 1) * (LEAF + 2); x += LNT) (&L.V[0][0][0])[x] = 0.0;
     __syncthreads();
     int top = 0;
     for (int sz = len; sz > 1; sz /= 2) ++top;
     int cur = 0;
     for (int lv = top; lv >= 0; --lv) {
-        for (int q = wv; q < (1 << lv); q += 4) {
+        for (int q = wv; q < (1 << lv); q += LNW) {
             const Node nd = node_at(0, len, lv, q);
-            leaf_merge(L, cur, nd.a, nd.m, nd.b, a0 + nd.b < n, wv, lane);
-            wave_fence();
+            leaf_deflate(L, cur, nd.a, nd.m, nd.b, a0 + nd.b < n, lane);
+        }
+        __syncthreads();
+        // row r = t / 32 (a root, then a pole, then a root again), lane j a pole
+        const int r = t >> 5, j = t & 31;
+        const bool mine = r < len && L.kind[r] == ROW_PRODUCT;
+        const int a = mine ? L.na[r] : 0, K = mine ? L.nk[r] : 0, i = r - a;
+        const bool pole = mine && j < K;
+        const double dj = pole ? L.dd[a + j] : 0.0, zj = pole ? L.zz[a + j] : 0.0, z2 = zj * zj;
+        double x = 0.0, dc = 0.0;
+        if (mine && K > 1) {
+            const bool last = i == K - 1;
+            const double di = L.dd[a + i], di1 = last ? 0.0 : L.dd[a + i + 1];
+            double lo = 0.0, hi;
+            dc = di;
+            if (last) {
+                hi = half_sum(z2) * (1.0 + 8.0 * EPS);
+                x = 0.5 * hi;
+            } else {
+                const double mid = 0.5 * (di1 - di) * (di1 + di);
+                const double f = 1.0 + half_sum(pole ? z2 * recip((dj - di) * (dj + di) - mid) : 0.0);
+                hi = mid;
+                x = mid;
+                if (!(f >= 0.0)) {
+                    dc = di1;
+                    lo = -mid;
+                    hi = 0.0;
+                    x = -mid;
+                }
+            }
+            const double del = (dj - dc) * (dj + dc);
+            const double da0 = (di - dc) * (di + dc), db0 = last ? 0.0 : (di1 - dc) * (di1 + dc);
+            for (int it = 0; it < ROOT_ITERS; ++it) {
+                const double rc = pole ? recip(del - x) : 0.0, tt = z2 * rc, t2 = tt * rc;
+                const double psi = half_sum(j <= i ? tt : 0.0), dpsi = half_sum(j <= i ? t2 : 0.0);
+                const double phi = half_sum(j > i ? tt : 0.0), dphi = half_sum(j > i ? t2 : 0.0);
+                if (root_step(x, lo, hi, psi, dpsi, phi, dphi, da0 - x, last ? 0.0 : db0 - x, last)) break;
+            }
+            if (j == 0) {
+                L.sg[cur ^ 1][r] = sigma_of(dc, x);
+                L.x[r] = x;
+                L.dc[r] = dc;
+            }
+        } else if (mine && j == 0) {
+            L.sg[cur ^ 1][r] = fabs(zj);
+        }
+        __syncthreads();
+        if (mine && K > 1) {
+            // z of pole i, lane j a root
+            const double di = L.dd[a + i];
+            double f = 1.0;
+            if (pole) {
+                f = L.x[a + j] - (di - L.dc[a + j]) * (di + L.dc[a + j]);
+                if (j < K - 1) {
+                    const double o = j < i ? dj : L.dd[a + j + 1];
+                    f *= recip((o - di) * (o + di));
+                }
+            }
+            f = sqrt(fabs(half_product(f)));
+            if (j == 0) L.zh[r] = L.zz[r] < 0.0 ? -f : f;
+        }
+        __syncthreads();
+        if (mine) {
+            double u = 1.0, v = zj < 0.0 ? -1.0 : 1.0;
+            if (K > 1) {
+                v = pole ? L.zh[a + j] * recip((dj - dc) * (dj + dc) - x) : 0.0;
+                u = j == 0 ? -1.0 : dj * v;
+                u *= 1.0 / sqrt(half_sum(u * u));
+                v *= 1.0 / sqrt(half_sum(v * v));
+            }
+            if (pole) {
+                L.Us[r][j] = u;
+                L.Vs[r][j] = v;
+            }
         }
         __syncthreads();
         const int W = len + 1;
         const bool null = a0 + len < n;
-        for (int x = t; x < W * W; x += 256) {
-            const int r = x / W, c = x % W;
-            if (r == len && !null) continue;
-            const int a = L.na[r], b = L.nb[r], kind = L.kind[r];
+        for (int e = t; e < W * W; e += LNT) {
+            const int rr = e / W, c = e % W;
+            if (rr == len && !null) continue;
+            const int ra = L.na[rr], rb = L.nb[rr], kind = L.kind[rr];
             double u = 0.0, v = 0.0;
-            if (c >= a && c <= b) {
+            if (c >= ra && c <= rb) {
                 if (kind == ROW_PRODUCT) {
-                    const int K = L.nk[r];
-                    for (int j = 0; j < K; ++j) {
-                        const int g = L.und[a + j];
-                        if (c < b) u += L.Us[r][j] * L.U[cur][g][c];
-                        v += L.Vs[r][j] * L.V[cur][g][c];
+                    const int k = L.nk[rr];
+                    for (int q = 0; q < k; ++q) {
+                        const int g = L.und[ra + q];
+                        u += L.Us[rr][q] * L.U[cur][g][c];
+                        v += L.Vs[rr][q] * L.V[cur][g][c];
                     }
                 } else {
-                    const int g = L.src[r];
-                    if (kind == ROW_COPY && c < b) u = L.U[cur][g][c];
+                    const int g = L.src[rr];
+                    if (kind == ROW_COPY) u = L.U[cur][g][c];
                     v = L.V[cur][g][c];
                 }
             }
-            if (r < len && c < len) L.U[cur ^ 1][r][c] = u;
-            L.V[cur ^ 1][r][c] = v;
+            if (rr < len && c < len) L.U[cur ^ 1][rr][c] = c < rb ? u : 0.0;
+            L.V[cur ^ 1][rr][c] = v;
         }
         __syncthreads();
         cur ^= 1;
     }
-    for (int x = t; x < (len + 1) * (len + 1); x += 256) {
+    for (int x = t; x < (len + 1) * (len + 1); x += LNT) {
         const int r = x / (len + 1), c = x % (len + 1);
         if (a0 + r >= n || a0 + c >= n) continue;
         const long at = (long)(a0 + r) * n + a0 + c;
@@ -484,12 +492,12 @@ __global__ __launch_bounds__(256) void dc_leaf_kernel(DcWork w, int depth) {
 // Levels above the subtrees
 // ---------------------------------------------------------------------------
 
-constexpr int PREP_NT = 1024;
 constexpr int PREP_CAP = 2048;      // rows of a node kept in LDS
 
 // Entry s of a node's order (ascending d, the middle row first): act 0 starts
 // an undeflated vector, 1 is deflated as it stands, 2 rotates with the entry
 // before it in its chain, 3 with the middle row (right vectors only).
+template <int PREP_NT>
 __global__ __launch_bounds__(PREP_NT) void dc_prep_kernel(DcWork w, int depth, int cur) {
     __shared__ double lkey[PREP_CAP], lsd[PREP_CAP], lsz[PREP_CAP];
     __shared__ int lrow[PREP_CAP], lact[PREP_CAP], lcl[PREP_CAP];
@@ -532,23 +540,59 @@ __global__ __launch_bounds__(PREP_NT) void dc_prep_kernel(DcWork w, int depth, i
     __syncthreads();
     for (int q = 0; q < PREP_NT / 64; ++q) mx = fmax(mx, red[q]);
     const double tol = DEFLATE * fmax(mx, fmax(fabs(alpha), fabs(beta)));
-    for (int i = t; i < N; i += PREP_NT) {
-        const int r = a + i;
-        const double v = key[i];
-        int rank = 0;
-        double z;
-        if (r == m) {
-            z = r0;
-            if (!(fabs(z) > tol)) z = z < 0.0 ? -tol : tol;
-        } else {
-            for (int q = 0; q < N; ++q) rank += key[q] < v || (key[q] == v && q < i);
-            // the middle row (key 0) comes first whatever ties with it
-            if (v == 0.0 && i < m - a) ++rank;
-            z = clean(r < m ? alpha * VT[(long)r * n + m] : beta * VT[(long)r * n + m + 1]);
+    // ascending order, the middle row first: a bitonic network over the keys in
+    // LDS (row numbers break ties; pairs up to 64 apart stay in a wavefront)
+    auto zof = [&](int r) {
+        if (r == m) return fabs(r0) > tol ? r0 : (r0 < 0.0 ? -tol : tol);
+        return clean(r < m ? alpha * VT[(long)r * n + m] : beta * VT[(long)r * n + m + 1]);
+    };
+    if (small) {
+        int n2 = 2;
+        while (n2 < N) n2 *= 2;
+        for (int i = t; i < n2; i += PREP_NT) {
+            lrow[i] = i;
+            if (i >= N) key[i] = INFINITY;
+            else if (a + i == m) key[i] = -1.0;
         }
-        sd[rank] = v;
-        sz[rank] = z;
-        srow[rank] = r;
+        __syncthreads();
+        for (int k = 2; k <= n2; k *= 2)
+            for (int h = k / 2; h > 0; h /= 2) {
+                if (h > 64) __syncthreads();
+                for (int p = t; p < n2 / 2; p += PREP_NT) {
+                    const int i = 2 * p - (p & (h - 1)), q = i + h;
+                    const double x = key[i], y = key[q];
+                    const int rx = lrow[i], rq = lrow[q];
+                    const bool up = (i & k) == 0, gt = x > y || (x == y && rx > rq);
+                    if (gt == up) {
+                        key[i] = y;
+                        key[q] = x;
+                        lrow[i] = rq;
+                        lrow[q] = rx;
+                    }
+                }
+                if (h > 64) __syncthreads();
+                else wave_fence();
+            }
+        __syncthreads();
+        for (int i = t; i < N; i += PREP_NT) {
+            const int r = a + lrow[i];
+            sd[i] = fmax(key[i], 0.0);
+            sz[i] = zof(r);
+            lrow[i] = r;
+        }
+    } else {
+        for (int i = t; i < N; i += PREP_NT) {
+            const int r = a + i;
+            const double v = key[i];
+            int rank = 0;
+            if (r != m) {
+                for (int q = 0; q < N; ++q) rank += key[q] < v || (key[q] == v && q < i);
+                if (v == 0.0 && i < m - a) ++rank;      // the middle row (key 0) comes first whatever ties with it
+            }
+            sd[rank] = v;
+            sz[rank] = zof(r);
+            srow[rank] = r;
+        }
     }
     __syncthreads();
     // survivors with d above the tolerance, compacted in order
@@ -922,14 +966,15 @@ DcWork dc_carve(double* ws, int n, const double* d, const double* e) {
 int bidiagonal_svd(const DcWork& w, hipStream_t s, LaunchProbe* probe) {
     const int n = w.n, depth = dc_depth(n);
     bool timed = probe && probe->begin(PK_MERGE, s);
-    hipLaunchKernelGGL(dc_leaf_kernel, dim3(1 << depth), dim3(256), 0, s, w, depth);
+    hipLaunchKernelGGL(dc_leaf_kernel, dim3(1 << depth), dim3(LNT), 0, s, w, depth);
     if (timed) probe->end(PK_MERGE, s);
     int cur = 0;
     for (int dep = depth - 1; dep >= 0; --dep) {
         const int nodes = 1 << dep, most = (n >> dep) + 1, waves = (n + 3) / 4;
         const int nch = (most + 255) / 256;
         timed = probe && probe->begin(PK_MERGE, s);
-        hipLaunchKernelGGL(dc_prep_kernel, dim3(nodes), dim3(PREP_NT), 0, s, w, dep, cur);
+        if (most <= 256) hipLaunchKernelGGL((dc_prep_kernel<256>), dim3(nodes), dim3(256), 0, s, w, dep, cur);
+        else hipLaunchKernelGGL((dc_prep_kernel<1024>), dim3(nodes), dim3(1024), 0, s, w, dep, cur);
         hipLaunchKernelGGL(dc_roots_kernel, dim3(waves + n * nch), dim3(256), 0, s, w, dep, cur, nch);
         hipLaunchKernelGGL(dc_zhat_kernel, dim3(waves), dim3(256), 0, s, w, dep);
         hipLaunchKernelGGL(dc_small_vectors_kernel, dim3(waves), dim3(256), 0, s, w, dep, cur);

@@ -262,7 +262,7 @@ void householder_rows(double* Z, int p, int q, int ld, double* ws, hipStream_t s
 // Bidiagonalisation A = Q B Z^T of a block (bidiag.hip).
 struct BdWork {
     int P, N;                 // rows >= columns
-    double *A, *VQ, *VP, *TQ, *TP, *col, *row, *tauq, *taup;
+    double *A, *VQ, *VP, *TQ, *TP, *part, *p, *tauq, *taup;
     double *d, *e;            // B: diagonal and superdiagonal
 };
 size_t bd_workspace(int P, int N);            // doubles

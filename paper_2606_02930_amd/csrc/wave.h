@@ -9,10 +9,16 @@
 namespace ite {
 
 // One DPP data movement on both halves of a double; lanes of rows outside
-// ROWS receive 0.
+// ROWS receive 0.  (With all rows in ROWS and a control that has a source for
+// every lane nothing is left to fill, and no register is zeroed for it.)
 template <int CTRL, int ROWS>
 __device__ inline double dpp_move(double v) {
     const long long bits = __double_as_longlong(v);
+    if constexpr (ROWS == 0xf) {
+        const int lo = __builtin_amdgcn_mov_dpp((int)bits, CTRL, 0xf, 0xf, true);
+        const int hi = __builtin_amdgcn_mov_dpp((int)(bits >> 32), CTRL, 0xf, 0xf, true);
+        return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+    }
     const int lo = __builtin_amdgcn_update_dpp(0, (int)bits, CTRL, ROWS, 0xf, false);
     const int hi = __builtin_amdgcn_update_dpp(0, (int)(bits >> 32), CTRL, ROWS, 0xf, false);
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
@@ -47,6 +53,20 @@ __device__ inline double wave_max_nonneg(double v) {
     v = fmax(v, dpp_move<0x142, 0xa>(v));
     v = fmax(v, dpp_move<0x143, 0xc>(v));
     return lane_value(v, 63);
+}
+
+// 1 / x and 1 / sqrt(x) to rounding for normal x away from the ends of the
+// range: the hardware estimate (relative error below 1e-7) and two Newton
+// steps.
+__device__ inline double recip(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+__device__ inline double recip_sqrt(double x) {
+    double r = __builtin_amdgcn_rsq(x);
+    r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
+    return fma(0.5 * r, fma(-x * r, r, 1.0), r);
 }
 
 }  // namespace ite
