@@ -405,7 +405,7 @@ int ite_evolve_grid(ite_mps* psi, const ite_mpo* H, const double* taus, int n_ta
  * end, at each site, the tensor T_j of O_j psi_j contracted with what is
  * already kept to its right, its reduced density matrix rho_j = T^T F_j T
  * (over the site index and the kept right index), and the eigenvectors of
- * rho_j's largest eigenvalues (from the split's FP64 SVD) as the new
+ * rho_j's largest eigenvalues (one-sided Jacobi, FP64) as the new
  * right-orthonormal site tensor; the kept count follows the split's rule
  * (cutoff, tie_rel) on the square roots of the eigenvalues, at most
  * min(chi_max, the bond's largest possible rank); site 1 keeps the rest
@@ -582,8 +582,7 @@ int ite_debug_env_update(ite_ctx* ctx, int dir, int Dxa, int Dya, int Dxb, int D
                          const double* Y, double* Eout);
 
 /* Truncated SVD split of theta [Dl][d1][d2][Dr] seen as an (Dl d1) x (d2 Dr)
- * matrix, by Householder bidiagonalisation and divide and conquer (one-sided
- * Jacobi up to 32 x 32): dir = 0 gives A1 = U, A2 = S V^T; dir = 1 gives
+ * matrix, by Householder bidiagonalisation and divide and conquer: dir = 0 gives A1 = U, A2 = S V^T; dir = 1 gives
  * A1 = U S, A2 = V^T.  A1 [Dl][d1][k], A2 [k][d2][Dr] (device, capacity
  * min(rows, cols, chi_max) columns).  sigma_out (host, nullable, capacity
  * min(rows, cols)) receives all singular values in descending order; *k_out

@@ -61,16 +61,19 @@ __device__ inline Refl reflector(double alpha, double sg) {
     }
     return r;
 }
+// The rows past the last reflector of either side.
+__device__ inline void clear_padding(int P, int N, double* VQ, double* VP, long id, long all) {
+    for (long i = (long)N * pad16(P) + id; i < (long)pad16(N) * pad16(P); i += all) VQ[i] = 0.0;
+    for (long i = (long)(N - 1) * pad16(N) + id; i < (long)pad16(N) * pad16(N); i += all) VP[i] = 0.0;
+}
+
 // A <- theta (P x N), or theta^T when tr (theta then N x P).
 __global__ __launch_bounds__(256) void bd_load_kernel(const double* __restrict__ theta, int P, int N, int tr,
                                                       double* __restrict__ A, double* __restrict__ VQ,
                                                       double* __restrict__ VP) {
     __shared__ double tile[32][33];
-    // the rows past the last reflector of either side
-    const long id = ((long)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
-    const long all = (long)gridDim.x * gridDim.y * 256;
-    for (long i = (long)N * pad16(P) + id; i < (long)pad16(N) * pad16(P); i += all) VQ[i] = 0.0;
-    for (long i = (long)(N - 1) * pad16(N) + id; i < (long)pad16(N) * pad16(N); i += all) VP[i] = 0.0;
+    clear_padding(P, N, VQ, VP, ((long)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x,
+                  (long)gridDim.x * gridDim.y * 256);
     const int x = threadIdx.x & 31, y0 = threadIdx.x >> 5;
     const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;      // of A
     if (tr) {
@@ -406,8 +409,10 @@ __device__ __forceinline__ void bd_tail_from(const BdWork& b, int c0, double (&a
     }
 }
 
+// c0 = 0: the block is theta itself (tr: its transpose), and the padding rows of
+// the reflectors are cleared here.
 template <int NW, int RS, int CS>
-__global__ __launch_bounds__(64 * NW) void bd_tail_kernel(BdWork b, int c0) {
+__global__ __launch_bounds__(64 * NW) void bd_tail_kernel(BdWork b, int c0, const double* __restrict__ theta, int tr) {
     constexpr int RW = 4 * NW;
     static_assert(RW % 16 == 0 && CS % 4 == 0 && 16 * CS <= 64 * NW, "slots");
     __shared__ TailLDS<NW, RS, CS> L;
@@ -419,8 +424,11 @@ __global__ __launch_bounds__(64 * NW) void bd_tail_kernel(BdWork b, int c0) {
 #pragma unroll
         for (int u = 0; u < CS; ++u) {
             const int i = ry + RW * s, j = cx + 16 * u;
-            a[s][u] = (i < R && j < C) ? b.A[(long)(c0 + i) * b.N + c0 + j] : 0.0;
+            const bool in = i < R && j < C;
+            if (theta) a[s][u] = in ? theta[tr ? (long)j * b.P + i : (long)i * b.N + j] : 0.0;
+            else a[s][u] = in ? b.A[(long)(c0 + i) * b.N + c0 + j] : 0.0;
         }
+    if (theta) clear_padding(b.P, b.N, b.VQ, b.VP, t, 64 * NW);
     bd_tail_from<NW, RS, CS, 0>(b, c0, a, L);
 }
 
@@ -698,8 +706,6 @@ BdWork bd_carve(double* ws, int P, int N) {
 
 void bidiagonalise(const BdWork& w, const double* theta, bool tr, hipStream_t s, LaunchProbe* probe) {
     const int P = w.P, N = w.N;
-    hipLaunchKernelGGL(bd_load_kernel, dim3((N + 31) / 32, (P + 31) / 32), dim3(256), 0, s, theta, P, N, (int)tr, w.A,
-                       w.VQ, w.VP);
     auto step = [&](int c, bool start) {
         const bool timed = probe && probe->begin(PK_BIDIAG, s);
         const int len = N - c - 1, g = (P + BS_NW - 1) / BS_NW;
@@ -713,7 +719,12 @@ void bidiagonalise(const BdWork& w, const double* theta, bool tr, hipStream_t s,
                                         (c + 1) / BS_NW, g);
         if (timed) probe->end(PK_BIDIAG, s);
     };
-    if (P > BD_TAIL) step(-1, true);
+    const bool whole = P <= BD_TAIL;
+    if (!whole) {
+        hipLaunchKernelGGL(bd_load_kernel, dim3((N + 31) / 32, (P + 31) / 32), dim3(256), 0, s, theta, P, N, (int)tr,
+                           w.A, w.VQ, w.VP);
+        step(-1, true);
+    }
     for (int c = 0; c < N; ++c) {
         const int len = P - c;
         if (len > BD_TAIL) {
@@ -721,9 +732,13 @@ void bidiagonalise(const BdWork& w, const double* theta, bool tr, hipStream_t s,
             continue;
         }
         const bool timed = probe && probe->begin(PK_BIDIAG, s);
-        if (len <= 64) hipLaunchKernelGGL((bd_tail_kernel<4, 4, 4>), dim3(1), dim3(256), 0, s, w, c);
-        else if (len <= 128) hipLaunchKernelGGL((bd_tail_kernel<4, 8, 8>), dim3(1), dim3(256), 0, s, w, c);
-        else hipLaunchKernelGGL((bd_tail_kernel<8, 6, 12>), dim3(1), dim3(512), 0, s, w, c);
+        const double* th = whole ? theta : nullptr;
+#define ITE_TAIL(NW, RS, CS) \
+    hipLaunchKernelGGL((bd_tail_kernel<NW, RS, CS>), dim3(1), dim3(64 * NW), 0, s, w, c, th, (int)tr)
+        if (len <= 64) ITE_TAIL(4, 4, 4);
+        else if (len <= 128) ITE_TAIL(4, 8, 8);
+        else ITE_TAIL(8, 6, 12);
+#undef ITE_TAIL
         if (timed) probe->end(PK_BIDIAG, s);
         break;
     }

@@ -74,6 +74,33 @@ __device__ inline Node node_of(int n, int depth, int g, int& q) {
 
 __device__ inline double clean(double v) { return v == v ? v : 0.0; }
 
+// r = sqrt(x^2 + y^2), c = x / r, s = y / r for values scaled to at most about 1
+// (both below 1e-150: as zeros).
+__device__ inline void plane_rotation(double x, double y, double& r, double& c, double& s) {
+    const double q = x * x + y * y;
+    if (q > 1e-300) {
+        const double i = recip_sqrt(q);
+        c = x * i;
+        s = y * i;
+        r = q * i;
+    } else {
+        c = 1.0;
+        s = 0.0;
+        r = q == q ? 0.0 : q;
+    }
+}
+
+// One Newton step: a relative error of about 1e-14, for the steps of an
+// iteration that checks its own result.
+__device__ inline double quick_recip(double x) {
+    const double r = __builtin_amdgcn_rcp(x);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+__device__ inline double quick_rsqrt(double x) {
+    const double r = __builtin_amdgcn_rsq(x);
+    return fma(0.5 * r, fma(-x * r, r, 1.0), r);
+}
+
 // One update of a root of f(x) = 1 + psi(x) + phi(x): psi (the poles up to
 // da = pole - x) and phi (those from db on) are replaced by r + s / (pole - x)
 // with their values and slopes at x (Bunch, Nielsen and Sorensen); kept inside
@@ -87,13 +114,13 @@ __device__ inline bool root_step(double& x, double& lo, double& hi, double psi, 
     double eta;
     const double s = dpsi * da * da;
     if (last) {
-        eta = da + s / (1.0 + (psi - dpsi * da));
+        eta = da + s * quick_recip(1.0 + (psi - dpsi * da));
     } else {
         const double tt = dphi * db * db;
         const double cc = 1.0 + (psi - dpsi * da) + (phi - dphi * db);
         const double A = cc * (da + db) + s + tt, B = da * db * f;
-        const double disc = sqrt(fmax(A * A - 4.0 * cc * B, 0.0));
-        eta = A > 0.0 ? 2.0 * B / (A + disc) : (A - disc) / (2.0 * cc);
+        const double q = fmax(A * A - 4.0 * cc * B, 1e-300), disc = q * quick_rsqrt(q);
+        eta = A > 0.0 ? 2.0 * B * quick_recip(A + disc) : (A - disc) * quick_recip(2.0 * cc);
     }
     double xn = x + eta;
     if (!(xn > lo && xn < hi)) xn = 0.5 * (lo + hi);
@@ -102,6 +129,24 @@ __device__ inline bool root_step(double& x, double& lo, double& hi, double psi, 
     return done;
 }
 constexpr int ROOT_ITERS = 100;
+
+// Start of a root between the poles di < di1 from f at the middle of their
+// squares: the nearer pole dc, the bracket, and the root with the other poles'
+// sum held at its value there.
+__device__ inline void first_root(double f, double mid, double zi2, double zn2, double di, double di1, double& x,
+                                  double& lo, double& hi, double& dc) {
+    // at the middle the two poles' terms are -zi2 / mid and zn2 / mid
+    const double im = quick_recip(mid), cc = f + (zi2 - zn2) * im;
+    const bool left = f >= 0.0;
+    dc = left ? di : di1;
+    lo = left ? 0.0 : -mid;
+    hi = left ? mid : 0.0;
+    const double p0 = left ? 0.0 : -2.0 * mid, p1 = left ? 2.0 * mid : 0.0;
+    const double A = cc * (p0 + p1) + zi2 + zn2, B = zi2 * p1 + zn2 * p0;
+    const double q = fmax(A * A - 4.0 * cc * B, 1e-300), disc = q * quick_rsqrt(q);
+    x = A > 0.0 ? 2.0 * B * quick_recip(A + disc) : (A - disc) * quick_recip(2.0 * cc);
+    if (!(x > lo && x < hi)) x = left ? mid : -mid;
+}
 
 // sigma from its pole and distance.
 __device__ inline double sigma_of(double dc, double x) {
@@ -114,10 +159,12 @@ __device__ inline double sigma_of(double dc, double x) {
 // ---------------------------------------------------------------------------
 
 // A level of a subtree in three steps: a wavefront a node sorts and deflates;
-// then 32 lanes a row find the roots, recompute z and form the vectors (a pole
-// each: a subtree has at most 32 rows, so the workgroup holds every row of
-// the level whatever its nodes are); then a thread an entry of the products.
-constexpr int LNT = LEAF * 32;
+// eight lanes a row find the roots, recompute z and form the vectors, four poles
+// a lane (one wavefront a SIMD: more would only wait for each other's issue
+// slots); eight wavefronts multiply.  Every row of the level is a row of one
+// LEAF x LEAF matrix of weights: the small vectors of its node, or a one for a
+// deflated row or a null vector, against source rows gathered by `src`.
+constexpr int LNT = 1024;
 constexpr int LNW = LNT / 64;
 
 struct LeafLDS {
@@ -126,10 +173,11 @@ struct LeafLDS {
     double sg[2][LEAF + 1], d[LEAF], e[LEAF];
     // a node's entries from its first row on: the order (scratch of its
     // wavefront), then poles, z and z recomputed
-    double key[LEAF], sd[LEAF], sz[LEAF], cr[LEAF], sr[LEAF], dd[LEAF], zz[LEAF], zh[LEAF], x[LEAF], dc[LEAF];
+    double sd[LEAF], sz[LEAF], cr[LEAF], sr[LEAF], dd[LEAF], zz[LEAF], zh[LEAF], x[LEAF], dc[LEAF];
     int srow[LEAF], prev[LEAF];
-    int und[LEAF];                 // source row of the node's pole i: und[a + i]
-    int kind[LEAF + 1], src[LEAF + 1], na[LEAF + 1], nb[LEAF + 1], nk[LEAF];
+    int src[LEAF];                 // source row of column c of the weights
+    int kind[LEAF], na[LEAF], nk[LEAF];
+    int lasta;                     // first row of the node whose null vector is row LEAF
     double red[LNW];
 };
 enum { ROW_PRODUCT = 0, ROW_COPY = 1, ROW_NULL = 2 };
@@ -141,15 +189,18 @@ __device__ inline void wave_fence() {
 
 // Sort and deflation of one node of a subtree by one wavefront (local rows, at
 // most 32).  `null`: column b exists.
-__device__ __forceinline__ void leaf_deflate(LeafLDS& L, int cur, int a, int m, int b, bool null, int lane) {
+__device__ __forceinline__ void leaf_deflate(LeafLDS& L, int cur, int a, int m, int b, bool null,
+                                             int lane) {
     const int N = b - a;
     auto& U = L.U[cur];
     auto& V = L.V[cur];
     if (lane == 0 && null) {
-        L.kind[b] = ROW_NULL;
-        L.src[b] = b;
-        L.na[b] = a;
-        L.nb[b] = b;
+        if (b < LEAF) {
+            L.kind[b] = ROW_NULL;
+            L.src[b] = b;
+        } else {
+            L.lasta = a;
+        }
     }
     if (N == 0) {
         if (null && lane <= LEAF) V[b][lane] = lane == b ? 1.0 : 0.0;
@@ -157,19 +208,13 @@ __device__ __forceinline__ void leaf_deflate(LeafLDS& L, int cur, int a, int m, 
     }
     if (lane < N) {
         L.na[a + lane] = a;
-        L.nb[a + lane] = b;
         L.kind[a + lane] = ROW_COPY;
         L.nk[a + lane] = 0;
     }
     const double alpha = L.d[m], beta = L.e[m];
     if (N == 1) {
-        const double r = null ? hypot(alpha, beta) : fabs(alpha);
-        double c = 1.0, s = 0.0;
-        if (!null) c = alpha < 0.0 ? -1.0 : 1.0;
-        else if (r > 0.0) {
-            c = alpha / r;
-            s = beta / r;
-        }
+        double r = fabs(alpha), c = alpha < 0.0 ? -1.0 : 1.0, s = 0.0;
+        if (null) plane_rotation(alpha, beta, r, c, s);
         if (lane == 0) {
             U[a][a] = 1.0;
             V[a][a] = c;
@@ -185,13 +230,7 @@ __device__ __forceinline__ void leaf_deflate(LeafLDS& L, int cur, int a, int m, 
     }
     const double x0 = alpha * V[m][m], y0 = null ? beta * V[b][m + 1] : 0.0;
     double r0 = x0, c0 = 1.0, s0 = 0.0;
-    if (null) {
-        r0 = hypot(x0, y0);
-        if (r0 > 0.0) {
-            c0 = x0 / r0;
-            s0 = y0 / r0;
-        }
-    }
+    if (null) plane_rotation(x0, y0, r0, c0, s0);
     double zv = 0.0, dv = 0.0;
     if (lane < N) {
         const int r = a + lane;
@@ -205,24 +244,22 @@ __device__ __forceinline__ void leaf_deflate(LeafLDS& L, int cur, int a, int m, 
         V[m][c] = c0 * w1 + s0 * w2;
         V[b][c] = c0 * w2 - s0 * w1;
     }
-    double* key = L.key + a;
     double* sd = L.sd + a;
     double* sz = L.sz + a;
     int* srow = L.srow + a;
     if (lane < N) {
         U[m][a + lane] = a + lane == m ? 1.0 : 0.0;
-        key[lane] = dv;
     }
     const double nrm = fmax(wave_max_nonneg(dv), fmax(fabs(clean(alpha)), fabs(clean(beta))));
     const double tol = DEFLATE * nrm;
     wave_fence();
     const int lm = m - a;
+    int rank = lane == lm ? 0 : 1;
+    for (int t = 0; t < N; ++t) {
+        const double k = lane_value(dv, t);
+        if (lane != lm && t != lm) rank += k < dv || (k == dv && t < lane);
+    }
     if (lane < N) {
-        int rank = lane == lm ? 0 : 1;
-        for (int t = 0; t < N; ++t) {
-            const double k = key[t];
-            if (lane != lm && t != lm) rank += k < dv || (k == dv && t < lane);
-        }
         sd[rank] = dv;
         sz[rank] = zv;
         srow[rank] = a + lane;
@@ -263,27 +300,21 @@ __device__ __forceinline__ void leaf_deflate(LeafLDS& L, int cur, int a, int m, 
             if (lane == 0) {
                 for (unsigned long long q = m3; q; q &= q - 1) {
                     const int t = __ffsll((long long)q) - 1;
-                    const double zt = sz[t], tau = hypot(z, zt);
-                    L.cr[a + t] = z / tau;
-                    L.sr[a + t] = zt / tau;
-                    z = tau;
+                    plane_rotation(z, sz[t], z, L.cr[a + t], L.sr[a + t]);
                 }
             } else if (m2) {
                 const unsigned long long later = ms & ~below & ~(1ull << lane);
                 for (unsigned long long q = later; q; q &= q - 1) {
                     const int t = __ffsll((long long)q) - 1;
                     if (!((m2 >> t) & 1)) break;
-                    const double zt = sz[t], tau = hypot(z, zt);
-                    L.cr[a + t] = zt / tau;
-                    L.sr[a + t] = z / tau;
-                    z = tau;
+                    plane_rotation(sz[t], z, z, L.cr[a + t], L.sr[a + t]);
                     dl = sd[t];
                     last = srow[t];
                 }
             }
             L.dd[a + slot] = dl;
             L.zz[a + slot] = z;
-            L.und[a + slot] = last;
+            L.src[a + slot] = last;
             L.kind[a + slot] = ROW_PRODUCT;
         } else {
             const int o = a + K + (lane - slot);      // lane - slot deflated entries before this one
@@ -321,20 +352,138 @@ __device__ __forceinline__ void leaf_deflate(LeafLDS& L, int cur, int a, int m, 
     }
 }
 
-// Sums and products over the 32 lanes of a half wavefront, to all of them.
-__device__ inline double half_sum(double v) {
+// Sums and products over groups of eight lanes, to all of them.
+__device__ inline double sum8(double v) {
     v += dpp_move<0xB1, 0xf>(v);
     v += dpp_move<0x4E, 0xf>(v);
-    v += dpp_move<0x141, 0xf>(v);
-    v += dpp_move<0x140, 0xf>(v);
-    return v + __shfl_xor(v, 16, 32);
+    return v + dpp_move<0x141, 0xf>(v);
 }
-__device__ inline double half_product(double v) {
+__device__ inline double product8(double v) {
     v *= dpp_move<0xB1, 0xf>(v);
     v *= dpp_move<0x4E, 0xf>(v);
-    v *= dpp_move<0x141, 0xf>(v);
-    v *= dpp_move<0x140, 0xf>(v);
-    return v * __shfl_xor(v, 16, 32);
+    return v * dpp_move<0x141, 0xf>(v);
+}
+
+// Roots, recomputed z and the rows of weights of a level whose nodes have at
+// most 8 PL rows: row r (a root, then a pole, then a root again), poles j0,
+// j0 + 8, ...
+template <int PL>
+__device__ __forceinline__ void leaf_vectors(LeafLDS& L, int cur, int len, int rows) {
+    const int t = threadIdx.x, r = t >> 3, j0 = t & 7;
+    const bool mine = t < 8 * LEAF && r < len && L.kind[r] == ROW_PRODUCT;
+    const int a = mine ? L.na[r] : 0, K = mine ? L.nk[r] : 0, i = r - a;
+    double dj[PL], z[PL], x = 0.0, dc = 0.0;
+    if (mine) {
+#pragma unroll
+        for (int q = 0; q < PL; ++q) {
+            const int j = j0 + 8 * q;
+            dj[q] = j < K ? L.dd[a + j] : 0.0;
+            z[q] = j < K ? L.zz[a + j] : 0.0;
+        }
+        if (K > 1) {
+            const bool last = i == K - 1;
+            const double di = L.dd[a + i], di1 = last ? 0.0 : L.dd[a + i + 1];
+            // poles up to i and after i by factors of one and zero
+            double z2[PL], del[PL], lower[PL], upper[PL];
+#pragma unroll
+            for (int q = 0; q < PL; ++q) {
+                z2[q] = z[q] * z[q];
+                lower[q] = j0 + 8 * q <= i ? 1.0 : 0.0;
+                upper[q] = 1.0 - lower[q];
+            }
+            double lo = 0.0, hi;
+            dc = di;
+            if (last) {
+                double tot = z2[0];
+#pragma unroll
+                for (int q = 1; q < PL; ++q) tot += z2[q];
+                hi = sum8(tot) * (1.0 + 8.0 * EPS);
+                x = 0.5 * hi;
+            } else {
+                const double mid = 0.5 * (di1 - di) * (di1 + di), zi = L.zz[a + i], zn = L.zz[a + i + 1];
+                double f = 0.0;
+#pragma unroll
+                for (int q = 0; q < PL; ++q)
+                    f += z2[q] * recip(j0 + 8 * q < K ? (dj[q] - di) * (dj[q] + di) - mid : 1.0);
+                first_root(1.0 + sum8(f), mid, zi * zi, zn * zn, di, di1, x, lo, hi, dc);
+            }
+#pragma unroll
+            for (int q = 0; q < PL; ++q) del[q] = j0 + 8 * q < K ? (dj[q] - dc) * (dj[q] + dc) : 1e100;
+            const double da0 = (di - dc) * (di + dc), db0 = last ? 0.0 : (di1 - dc) * (di1 + dc);
+            for (int it = 0; it < ROOT_ITERS; ++it) {
+                double psi = 0.0, dpsi = 0.0, phi = 0.0, dphi = 0.0;
+#pragma unroll
+                for (int q = 0; q < PL; ++q) {
+                    const double rc = recip(del[q] - x), tt = z2[q] * rc, t2 = tt * rc;
+                    psi = fma(tt, lower[q], psi);
+                    dpsi = fma(t2, lower[q], dpsi);
+                    phi = fma(tt, upper[q], phi);
+                    dphi = fma(t2, upper[q], dphi);
+                }
+                if (root_step(x, lo, hi, sum8(psi), sum8(dpsi), sum8(phi), sum8(dphi), da0 - x,
+                              last ? 0.0 : db0 - x, last))
+                    break;
+            }
+            if (j0 == 0) {
+                L.sg[cur ^ 1][r] = sigma_of(dc, x);
+                L.x[r] = x;
+                L.dc[r] = dc;
+            }
+        } else if (j0 == 0) {
+            L.sg[cur ^ 1][r] = fabs(z[0]);
+        }
+    }
+    __syncthreads();
+    if (mine && K > 1) {
+        // z of pole i from the roots
+        const double di = L.dd[a + i];
+        double f = 1.0;
+#pragma unroll
+        for (int q = 0; q < PL; ++q) {
+            const int j = j0 + 8 * q;
+            if (j >= K) continue;
+            f *= L.x[a + j] - (di - L.dc[a + j]) * (di + L.dc[a + j]);
+            if (j < K - 1) {
+                const double o = j < i ? dj[q] : L.dd[a + j + 1];
+                f *= recip((o - di) * (o + di));
+            }
+        }
+        f = sqrt(fabs(product8(f)));
+        if (j0 == 0) L.zh[r] = L.zz[r] < 0.0 ? -f : f;
+    }
+    __syncthreads();
+    if (t < 8 * LEAF) {
+        double u[PL], v[PL], nu = 0.0, nv = 0.0;
+#pragma unroll
+        for (int q = 0; q < PL; ++q) {
+            const int j = j0 + 8 * q;
+            u[q] = v[q] = 0.0;
+            if (!mine || j >= K) continue;
+            v[q] = K > 1 ? L.zh[a + j] * recip((dj[q] - dc) * (dj[q] + dc) - x) : (z[0] < 0.0 ? -1.0 : 1.0);
+            u[q] = K > 1 ? (j == 0 ? -1.0 : dj[q] * v[q]) : 1.0;
+            nu += u[q] * u[q];
+            nv += v[q] * v[q];
+        }
+        nu = recip_sqrt(sum8(nu));
+        nv = recip_sqrt(sum8(nv));
+        // zero but for the node's poles, or a one for the row itself
+        const int kind = r < rows ? L.kind[r] : -1;
+#pragma unroll
+        for (int c = 0; c < LEAF; c += 8)
+            if (!mine || c + j0 < a || c + j0 >= a + K) {
+                L.Us[r][c + j0] = kind == ROW_COPY && c + j0 == r ? 1.0 : 0.0;
+                L.Vs[r][c + j0] = (kind == ROW_COPY || kind == ROW_NULL) && c + j0 == r ? 1.0 : 0.0;
+            }
+#pragma unroll
+        for (int q = 0; q < PL; ++q) {
+            const int j = j0 + 8 * q;
+            if (mine && j < K) {
+                L.Us[r][a + j] = u[q] * nu;
+                L.Vs[r][a + j] = v[q] * nv;
+            }
+        }
+    }
+    __syncthreads();
 }
 
 // A power of two near the largest |d|, |e|.
@@ -362,6 +511,10 @@ __global__ __launch_bounds__(LNT) void dc_leaf_kernel(DcWork w, int depth) {
     }
     const Node root = node_at(0, n, depth, blockIdx.x);
     const int a0 = root.a, len = root.b - root.a;
+    if (t < LEAF) {
+        L.kind[t] = ROW_COPY;      // (rows past the subtree's)
+        L.src[t] = 0;
+    }
     if (t < len) {
         L.d[t] = w.d[a0 + t] * inv;
         L.e[t] = a0 + t + 1 < n ? w.e[a0 + t] * inv : 0.0;
@@ -369,6 +522,7 @@ __global__ __launch_bounds__(LNT) void dc_leaf_kernel(DcWork w, int depth) {
     for (int x = t; x < 2 * LEAF * (LEAF + 1); x += LNT) (&L.U[0][0][0])[x] = 0.0;
     for (int x = t; x < 2 * (LEAF + 1) * (LEAF + 2); x += LNT) (&L.V[0][0][0])[x] = 0.0;
     __syncthreads();
+    const int rows = min(LEAF, len + (a0 + len < n));      // with the subtree's null vector
     int top = 0;
     for (int sz = len; sz > 1; sz /= 2) ++top;
     int cur = 0;
@@ -378,102 +532,38 @@ __global__ __launch_bounds__(LNT) void dc_leaf_kernel(DcWork w, int depth) {
             leaf_deflate(L, cur, nd.a, nd.m, nd.b, a0 + nd.b < n, lane);
         }
         __syncthreads();
-        // row r = t / 32 (a root, then a pole, then a root again), lane j a pole
-        const int r = t >> 5, j = t & 31;
-        const bool mine = r < len && L.kind[r] == ROW_PRODUCT;
-        const int a = mine ? L.na[r] : 0, K = mine ? L.nk[r] : 0, i = r - a;
-        const bool pole = mine && j < K;
-        const double dj = pole ? L.dd[a + j] : 0.0, zj = pole ? L.zz[a + j] : 0.0, z2 = zj * zj;
-        double x = 0.0, dc = 0.0;
-        if (mine && K > 1) {
-            const bool last = i == K - 1;
-            const double di = L.dd[a + i], di1 = last ? 0.0 : L.dd[a + i + 1];
-            double lo = 0.0, hi;
-            dc = di;
-            if (last) {
-                hi = half_sum(z2) * (1.0 + 8.0 * EPS);
-                x = 0.5 * hi;
-            } else {
-                const double mid = 0.5 * (di1 - di) * (di1 + di);
-                const double f = 1.0 + half_sum(pole ? z2 * recip((dj - di) * (dj + di) - mid) : 0.0);
-                hi = mid;
-                x = mid;
-                if (!(f >= 0.0)) {
-                    dc = di1;
-                    lo = -mid;
-                    hi = 0.0;
-                    x = -mid;
+        if ((len >> lv) <= 8) leaf_vectors<1>(L, cur, len, rows);
+        else if ((len >> lv) <= 16) leaf_vectors<2>(L, cur, len, rows);
+        else leaf_vectors<LEAF / 8>(L, cur, len, rows);
+        // the products: a 16 x 16 tile of U or V a wavefront; column LEAF of V and
+        // the subtree's null vector by others
+        if (wv < 8) {
+            const int side = wv >> 2, r0 = 16 * ((wv >> 1) & 1), c0 = 16 * (wv & 1), l16 = lane & 15, kg = lane >> 4;
+            if (r0 < rows && c0 < len + 1) {
+                d4_t acc = {0, 0, 0, 0};
+#pragma unroll
+                for (int k = 0; k < LEAF; k += 4) {
+                    const int g = L.src[k + kg];
+                    const double wt = side ? L.Vs[r0 + l16][k + kg] : L.Us[r0 + l16][k + kg];
+                    const double y = side ? L.V[cur][g][c0 + l16] : L.U[cur][g][c0 + l16];
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(wt, y, acc, 0, 0, 0);
+                }
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) {
+                    const int row = r0 + 4 * rr + kg;
+                    if (side) L.V[cur ^ 1][row][c0 + l16] = acc[rr];
+                    else L.U[cur ^ 1][row][c0 + l16] = acc[rr];
                 }
             }
-            const double del = (dj - dc) * (dj + dc);
-            const double da0 = (di - dc) * (di + dc), db0 = last ? 0.0 : (di1 - dc) * (di1 + dc);
-            for (int it = 0; it < ROOT_ITERS; ++it) {
-                const double rc = pole ? recip(del - x) : 0.0, tt = z2 * rc, t2 = tt * rc;
-                const double psi = half_sum(j <= i ? tt : 0.0), dpsi = half_sum(j <= i ? t2 : 0.0);
-                const double phi = half_sum(j > i ? tt : 0.0), dphi = half_sum(j > i ? t2 : 0.0);
-                if (root_step(x, lo, hi, psi, dpsi, phi, dphi, da0 - x, last ? 0.0 : db0 - x, last)) break;
-            }
-            if (j == 0) {
-                L.sg[cur ^ 1][r] = sigma_of(dc, x);
-                L.x[r] = x;
-                L.dc[r] = dc;
-            }
-        } else if (mine && j == 0) {
-            L.sg[cur ^ 1][r] = fabs(zj);
-        }
-        __syncthreads();
-        if (mine && K > 1) {
-            // z of pole i, lane j a root
-            const double di = L.dd[a + i];
-            double f = 1.0;
-            if (pole) {
-                f = L.x[a + j] - (di - L.dc[a + j]) * (di + L.dc[a + j]);
-                if (j < K - 1) {
-                    const double o = j < i ? dj : L.dd[a + j + 1];
-                    f *= recip((o - di) * (o + di));
-                }
-            }
-            f = sqrt(fabs(half_product(f)));
-            if (j == 0) L.zh[r] = L.zz[r] < 0.0 ? -f : f;
-        }
-        __syncthreads();
-        if (mine) {
-            double u = 1.0, v = zj < 0.0 ? -1.0 : 1.0;
-            if (K > 1) {
-                v = pole ? L.zh[a + j] * recip((dj - dc) * (dj + dc) - x) : 0.0;
-                u = j == 0 ? -1.0 : dj * v;
-                u *= 1.0 / sqrt(half_sum(u * u));
-                v *= 1.0 / sqrt(half_sum(v * v));
-            }
-            if (pole) {
-                L.Us[r][j] = u;
-                L.Vs[r][j] = v;
-            }
-        }
-        __syncthreads();
-        const int W = len + 1;
-        const bool null = a0 + len < n;
-        for (int e = t; e < W * W; e += LNT) {
-            const int rr = e / W, c = e % W;
-            if (rr == len && !null) continue;
-            const int ra = L.na[rr], rb = L.nb[rr], kind = L.kind[rr];
-            double u = 0.0, v = 0.0;
-            if (c >= ra && c <= rb) {
-                if (kind == ROW_PRODUCT) {
-                    const int k = L.nk[rr];
-                    for (int q = 0; q < k; ++q) {
-                        const int g = L.und[ra + q];
-                        u += L.Us[rr][q] * L.U[cur][g][c];
-                        v += L.Vs[rr][q] * L.V[cur][g][c];
-                    }
-                } else {
-                    const int g = L.src[rr];
-                    if (kind == ROW_COPY) u = L.U[cur][g][c];
-                    v = L.V[cur][g][c];
-                }
-            }
-            if (rr < len && c < len) L.U[cur ^ 1][rr][c] = c < rb ? u : 0.0;
-            L.V[cur ^ 1][rr][c] = v;
+        } else if (wv < 12) {
+            const int rr = (t - 512) >> 3, j0 = t & 7;
+            double v = 0.0;
+#pragma unroll
+            for (int c = j0; c < LEAF; c += 8) v += L.Vs[rr][c] * L.V[cur][L.src[c]][LEAF];
+            v = sum8(v);
+            if (j0 == 0 && len == LEAF) L.V[cur ^ 1][rr][LEAF] = v;
+        } else if (wv == 12 && len == LEAF && a0 + len < n && lane <= len) {
+            L.V[cur ^ 1][len][lane] = lane >= L.lasta ? L.V[cur][len][lane] : 0.0;
         }
         __syncthreads();
         cur ^= 1;
@@ -521,14 +611,7 @@ __global__ __launch_bounds__(PREP_NT) void dc_prep_kernel(DcWork w, int depth, i
     const double alpha = clean(w.d[m] * inv), beta = m + 1 < n ? clean(w.e[m] * inv) : 0.0;
     const bool null = b < n;
     double r0 = alpha * clean(VT[(long)m * n + m]), c0 = 1.0, s0 = 0.0;
-    if (null) {
-        const double x0 = r0, y0 = beta * clean(VT[(long)b * n + m + 1]);
-        r0 = hypot(x0, y0);
-        if (r0 > 0.0) {
-            c0 = x0 / r0;
-            s0 = y0 / r0;
-        }
-    }
+    if (null) plane_rotation(r0, beta * clean(VT[(long)b * n + m + 1]), r0, c0, s0);
     double mx = 0.0;
     for (int i = t; i < N; i += PREP_NT) {
         const double v = a + i == m ? 0.0 : clean(sg[a + i]);
@@ -643,10 +726,10 @@ __global__ __launch_bounds__(PREP_NT) void dc_prep_kernel(DcWork w, int depth, i
     __syncthreads();
     // chains: z accumulates along them, the values before the last deflate
     auto rotate = [&](int prev, int s, double& z, bool mid) {
-        const double zt = sz[s], tau = hypot(z, zt);
-        w.cr[a + s] = (mid ? z : zt) / tau;
-        w.sr[a + s] = (mid ? zt : z) / tau;
-        z = tau;
+        double c, q;
+        plane_rotation(z, sz[s], z, c, q);
+        w.cr[a + s] = mid ? c : q;
+        w.sr[a + s] = mid ? q : c;
         w.nxt[a + prev] = s;
     };
     if (t == 0) {
@@ -713,18 +796,10 @@ __global__ __launch_bounds__(256) void dc_roots_kernel(DcWork w, int depth, int 
             hi = wave_sum(tot) * (1.0 + 8.0 * EPS);
             x = 0.5 * hi;
         } else {
-            const double mid = 0.5 * (di1 - di) * (di1 + di);
+            const double mid = 0.5 * (di1 - di) * (di1 + di), zi = zz[i], zn = zz[i + 1];
             double f = 0.0;
             for (int j = lane; j < K; j += 64) f += zz[j] * zz[j] * recip((dd[j] - di) * (dd[j] + di) - mid);
-            f = 1.0 + wave_sum(f);
-            hi = mid;
-            x = mid;
-            if (!(f >= 0.0)) {
-                dc = di1;
-                lo = -mid;
-                hi = 0.0;
-                x = -mid;
-            }
+            first_root(1.0 + wave_sum(f), mid, zi * zi, zn * zn, di, di1, x, lo, hi, dc);
         }
         for (int it = 0; it < ROOT_ITERS; ++it) {
             double psi = 0.0, dpsi = 0.0, phi = 0.0, dphi = 0.0;

@@ -439,8 +439,9 @@ static SplitResult truncate(const std::vector<double>& nv, int r, double cutoff,
 // The split by bidiagonalisation and divide and conquer: the singular values
 // come to the host for the truncation, then only the kept vectors are
 // transformed back, straight into the two site tensors.
-static SplitResult split_dc(ite_ctx* c, int dir, int m, int n, const double* theta, int chi_max, double cutoff,
-                            double tie_rel, double* A1, double* A2, std::vector<double>* sigma) {
+SplitResult split(ite_ctx* c, int dir, int Dl, int d1, int d2, int Dr, const double* theta, int chi_max,
+                  double cutoff, double tie_rel, double* A1, double* A2, std::vector<double>* sigma) {
+    const int m = Dl * d1, n = d2 * Dr;
     const bool tr = m < n;
     const int P = std::max(m, n), N = std::min(m, n);
     CtxProbe probe(c);
@@ -471,19 +472,29 @@ static SplitResult split_dc(ite_ctx* c, int dir, int m, int n, const double* the
     return res;
 }
 
-SplitResult split(ite_ctx* c, int dir, int Dl, int d1, int d2, int Dr, const double* theta, int chi_max,
-                  double cutoff, double tie_rel, double* A1, double* A2, std::vector<double>* sigma) {
-    const int m = Dl * d1, n = d2 * Dr;
-    if (std::max(m, n) > 32) return split_dc(c, dir, m, n, theta, chi_max, cutoff, tie_rel, A1, A2, sigma);
+SplitResult split_jacobi(ite_ctx* c, int dir, int m, int n, const double* theta, int chi_max, double cutoff,
+                         double tie_rel, double* A1, double* A2, std::vector<double>* sigma) {
     const int p = dir == 0 ? m : n, q = dir == 0 ? n : m, ld = p + q;
     double* Z = slot_t<double>(c, SL_Z, (size_t)p * ld);
+    size_t ngram = 0, nrot = 0, noff = 0;
+    jacobi_workspace(p, q, &ngram, &nrot, &noff);
+    double* gram = slot_t<double>(c, SL_GRAM, ngram);
+    double* rot = slot_t<double>(c, SL_ROT, nrot);
+    double* off = slot_t<double>(c, SL_OFF, noff);
     double* norms = slot_t<double>(c, SL_NORM, (size_t)p + 16);
     int* perm = slot_t<int>(c, SL_PERM, (size_t)p + 16);
     jacobi_input(theta, m, n, dir, Z, c->stream);
+    // Householder preconditioning: the Jacobi then works on the rows of R,
+    // of which only the first min(p, q) can be non-zero
+    int pj = p;
+    if (householder_applies(p, q)) {
+        double* qws = slot_t<double>(c, SL_QR, householder_workspace(p, q, ld));
+        householder_rows(Z, p, q, ld, qws, c->stream);
+        pj = std::min(p, q);
+    }
     double* host = pinned(c, (size_t)p + 64);
     const double tol = 8.0 * std::sqrt((double)std::max(q, 1)) * 2.220446049250313e-16;
-    CtxProbe probe(c);
-    jacobi_rows(Z, p, q, ld, tol, 60, norms + p, c->stream, c->prof_on ? &probe : nullptr);
+    jacobi_rows(Z, pj, q, ld, tol, 60, gram, rot, off, host, c->stream);
     row_norms(Z, p, q, ld, norms, c->stream);
     d2h(c, host, norms, p);
     sync(c);

@@ -15,7 +15,8 @@ enum SlotId {
     SL_TPSI, SL_B, SL_TH,          // theta_psi, right-hand side, solution
     SL_V, SL_W,                    // Krylov basis, work vector
     SL_PART, SL_SMALL,             // reduction partials, small device scalars
-    SL_Z, SL_DC, SL_VECS, SL_NORM, SL_PERM,   // split: block, divide and conquer, long vectors
+    SL_Z, SL_DC, SL_VECS, SL_PERM,   // split: block, divide and conquer, long vectors
+    SL_GRAM, SL_ROT, SL_OFF, SL_NORM,      // Jacobi of the density matrices
     SL_QR,                         // Householder preconditioning
     SL_TMPA, SL_TMPB,              // scratch environments (overlap, energy)
     SL_LO_L, SL_LO_R, SL_LO_T, SL_LO_X,   // low-precision shadows (mixed precision)
@@ -171,6 +172,10 @@ struct SplitResult {
 };
 SplitResult split(ite_ctx* c, int dir, int Dl, int d1, int d2, int Dr, const double* theta, int chi_max,
                   double cutoff, double tie_rel, double* A1, double* A2, std::vector<double>* sigma);
+// The same by one-sided Jacobi, for matrices whose small rows carry information
+// below the rounding of the large ones (density matrices).
+SplitResult split_jacobi(ite_ctx* c, int dir, int m, int n, const double* theta, int chi_max, double cutoff,
+                         double tie_rel, double* A1, double* A2, std::vector<double>* sigma);
 // Truncation rule on sigma sorted descending (host).
 int truncation_rank(const std::vector<double>& s, double cutoff, int chi_max, double tie_rel);
 

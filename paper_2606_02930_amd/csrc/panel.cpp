@@ -34,7 +34,7 @@
 // The eigenvectors of rho_j's largest eigenvalues (their square roots are
 // phi's singular values at bond j) are the rows of the new site tensor and
 // C_j = T_j V; site 1 keeps T_1 whole.  Every contraction is an FP64 GEMM or
-// a sparse MPO stage; the eigenvectors come from the split
+// a sparse MPO stage; the eigenvectors come from the one-sided Jacobi
 // of rho_j (for a symmetric positive semi-definite matrix the right singular
 // vectors are eigenvectors and the singular values the eigenvalues).
 #include "engine.h"
@@ -530,7 +530,7 @@ double mpo_apply_dm(ite_mps* psi, const ite_mpo* O, int chi_max, double cutoff, 
         const int kall = std::min(nk, kcap);
         double* Vt = slot_t<double>(c, SL_DMV, (size_t)kall * nk);
         double* US = slot_t<double>(c, SL_DMU, (size_t)kall * nk);
-        split(c, 1, nk, 1, 1, nk, rho, kall, 0.0, 0.0, US, Vt, &lam);
+        split_jacobi(c, 1, nk, nk, rho, kall, 0.0, 0.0, US, Vt, &lam);
         std::vector<double> sq(lam.size());
         double total = 0.0;
         for (size_t i = 0; i < lam.size(); ++i) {

@@ -1,7 +1,15 @@
-// Householder QR of the first columns of a work matrix Z = [X | I] (p rows):
-// Z <- Q^T Z for X = Q R, so the second part becomes Q^T, whose trailing rows
-// complete the rows of X^T to an orthonormal basis (the widened bonds of a
-// Gauss-Legendre panel).
+// Householder QR preconditioning of the one-sided Jacobi (svd.hip), and the
+// completion of a site's rows to an orthonormal basis (panel.cpp).
+//
+// The Jacobi work matrix Z = [X | I] (p rows) is replaced by Q^T Z, where
+// X = Q R is the Householder QR of X: the rows of the first part become the
+// rows of R, and the second part becomes Q^T.  An orthogonal transform of the
+// rows changes nothing the one-sided Jacobi computes (it ends at the same
+// [Sigma V^T | U^T] up to the choice of basis within equal singular values),
+// but the rows of R are graded like the singular values, and on such rows
+// the Jacobi sweeps converge in far fewer sweeps (Drmac and Veselic's
+// preconditioned Jacobi).  When p > q the rows q..p-1 of R vanish and the
+// Jacobi only needs the first q rows; their Q^T part completes the basis.
 //
 // Blocked Householder with the compact WY form (Schreiber and Van Loan):
 // per panel of QB columns, one workgroup factors the panel (wavefront j owns
@@ -302,6 +310,8 @@ __global__ __launch_bounds__(1024) void qr_apply_kernel(double* __restrict__ Zt,
 constexpr int QNCT = 1;       // column tiles per apply workgroup
 
 }  // namespace
+
+bool householder_applies(int p, int q) { return p >= 256 && p <= 64 * QRPL && q >= QB; }
 
 size_t householder_workspace(int p, int q, int ld) {
     (void)q;

@@ -1,16 +1,39 @@
-// One-sided (Hestenes) Jacobi SVD of a two-site block of at most 32 rows, by
-// one workgroup.
+// One-sided (Hestenes) block-Jacobi SVD for the reduced density matrices of the
+// MPO-MPS product (Appendix B).  Their eigenvalues are squares, so the part of
+// a state with amplitude 1e-9 sits at 1e-18 of the largest: Jacobi rotations
+// keep the small rows of a graded matrix accurate to their own size, where the
+// bidiagonalisation of the bond splits (bidiag.hip) leaves an absolute error of
+// 1e-16 of the largest value (a step at complete bonds: 6e-9 in the energy
+// against the full-vector step instead of below 1e-9).
 //
 // The rows of the first q columns of a work matrix Z[p][ld] are made mutually
 // orthogonal by orthogonal row rotations, and the same rotations are applied
 // to all ld columns.  With Z = [X | I_p] the final rows are
 // [sigma_i v_i^T | u_i^T] for X = U diag(sigma) V^T, so both factors come out
 // of one run and the rotation part is a complete orthonormal basis even when
-// some sigma_i are zero.  Per sweep: the Gram of the rows (FP64 MFMA), one
-// cyclic sweep of two-sided Jacobi rotations on it in LDS (the accumulated
-// rotation made orthogonal to rounding by a Newton-Schulz step), and the
-// rotation of the rows (FP64 MFMA).  Larger blocks are bidiagonalised
-// (bidiag.hip, dcsvd.hip).
+// some sigma_i are zero.
+//
+// Up to 64 rows one workgroup runs the whole Jacobi (blocks of 16 rows up to
+// 32 rows, of 32 up to 64).  Beyond that the rows are grouped in blocks of
+// RB = 32; a round-robin (circle) schedule pairs the blocks so that every
+// pair meets once per sweep.
+// For each pair of blocks (PR = 2 RB rows):
+//   1. gram:   G = X_pair X_pair^T, summed over column chunks with FP64 MFMA;
+//   2. inner:  one cyclic sweep of two-sided Jacobi rotations on the PR x PR
+//              matrix in LDS (in FP32 while the previous sweep's measure is
+//              above 1e-3, the measure itself always FP64); Q accumulates
+//              the rotations and is made orthogonal to FP64 rounding by
+//              Newton-Schulz steps;
+//   3. rotate: Z_pair <- Q^T Z_pair over all ld columns (FP64 MFMA).
+// Step 3 of a round and step 1 of the next are one launch
+// (the data columns alternate between Z and a second buffer), and the
+// identity part of step 3 runs inside the next round's inner launch.  Pairs
+// whose rows are already orthogonal to the working tolerance produce no
+// rotation.  A sweep ends with one host read of the largest off-diagonal
+// measure seen in it; in the quadratic phase one product X X^T checks all row
+// pairs at once instead of a sweep that would only confirm convergence.
+// Larger blocks halve the number of rounds per sweep, and with it the traffic
+// over the whole work matrix, at the price of a longer inner sweep.
 #include "internal.h"
 #include "wave.h"
 
@@ -50,6 +73,99 @@ __device__ inline int pair_row(int P, int lr, int r, int nb) {
     const int b1 = circle_block(nb - 1 - P, r, nb);
     const int bi = b0 < b1 ? b0 : b1, bj = b0 < b1 ? b1 : b0;
     return lr < RB ? bi * RB + lr : bj * RB + (lr - RB);
+}
+
+// 4 GRAM_KS wavefronts: wavefront w forms tiles (w mod 4), (w mod 4) + 4, ...
+// over the part w / 4 of each stage's columns; the parts are summed in LDS.
+constexpr int GRAM_KS = 2, GRAM_NT = 256 * GRAM_KS;
+template <int RB>
+__global__ __launch_bounds__(GRAM_NT) void gram_kernel(const double* __restrict__ Z, int p, int q, int ld, int r,
+                                                       int nb, int nchunks, double* __restrict__ gram) {
+    constexpr int PR = Blk<RB>::PR, GW = Blk<RB>::GW, GS = Blk<RB>::GS;
+    constexpr int NTL = PR / 16, NTILE = NTL * (NTL + 1) / 2, TPW = (NTILE + 3) / 4;
+    constexpr int RPP = GRAM_NT / GW, NPASS = PR / RPP, KH = GW / GRAM_KS;
+    static_assert(NPASS * RPP == PR && (GRAM_KS - 1) * 4 * TPW * 256 <= PR * (GW + 1), "gram layout");
+    __shared__ double Xs[PR][GW + 1];
+    const int P = blockIdx.y, chunk = blockIdx.x;
+    const int t = threadIdx.x;
+    const int cc = t % GW, lr0 = t / GW;
+    long ro[NPASS];
+#pragma unroll
+    for (int u = 0; u < NPASS; ++u) {
+        const int row = pair_row<RB>(P, lr0 + RPP * u, r, nb);
+        ro[u] = row < p ? (long)row * ld : -1;
+    }
+    // all PR * GW / GRAM_NT loads of a stage in flight together; the next
+    // stage is fetched while the matrix cores work on the current one
+    double v[NPASS];
+    {
+        const int c = chunk * Blk<RB>::GC + cc;
+#pragma unroll
+        for (int u = 0; u < NPASS; ++u) v[u] = (ro[u] >= 0 && c < q) ? Z[ro[u] + c] : 0.0;
+    }
+    const int lane = t & 63, w = t >> 6, wt = w & 3, kh = w >> 2;
+    const int l16 = lane & 15, kg = lane >> 4;
+    // the Gram is symmetric: only the tiles I <= J are formed and stored
+    int ti[TPW], tj[TPW];
+#pragma unroll
+    for (int i = 0; i < TPW; ++i) {
+        int I = 0, J = wt + 4 * i;
+        while (J >= NTL - I && I < NTL) {
+            J -= NTL - I;
+            ++I;
+        }
+        ti[i] = I;
+        tj[i] = J + I;
+    }
+    d4_t acc[TPW];
+#pragma unroll
+    for (int i = 0; i < TPW; ++i) acc[i] = d4_t{0, 0, 0, 0};
+    for (int st = 0; st < GS; ++st) {
+        if (st > 0) __syncthreads();
+#pragma unroll
+        for (int u = 0; u < NPASS; ++u) Xs[lr0 + RPP * u][cc] = v[u];
+        __syncthreads();
+        if (st + 1 < GS) {
+            const int c = chunk * Blk<RB>::GC + (st + 1) * GW + cc;
+#pragma unroll
+            for (int u = 0; u < NPASS; ++u) v[u] = (ro[u] >= 0 && c < q) ? Z[ro[u] + c] : 0.0;
+        }
+#pragma unroll
+        for (int i = 0; i < TPW; ++i) {
+            if (wt + 4 * i >= NTILE) break;
+            const int I = ti[i], J = tj[i];
+            for (int k0 = kh * KH; k0 < (kh + 1) * KH; k0 += 4)
+                acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(Xs[I * 16 + l16][k0 + kg], Xs[J * 16 + l16][k0 + kg],
+                                                              acc[i], 0, 0, 0);
+        }
+    }
+    // column parts 1.. into LDS, summed by part 0 in a fixed order
+    __syncthreads();
+    double* red = &Xs[0][0];
+    if (kh > 0) {
+#pragma unroll
+        for (int i = 0; i < TPW; ++i) {
+            if (wt + 4 * i >= NTILE) break;
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr)
+                red[((((kh - 1) * 4 + wt) * TPW + i) * 4 + rr) * 64 + lane] = acc[i][rr];
+        }
+    }
+    __syncthreads();
+    if (kh == 0) {
+        double* out = gram + ((long)P * nchunks + chunk) * (PR * PR);
+#pragma unroll
+        for (int i = 0; i < TPW; ++i) {
+            if (wt + 4 * i >= NTILE) break;
+            // FP64 MFMA accumulator element rr of lane group kg is tile row 4 rr + kg
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                double sum = acc[i][rr];
+                for (int k = 1; k < GRAM_KS; ++k) sum += red[((((k - 1) * 4 + wt) * TPW + i) * 4 + rr) * 64 + lane];
+                out[(ti[i] * 16 + 4 * rr + kg) * PR + tj[i] * 16 + l16] = sum;
+            }
+        }
+    }
 }
 
 __device__ inline void atomic_max_pos(double* addr, double v) {
@@ -556,6 +672,94 @@ __device__ __forceinline__ int pair_sweep(PairLDS<RB>& sh, double tol, double ka
     return anyrot ? 2 : 1;
 }
 
+// One workgroup per pair: sum the chunk partials of the pair's Gram (tiles on
+// and above the diagonal) and run pair_sweep; writes Q and whether any
+// rotation was applied.
+//
+// Workgroups npairs and up rotate the identity part (columns q .. ld) of
+// the rows of the previous round's pairs (round rprev, rotations rot_prev),
+// UW columns each: that work is off the critical path of the sweep and
+// fills the compute units the pairs leave idle.
+template <int RB, typename GT>
+__global__ __launch_bounds__(Blk<RB>::NTI) void inner_kernel(const double* __restrict__ gram, int nchunks, int p,
+                                                             int r, int nb, double tol, double kappa,
+                                                             double sigma1sq, double* __restrict__ rot,
+                                                             int* __restrict__ rotated,
+                                                             double* __restrict__ sweep_off,
+                                                             double* __restrict__ Z, int ld, int q, int npairs,
+                                                             int rprev, const double* __restrict__ rot_prev,
+                                                             const int* __restrict__ rotated_prev, int nuch) {
+    constexpr int PR = Blk<RB>::PR, NT = Blk<RB>::NT, XS = Blk<RB>::XS, EPT = PR / XS;
+    constexpr int NW = NT / 64;
+    constexpr int NTI = Blk<RB>::NTI, UW = Blk<RB>::UW;
+    __shared__ PairLDS<RB> sh;
+    if ((int)blockIdx.x >= npairs) {
+        const int u = blockIdx.x - npairs, Pu = u / nuch, ch = u % nuch;
+        if (!rotated_prev[Pu]) return;
+        const int cb = q + ch * UW, ce = min(cb + UW, ld);
+        const double* qsrc = rot_prev + (long)Pu * PR * PR;
+        for (int e = threadIdx.x; e < PR * PR; e += NTI) sh.Gb[0][e / PR][e % PR] = qsrc[e];
+        rotate_cols<RB, NW, false, false>(Z, p, ld, Pu, rprev, nb, sh.Gb[0], cb, ce, threadIdx.x, threadIdx.x < NT);
+        return;
+    }
+    const int P = blockIdx.x;
+    const int t = threadIdx.x;
+    const bool upd = t < NT;
+    const int y = t % PR, xh = t / PR;
+    const double* src = gram + (long)P * nchunks * (PR * PR);
+    if (upd) {
+        // LB chunks per step so that LB EPT loads are in flight together
+        // (the summation order is fixed: results do not depend on timing)
+        constexpr int LB = 4;
+        double s[EPT];
+#pragma unroll
+        for (int u = 0; u < EPT; ++u) s[u] = 0.0;
+        int c = 0;
+        for (; c + LB - 1 < nchunks; c += LB) {
+            const double* g = src + (long)c * PR * PR + y;
+            double v[LB][EPT];
+#pragma unroll
+            for (int h = 0; h < LB; ++h)
+#pragma unroll
+                for (int u = 0; u < EPT; ++u)
+                    v[h][u] = ((xh + XS * u) >> 4) <= (y >> 4) ? g[(long)h * PR * PR + (xh + XS * u) * PR] : 0.0;
+#pragma unroll
+            for (int u = 0; u < EPT; ++u) {
+                double t4 = 0.0;
+#pragma unroll
+                for (int h = 0; h < LB; h += 4) t4 += (v[h][u] + v[h + 1][u]) + (v[h + 2][u] + v[h + 3][u]);
+                s[u] += t4;
+            }
+        }
+        for (; c < nchunks; ++c) {
+            const double* g = src + (long)c * PR * PR + y;
+#pragma unroll
+            for (int u = 0; u < EPT; ++u)
+                if (((xh + XS * u) >> 4) <= (y >> 4)) s[u] += g[(xh + XS * u) * PR];
+        }
+#pragma unroll
+        for (int u = 0; u < EPT; ++u) {
+            const int x = xh + XS * u;
+            sh.Gb[0][x][y] = s[u];
+            sh.Ab[0][x][y] = (x == y) ? 1.0 : 0.0;
+        }
+    }
+    double off;
+    const int res = pair_sweep<RB, GT>(sh, tol, kappa, sigma1sq, sweep_off, off);
+    // Q of every pair is written (the identity when the rows are already
+    // orthogonal), so that the fused rotation reads it unconditionally
+    if (upd) {
+        const auto& T = sh.Gb[q_buffer<RB>()];
+        double* out = rot + (long)P * PR * PR;
+#pragma unroll
+        for (int u = 0; u < EPT; ++u) {
+            const int x = xh + XS * u;
+            out[x * PR + y] = res == 0 ? (x == y ? 1.0 : 0.0) : T[x][y];
+        }
+    }
+    if (t == 0) rotated[P] = res == 2;
+}
+
 // The whole one-sided Jacobi of p <= PR rows (a single block pair) in one
 // workgroup, for small splits where launches and host round trips would
 // dominate: per sweep the Gram of the rows over the first q columns (FP64
@@ -614,6 +818,243 @@ __global__ __launch_bounds__(Blk<RB>::NTI) void single_pair_jacobi_kernel(double
         res[0] = off;
         res[1] = sweeps;
     }
+}
+
+// Position-to-pair bookkeeping of the circle schedule: the pair of round r
+// that holds block b, and whether b is that pair's higher-indexed block.
+__device__ inline void block_pair(int b, int r, int nb, int& P, int& side) {
+    const int m = nb - 1;
+    const int pos = b == 0 ? 0 : ((b - 1 - r) % m + m) % m + 1;
+    P = pos < nb / 2 ? pos : nb - 1 - pos;
+    const int b0 = circle_block(P, r, nb), b1 = circle_block(nb - 1 - P, r, nb);
+    side = b == (b0 < b1 ? b0 : b1) ? 0 : 1;
+}
+
+// Round r's rotation of the data columns fused with round r + 1's Gram: one
+// workgroup per pair P' of round r + 1 and column chunk (GC columns).  Its
+// two blocks come from two different pairs of round r; for each, the block's
+// new rows are formed from that pair's 2 RB old rows and the block's half of
+// Q (FP64 MFMA, all operand loads of the chunk issued up front), written to
+// the other data buffer (Xd: the old rows are read by two workgroups, so the
+// update cannot be in place), and kept in LDS for the Gram partial of P'
+// (tiles on and above the diagonal).  Pairs of round r without rotation
+// carry Q = I (written by the inner launch), so their rows are copied.
+// Eight wavefronts: wavefront w rotates the 16-column slab w mod 4 of half
+// w / 4 of every 64-column slice.  Xs is not declared __restrict__: its loads
+// must stay above the compiler barrier that keeps them in flight together.
+template <int RB>
+__global__ __launch_bounds__(512) void rotate_gram_kernel(const double* Xs, int lds,
+                                                          double* __restrict__ Xd, int ldd, int p, int q, int r,
+                                                          int nb, int nchunks, const double* __restrict__ rot,
+                                                          double* __restrict__ gram) {
+    constexpr int PR = Blk<RB>::PR, GC = Blk<RB>::GC, KS = PR / 4, SW = 64;   // slice width
+    constexpr int NTL = PR / 16, NTILE = NTL * (NTL + 1) / 2, GTW = (NTILE + 7) / 8;
+    static_assert(RB == 32, "two 16-row tiles per half");
+    __shared__ double Qh[2][PR][RB + 1];     // Q[k][side RB + i] of each half's round-r pair
+    __shared__ double Ys[2][PR][SW + 1];     // new rows of P' over a slice (two slices in flight)
+    const int Pn = blockIdx.y, chunk = blockIdx.x;
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);   // wavefront-uniform: schedule arithmetic stays scalar
+    const int l16 = lane & 15, kg = lane >> 4;
+    const int rn = r + 1;
+    const int bn0 = circle_block(Pn, rn, nb), bn1 = circle_block(nb - 1 - Pn, rn, nb);
+    const int blk[2] = {bn0 < bn1 ? bn0 : bn1, bn0 < bn1 ? bn1 : bn0};
+    int Ph[2], sh[2];
+    block_pair(blk[0], r, nb, Ph[0], sh[0]);
+    block_pair(blk[1], r, nb, Ph[1], sh[1]);
+    // Q of both round-r pairs (the identity for pairs without rotation is
+    // written by the inner launch), loaded before the data so that waiting
+    // for it leaves the data loads in flight
+    constexpr int QPT = 2 * PR * RB / 512;
+    double qv[QPT];
+#pragma unroll
+    for (int u = 0; u < QPT; ++u) {
+        const int e = t + 512 * u;
+        const int h = e / (PR * RB), k = (e / RB) % PR, i = e % RB;
+        qv[u] = rot[(long)Ph[h] * PR * PR + k * PR + sh[h] * RB + i];
+    }
+    // this wavefront: half hw, 16-column slab cs of each slice
+    const int hw = w >> 2, csl = w & 3;
+    int rk[KS], ro[2][4];
+    {
+        // local rows 0..RB-1 of the round-r pair are its lower-indexed block
+        const int s0 = circle_block(Ph[hw], r, nb), s1 = circle_block(nb - 1 - Ph[hw], r, nb);
+        const int bi = s0 < s1 ? s0 : s1, bj = s0 < s1 ? s1 : s0;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int lr = 4 * ks + kg;
+            const int row = ks < KS / 2 ? bi * RB + lr : bj * RB + (lr - RB);
+            rk[ks] = row < p ? row * lds : -1;
+        }
+    }
+#pragma unroll
+    for (int tm = 0; tm < 2; ++tm)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+            const int row = blk[hw] * RB + tm * 16 + 4 * rr + kg;   // FP64 MFMA accumulator row
+            ro[tm][rr] = row < p ? row * ldd : -1;
+        }
+    const int cb = chunk * GC, ce = min(q, cb + GC);
+    const int nsl = (ce - cb + SW - 1) / SW;
+    // Gram tiles of this wavefront: w, w + 8 (of the NTILE tiles I <= J)
+    int ti[GTW], tj[GTW];
+#pragma unroll
+    for (int i = 0; i < GTW; ++i) {
+        int I = 0, J = w + 8 * i;
+        while (J >= NTL - I && I < NTL) {
+            J -= NTL - I;
+            ++I;
+        }
+        ti[i] = I;
+        tj[i] = J + I;
+    }
+    d4_t gacc[GTW];
+#pragma unroll
+    for (int i = 0; i < GTW; ++i) gacc[i] = d4_t{0, 0, 0, 0};
+    // Data operands one slice ahead: the loads of slice sl + 1 are issued
+    // right after the products of slice sl, into the registers those
+    // products consumed, and unconditionally (an out-of-range operand reads
+    // element 0 and is replaced by zero where it is used; past the last slice
+    // they reread element 0), so that the wait before each slice's products
+    // covers exactly that slice's loads.
+    double b[KS];
+    {
+        const int c = cb + csl * 16 + l16;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) b[ks] = Xs[(rk[ks] >= 0 && c < ce) ? rk[ks] + c : 0];
+    }
+    asm volatile("" ::: "memory");   // keeps the loads above from being moved down to their uses
+#pragma unroll
+    for (int u = 0; u < QPT; ++u) {
+        const int e = t + 512 * u;
+        Qh[e / (PR * RB)][(e / RB) % PR][e % RB] = qv[u];
+    }
+    __syncthreads();
+    // this wavefront's Q operands stay in registers for every slice
+    double qa[KS][2];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int tm = 0; tm < 2; ++tm) {
+            qa[ks][tm] = Qh[hw][4 * ks + kg][tm * 16 + l16];
+            asm volatile("" : "+v"(qa[ks][tm]));   // held in registers, not reread from LDS per slice
+        }
+    for (int sl = 0; sl < nsl; ++sl) {
+        const int c = cb + sl * SW + csl * 16 + l16;
+        d4_t acc[2] = {d4_t{0, 0, 0, 0}, d4_t{0, 0, 0, 0}};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const double bv = (rk[ks] >= 0 && c < ce) ? b[ks] : 0.0;
+#pragma unroll
+            for (int tm = 0; tm < 2; ++tm)
+                acc[tm] = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[ks][tm], bv, acc[tm], 0, 0, 0);
+        }
+        {
+            const int cn = c + SW;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) b[ks] = Xs[(rk[ks] >= 0 && cn < ce) ? rk[ks] + cn : 0];
+        }
+#pragma unroll
+        for (int tm = 0; tm < 2; ++tm)
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                const bool in = ro[tm][rr] >= 0 && c < ce;
+                if (in) Xd[ro[tm][rr] + c] = acc[tm][rr];
+                Ys[sl & 1][hw * RB + tm * 16 + 4 * rr + kg][csl * 16 + l16] = in ? acc[tm][rr] : 0.0;
+            }
+        // one barrier per slice: a wavefront writes the other buffer next,
+        // which every wavefront finished reading before reaching this barrier
+        __syncthreads();
+        const auto& Y = Ys[sl & 1];
+        // per tile: all operands read from LDS first, then two independent
+        // accumulation chains (even and odd k steps)
+#pragma unroll
+        for (int i = 0; i < GTW; ++i) {
+            if (w + 8 * i >= NTILE) break;
+            double ya[SW / 4], yb[SW / 4];
+#pragma unroll
+            for (int k = 0; k < SW / 4; ++k) {
+                ya[k] = Y[ti[i] * 16 + l16][4 * k + kg];
+                yb[k] = Y[tj[i] * 16 + l16][4 * k + kg];
+            }
+            d4_t g2[2] = {d4_t{0, 0, 0, 0}, d4_t{0, 0, 0, 0}};
+#pragma unroll
+            for (int k = 0; k < SW / 4; ++k) g2[k & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ya[k], yb[k], g2[k & 1], 0, 0, 0);
+            gacc[i] += g2[0] + g2[1];
+        }
+    }
+    double* out = gram + ((long)Pn * nchunks + chunk) * (PR * PR);
+#pragma unroll
+    for (int i = 0; i < GTW; ++i) {
+        if (w + 8 * i >= NTILE) break;
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) out[(ti[i] * 16 + 4 * rr + kg) * PR + tj[i] * 16 + l16] = gacc[i][rr];
+    }
+}
+
+// Convergence check over all row pairs at once, in place of a sweep that
+// would only confirm convergence: with G = X X^T (n x n, leading dimension
+// ldg) of the current rows, the largest orthogonality measure over i < j
+// (the measure and rounding floor of pair_sweep, sigma1^2 = the larger of
+// sigma1sq and the largest diagonal entry).  out[0]: the measure (atomic
+// maximum, cleared by the caller), out[1]: the largest diagonal entry.
+__global__ __launch_bounds__(256) void gram_diag_kernel(const double* __restrict__ G, int n, long ldg,
+                                                        double* __restrict__ diag, double* __restrict__ out) {
+    __shared__ double red[4];
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    const double v = j < n ? fmax(G[(long)j * ldg + j], 0.0) : 0.0;
+    if (j < n) diag[j] = v;
+    const double m = wave_max_nonneg(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) atomic_max_pos(out + 1, fmax(fmax(red[0], red[1]), fmax(red[2], red[3])));
+}
+
+__global__ __launch_bounds__(256) void gram_off_kernel(const double* __restrict__ G, int n, long ldg,
+                                                       const double* __restrict__ diag, double kappa,
+                                                       double sigma1sq, double* __restrict__ out) {
+    __shared__ double red[4];
+    const int i = blockIdx.x, t = threadIdx.x;
+    const double kappa_s1 = kappa * sqrt(fmax(sigma1sq, out[1]));
+    const double gii = diag[i];
+    double off = 0.0;
+    for (int j = i + 1 + t; j < n; j += 256) {
+        const double den = off_den(gii, diag[j], kappa_s1);
+        if (den > 0.0) off = fmax(off, fabs(G[(long)i * ldg + j]) / den);
+    }
+    off = wave_max_nonneg(off);
+    if ((t & 63) == 0) red[t >> 6] = off;
+    __syncthreads();
+    if (t == 0) atomic_max_pos(out, fmax(fmax(red[0], red[1]), fmax(red[2], red[3])));
+}
+
+// Dst[i][c] = Src[i][c] for i < p, c < q (data columns back to the work matrix).
+__global__ void copy_cols_kernel(const double* __restrict__ src, int lds, double* __restrict__ dst, int ldd, int p,
+                                 int q) {
+    const long total = (long)p * q;
+    for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (long)gridDim.x * blockDim.x) {
+        const int i = (int)(e / q), c = (int)(e % q);
+        dst[(long)i * ldd + c] = src[(long)i * lds + c];
+    }
+}
+
+// Rotation of columns [cb, ce) for the pairs of round r, cw columns per
+// workgroup (grid: column chunks x pairs).  Pairs without rotation skip.
+// Eight wavefronts per workgroup with Q read from LDS for every slice (two
+// wavefronts per SIMD) measured faster than four holding Q in registers.
+constexpr int ROT_WAVES = 8;
+template <int RB>
+__global__ __launch_bounds__(64 * ROT_WAVES) void rotate_kernel(double* __restrict__ Z, int p, int ld, int r, int nb,
+                                                     const double* __restrict__ rot,
+                                                     const int* __restrict__ rotated, int cb, int ce, int cw) {
+    constexpr int PR = Blk<RB>::PR;
+    const int P = blockIdx.y;
+    if (!rotated[P]) return;
+    const int c0 = cb + blockIdx.x * cw, c1 = min(c0 + cw, ce);
+    __shared__ double Qs[PR][PR + 1];        // Q[k][m]
+    const double* src = rot + (long)P * PR * PR;
+    for (int e = threadIdx.x; e < PR * PR; e += 64 * ROT_WAVES) Qs[e / PR][e % PR] = src[e];
+    rotate_cols<RB, ROT_WAVES, true, false>(Z, p, ld, P, r, nb, Qs, c0, c1, threadIdx.x, true);
 }
 
 __global__ __launch_bounds__(256) void row_norms_kernel(const double* __restrict__ Z, int q, int ld,
@@ -681,17 +1122,185 @@ void jacobi_input(const double* theta, int m, int n, int dir, double* Z, hipStre
     HIP_CHECK(hipGetLastError());
 }
 
-void jacobi_rows(double* Z, int p, int q, int ld, double tol, int max_sweeps, double* res, hipStream_t s,
-                 LaunchProbe* probe) {
-    if (p <= 1) return;
-    if (p > Blk<16>::PR) ITE_FAIL(ITE_EINVAL, "jacobi_rows: at most 32 rows");
-    const bool timed = probe && probe->begin(PK_MERGE, s);
-    hipLaunchKernelGGL((single_pair_jacobi_kernel<16>), dim3(1), dim3(Blk<16>::NTI), 0, s, Z, p, q, ld, tol, 1e-3,
-                       max_sweeps, res);
-    if (timed) probe->end(PK_MERGE, s);
-    HIP_CHECK(hipGetLastError());
-    // one sweep's Gram, inner sweep and rotation (the count stays on the device)
-    if (probe) probe->work(PK_MERGE, 2.0 * p * p * (q + ld) + 9.0 * p * p * p, 8.0 * (double)p * (q + 2.0 * ld));
+namespace {
+
+template <int RB>
+void ws_sizes(int p, int q, size_t* gram, size_t* rot, size_t* off) {
+    constexpr int PR = Blk<RB>::PR, GC = Blk<RB>::GC;
+    int nb = (p + RB - 1) / RB;
+    if (nb < 2) nb = 2;
+    if (nb & 1) ++nb;
+    const size_t npairs = nb / 2, nchunks = std::max(1, (q + GC - 1) / GC);
+    // Gram partials, then (32-row blocks) the second buffer of the data columns
+    *gram = npairs * nchunks * PR * PR + (RB == 32 ? (size_t)p * q : 0);
+    *rot = 2 * npairs * PR * PR;     // rotations of two consecutive rounds
+    *off = npairs + 24 + (size_t)p;     // flags, counters, check result, Gram diagonal
+}
+
+// Columns per rotate workgroup: wide chunks amortise the load of Q, narrow
+// ones give the launch enough workgroups to fill the chip.
+inline int rotate_width(int npairs, int ncols) {
+    int cw = 512;
+    while (cw > 128 && (long)npairs * ((ncols + cw - 1) / cw) < 256) cw /= 2;
+    return cw;
+}
+
+template <int RB>
+JacobiResult run_jacobi(double* Z, int p, int q, int ld, double tol, int max_sweeps, double* gram_ws,
+                        double* rot_ws, double* off_ws, double* host_off, hipStream_t s) {
+    constexpr int GC = Blk<RB>::GC, NT = Blk<RB>::NT, PR = Blk<RB>::PR, UW = Blk<RB>::UW;
+    JacobiResult res;
+    int nb = (p + RB - 1) / RB;
+    if (nb < 2) nb = 2;
+    if (nb & 1) ++nb;
+    const int npairs = nb / 2;
+    const int nchunks = std::max(1, (q + GC - 1) / GC);
+    const int nu = ld - q;                         // identity-part columns
+    const int nuch = (nu + UW - 1) / UW;
+    // off_ws[0]: largest off-diagonal measure of the sweep, off_ws[1]: largest
+    // row norm squared seen in it, then the rotated flags of two consecutive
+    // rounds (npairs ints each), then the check of all row pairs
+    int* rotated = reinterpret_cast<int*>(off_ws + 2);
+    // 32-row blocks: the rotation of round r and the Gram of round r + 1 are
+    // one launch, whose new data rows go to the other of two buffers (the Z
+    // columns 0..q and Xb); round g reads buffer g mod 2
+    static_assert(RB == 32, "the multi-pair rounds use 32-row blocks and the fused rotation + Gram");
+    double* Xb = gram_ws + (size_t)npairs * nchunks * PR * PR;
+    {
+        hipLaunchKernelGGL((gram_kernel<RB>), dim3(nchunks, npairs), dim3(GRAM_NT), 0, s, Z, p, q, ld, 0, nb,
+                           nchunks, gram_ws);
+    }
+    constexpr double kappa = 1e-3;
+    double prev = 1e300, sigma1sq = 0.0;
+    int checks = 0;
+    // The identity part of round g's rotations is applied during round
+    // g + 1 (by the extra workgroups of its inner launch) and after the last
+    // round; rotations and flags alternate between two buffers.
+    long g = 0;
+    int rprev = -1;
+    for (int sw = 0; sw < max_sweeps; ++sw) {
+        fill(off_ws, 0.0, 2, s);
+        // far from convergence the pair sweeps rotate a single-precision copy
+        // of the Gram (the measure and the accumulated rotation stay FP64):
+        // their angles only need to be roughly right while the measure is
+        // large, and the sweeps that reach the tolerance run in FP64
+        const bool lowg = prev > 1e-3;
+        for (int r = 0; r < nb - 1; ++r, ++g) {
+            const int cur = (int)(g & 1);
+            double* rcur = rot_ws + (long)cur * npairs * PR * PR;
+            const double* rold = rot_ws + (long)(cur ^ 1) * npairs * PR * PR;
+            int* fcur = rotated + cur * npairs;
+            const int* fold = rotated + (cur ^ 1) * npairs;
+            const int ublocks = (rprev >= 0 && nu > 0) ? npairs * nuch : 0;
+            if (lowg)
+                hipLaunchKernelGGL((inner_kernel<RB, float>), dim3(npairs + ublocks), dim3(Blk<RB>::NTI), 0, s,
+                                   gram_ws, nchunks, p, r, nb, tol, kappa, sigma1sq, rcur, fcur, off_ws, Z, ld,
+                                   q, npairs, rprev, rold, fold, nuch);
+            else
+                hipLaunchKernelGGL((inner_kernel<RB, double>), dim3(npairs + ublocks), dim3(Blk<RB>::NTI), 0, s,
+                                   gram_ws, nchunks, p, r, nb, tol, kappa, sigma1sq, rcur, fcur, off_ws, Z, ld,
+                                   q, npairs, rprev, rold, fold, nuch);
+            {
+                const bool odd = g & 1;
+                hipLaunchKernelGGL((rotate_gram_kernel<RB>), dim3(nchunks, npairs), dim3(512), 0, s,
+                                   odd ? Xb : Z, odd ? q : ld, odd ? Z : Xb, odd ? ld : q, p, q, r, nb, nchunks, rcur,
+                                   gram_ws);
+            }
+            rprev = r;
+        }
+        HIP_CHECK(hipGetLastError());
+        HIP_CHECK(hipMemcpyAsync(host_off, off_ws, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
+        HIP_CHECK(hipStreamSynchronize(s));
+        const double soff = host_off[0];
+        sigma1sq = host_off[1];
+        res.sweeps = sw + 1;
+        res.last_off = soff;
+        if (soff <= tol) break;
+        // In the quadratic phase the next sweep would most likely only
+        // confirm convergence: check all row pairs at once instead, with the
+        // Gram of the current rows formed in the free data buffer (at most
+        // two checks per split)
+        if (p <= q && soff < 1e-6 && checks < 2) {
+            ++checks;
+            const bool odd = g & 1;                    // the rows are in Xb when odd
+            const double* X = odd ? Xb : Z;
+            const long ldx = odd ? q : ld;
+            double* G = odd ? Z : Xb;
+            const long ldg = odd ? ld : p;
+            double* chk = off_ws + 2 + npairs + 8;
+            double* diag = chk + 8;
+            Gemm gm;
+            gm.M = p;
+            gm.N = p;
+            gm.K = q;
+            gm.tB = true;
+            gm.A = X;
+            gm.lda = ldx;
+            gm.B = X;
+            gm.ldb = ldx;
+            gm.D = G;
+            gm.ldd = ldg;
+            gemm_f64(gm, s);
+            fill(chk, 0.0, 2, s);
+            hipLaunchKernelGGL(gram_diag_kernel, dim3((p + 255) / 256), dim3(256), 0, s, G, p, ldg, diag, chk);
+            hipLaunchKernelGGL(gram_off_kernel, dim3(p), dim3(256), 0, s, G, p, ldg, diag, kappa, sigma1sq, chk);
+            HIP_CHECK(hipGetLastError());
+            HIP_CHECK(hipMemcpyAsync(host_off, chk, sizeof(double), hipMemcpyDeviceToHost, s));
+            HIP_CHECK(hipStreamSynchronize(s));
+            if (*host_off <= tol) {
+                res.last_off = *host_off;
+                break;
+            }
+        }
+        // stagnation at the rounding floor: stop once the measure no longer drops
+        if (sw >= 3 && soff > 0.5 * prev && soff < 1e3 * tol) break;
+        prev = soff;
+    }
+    if (g & 1) {
+        // the final data rows are in Xb
+        const long total = (long)p * q;
+        hipLaunchKernelGGL(copy_cols_kernel, dim3((int)std::min<long>(4096, (total + 255) / 256)), dim3(256), 0, s, Xb,
+                           q, Z, ld, p, q);
+        HIP_CHECK(hipGetLastError());
+    }
+    if (rprev >= 0 && nu > 0) {
+        // identity part of the last round
+        const int cur = (int)((g - 1) & 1);
+        const int uw = rotate_width(npairs, nu);
+        hipLaunchKernelGGL((rotate_kernel<RB>), dim3((nu + uw - 1) / uw, npairs), dim3(64 * ROT_WAVES), 0, s, Z, p, ld, rprev,
+                           nb, rot_ws + (long)cur * npairs * PR * PR, rotated + cur * npairs, q, ld, uw);
+        HIP_CHECK(hipGetLastError());
+    }
+    return res;
+}
+
+}  // namespace
+
+void jacobi_workspace(int p, int q, size_t* gram, size_t* rot, size_t* off) {
+    ws_sizes<32>(p, q, gram, rot, off);
+}
+
+JacobiResult jacobi_rows(double* Z, int p, int q, int ld, double tol, int max_sweeps, double* gram_ws,
+                         double* rot_ws, double* off_ws, double* host_off, hipStream_t s) {
+    if (p <= 1) return JacobiResult{};
+    ITE_REQUIRE((long)p * ld < 2147483647L, "svd: work matrix too large for 32-bit element offsets");
+    if (p <= Blk<32>::PR) {
+        // one block pair: the whole Jacobi in one launch and one host read
+        if (p <= Blk<16>::PR)
+            hipLaunchKernelGGL((single_pair_jacobi_kernel<16>), dim3(1), dim3(Blk<16>::NTI), 0, s, Z, p, q, ld, tol,
+                               1e-3, max_sweeps, off_ws);
+        else
+            hipLaunchKernelGGL((single_pair_jacobi_kernel<32>), dim3(1), dim3(Blk<32>::NTI), 0, s, Z, p, q, ld, tol,
+                               1e-3, max_sweeps, off_ws);
+        HIP_CHECK(hipGetLastError());
+        HIP_CHECK(hipMemcpyAsync(host_off, off_ws, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
+        HIP_CHECK(hipStreamSynchronize(s));
+        JacobiResult res;
+        res.last_off = host_off[0];
+        res.sweeps = (int)host_off[1];
+        return res;
+    }
+    return run_jacobi<32>(Z, p, q, ld, tol, max_sweeps, gram_ws, rot_ws, off_ws, host_off, s);
 }
 
 void row_norms(const double* Z, int p, int q, int ld, double* norms, hipStream_t s) {
