@@ -6,11 +6,10 @@
 // batch size, budget and precision (the last few kept per context) and
 // replayed (the kernels read every shape and address from descriptors in
 // device memory); a capture that a call on another thread invalidates is
-// issued directly instead.  The
-// tile size of each product is picked per GEMM shape by a small autotuner;
-// both tile sizes give the same bits, and every per-state reduction has the
-// single-state partition and order, so a state's step does not depend on the
-// batch it runs in.  FP32 refinement with a fixed number of corrections runs
+// issued directly instead.  A
+// product's tile and K parts depend on its shape alone, and every per-state
+// reduction has the single-state partition and order, so a state's step does
+// not depend on the batch it runs in.  FP32 refinement with a fixed number of corrections runs
 // the same sequence with one cycle per correction: the residual product in
 // FP64, the Arnoldi products with FP32 operands (grouped FP32 launches and the
 // FP32 MPO stage), the Krylov basis and its reductions in FP64.
@@ -19,72 +18,9 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <map>
 #include <memory>
-#include <mutex>
-#include <tuple>
 
 namespace ite {
-
-// ---------------------------------------------------------------------------
-// Tile autotuner
-// ---------------------------------------------------------------------------
-
-namespace {
-std::mutex g_tune_mu;
-std::map<std::tuple<int, int, int, int, int, int>, int> g_tune;   // (device, M, N, K, tA, tB) -> tile
-
-float time_variant(ite_ctx* c, void* desc, int* cnt, bool tA, bool tB, int bs) {
-    hipEvent_t a, b;
-    HIP_CHECK(hipEventCreate(&a));
-    HIP_CHECK(hipEventCreate(&b));
-    gemm_grouped_f64(desc, cnt, tA, tB, bs, 512, c->stream);   // warm-up
-    HIP_CHECK(hipEventRecord(a, c->stream));
-    for (int r = 0; r < 3; ++r) gemm_grouped_f64(desc, cnt, tA, tB, bs, 512, c->stream);
-    HIP_CHECK(hipEventRecord(b, c->stream));
-    HIP_CHECK(hipEventSynchronize(b));
-    float ms = 0.f;
-    HIP_CHECK(hipEventElapsedTime(&ms, a, b));
-    (void)hipEventDestroy(a);
-    (void)hipEventDestroy(b);
-    return ms;
-}
-}  // namespace
-
-// On the first product of a shape the two tile sizes run three times each on
-// the real operands into a scratch output, and the faster is kept for the
-// process; results do not depend on the choice (same K order per element).
-int tuned_tile(ite_ctx* c, const Gemm& g0) {
-    const auto key = std::make_tuple(c->device, g0.M, g0.N, g0.K, (int)g0.tA, (int)g0.tB);
-    {
-        std::lock_guard<std::mutex> lk(g_tune_mu);
-        auto it = g_tune.find(key);
-        if (it != g_tune.end()) return it->second;
-    }
-    Gemm g = g0;
-    g.D = slot_t<double>(c, SL_TUNE, (size_t)g.M * g.N + 64 + grouped_desc_bytes() / 8 + 8);
-    g.ldd = g.N;
-    char* base = reinterpret_cast<char*>(g.D + (size_t)g.M * g.N + 32);
-    void* desc = base;
-    int* cnt = reinterpret_cast<int*>(base + grouped_desc_bytes());
-    float best = 0.f;
-    int pick = 128;
-    for (int bs : {128, 64}) {
-        std::vector<char> hd(grouped_desc_bytes());
-        grouped_desc_fill(g, bs, 0, hd.data());
-        const int hc[2] = {1, grouped_tiles(g, bs)};
-        HIP_CHECK(hipMemcpyAsync(desc, hd.data(), hd.size(), hipMemcpyHostToDevice, c->stream));
-        HIP_CHECK(hipMemcpyAsync(cnt, hc, sizeof(hc), hipMemcpyHostToDevice, c->stream));
-        const float ms = time_variant(c, desc, cnt, g.tA, g.tB, bs);
-        if (bs == 128 || ms < best) {
-            best = ms;
-            pick = bs;
-        }
-    }
-    std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tune[key] = pick;
-    return pick;
-}
 
 // ---------------------------------------------------------------------------
 // Batched fixed-budget GMRES
@@ -94,9 +30,9 @@ namespace {
 
 // The products of one batch: for product p (0: the residual's product with
 // x, k + 1: the Arnoldi product with V_k) and each of the two GEMMs, the
-// descriptors by tile size; counts[p][gemm][tile] = {problems, tiles}.
+// descriptors; counts[p][gemm] = {problems, tiles}.
 // With FP32 products (lo): for product p >= 1 and each GEMM one more
-// descriptor set (128 tiles), counts_lo[p][gemm] = {problems, tiles}.
+// descriptor set, counts_lo[p][gemm] = {problems, tiles}.
 struct BatchLayout {
     size_t vec_off = 0, tot_off = 0, desc_off = 0, cnt_off = 0, dlo_off = 0, clo_off = 0, bytes = 0;
     int G = 0, np = 0;
@@ -112,8 +48,8 @@ BatchLayout layout(int G, int np, bool lo) {
     l.vec_off = 0;
     l.tot_off = al(sizeof(BatchVec) * G);
     l.desc_off = al(l.tot_off + sizeof(int) * BT_N);
-    l.cnt_off = al(l.desc_off + grouped_desc_bytes() * (size_t)np * 4 * G);
-    l.dlo_off = al(l.cnt_off + sizeof(int) * 2 * (size_t)np * 4);
+    l.cnt_off = al(l.desc_off + grouped_desc_bytes() * (size_t)np * 2 * G);
+    l.dlo_off = al(l.cnt_off + sizeof(int) * 2 * (size_t)np * 2);
     l.clo_off = al(l.dlo_off + (lo ? grouped_desc_bytes() * (size_t)np * 2 * G : 0));
     l.bytes = al(l.clo_off + sizeof(int) * 2 * (size_t)np * 2);
     return l;
@@ -133,18 +69,16 @@ void issue(char* dev, const BatchLayout& l, int mm, int max_cycles, hipStream_t 
                 const int q = p * 2 + gm;
                 const void* desc = dev + l.dlo_off + grouped_desc_bytes() * (size_t)q * G;
                 const int* cnt = reinterpret_cast<const int*>(dev + l.clo_off) + 2 * q;
-                gemm_grouped_f32(desc, cnt, false, gm == 1, 512, s);
+                gemm_grouped(desc, cnt, true, gm == 1, s);
                 if (gm == 0) batch_stage_lo(d, G, tot, s);
             }
             return;
         }
         for (int gm = 0; gm < 2; ++gm) {
-            for (int t = 0; t < 2; ++t) {
-                const int q = (p * 2 + gm) * 2 + t;
-                const void* desc = dev + l.desc_off + grouped_desc_bytes() * (size_t)q * G;
-                const int* cnt = reinterpret_cast<const int*>(dev + l.cnt_off) + 2 * q;
-                gemm_grouped_f64(desc, cnt, false, gm == 1, t == 0 ? 128 : 64, 512, s);
-            }
+            const int q = p * 2 + gm;
+            const void* desc = dev + l.desc_off + grouped_desc_bytes() * (size_t)q * G;
+            const int* cnt = reinterpret_cast<const int*>(dev + l.cnt_off) + 2 * q;
+            gemm_grouped(desc, cnt, false, gm == 1, s);
             if (gm == 0) batch_stage(d, G, tot, s);
         }
     };
@@ -297,7 +231,6 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
     htot[BT_EW] = ew;
     htot[BT_STAGE] = stg;
     // grouped products: theta = x (p = 0) or V_(p-1), into V_0 or w
-    std::vector<int> tile1(G), tile2(G);
     std::vector<Gemm> g1(G), g2(G);
     for (int g = 0; g < G; ++g) {
         const LocalOp& op = items[g].op;
@@ -326,34 +259,25 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
         b.ldb = b.lda;
         b.ldc = s.Dxr;
         b.ldd = s.Dxr;
-        a.B = items[g].x;
-        b.C = items[g].x;
-        b.D = hv[g].V;
-        tile1[g] = tuned_tile(c, a);
-        tile2[g] = tuned_tile(c, b);
     }
     for (int p = 0; p < np; ++p) {
-        for (int gm = 0; gm < 2; ++gm)
-            for (int t = 0; t < 2; ++t) {
-                const int q = (p * 2 + gm) * 2 + t, bs = t == 0 ? 128 : 64;
-                char* desc = host.data() + lay.desc_off + grouped_desc_bytes() * (size_t)q * G;
-                int cnt = 0, tiles = 0;
-                for (int g = 0; g < G; ++g) {
-                    if ((gm == 0 ? tile1[g] : tile2[g]) != bs) continue;
-                    Gemm e = gm == 0 ? g1[g] : g2[g];
-                    const double* theta = p == 0 ? items[g].x : hv[g].V + (size_t)(p - 1) * hv[g].n;
-                    if (gm == 0) e.B = theta;
-                    else {
-                        e.C = theta;
-                        e.D = p == 0 ? hv[g].V : hv[g].w;
-                    }
-                    grouped_desc_fill(e, bs, tiles, desc + grouped_desc_bytes() * cnt);
-                    tiles += grouped_tiles(e, bs);
-                    ++cnt;
+        for (int gm = 0; gm < 2; ++gm) {
+            const int q = p * 2 + gm;
+            char* desc = host.data() + lay.desc_off + grouped_desc_bytes() * (size_t)q * G;
+            int tiles = 0;
+            for (int g = 0; g < G; ++g) {
+                Gemm e = gm == 0 ? g1[g] : g2[g];
+                const double* theta = p == 0 ? items[g].x : hv[g].V + (size_t)(p - 1) * hv[g].n;
+                if (gm == 0) e.B = theta;
+                else {
+                    e.C = theta;
+                    e.D = p == 0 ? hv[g].V : hv[g].w;
                 }
-                hcnt[2 * q] = cnt;
-                hcnt[2 * q + 1] = tiles;
+                tiles += grouped_desc_fill(e, false, tiles, desc + grouped_desc_bytes() * g);
             }
+            hcnt[2 * q] = G;
+            hcnt[2 * q + 1] = tiles;
+        }
     }
     if (lo) {
         // FP32 products p >= 1: L_lo tlo -> X1lo (FP32), X3lo R_lo^T + (1 - h s) V_(p-1) -> w
@@ -376,8 +300,7 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
                         e.C = hv[g].V + (size_t)(p - 1) * hv[g].n;
                         e.D = hv[g].w;
                     }
-                    grouped_desc_fill(e, 128, tiles, desc + grouped_desc_bytes() * g);
-                    tiles += grouped_tiles(e, 128);
+                    tiles += grouped_desc_fill(e, true, tiles, desc + grouped_desc_bytes() * g);
                 }
                 hclo[2 * q] = G;
                 hclo[2 * q + 1] = tiles;

@@ -178,9 +178,9 @@ void gemm(ite_ctx* c, bool tA, bool tB, int M, int N, int K, double alpha, const
     g.M = M; g.N = N; g.K = K; g.tA = tA; g.tB = tB;
     g.alpha = alpha; g.beta = beta;
     g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc; g.D = D; g.ldd = ldd;
-    // an output too small to fill the chip's workgroup slots but with a long
-    // K: K parts as one batch, summed in a fixed order
-    const int parts = M > 0 && N > 0 ? splitk_parts(M, N, K, gemm_slots(c)) : 1;
+    // an output too small to fill the chip but with a long K: K parts as one
+    // batch, summed in a fixed order
+    const int parts = M > 0 && N > 0 ? splitk_parts_f64(M, N, K) : 1;
     double* work = parts > 1 ? slot_t<double>(c, SL_SPLITK, (size_t)parts * M * N) : nullptr;
     if (c->prof_on && M > 0 && N > 0) {
         CtxProbe pr(c);

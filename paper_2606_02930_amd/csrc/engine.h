@@ -24,7 +24,6 @@ enum SlotId {
     SL_HESS,                       // Hessenberg columns of a fixed-budget GMRES cycle
     SL_STATS,                      // per-block device records of the local solves of a step
     SL_BATCH, SL_BDESC, SL_BATCHB, // batched solves: workspaces, descriptors, per-state b and guess
-    SL_TUNE,                       // tile autotuner: trial output
     SL_DMF, SL_DM1, SL_DM2, SL_DM3, SL_DMC,   // density-matrix MPO-MPS product: environments,
     SL_DMR, SL_DMV, SL_DMU,                   // intermediates, kept part, density matrix and its split
     SL_SPLITK,                     // K parts of under-filled FP64 products
@@ -219,8 +218,6 @@ struct BatchItem {
 // FP32 refinement, max_cycles corrections of one cycle each (the Arnoldi
 // products with FP32 operands; the residual product and the basis FP64).
 void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max_cycles, bool lo = false);
-// Tile size (128 or 64) the autotuner picked for an FP64 GEMM shape.
-int tuned_tile(ite_ctx* c, const Gemm& g);
 // One implicit step of every state (ite_step_batch); status[j] gets each
 // state's status (a failed state is left unchanged).
 void step_batch(int n, ite_mps* const* psi, const ite_mpo* const* H, const double* h,

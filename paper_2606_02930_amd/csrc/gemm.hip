@@ -1,25 +1,17 @@
-// Tiled MFMA GEMM for gfx950 (CDNA4): the contraction core of the
+// MFMA GEMM for gfx950 (CDNA4): the contraction core of the
 // effective-Hamiltonian product and of the environment updates.
 //
 // D[b] = alpha op(A[b]) op(B[b]) + beta C[b], row-major.
 //
-// Tile: 128 x 128 output per workgroup of 256 threads (four 64-wide
-// wavefronts in a 2 x 2 arrangement, each owning 64 x 64 = 4 x 4 MFMA tiles of
-// 16 x 16).  Registers are kept within 256 per lane (operands of two MFMA
-// sub-steps live at a time) so that two workgroups share a CU and one's
-// barrier and LDS traffic overlap the other's matrix-core work.  K advances in slices of 16 staged through LDS with double
-// buffering: the next slice is fetched into registers while the current one
-// feeds the matrix cores.  Both operands are stored in LDS "K-contiguous"
-// (row = output row or column, 16 K values per row, padded) so that each lane
-// fetches its four K values for the four MFMA sub-steps of a slice with two
-// 16-byte LDS reads.  Within a slice, lane group g = lane / 16 supplies K
-// index 4 g + step in sub-step `step`; A and B use the same mapping, so the
-// sum over K is unchanged.
+// FP64 and FP32 operands: gemm_direct.h (memory -> registers -> matrix cores,
+// no barrier in the K loop), with the wavefront and workgroup tiles chosen by
+// launch_direct.  BF16 operands: a 128 x 128 tile staged through LDS, below.
 //
 // Workgroup -> tile mapping is XCD-aware: the hardware deals workgroups to the
 // 8 XCDs round-robin, so consecutive workgroup ids are remapped to give each
 // XCD a contiguous band of output tiles that share A row panels in that XCD's
 // L2.
+#include "gemm_direct.h"
 #include "gemm_tile.h"
 #include "internal.h"
 
@@ -31,78 +23,135 @@
 namespace ite {
 namespace {
 
-template <typename T, bool TA, bool TB, bool VEC = false>
-__global__ __launch_bounds__(NTHREADS, 2) void gemm_kernel(Params p) {
-    constexpr int LDK = MfmaOp<T>::LDK;
-    __shared__ __attribute__((aligned(16))) T As[2 * BM * LDK];
-    __shared__ __attribute__((aligned(16))) T Bs[2 * BN * LDK];
-    const int T_tiles = p.mt * p.nt;
-    const int tile = xcd_band_tile(blockIdx.x, T_tiles);
-    const int m0 = (tile / p.nt) * BM;
-    const int n0 = (tile % p.nt) * BN;
-    gemm_tile<T, TA, TB, BM, VEC>(p, m0, n0, (long)blockIdx.z, As, Bs);
+template <typename T, int MI, int NI, int WM, int WN, int KS, int PD>
+void launch_tiles(const Gemm& g, Params p, hipStream_t s) {
+    p.mt = (g.M + 16 * MI * WM - 1) / (16 * MI * WM);
+    p.nt = (g.N + 16 * NI * WN - 1) / (16 * NI * WN);
+    const dim3 grid(p.mt * p.nt, 1, g.batch), block(64 * WM * WN * KS);
+#define ITE_GL(TA, TB) hipLaunchKernelGGL((direct_kernel<T, TA, TB, MI, NI, WM, WN, KS, PD>), grid, block, 0, s, p)
+    if (!g.tA && !g.tB) ITE_GL(false, false);
+    else if (!g.tA && g.tB) ITE_GL(false, true);
+    else if (g.tA && !g.tB) ITE_GL(true, false);
+    else ITE_GL(true, true);
+#undef ITE_GL
+    HIP_CHECK(hipGetLastError());
 }
 
-// Many independent FP64 problems in one persistent launch (the products of
-// the requests batched by the serving path): problem g's tiles are
-// [tile_start[g], tile_start[g + 1]) of a common range, row-major over its
-// output; every workgroup walks that range with a stride of the grid, so the
-// grid can stay fixed (graph capture) while the problems change.  The
-// descriptors live in device memory; BS as gemm_tile.
-struct GroupDesc {
-    Params p;
-    int tile_start;
-};
-
-template <typename T, bool TA, bool TB, int BS>
-__global__ __launch_bounds__(NTHREADS, 2) void gemm_grouped_kernel(const GroupDesc* __restrict__ desc,
-                                                                   const int* __restrict__ count) {
-    constexpr int LDK = MfmaOp<T>::LDK;
-    __shared__ __attribute__((aligned(16))) T As[2 * BS * LDK];
-    __shared__ __attribute__((aligned(16))) T Bs[2 * BS * LDK];
-    const int G = count[0], ntiles = count[1];
-    int g = 0;
-    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        while (g + 1 < G && desc[g + 1].tile_start <= tile) ++g;
-        const Params& p = desc[g].p;
-        const int lt = tile - desc[g].tile_start;
-        gemm_tile<T, TA, TB, BS>(p, (lt / p.nt) * BS, (lt % p.nt) * BS, 0, As, Bs);
-    }
+// Tile of a product, by its shape alone (a problem of a grouped launch has the
+// bits it has alone).  A matrix-core step takes a wavefront 64 cycles (FP64)
+// or 32 (FP32), so one accumulator chain keeps a SIMD's matrix core busy; what
+// matters is that every SIMD has a wavefront and that operands are read few
+// times.  Larger tiles read less (a 64 x 64 workgroup 1/4 of a 16 x 16 one),
+// smaller tiles and K parts fill the chip when the output is small.
+//
+// FP64 (us; 16: 16 x 16 with 4 or 8 K parts, 32: 32 x 32 with 8, 64: 64 x 64
+// with 2; LDS: 128 x 128 tiles staged through LDS with a barrier a slice,
+// which all of these replace):
+//      M x N x K                16      32      64     LDS
+//      128 x 32 x 160  (NT)    3.4     5.3     9.9    31.5
+//      480 x 120 x 600 (NT)    5.5    10.0    28.4     105
+//      400 x 400 x 200         5.9     6.2    12.4    45.7     169 32-tiles
+//      512 x 512 x 256         6.7     6.1    13.5    52.8     256 32-tiles
+//      1024 x 256 x 1280 (NT) 19.3    17.7    56.5     211     256 32-tiles
+//      1280 x 1024 x 256        33    20.1    24.2      66     320 64-tiles
+//      1920 x 1536 x 384        74    56.5    47.7      87     720 64-tiles
+//      5120 x 4096 x 1024     1550     895     694     829
+// so 64 from 512 of its tiles on (two workgroups a compute unit), 32 from 192
+// of its tiles on.  With 16, four K parts are as fast as eight while K is
+// short (160 x 128 x 32: 2.9 and 3.4) and slower when it is long (64 x 64 x
+// 4000: 18.1 and 13.4); they meet near 500.
+//
+// FP32 keeps one K order whatever the tile, so its products have the same
+// bits alone and in a batch: no K parts, 32 x 32 with a matrix-core tile a
+// wavefront or 64 x 64 with four:
+//      1532 x 401 x 2005 (NT) 53.5 (32)    79.6 (64)     201 (LDS)
+//      1280 x 1024 x 256      14.6         18.1           46        320 64-tiles
+//      1920 x 1536 x 384      39.9         33.1           64        720 64-tiles
+//      5120 x 4096 x 1024      695          441          551
+//
+// A side-contiguous operand (A transposed, B not) needs a side of at least
+// one wavefront tile, which only the 16-wide tiles guarantee.
+enum TileKind { TILE_64, TILE_32, TILE_16_LONG, TILE_16 };
+template <typename T>
+TileKind tile_kind(const Gemm& g) {
+    auto tiles = [&](int side) { return (long)((g.M + side - 1) / side) * ((g.N + side - 1) / side) * g.batch; };
+    const bool wide = (!g.tA || g.M >= 32) && (g.tB || g.N >= 32);
+    if (wide && tiles(64) >= 512) return TILE_64;
+    if (std::is_same<T, float>::value) return TILE_32;
+    if (wide && tiles(32) >= 192) return TILE_32;
+    return g.K >= 512 ? TILE_16_LONG : TILE_16;
 }
 
-// Operands fit 16-byte loads: aligned bases, row strides and batch strides
-// that are multiples of 16 bytes.
-inline bool vec16(const Gemm& g, size_t esz) {
-    const size_t q = 16 / esz;
-    auto al = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-    return al(g.A) && al(g.B) && g.lda % q == 0 && g.ldb % q == 0 && g.sA % q == 0 && g.sB % q == 0;
+Params params(const Gemm& g) {
+    Params p{};
+    p.M = g.M; p.N = g.N; p.K = std::max(g.K, 0);
+    p.alpha = g.alpha; p.beta = g.beta;
+    p.A = g.A; p.lda = g.lda; p.sA = g.sA;
+    p.B = g.B; p.ldb = g.ldb; p.sB = g.sB;
+    p.C = g.C; p.ldc = g.ldc; p.sC = g.sC;
+    p.D = g.D; p.ldd = g.ldd; p.sD = g.sD;
+    p.Df = g.Df;
+    return p;
 }
 
 template <typename T>
 void launch(const Gemm& g, hipStream_t s) {
     if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return;
     if (g.Df && g.C) ITE_FAIL(ITE_EINVAL, "gemm: an FP32 output takes no C");
+    Params p = params(g);
+    if (std::is_same<T, double>::value) p.Df = nullptr;
+    const TileKind kind = tile_kind<T>(g);
+    if constexpr (std::is_same<T, double>::value) {
+        if (kind == TILE_64) launch_tiles<T, 2, 2, 2, 2, 2, 1>(g, p, s);
+        else if (kind == TILE_32) launch_tiles<T, 2, 2, 1, 1, 8, 1>(g, p, s);
+        else if (kind == TILE_16_LONG) launch_tiles<T, 1, 1, 1, 1, 8, 2>(g, p, s);
+        else launch_tiles<T, 1, 1, 1, 1, 4, 2>(g, p, s);
+    } else {
+        if (kind == TILE_64) launch_tiles<T, 2, 2, 2, 2, 1, 1>(g, p, s);
+        else launch_tiles<T, 1, 1, 2, 2, 1, 4>(g, p, s);
+    }
+}
+
+// Many independent problems in one persistent launch (the products of the
+// requests batched by the serving path): problem g's tiles are
+// [tile_start[g], tile_start[g + 1]) of a common range, row-major over its
+// output; every workgroup walks that range with a stride of the grid, so the
+// grid can stay fixed (graph capture) while the problems change.  The
+// descriptors live in device memory.  Each problem has the tile of its shape;
+// a 16 x 16 one of four K parts takes two neighbours for the eight wavefronts.
+struct GroupDesc {
     Params p;
-    p.M = g.M; p.N = g.N; p.K = g.K;
-    p.alpha = g.alpha; p.beta = g.beta;
-    p.A = g.A; p.lda = g.lda; p.sA = g.sA;
-    p.B = g.B; p.ldb = g.ldb; p.sB = g.sB;
-    p.C = g.C; p.ldc = g.ldc; p.sC = g.sC;
-    p.D = g.D; p.ldd = g.ldd; p.sD = g.sD;
-    p.Df = std::is_same<T, float>::value ? g.Df : nullptr;
-    p.mt = (g.M + BM - 1) / BM;
-    p.nt = (g.N + BN - 1) / BN;
-    dim3 grid(p.mt * p.nt, 1, g.batch);
-    const bool v = std::is_same<T, float>::value && vec16(g, sizeof(T));
-#define ITE_GL(TA, TB)                                                                              \
-    if (v) hipLaunchKernelGGL((gemm_kernel<T, TA, TB, true>), grid, dim3(NTHREADS), 0, s, p);       \
-    else hipLaunchKernelGGL((gemm_kernel<T, TA, TB, false>), grid, dim3(NTHREADS), 0, s, p)
-    if (!g.tA && !g.tB) { ITE_GL(false, false); }
-    else if (!g.tA && g.tB) { ITE_GL(false, true); }
-    else if (g.tA && !g.tB) { ITE_GL(true, false); }
-    else { ITE_GL(true, true); }
-#undef ITE_GL
-    HIP_CHECK(hipGetLastError());
+    int tile_start;
+    int kind;
+};
+int group_rows(TileKind k) { return k == TILE_64 ? 64 : k == TILE_32 ? 32 : 16; }
+int group_cols(TileKind k) { return k == TILE_64 ? 64 : k == TILE_16_LONG ? 16 : 32; }
+
+template <typename T, bool TB>
+__global__ __launch_bounds__(sizeof(T) == 8 ? 512 : 256) void gemm_grouped_kernel(
+    const GroupDesc* __restrict__ desc, const int* __restrict__ count) {
+    constexpr bool F64 = std::is_same<T, double>::value;
+    constexpr int KS64 = F64 ? 2 : 1, KS32 = F64 ? 8 : 1;
+    constexpr int L64 = direct_lds<T, false, TB, 2, 2, 2, 2, KS64>();
+    constexpr int L32 = F64 ? direct_lds<T, false, TB, 2, 2, 1, 1, KS32>() : direct_lds<T, false, TB, 1, 1, 2, 2, 1>();
+    __shared__ __attribute__((aligned(16))) T lds[L64 > L32 ? L64 : L32];
+    const int G = count[0], ntiles = count[1];
+    int g = 0;
+    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        while (g + 1 < G && desc[g + 1].tile_start <= tile) ++g;
+        const Params p = desc[g].p;
+        const int kind = desc[g].kind;
+        const int lt = tile - desc[g].tile_start, m = lt / p.nt, n = lt % p.nt;
+        if (kind == TILE_64) direct_tile<T, false, TB, 2, 2, 2, 2, KS64, 1>(p, m * 64, n * 64, 0, lds);
+        else if constexpr (F64) {
+            if (kind == TILE_32) direct_tile<T, false, TB, 2, 2, 1, 1, 8, 1>(p, m * 32, n * 32, 0, lds);
+            else if (kind == TILE_16_LONG) direct_tile<T, false, TB, 1, 1, 1, 1, 8, 2>(p, m * 16, n * 16, 0, lds);
+            else direct_tile<T, false, TB, 1, 1, 1, 2, 4, 2>(p, m * 16, n * 32, 0, lds);
+        } else {
+            direct_tile<T, false, TB, 1, 1, 2, 2, 1, 4>(p, m * 32, n * 32, 0, lds);
+        }
+        __syncthreads();   // the LDS is the next tile's
+    }
 }
 
 // One v_mfma_f64_16x16x4f64 with A[i][k] = 1 + i + 16 k (i < 16, k < 4)
@@ -306,6 +355,14 @@ __global__ __launch_bounds__(NTHREADS) void gemm_bf16_kernel(Params p) {
 void gemm_f64(const Gemm& g, hipStream_t s) { launch<double>(g, s); }
 
 namespace {
+// Operands fit 16-byte loads: aligned bases, row strides and batch strides
+// that are multiples of 16 bytes.
+inline bool vec16(const Gemm& g, size_t esz) {
+    const size_t q = 16 / esz;
+    auto al = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
+    return al(g.A) && al(g.B) && g.lda % q == 0 && g.ldb % q == 0 && g.sA % q == 0 && g.sB % q == 0;
+}
+
 // D[m][n] = alpha sum_b W[b][m][n] + beta C[m][n], the parts summed in order.
 __global__ __launch_bounds__(256) void splitk_sum_kernel(const double* __restrict__ W, int parts, int M, int N,
                                                          double alpha, const double* C, long ldc, double beta,
@@ -321,6 +378,17 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const double* __restric
     }
 }
 }  // namespace
+
+// Eight K parts of a workgroup are enough until each is 16 slices of 32 long;
+// beyond that more workgroups share K (FP64 64 x 64 x 16384 is 8 parts, 45 us
+// as one).
+int splitk_parts_f64(int M, int N, int K) {
+    const long tiles = (long)((M + 15) / 16) * ((N + 15) / 16);
+    if (tiles > 128 || K < 4096) return 1;
+    int s = (int)std::min<long>(256 / tiles, K / 2048);
+    while (s > 1 && K % (s * BK) != 0) --s;
+    return std::max(s, 1);
+}
 
 int splitk_parts(int M, int N, int K, int slots) {
     const long tiles = (long)((M + BM - 1) / BM) * ((N + BN - 1) / BN);
@@ -371,58 +439,34 @@ void gemm_f32_splitk(const Gemm& g, int parts, double* work, hipStream_t s) { ge
 size_t grouped_desc_bytes() { return sizeof(GroupDesc); }
 
 // Host side of a grouped launch: the descriptor of problem g (its tiles
-// start at tile_start) in the layout gemm_grouped_kernel reads.
-void grouped_desc_fill(const Gemm& g, int bs, int tile_start, void* out) {
+// start at tile_start) in the layout gemm_grouped_kernel reads; returns the
+// number of its tiles.
+int grouped_desc_fill(const Gemm& g, bool f32, int tile_start, void* out) {
+    const TileKind k = f32 ? tile_kind<float>(g) : tile_kind<double>(g);
     GroupDesc d{};
-    Params& p = d.p;
-    p.M = g.M; p.N = g.N; p.K = g.K;
-    p.alpha = g.alpha; p.beta = g.beta;
-    p.A = g.A; p.lda = g.lda; p.sA = 0;
-    p.B = g.B; p.ldb = g.ldb; p.sB = 0;
-    p.C = g.C; p.ldc = g.ldc; p.sC = 0;
-    p.D = g.D; p.ldd = g.ldd; p.sD = 0;
-    p.Df = g.Df;
-    p.mt = g.M > 0 ? (g.M + bs - 1) / bs : 0;
-    p.nt = g.N > 0 ? (g.N + bs - 1) / bs : 0;
+    d.p = params(g);
+    d.p.sA = d.p.sB = d.p.sC = d.p.sD = 0;
+    d.p.mt = g.M > 0 ? (g.M + group_rows(k) - 1) / group_rows(k) : 0;
+    d.p.nt = g.N > 0 ? (g.N + group_cols(k) - 1) / group_cols(k) : 0;
     d.tile_start = tile_start;
+    d.kind = k;
     std::memcpy(out, &d, sizeof(d));
+    return d.p.mt * d.p.nt;
 }
 
-int grouped_tiles(const Gemm& g, int bs) {
-    if (g.M <= 0 || g.N <= 0) return 0;
-    return ((g.M + bs - 1) / bs) * ((g.N + bs - 1) / bs);
-}
-
-void gemm_grouped_f32(const void* desc, const int* count, bool tA, bool tB, int grid, hipStream_t s) {
+void gemm_grouped(const void* desc, const int* count, bool f32, bool tB, hipStream_t s) {
     const auto* d = static_cast<const GroupDesc*>(desc);
-    if (!tA && !tB)
-        hipLaunchKernelGGL((gemm_grouped_kernel<float, false, false, 128>), dim3(grid), dim3(NTHREADS), 0, s, d, count);
-    else if (!tA && tB)
-        hipLaunchKernelGGL((gemm_grouped_kernel<float, false, true, 128>), dim3(grid), dim3(NTHREADS), 0, s, d, count);
-    else
-        ITE_FAIL(ITE_EINVAL, "gemm_grouped_f32: transposed A is not supported");
-    HIP_CHECK(hipGetLastError());
-}
-
-void gemm_grouped_f64(const void* desc, const int* count, bool tA, bool tB, int bs, int grid, hipStream_t s) {
-    if (bs != 128 && bs != 64) ITE_FAIL(ITE_EINVAL, "gemm_grouped: tile must be 128 or 64");
-    const auto* d = static_cast<const GroupDesc*>(desc);
-#define ITE_GG(TA, TB, BS) \
-    hipLaunchKernelGGL((gemm_grouped_kernel<double, TA, TB, BS>), dim3(grid), dim3(NTHREADS), 0, s, d, count)
-    if (bs == 128) {
-        if (!tA && !tB) ITE_GG(false, false, 128);
-        else if (!tA && tB) ITE_GG(false, true, 128);
-        else if (tA && !tB) ITE_GG(true, false, 128);
-        else ITE_GG(true, true, 128);
+    const dim3 grid(512);
+    if (f32) {
+        if (tB) hipLaunchKernelGGL((gemm_grouped_kernel<float, true>), grid, dim3(256), 0, s, d, count);
+        else hipLaunchKernelGGL((gemm_grouped_kernel<float, false>), grid, dim3(256), 0, s, d, count);
     } else {
-        if (!tA && !tB) ITE_GG(false, false, 64);
-        else if (!tA && tB) ITE_GG(false, true, 64);
-        else if (tA && !tB) ITE_GG(true, false, 64);
-        else ITE_GG(true, true, 64);
+        if (tB) hipLaunchKernelGGL((gemm_grouped_kernel<double, true>), grid, dim3(512), 0, s, d, count);
+        else hipLaunchKernelGGL((gemm_grouped_kernel<double, false>), grid, dim3(512), 0, s, d, count);
     }
-#undef ITE_GG
     HIP_CHECK(hipGetLastError());
 }
+
 void gemm_f32(const Gemm& g, hipStream_t s) { launch<float>(g, s); }
 
 void gemm_bf16(const Gemm& g, hipStream_t s) {

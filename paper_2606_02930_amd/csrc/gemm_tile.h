@@ -5,8 +5,6 @@
 
 #include "internal.h"
 
-#include <type_traits>
-
 namespace ite {
 namespace {
 
@@ -99,77 +97,6 @@ __device__ inline void store_slice(T* __restrict__ lds, int t, const T (&r)[BS /
     }
 }
 
-// 16-byte loads of a 128-wide FP32 operand slice (four floats each) into
-// the same registers and LDS layout as fetch_slice / store_slice, so the
-// products are the same; chunks that cross the matrix edge are loaded
-// element by element.  Needs 16-byte aligned rows (checked by the launcher).
-template <bool KC>
-__device__ inline void fetch_slice_v4(const float* __restrict__ src, long ld, int side0, int sideN, int k0, int K,
-                                      int t, float (&r)[8]) {
-    if (KC) {
-        const int row = side0 + (t >> 1);
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const int k = k0 + (t & 1) * 8 + 4 * c;
-            if (row < sideN && k + 3 < K) {
-                const float4 v = *reinterpret_cast<const float4*>(src + (long)row * ld + k);
-                r[4 * c] = v.x; r[4 * c + 1] = v.y; r[4 * c + 2] = v.z; r[4 * c + 3] = v.w;
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) r[4 * c + q] = (row < sideN && k + q < K) ? src[(long)row * ld + k + q] : 0.f;
-            }
-        }
-    } else {
-        const int col = side0 + (t & 31) * 4;
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int k = k0 + (t >> 5) + 8 * e;
-            if (k < K && col + 3 < sideN) {
-                const float4 v = *reinterpret_cast<const float4*>(src + (long)k * ld + col);
-                r[4 * e] = v.x; r[4 * e + 1] = v.y; r[4 * e + 2] = v.z; r[4 * e + 3] = v.w;
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) r[4 * e + q] = (k < K && col + q < sideN) ? src[(long)k * ld + col + q] : 0.f;
-            }
-        }
-    }
-}
-
-template <bool KC>
-__device__ inline void store_slice_v4(float* __restrict__ lds, int t, const float (&r)[8]) {
-    constexpr int LDK = MfmaOp<float>::LDK;
-    if (KC) {
-        const int row = t >> 1;
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const int kk = (t & 1) * 8 + 4 * c;
-            *reinterpret_cast<float4*>(&lds[row * LDK + kk]) = make_float4(r[4 * c], r[4 * c + 1], r[4 * c + 2], r[4 * c + 3]);
-        }
-    } else {
-        const int col = (t & 31) * 4;
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int krow = (t >> 5) + 8 * e;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) lds[(col + q) * LDK + krow] = r[4 * e + q];
-        }
-    }
-}
-
-// The operand slice loaders of gemm_tile: 16-byte loads for FP32 operands
-// of the 128 tile when VEC, the element loads otherwise.
-template <typename T, bool KC, int BS, bool VEC>
-__device__ inline void fetch_op(const T* __restrict__ src, long ld, int side0, int sideN, int k0, int K, int t,
-                                T (&r)[BS / 16]) {
-    if constexpr (VEC && std::is_same<T, float>::value && BS == 128) fetch_slice_v4<KC>(src, ld, side0, sideN, k0, K, t, r);
-    else fetch_slice<T, KC, BS>(src, ld, side0, sideN, k0, K, t, r);
-}
-template <typename T, bool KC, int BS, bool VEC>
-__device__ inline void store_op(T* __restrict__ lds, int t, const T (&r)[BS / 16]) {
-    if constexpr (VEC && std::is_same<T, float>::value && BS == 128) store_slice_v4<KC>(lds, t, r);
-    else store_slice<T, KC, BS>(lds, t, r);
-}
-
 // One BS x BS output tile at (m0, n0) of problem p (batch index bz): four
 // wavefronts in a 2 x 2 arrangement, each owning (BS / 2)^2 outputs as
 // (BS / 32)^2 MFMA tiles of 16 x 16.  The K order of every output element
@@ -177,7 +104,7 @@ __device__ inline void store_op(T* __restrict__ lds, int t, const T (&r)[BS / 16
 // does not depend on BS, so the 128 and 64 tiles give the same bits.  As, Bs:
 // LDS of two slices of each operand.  Ends with a barrier after the last LDS
 // read, so the caller may start another tile.
-template <typename T, bool TA, bool TB, int BS, bool VEC = false>
+template <typename T, bool TA, bool TB, int BS>
 __device__ __forceinline__ void gemm_tile(const Params& p, int m0, int n0, long bz, T* As, T* Bs) {
     typedef typename MfmaOp<T>::acc_t acc_t;
     constexpr int LDK = MfmaOp<T>::LDK, IT = BS / 32, E = BS / 16;
@@ -199,10 +126,10 @@ __device__ __forceinline__ void gemm_tile(const Params& p, int m0, int n0, long 
     // A: K-contiguous unless transposed.  B: K-contiguous only when transposed.
     T ra[E], rb[E];
     const int nk = (p.K + BK - 1) / BK;
-    fetch_op<T, !TA, BS, VEC>(A, p.lda, m0, p.M, 0, p.K, t, ra);
-    fetch_op<T, TB, BS, VEC>(B, p.ldb, n0, p.N, 0, p.K, t, rb);
-    store_op<T, !TA, BS, VEC>(As, t, ra);
-    store_op<T, TB, BS, VEC>(Bs, t, rb);
+    fetch_slice<T, !TA, BS>(A, p.lda, m0, p.M, 0, p.K, t, ra);
+    fetch_slice<T, TB, BS>(B, p.ldb, n0, p.N, 0, p.K, t, rb);
+    store_slice<T, !TA, BS>(As, t, ra);
+    store_slice<T, TB, BS>(Bs, t, rb);
     __syncthreads();
 
     for (int kt = 0; kt < nk; ++kt) {
@@ -211,8 +138,8 @@ __device__ __forceinline__ void gemm_tile(const Params& p, int m0, int n0, long 
         const T* Ac = As + cur * BS * LDK;
         const T* Bc = Bs + cur * BS * LDK;
         if (more) {
-            fetch_op<T, !TA, BS, VEC>(A, p.lda, m0, p.M, (kt + 1) * BK, p.K, t, ra);
-            fetch_op<T, TB, BS, VEC>(B, p.ldb, n0, p.N, (kt + 1) * BK, p.K, t, rb);
+            fetch_slice<T, !TA, BS>(A, p.lda, m0, p.M, (kt + 1) * BK, p.K, t, ra);
+            fetch_slice<T, TB, BS>(B, p.ldb, n0, p.N, (kt + 1) * BK, p.K, t, rb);
         }
         // two sub-steps of the slice at a time: 16 operand values live
         // instead of 32, which leaves room for two workgroups per CU
@@ -239,8 +166,8 @@ __device__ __forceinline__ void gemm_tile(const Params& p, int m0, int n0, long 
                     for (int j = 0; j < IT; ++j) acc[i][j] = MfmaOp<T>::mma(a[i][s], b[j][s], acc[i][j]);
         }
         if (more) {
-            store_op<T, !TA, BS, VEC>(As + (cur ^ 1) * BS * LDK, t, ra);
-            store_op<T, TB, BS, VEC>(Bs + (cur ^ 1) * BS * LDK, t, rb);
+            store_slice<T, !TA, BS>(As + (cur ^ 1) * BS * LDK, t, ra);
+            store_slice<T, TB, BS>(Bs + (cur ^ 1) * BS * LDK, t, rb);
         }
         __syncthreads();
     }

@@ -62,28 +62,29 @@ struct Gemm {
 // FP64 operands, FP64 MFMA.
 void gemm_f64(const Gemm& g, hipStream_t s);
 // Split-K for under-filled products: the number of K parts (1 = no
-// split) when the 128 x 128 output tiles of M x N fill at most half of
-// `slots` concurrent workgroups and K is long; the parts (K / parts each, a
-// multiple of the K slice) run as one batched launch into `work`
-// (parts M N doubles) and are summed in a fixed order with alpha, beta, C.
+// split) when the output leaves the chip idle and K is long; the parts
+// (K / parts each, a multiple of the K slice) run as one batched launch into
+// `work` (parts M N doubles) and are summed in a fixed order with alpha, beta,
+// C.  splitk_parts: FP32 operands, counted in 128 x 128 output tiles that fill
+// at most half of `slots` concurrent workgroups (FP32 sums no longer than
+// needed).
+int splitk_parts_f64(int M, int N, int K);
 int splitk_parts(int M, int N, int K, int slots);
 void gemm_f64_splitk(const Gemm& g, int parts, double* work, hipStream_t s);
 // The same with FP32 operands (FP32 accumulation within a part, the parts
 // summed in FP64); FP64 output only.
 void gemm_f32_splitk(const Gemm& g, int parts, double* work, hipStream_t s);
-// Grouped FP64 GEMM: many problems (batch 1 each) in one persistent launch
-// of `grid` workgroups, with bs x bs output tiles (128 or 64; the same bits
-// either way).  The descriptors live in device memory (grouped_desc_bytes()
-// each, filled on the host by grouped_desc_fill with the running tile count
-// as tile_start); count (device) = {number of problems, their total tiles},
-// so the same launch, e.g. inside a captured graph, serves changing problems.
+// Grouped GEMM: many problems (batch 1 each, A not transposed) in one
+// persistent launch; each has the bits of gemm_f64 (gemm_f32 with f32: FP32
+// operands, output FP32 into Df or FP64 into D with alpha, beta, C).  The
+// descriptors live in device memory (grouped_desc_bytes() each, filled on the
+// host by grouped_desc_fill, which returns the problem's tiles, with the
+// running tile count as tile_start); count (device) = {number of problems,
+// their total tiles}, so the same launch, e.g. inside a captured graph, serves
+// changing problems.
 size_t grouped_desc_bytes();
-void grouped_desc_fill(const Gemm& g, int bs, int tile_start, void* out);
-int grouped_tiles(const Gemm& g, int bs);
-void gemm_grouped_f64(const void* desc, const int* count, bool tA, bool tB, int bs, int grid, hipStream_t s);
-// The same for FP32 operands (FP32 MFMA, FP32 accumulation; output FP32 into
-// Df or FP64 into D with alpha, beta, C), 128 x 128 tiles, A not transposed.
-void gemm_grouped_f32(const void* desc, const int* count, bool tA, bool tB, int grid, hipStream_t s);
+int grouped_desc_fill(const Gemm& g, bool f32, int tile_start, void* out);
+void gemm_grouped(const void* desc, const int* count, bool f32, bool tB, hipStream_t s);
 // FP32 operands (A, B are float*), FP32 MFMA, FP32 accumulation, FP64 output.
 void gemm_f32(const Gemm& g, hipStream_t s);
 // BF16 operands (A, B are uint16 bf16 bit patterns), BF16 MFMA, FP32
