@@ -135,7 +135,7 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
         const size_t n = op.n();
         ITE_REQUIRE((size_t)mm < n, "gmres_batch: Krylov dimension must be below the vector length");
         const int I = op.s.w0 * op.s.d1 * op.s.d2, O = op.s.d1 * op.s.d2 * op.s.w2;
-        ITE_REQUIRE(I <= BATCH_STAGE_SC, "gmres_batch: more than 128 MPO-stage inputs");
+        ITE_REQUIRE(I <= BATCH_STAGE_I, "gmres_batch: more than 128 MPO-stage inputs");
         const size_t nxi = (size_t)op.s.Dxl * std::max(I, O) * op.s.Dyr;
         off[g] = total;
         total += al((size_t)(mm + 1) * n) + al(n) + 2 * al(nxi) + al((size_t)reduce_blocks(n) * 64 + 64) +
@@ -211,6 +211,8 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
         st.rowptr = op.ww->rowptr;
         st.col = op.ww->col;
         st.val = op.ww->val;
+        st.nnz = op.ww->nnz;
+        st.csr_lds = st.nnz >= 0 && (size_t)st.nnz * 12 + (size_t)(st.O + 1) * 4 <= BATCH_STAGE_CSR;
         if (lo) {
             Stage& sl = v.st_lo;
             sl = st;
@@ -225,7 +227,7 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
         v.stage_start = stg;
         red += v.nb;
         ew += (int)((n + BATCH_EW - 1) / BATCH_EW);
-        stg += op.s.Dxl * ((op.s.Dyr + BATCH_STAGE_SC - 1) / BATCH_STAGE_SC);
+        stg += op.s.Dxl * ((op.s.Dyr + (1 << BATCH_STAGE_LC) - 1) >> BATCH_STAGE_LC);
     }
     htot[BT_RED] = red;
     htot[BT_EW] = ew;

@@ -1213,7 +1213,7 @@ struct StepRun {
         const bool prec_ok = o.precision == ITE_PREC_FP64 ||
                              (o.precision == ITE_PREC_FP32_IR && o.tol_refine <= 0.0 && o.max_cycles == 1);
         return prec_ok && o.tol_loc <= 0.0 && o.krylov_dim <= 16 && (size_t)o.krylov_dim < block_n(slot) &&
-               I <= BATCH_STAGE_SC;
+               I <= BATCH_STAGE_I;
     }
     // The batch's cycles and precision for a batchable solve.
     bool batch_lo() const { return o.precision != ITE_PREC_FP64; }

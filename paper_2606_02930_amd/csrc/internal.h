@@ -225,7 +225,9 @@ void batch_zero_stats(const BatchVec* d, int G, hipStream_t s);
 void batch_stage(const BatchVec* d, int G, const int* tot, hipStream_t s);
 // The FP32 stage st_lo of every problem (FP32 in, FP32 out).
 void batch_stage_lo(const BatchVec* d, int G, const int* tot, hipStream_t s);
-constexpr int BATCH_STAGE_SC = 128;
+constexpr int BATCH_STAGE_I = 128;        // inputs at most
+constexpr int BATCH_STAGE_LC = 5;         // log2 of the columns of a unit
+constexpr size_t BATCH_STAGE_CSR = 16384; // bytes of LDS for the CSR matrix
 
 // Observability of kernel launches: every launch of a kind is counted, some
 // are bracketed by events (begin returns true for those), and the

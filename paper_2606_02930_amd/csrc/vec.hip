@@ -379,85 +379,33 @@ __global__ void transpose_kernel(const double* __restrict__ in, int rows, int co
 }
 
 // ---------------------------------------------------------------------------
-// Sparse MPO stage.  A block handles one g and SC consecutive columns; the
-// I inputs of those columns are staged in LDS, then every thread produces the
-// O outputs of its column from the CSR rows (uniform across the block, so the
-// matrix entries come through scalar loads).  SC shrinks with I so that the
-// staged inputs stay within 128 KiB of LDS: SC = 128 up to 128 inputs, down
-// to 16 columns for the largest stage an MPO can have (w = 16, d = 8: 1024).
+// Sparse MPO stage.  A workgroup handles one g and CL V consecutive columns
+// (CL = 2^lc lanes of V columns): the I inputs of those columns and the CSR
+// matrix are staged in LDS, then the STAGE_NT / CL groups of lanes share the O
+// outputs.  It is a copy with a few multiply-adds, so memory bounds it when
+// it is large and latency when it is small: the lanes over the outputs keep
+// the chain of LDS reads short and let a small column tile fill the chip
+// without idle lanes.  Against one thread a column looping over all outputs,
+// whose inputs left room for one or two wavefronts a compute unit: bond 32
+// (d 2, w 5) 13.4 -> 3.7 us, bond 64 (d 4, w 6) 62 -> 4.7, bond 1024 (d 2)
+// 121 -> 59 us (5.7 TB/s), FP32 in and BF16 out at bond 256 (d 4) 87 -> 16.  The terms of an output are summed in CSR order
+// whatever the tile.
+// V = 4: unit column strides, every stride a multiple of 4, 16-byte aligned
+// bases: 16-byte loads and stores.  V = 1: any strides.
+// OUT: 0 writes FP64 to st.out, 1 rounds to FP32 and 2 to BF16 into st.out_lo
+// (the operand of a following low-precision contraction).
 // ---------------------------------------------------------------------------
+constexpr int STAGE_NT = 256;
 constexpr size_t STAGE_LDS = 128 * 1024;
 // LDS of a stage workgroup: the inputs (at most STAGE_LDS) and, when it fits,
 // the CSR matrix behind them
 constexpr size_t STAGE_LDS_TOTAL = 152 * 1024;
 
-// OUT: 0 writes FP64 to st.out, 1 rounds to FP32 and 2 to BF16 into st.out_lo
-// (the operand of a following low-precision contraction).
-template <int OUT, int SC>
-__device__ inline void stage_unit(const Stage& st, int g, int cblk, double* xin) {
-    const int c = cblk * SC + threadIdx.x;
-    const long cin = (long)g * st.in_gs + (long)c * st.in_cs;
-    if (st.in_f32) {
-        const float* __restrict__ in = st.in_f32 + cin;
-        for (int i = 0; i < st.I; ++i) {
-            const long off = (long)(i / st.in_div) * st.in_s1 + (long)(i % st.in_div) * st.in_s2;
-            xin[i * SC + threadIdx.x] = (c < st.C) ? (double)in[off] : 0.0;
-        }
-    } else {
-        const double* __restrict__ in = st.in + cin;
-        for (int i = 0; i < st.I; ++i) {
-            const long off = (long)(i / st.in_div) * st.in_s1 + (long)(i % st.in_div) * st.in_s2;
-            xin[i * SC + threadIdx.x] = (c < st.C) ? in[off] : 0.0;
-        }
-    }
-    // the CSR matrix in LDS when it fits behind the inputs (read as
-    // broadcasts instead of a chain of dependent scalar loads)
-    const int nnz = st.nnz;
-    const bool lcsr = st.csr_lds != 0;
-    double* sval = xin + (size_t)st.I * SC;
-    int* scol = reinterpret_cast<int*>(sval + nnz);
-    int* srow = scol + nnz;
-    if (lcsr) {
-        for (int e = threadIdx.x; e < nnz; e += SC) {
-            sval[e] = st.val[e];
-            scol[e] = st.col[e];
-        }
-        for (int o = threadIdx.x; o <= st.O; o += SC) srow[o] = st.rowptr[o];
-    }
-    __syncthreads();
-    if (c < st.C) {
-        const long base = (long)g * st.out_gs + (long)c * st.out_cs;
-        const int* rp = lcsr ? srow : st.rowptr;
-        const int* cl = lcsr ? scol : st.col;
-        const double* vl = lcsr ? sval : st.val;
-        for (int o = 0; o < st.O; ++o) {
-            double acc = 0.0;
-            const int e1 = rp[o + 1];
-            for (int e = rp[o]; e < e1; ++e) acc += vl[e] * xin[cl[e] * SC + threadIdx.x];
-            const long at = base + (long)(o / st.out_div) * st.out_s1 + (long)(o % st.out_div) * st.out_s2;
-            if (OUT == 0) st.out[at] = acc;
-            else if (OUT == 1) static_cast<float*>(st.out_lo)[at] = (float)acc;
-            else static_cast<uint16_t*>(st.out_lo)[at] = to_bf16(acc);
-        }
-    }
-    __syncthreads();   // xin may be refilled by the caller's next unit
-}
-
-template <int OUT, int SC>
-__global__ __launch_bounds__(SC) void stage_kernel(Stage st) {
-    extern __shared__ double xin[];   // [I][SC]
-    stage_unit<OUT, SC>(st, blockIdx.y, blockIdx.x, xin);
-}
-
-// Four adjacent columns per thread (unit column strides, every stride a
-// multiple of 4, 16-byte aligned bases): 16-byte loads and stores instead of
-// one element per lane.  The inputs keep their type in LDS (an FP32 input
-// takes half the space, so twice the columns fit per compute unit), laid out
-// [I][4][SC] so that each LDS read is lane-contiguous.  Same sums in the same
-// order as stage_unit.
-template <typename TIN>
-__device__ inline void load4(const TIN* p, TIN (&v)[4]) {
-    if constexpr (sizeof(TIN) == 4) {
+template <int V, typename TIN>
+__device__ inline void load_cols(const TIN* p, TIN (&v)[V]) {
+    if constexpr (V == 1) {
+        v[0] = p[0];
+    } else if constexpr (sizeof(TIN) == 4) {
         const float4 q = *reinterpret_cast<const float4*>(p);
         v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
     } else {
@@ -467,70 +415,93 @@ __device__ inline void load4(const TIN* p, TIN (&v)[4]) {
     }
 }
 
-template <int OUT, int SC, typename TIN>
-__global__ __launch_bounds__(SC) void stage4_kernel(Stage st) {
-    extern __shared__ double lds_raw[];
-    TIN* xin = reinterpret_cast<TIN*>(lds_raw);   // [I][4][SC]
-    const int g = blockIdx.y;
-    const int t = threadIdx.x;
-    const int c0 = (blockIdx.x * SC + t) * 4;
-    const bool live = c0 < st.C;
+// Columns cb .. cb + CL V - 1 of group g; xin: LDS of I CL V inputs of type
+// TIN ([I][V][CL]: lane-contiguous reads), then the CSR copy.
+template <int OUT, int V, typename TIN>
+__device__ inline void stage_tile(const Stage& st, int g, int cb, int lc, TIN* xin) {
+    const int CL = 1 << lc, OG = STAGE_NT >> lc;
+    const int t = threadIdx.x, cl = t & (CL - 1), og = t >> lc;
+    const int c = cb + cl * V;
+    const bool live = c < st.C;
     const TIN* __restrict__ in;
     if constexpr (sizeof(TIN) == 4) in = st.in_f32;
     else in = st.in;
-    in += (long)g * st.in_gs + c0;
+    in += (long)g * st.in_gs + (long)c * (V == 1 ? st.in_cs : 1);
     const bool in_flat = st.in_div == 1;   // no division in the common layout
-    for (int i = 0; i < st.I; ++i) {
-        TIN v[4] = {0, 0, 0, 0};
+    for (int i = og; i < st.I; i += OG) {
+        TIN v[V];
+#pragma unroll
+        for (int q = 0; q < V; ++q) v[q] = 0;
         const long off = in_flat ? (long)i * st.in_s1
                                  : (long)(i / st.in_div) * st.in_s1 + (long)(i % st.in_div) * st.in_s2;
-        if (live) load4(in + off, v);
+        if (live) load_cols<V>(in + off, v);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) xin[(i * 4 + q) * SC + t] = v[q];
+        for (int q = 0; q < V; ++q) xin[(i * V + q) * CL + cl] = v[q];
     }
+    // the CSR matrix in LDS when it fits behind the inputs (read as
+    // broadcasts instead of a chain of dependent scalar loads)
     const int nnz = st.nnz;
     const bool lcsr = st.csr_lds != 0;
-    double* sval = reinterpret_cast<double*>(xin + (size_t)st.I * 4 * SC);
+    double* sval = reinterpret_cast<double*>(xin + ((size_t)st.I * V << lc));
     int* scol = reinterpret_cast<int*>(sval + nnz);
     int* srow = scol + nnz;
     if (lcsr) {
-        for (int e = t; e < nnz; e += SC) {
+        for (int e = t; e < nnz; e += STAGE_NT) {
             sval[e] = st.val[e];
             scol[e] = st.col[e];
         }
-        for (int o = t; o <= st.O; o += SC) srow[o] = st.rowptr[o];
+        for (int o = t; o <= st.O; o += STAGE_NT) srow[o] = st.rowptr[o];
     }
     __syncthreads();
-    if (!live) return;
-    const int* rp = lcsr ? srow : st.rowptr;
-    const int* cl = lcsr ? scol : st.col;
-    const double* vl = lcsr ? sval : st.val;
-    const long base = (long)g * st.out_gs + c0;
-    const bool out_flat = st.out_div == 1;
-    for (int o = 0; o < st.O; ++o) {
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        const int e1 = rp[o + 1];
-        for (int e = rp[o]; e < e1; ++e) {
-            const double w = vl[e];
-            const TIN* x = xin + cl[e] * 4 * SC + t;
+    if (live) {
+        const int* rp = lcsr ? srow : st.rowptr;
+        const int* col = lcsr ? scol : st.col;
+        const double* val = lcsr ? sval : st.val;
+        const long base = (long)g * st.out_gs + (long)c * (V == 1 ? st.out_cs : 1);
+        const bool out_flat = st.out_div == 1;
+        for (int o = og; o < st.O; o += OG) {
+            double acc[V];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) acc[q] += w * (double)x[q * SC];
-        }
-        const long at = base + (out_flat ? (long)o * st.out_s1
-                                         : (long)(o / st.out_div) * st.out_s1 + (long)(o % st.out_div) * st.out_s2);
-        if (OUT == 0) {
-            *reinterpret_cast<double2*>(st.out + at) = double2{acc[0], acc[1]};
-            *reinterpret_cast<double2*>(st.out + at + 2) = double2{acc[2], acc[3]};
-        } else if (OUT == 1) {
-            *reinterpret_cast<float4*>(static_cast<float*>(st.out_lo) + at) =
-                float4{(float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]};
-        } else {
-            uint2 v;
-            v.x = (uint32_t)to_bf16(acc[0]) | ((uint32_t)to_bf16(acc[1]) << 16);
-            v.y = (uint32_t)to_bf16(acc[2]) | ((uint32_t)to_bf16(acc[3]) << 16);
-            *reinterpret_cast<uint2*>(static_cast<uint16_t*>(st.out_lo) + at) = v;
+            for (int q = 0; q < V; ++q) acc[q] = 0.0;
+            const int e1 = rp[o + 1];
+            for (int e = rp[o]; e < e1; ++e) {
+                const double w = val[e];
+                const TIN* x = xin + ((col[e] * V) << lc) + cl;
+#pragma unroll
+                for (int q = 0; q < V; ++q) acc[q] += w * (double)x[q << lc];
+            }
+            const long at = base + (out_flat ? (long)o * st.out_s1
+                                             : (long)(o / st.out_div) * st.out_s1 + (long)(o % st.out_div) * st.out_s2);
+            if constexpr (OUT == 0) {
+                if constexpr (V == 1) {
+                    st.out[at] = acc[0];
+                } else {
+                    *reinterpret_cast<double2*>(st.out + at) = double2{acc[0], acc[1]};
+                    *reinterpret_cast<double2*>(st.out + at + 2) = double2{acc[2], acc[3]};
+                }
+            } else if constexpr (OUT == 1) {
+                float* out = static_cast<float*>(st.out_lo) + at;
+                if constexpr (V == 1) *out = (float)acc[0];
+                else *reinterpret_cast<float4*>(out) = float4{(float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]};
+            } else {
+                uint16_t* out = static_cast<uint16_t*>(st.out_lo) + at;
+                if constexpr (V == 1) {
+                    *out = to_bf16(acc[0]);
+                } else {
+                    uint2 v;
+                    v.x = (uint32_t)to_bf16(acc[0]) | ((uint32_t)to_bf16(acc[1]) << 16);
+                    v.y = (uint32_t)to_bf16(acc[2]) | ((uint32_t)to_bf16(acc[3]) << 16);
+                    *reinterpret_cast<uint2*>(out) = v;
+                }
+            }
         }
     }
+}
+
+template <int OUT, int V, typename TIN>
+__global__ __launch_bounds__(STAGE_NT) void stage_kernel(Stage st, int lc) {
+    extern __shared__ double stage_lds[];
+    stage_tile<OUT, V, TIN>(st, blockIdx.y, (blockIdx.x * V) << lc, lc, reinterpret_cast<TIN*>(stage_lds));
 }
 
 inline int grid_for(size_t n, int threads, int cap = 4096) {
@@ -864,19 +835,6 @@ void transpose(const double* in, int rows, int cols, double* out, hipStream_t s)
     HIP_CHECK(hipGetLastError());
 }
 
-template <int SC>
-static void stage_launch(Stage st, hipStream_t s) {
-    dim3 grid((st.C + SC - 1) / SC, st.G);
-    size_t lds = (size_t)st.I * SC * sizeof(double);
-    const size_t csr = (size_t)st.nnz * 12 + (size_t)(st.O + 1) * 4;
-    st.csr_lds = st.nnz >= 0 && lds + csr <= STAGE_LDS_TOTAL;
-    if (st.csr_lds) lds += csr;
-    if (st.out_prec == 0) hipLaunchKernelGGL((stage_kernel<0, SC>), grid, dim3(SC), lds, s, st);
-    else if (st.out_prec == 1) hipLaunchKernelGGL((stage_kernel<1, SC>), grid, dim3(SC), lds, s, st);
-    else hipLaunchKernelGGL((stage_kernel<2, SC>), grid, dim3(SC), lds, s, st);
-    HIP_CHECK(hipGetLastError());
-}
-
 // Whether the four-column kernel applies: unit column strides, strides and
 // the column count multiples of 4, 16-byte aligned bases.
 static bool stage4_ok(const Stage& st) {
@@ -891,42 +849,38 @@ static bool stage4_ok(const Stage& st) {
     return al(st.out_lo, st.out_prec == 1 ? 16 : 8);
 }
 
-template <int SC, typename TIN>
-static void stage4_launch(Stage st, hipStream_t s) {
-    dim3 grid((st.C / 4 + SC - 1) / SC, st.G);
-    size_t lds = (size_t)st.I * 4 * SC * sizeof(TIN);
-    lds = (lds + 7) & ~(size_t)7;
+// Column tile: as wide as leaves four workgroups a compute unit and their
+// inputs in a quarter of its LDS, but 16 columns (a 128-byte line of FP64) at
+// least; the narrowest tile holds the 1024 inputs of the largest stage an MPO
+// can have (w = 16, d = 8) in STAGE_LDS.
+template <int V, typename TIN>
+static void stage_launch(Stage st, hipStream_t s) {
+    constexpr int LMIN = V == 4 ? 2 : 4;
+    int lc = 6;
+    auto blocks = [&] { return (long)st.G * ((st.C + (V << lc) - 1) / (V << lc)); };
+    while (lc > LMIN && (blocks() < 1024 || ((size_t)st.I * V * sizeof(TIN) << lc) > 36 * 1024)) --lc;
+    const dim3 grid((st.C + (V << lc) - 1) / (V << lc), st.G);
+    size_t lds = (size_t)st.I * V * sizeof(TIN) << lc;
     const size_t csr = (size_t)st.nnz * 12 + (size_t)(st.O + 1) * 4;
     st.csr_lds = st.nnz >= 0 && lds + csr <= STAGE_LDS_TOTAL;
     if (st.csr_lds) lds += csr;
-    if (st.out_prec == 0) hipLaunchKernelGGL((stage4_kernel<0, SC, TIN>), grid, dim3(SC), lds, s, st);
-    else if (st.out_prec == 1) hipLaunchKernelGGL((stage4_kernel<1, SC, TIN>), grid, dim3(SC), lds, s, st);
-    else hipLaunchKernelGGL((stage4_kernel<2, SC, TIN>), grid, dim3(SC), lds, s, st);
+    if (st.out_prec == 0) hipLaunchKernelGGL((stage_kernel<0, V, TIN>), grid, dim3(STAGE_NT), lds, s, st, lc);
+    else if (st.out_prec == 1) hipLaunchKernelGGL((stage_kernel<1, V, TIN>), grid, dim3(STAGE_NT), lds, s, st, lc);
+    else hipLaunchKernelGGL((stage_kernel<2, V, TIN>), grid, dim3(STAGE_NT), lds, s, st, lc);
     HIP_CHECK(hipGetLastError());
-}
-
-template <typename TIN>
-static void stage4_pick(const Stage& st, hipStream_t s) {
-    const size_t per_col = (size_t)st.I * 4 * sizeof(TIN);
-    if (per_col * 64 <= STAGE_LDS) stage4_launch<64, TIN>(st, s);
-    else stage4_launch<32, TIN>(st, s);
 }
 
 void stage_f64(const Stage& st, hipStream_t s) {
     if (st.G <= 0 || st.C <= 0 || st.O <= 0) return;
     if (st.I < 1 || (size_t)st.I * 16 * sizeof(double) > STAGE_LDS)
         ITE_FAIL(ITE_EINVAL, "MPO stage: more than 1024 inputs per column");
-    const size_t in_bytes = st.in_f32 ? sizeof(float) : sizeof(double);
-    if (stage4_ok(st) && (size_t)st.I * 4 * 32 * in_bytes <= STAGE_LDS) {
-        if (st.in_f32) stage4_pick<float>(st, s);
-        else stage4_pick<double>(st, s);
-        return;
+    if (stage4_ok(st)) {
+        if (st.in_f32) stage_launch<4, float>(st, s);
+        else stage_launch<4, double>(st, s);
+    } else {
+        if (st.in_f32) stage_launch<1, float>(st, s);
+        else stage_launch<1, double>(st, s);
     }
-    const size_t per_col = (size_t)st.I * sizeof(double);
-    if (per_col * 128 <= STAGE_LDS) stage_launch<128>(st, s);
-    else if (per_col * 64 <= STAGE_LDS) stage_launch<64>(st, s);
-    else if (per_col * 32 <= STAGE_LDS) stage_launch<32>(st, s);
-    else stage_launch<16>(st, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -1052,16 +1006,19 @@ __global__ __launch_bounds__(64) void batch_hess_kernel(const BatchVec* __restri
 
 // LO: the FP32 stage st_lo (FP32 output) instead of st.
 template <bool LO>
-__global__ __launch_bounds__(BATCH_STAGE_SC) void batch_stage_kernel(const BatchVec* __restrict__ d, int G,
-                                                                     const int* __restrict__ tot) {
-    __shared__ double xin[BATCH_STAGE_SC * BATCH_STAGE_SC];
+__global__ __launch_bounds__(STAGE_NT) void batch_stage_kernel(const BatchVec* __restrict__ d, int G,
+                                                               const int* __restrict__ tot) {
+    __shared__ double lds[(BATCH_STAGE_I << BATCH_STAGE_LC) + BATCH_STAGE_CSR / 8];
     const int total = tot[BT_STAGE];
     for (int u = blockIdx.x; u < total; u += gridDim.x) {
         const int g = unit_problem(u, G, [&](int q) { return d[q].stage_start; });
         const Stage& st = LO ? d[g].st_lo : d[g].st;
-        const int nc = (st.C + BATCH_STAGE_SC - 1) / BATCH_STAGE_SC;
+        const int nc = (st.C + (1 << BATCH_STAGE_LC) - 1) >> BATCH_STAGE_LC;
         const int lu = u - d[g].stage_start;
-        stage_unit<LO ? 1 : 0, BATCH_STAGE_SC>(st, lu / nc, lu % nc, xin);
+        const int cb = (lu % nc) << BATCH_STAGE_LC;
+        if (LO) stage_tile<1, 1, float>(st, lu / nc, cb, BATCH_STAGE_LC, reinterpret_cast<float*>(lds));
+        else stage_tile<0, 1, double>(st, lu / nc, cb, BATCH_STAGE_LC, lds);
+        __syncthreads();   // the LDS is the next unit's
     }
 }
 
@@ -1123,13 +1080,13 @@ void batch_hess(const BatchVec* d, int G, int mm, bool r_product, bool last_cycl
 
 void batch_stage(const BatchVec* d, int G, const int* tot, hipStream_t s) {
     if (G <= 0) return;
-    hipLaunchKernelGGL(batch_stage_kernel<false>, dim3(BATCH_GRID), dim3(BATCH_STAGE_SC), 0, s, d, G, tot);
+    hipLaunchKernelGGL(batch_stage_kernel<false>, dim3(BATCH_GRID), dim3(STAGE_NT), 0, s, d, G, tot);
     HIP_CHECK(hipGetLastError());
 }
 
 void batch_stage_lo(const BatchVec* d, int G, const int* tot, hipStream_t s) {
     if (G <= 0) return;
-    hipLaunchKernelGGL(batch_stage_kernel<true>, dim3(BATCH_GRID), dim3(BATCH_STAGE_SC), 0, s, d, G, tot);
+    hipLaunchKernelGGL(batch_stage_kernel<true>, dim3(BATCH_GRID), dim3(STAGE_NT), 0, s, d, G, tot);
     HIP_CHECK(hipGetLastError());
 }
 
