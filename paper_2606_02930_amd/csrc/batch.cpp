@@ -57,14 +57,14 @@ BatchLayout layout(int G, int np, bool lo) {
 
 // The launch sequence of the batched solve on stream s; every argument is
 // either fixed for the batch's size and budget or read from `dev`.
-void issue(char* dev, const BatchLayout& l, int mm, int max_cycles, hipStream_t s) {
+void issue(char* dev, const BatchLayout& l, unsigned classes, int mm, int max_cycles, hipStream_t s) {
     const auto* d = reinterpret_cast<const BatchVec*>(dev + l.vec_off);
     const int* tot = reinterpret_cast<const int*>(dev + l.tot_off);
     const int G = l.G;
     auto product = [&](int p) {
         if (l.lo && p > 0) {
             // FP32 operands: the vector rounded, L_lo x, the FP32 stage, x3 R_lo^T
-            batch_vec(d, G, tot, 6, p - 1, s);
+            batch_vec(d, G, tot, 1, p - 1, s);
             for (int gm = 0; gm < 2; ++gm) {
                 const int q = p * 2 + gm;
                 const void* desc = dev + l.dlo_off + grouped_desc_bytes() * (size_t)q * G;
@@ -82,32 +82,17 @@ void issue(char* dev, const BatchLayout& l, int mm, int max_cycles, hipStream_t 
             if (gm == 0) batch_stage(d, G, tot, s);
         }
     };
-    batch_zero_stats(d, G, s);
-    batch_reduce(d, G, tot, 3, 1, s);
-    batch_finish(d, G, mm, 1, 3, s);
     for (int cyc = 0; cyc < max_cycles; ++cyc) {
         product(0);                              // V_0 = A x
-        batch_vec(d, G, tot, 3, 0, s);           // V_0 = b - V_0
-        batch_reduce(d, G, tot, 2, 1, s);
-        batch_finish(d, G, mm, 1, 4, s);         // ||r0||
-        batch_vec(d, G, tot, 4, mm, s);          // V_0 /= ||r0||
+        batch_start(d, G, tot, classes, mm, cyc == 0, s);
         for (int k = 0; k < mm; ++k) {
             product(k + 1);                      // w = A V_k
-            batch_cgs2_small(d, G, k, mm, s);
-            batch_reduce(d, G, tot, 0, k + 1, s);
-            batch_finish(d, G, k, k + 1, 0, s);
-            batch_vec(d, G, tot, 0, k, s);
-            batch_reduce(d, G, tot, 0, k + 1, s);
-            batch_finish(d, G, k, k + 1, 1, s);
-            batch_vec(d, G, tot, 1, k, s);
-            batch_reduce(d, G, tot, 1, 1, s);
-            batch_finish(d, G, k, 1, 2, s);
-            if (k + 1 < mm) batch_vec(d, G, tot, 2, k, s);
+            batch_gram_schmidt(d, G, tot, classes, k, mm, s);
         }
         // mixed precision: the budget is the number of corrections, not a
         // GMRES budget, so its end sets no flag
         batch_hess(d, G, mm, true, !l.lo && cyc + 1 == max_cycles, s);
-        batch_vec(d, G, tot, 5, mm, s);          // x += V y
+        batch_vec(d, G, tot, 0, mm, s);          // x += V y
     }
 }
 
@@ -153,6 +138,7 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
     std::vector<double*> X1(G), X3(G);
     std::vector<float*> Llo(G), Rlo(G), X1lo(G), X3lo(G);
     int red = 0, ew = 0, stg = 0;
+    unsigned classes = 0;
     for (int g = 0; g < G; ++g) {
         const LocalOp& op = items[g].op;
         const size_t n = op.n();
@@ -163,7 +149,7 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
         v = BatchVec{};   // the stage's default strides (the buffer itself is zeroed bytes)
         v.n = (long)n;
         v.nb = reduce_blocks(n);
-        v.small = n <= 8192;
+        classes |= 1u << krylov_class(n);
         v.V = q;
         q += al((size_t)(mm + 1) * n);
         v.w = q;
@@ -309,12 +295,12 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
             }
     }
     // upload (ordered before the solve on the context's stream), then run the
-    // sequence on the private stream, captured once per batch size, budget and
-    // precision
+    // sequence on the private stream, captured once per batch size, budget,
+    // precision and kinds of vectors
     HIP_CHECK(hipMemcpyAsync(dev, host.data(), lay.bytes, hipMemcpyHostToDevice, c->stream));
     c->batch_solves++;
     if (!c->use_graphs) {
-        issue(dev, lay, mm, max_cycles, c->stream);
+        issue(dev, lay, classes, mm, max_cycles, c->stream);
         return;
     }
     if (!c->side) {
@@ -322,7 +308,7 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
         HIP_CHECK(hipEventCreateWithFlags(&c->ev_in, hipEventDisableTiming));
         HIP_CHECK(hipEventCreateWithFlags(&c->ev_out, hipEventDisableTiming));
     }
-    const long long key[5] = {G, mm + (lo ? 1000 : 0), max_cycles, (long long)(uintptr_t)dev, (long long)lay.bytes};
+    const long long key[5] = {G, mm + (lo ? 1000 : 0) + 2000 * (int)classes, max_cycles, (long long)(uintptr_t)dev, (long long)lay.bytes};
     auto& cache = c->bgraphs;
     auto hit = std::find_if(cache.begin(), cache.end(),
                             [&](const ite_ctx::BatchGraph& e) { return std::memcmp(key, e.key, sizeof(key)) == 0; });
@@ -342,7 +328,7 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
         HIP_CHECK(hipStreamBeginCapture(c->side, hipStreamCaptureModeThreadLocal));
         bool ok = true;
         try {
-            issue(dev, lay, mm, max_cycles, c->side);
+            issue(dev, lay, classes, mm, max_cycles, c->side);
         } catch (const Error&) {
             ok = false;
         }
@@ -358,7 +344,7 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
             // issued directly (where a genuine launch error surfaces)
             (void)hipGetLastError();
             c->graph_fallbacks++;
-            issue(dev, lay, mm, max_cycles, c->stream);
+            issue(dev, lay, classes, mm, max_cycles, c->stream);
             return;
         }
         ite_ctx::BatchGraph ent;

@@ -555,41 +555,20 @@ static SolveStats gmres_budget(ite_ctx* c, const LocalOp& op, const double* b, d
     const int nb = reduce_blocks(n);
     double* part = slot_t<double>(c, SL_PART, (size_t)nb * 64 + 64);
     double* hd = slot_t<double>(c, SL_HESS, (size_t)mm * HC + 8 + 64 + 8);
-    double* bnorm_d = hd + (size_t)mm * HC;       // ||b||
-    double* beta_d = bnorm_d + 1;                 // ||r0||
+    double* norms = hd + (size_t)mm * HC;         // ||b||, ||r0||
     double* ydev = hd + (size_t)mm * HC + 8;      // combination coefficients (64)
     const bool own_stats = stats == nullptr;
     if (own_stats) stats = hd + (size_t)mm * HC + 8 + 64;
-    fill(stats, 0.0, 8, c->stream);
-    dot_partials(b, b, n, part, c->stream);
-    finish_partials(part, 1, nb, bnorm_d, 2, c->stream);
     for (int cyc = 0; cyc < max_cycles; ++cyc) {
         // r0 = b - A x
-        bool r_product = false;
-        if (x_is_zero && cyc == 0) {
-            d2d(c, V, b, n);
-        } else {
-            op_apply(c, op, x, V);
-            r_product = true;
-            axpby(n, 1.0, b, -1.0, V, V, c->stream);
-        }
-        dot_partials(V, V, n, part, c->stream);
-        finish_partials(part, 1, nb, beta_d, 2, c->stream);
-        scale_inv(V, beta_d, V, n, c->stream);
+        const bool r_product = !(x_is_zero && cyc == 0);
+        if (r_product) op_apply(c, op, x, V);
+        krylov_start(b, V, r_product, n, norms, part, cyc == 0 ? stats : nullptr, c->stream);
         for (int k = 0; k < mm; ++k) {
             double* col = hd + (size_t)k * HC;
             double* vnext = k + 1 < mm ? V + (size_t)(k + 1) * n : nullptr;
             op_apply(c, op, V + (size_t)k * n, w);
-            if (cgs2_small(V, (long)n, k + 1, w, n, col, vnext, c->stream)) continue;
-            mdot_partials(V, (long)n, k + 1, w, n, part, c->stream);
-            finish_partials(part, k + 1, nb, col, 0, c->stream);
-            gemv_sub(V, (long)n, k + 1, col, w, n, c->stream);
-            mdot_partials(V, (long)n, k + 1, w, n, part, c->stream);
-            finish_partials(part, k + 1, nb, col + 64, 0, c->stream);
-            gemv_sub(V, (long)n, k + 1, col + 64, w, n, c->stream);
-            dot_partials(w, w, n, part, c->stream);
-            finish_partials(part, 1, nb, col + 128, 2, c->stream);
-            if (vnext) scale_inv(w, col + 128, vnext, n, c->stream);
+            gram_schmidt(V, (long)n, k + 1, w, n, col, vnext, part, c->stream);
         }
         hess_solve(hd, mm, ydev, stats, r_product, cyc + 1 == max_cycles, c->stream);
         gemv_add(V, (long)n, mm, ydev, x, n, c->stream);
@@ -623,25 +602,20 @@ static SolveStats gmres(ite_ctx* c, const LocalOp& op, const double* b, double* 
     double* part = slot_t<double>(c, SL_PART, (size_t)nb * 64 + 64);
     double* sm = slot_t<double>(c, SL_SMALL, 512);   // [0,64) h1, [64,128) h2, 128 norm, [192,256) y
     double* host = pinned(c, 512);
-    const double bnorm = std::sqrt(std::max(0.0, dot(c, b, b, n)));
     std::vector<double> H((size_t)(mm + 1) * mm), cs(mm), sn(mm), g(mm + 1), y(mm);
     for (int cyc = 0; cyc < max_cycles; ++cyc) {
         // r0 = b - A x
-        if (x_is_zero && cyc == 0) {
-            d2d(c, V, b, n);
-        } else {
+        const bool ax = !(x_is_zero && cyc == 0);
+        if (ax) {
             op_apply(c, op, x, V);
             mv++;
-            axpby(n, 1.0, b, -1.0, V, V, c->stream);
         }
-        dot_partials(V, V, n, part, c->stream);
-        finish_partials(part, 1, nb, sm + 128, 2, c->stream);
-        d2h(c, host, sm + 128, 1);
+        krylov_start(b, V, ax, n, sm + 128, part, nullptr, c->stream);
+        d2h(c, host, sm + 128, 2);
         sync(c);
-        const double beta = host[0];
+        const double bnorm = host[0], beta = host[1];
         st.res_rel = bnorm > 0 ? beta / bnorm : 0.0;
         if (!(beta > 0.0) || (tol > 0 && beta <= tol * bnorm)) return st;
-        scale_inv(V, sm + 128, V, n, c->stream);
         std::fill(H.begin(), H.end(), 0.0);
         std::fill(g.begin(), g.end(), 0.0);
         g[0] = beta;
@@ -650,16 +624,7 @@ static SolveStats gmres(ite_ctx* c, const LocalOp& op, const double* b, double* 
         for (int k = 0; k < mm; ++k) {
             op_apply(c, op, V + (size_t)k * n, w);
             mv++;
-            if (!cgs2_small(V, (long)n, k + 1, w, n, sm, nullptr, c->stream)) {
-                mdot_partials(V, (long)n, k + 1, w, n, part, c->stream);
-                finish_partials(part, k + 1, nb, sm, 0, c->stream);
-                gemv_sub(V, (long)n, k + 1, sm, w, n, c->stream);
-                mdot_partials(V, (long)n, k + 1, w, n, part, c->stream);
-                finish_partials(part, k + 1, nb, sm + 64, 0, c->stream);
-                gemv_sub(V, (long)n, k + 1, sm + 64, w, n, c->stream);
-                dot_partials(w, w, n, part, c->stream);
-                finish_partials(part, 1, nb, sm + 128, 2, c->stream);
-            }
+            gram_schmidt(V, (long)n, k + 1, w, n, sm, nullptr, part, c->stream);
             d2h(c, host, sm, 129);
             sync(c);
             for (int i = 0; i <= k; ++i) H[(size_t)i * mm + k] = host[i] + host[64 + i];
@@ -1560,16 +1525,7 @@ static void lanczos_lowest(ite_ctx* c, const LocalOp& op, double* x, int m, int 
             double* col = hd + (size_t)k * HC;
             double* vnext = k + 1 < mm ? V + (size_t)(k + 1) * n : nullptr;
             op_apply(c, op, V + (size_t)k * n, w);
-            if (cgs2_small(V, (long)n, k + 1, w, n, col, vnext, c->stream)) continue;
-            mdot_partials(V, (long)n, k + 1, w, n, part, c->stream);
-            finish_partials(part, k + 1, nb, col, 0, c->stream);
-            gemv_sub(V, (long)n, k + 1, col, w, n, c->stream);
-            mdot_partials(V, (long)n, k + 1, w, n, part, c->stream);
-            finish_partials(part, k + 1, nb, col + 64, 0, c->stream);
-            gemv_sub(V, (long)n, k + 1, col + 64, w, n, c->stream);
-            dot_partials(w, w, n, part, c->stream);
-            finish_partials(part, 1, nb, col + 128, 2, c->stream);
-            if (vnext) scale_inv(w, col + 128, vnext, n, c->stream);
+            gram_schmidt(V, (long)n, k + 1, w, n, col, vnext, part, c->stream);
         }
         lanczos_eig(hd, mm, ydev, rec, c->stream);
         fill(x, 0.0, n, c->stream);

@@ -143,13 +143,22 @@ constexpr int SAMPLE_DMAX = 16;
 // is zero or not finite, flag[1] when its uniform is outside [0, 1).
 void sample_site(const double* T, int nsamples, int d, int Dr, const double* u, double* vnext, int* cfg, int L,
                  int site, double* flag, hipStream_t s);
-// Both classical Gram-Schmidt passes of one Arnoldi step in a single
-// workgroup for n <= 8192 (k1 <= 64 basis vectors): coefficients to
-// col[0..k1) and col[64..64+k1), ||w|| to col[128], vnext = w / ||w|| when
-// not null.  Returns false (and does nothing) for longer vectors.
-bool cgs2_small(const double* V, long ldv, int k1, double* w, size_t n, double* col, double* vnext, hipStream_t s);
+// Krylov vector operations (krylov.hip).  part: reduce_blocks(n) * 64 + 64
+// doubles of workspace.
+// Kernel class of vectors of n entries, 0..3: one workgroup of one of three
+// shapes, or many (3).
+int krylov_class(size_t n);
+// Start of a cycle: r = b - v0 (ax: v0 holds A x) or r = b, norms[0] = ||b||,
+// norms[1] = ||r||, v0 = r / ||r||; zeroes stats (8 doubles) unless null.
+void krylov_start(const double* b, double* v0, bool ax, size_t n, double* norms, double* part, double* stats,
+                  hipStream_t s);
+// Both classical Gram-Schmidt passes of one Arnoldi step (k1 <= 64 basis
+// vectors): coefficients to col[0..k1) and col[64..64+k1), ||w|| to col[128],
+// vnext = w / ||w|| when not null.
+void gram_schmidt(const double* V, long ldv, int k1, double* w, size_t n, double* col, double* vnext, double* part,
+                  hipStream_t s);
 // Device least-squares solve of one GMRES cycle (see hess_solve_one in
-// vec.hip): hd holds the cycle's Hessenberg columns, HESS_HC doubles each,
+// krylov.hip): hd holds the cycle's Hessenberg columns, HESS_HC doubles each,
 // then ||b|| and ||r0||; y gets the mm combination coefficients; stats (8
 // doubles per local solve, zeroed before the first cycle) accumulate the
 // residual estimate, the product count and the flags.
@@ -182,7 +191,6 @@ void transpose(const double* in, int rows, int cols, double* out, hipStream_t s)
 struct BatchVec {
     long n;                 // vector length
     int nb;                 // reduction blocks, reduce_blocks(n)
-    int small;              // Gram-Schmidt in one workgroup (cgs2_small applies)
     double* V;              // Krylov basis, (mm + 1) vectors of n
     double* w;              // work vector
     double* x;              // solution (in: initial guess)
@@ -202,25 +210,18 @@ struct BatchVec {
 // Unit totals of a batch (device ints): reductions, elementwise, stage.
 enum { BT_RED = 0, BT_EW = 1, BT_STAGE = 2, BT_N = 4 };
 constexpr int BATCH_GRID = 1024;      // workgroups of every batched vector launch
-constexpr int BGRAPH_CACHE = 4;       // captured batched solves kept per context
+constexpr int BGRAPH_CACHE = 12;      // captured batched solves kept per context
 constexpr long BATCH_EW = 4096;       // elements per elementwise unit
-// Reductions: mode 0 V_j . w (j < k1; large problems), 1 w . w (large),
-// 2 V_0 . V_0, 3 b . b (all problems).
-void batch_reduce(const BatchVec* d, int G, const int* tot, int mode, int k1, hipStream_t s);
-// Sum the partials: target 0 hd col k [j], 1 col k [64 + j], 2 col k [128]
-// (sqrt; large problems), 3 ||b|| (sqrt), 4 ||r0|| (sqrt) (all).
-void batch_finish(const BatchVec* d, int G, int k, int k1, int target, hipStream_t s);
-// Elementwise: 0 w -= sum_(j <= k) col_k[j] V_j, 1 the same with col_k[64 + j]
-// (large problems), 2 V_(k+1) = w / col_k[128] (large), 3 V_0 = b - V_0,
-// 4 V_0 /= ||r0||, 5 x += sum_(j < k) y_j V_j, 6 tlo = V_k rounded to FP32
-// (all).
+// Start of a cycle for every problem (V_0 holds A x; first: the solve records
+// are zeroed) and Gram-Schmidt of Arnoldi step k; classes: bit krylov_class(n)
+// of every problem.
+void batch_start(const BatchVec* d, int G, const int* tot, unsigned classes, int mm, bool first, hipStream_t s);
+void batch_gram_schmidt(const BatchVec* d, int G, const int* tot, unsigned classes, int k, int mm,
+                        hipStream_t s);
+// Elementwise: 0 x += sum_(j < k) y_j V_j, 1 tlo = V_k rounded to FP32.
 void batch_vec(const BatchVec* d, int G, const int* tot, int op, int k, hipStream_t s);
-// Both Gram-Schmidt passes of Arnoldi step k of the small problems.
-void batch_cgs2_small(const BatchVec* d, int G, int k, int mm, hipStream_t s);
 // The cycle's least-squares solve of every problem.
 void batch_hess(const BatchVec* d, int G, int mm, bool r_product, bool last_cycle, hipStream_t s);
-// Zero every problem's solve record (8 doubles).
-void batch_zero_stats(const BatchVec* d, int G, hipStream_t s);
 // The MPO stage of every problem (inputs per column at most 128).
 void batch_stage(const BatchVec* d, int G, const int* tot, hipStream_t s);
 // The FP32 stage st_lo of every problem (FP32 in, FP32 out).

@@ -1,11 +1,11 @@
-// Bandwidth-bound kernels of the local solver: the Krylov vector operations
-// of GMRES (dots, norms, classical Gram-Schmidt updates, combinations), the
-// sparse MPO contraction stage, precision conversions and small helpers.
+// Bandwidth-bound kernels of the local solver: dots, norms and combinations,
+// the sparse MPO contraction stage, precision conversions and small helpers.
 //
 // Reductions are deterministic: a fixed number of blocks (a function of n
 // only), a fixed per-block order (wavefront shuffles, then LDS), and a second
 // pass that sums the block partials in index order.
 #include "internal.h"
+#include "units.h"
 #include "wave.h"
 
 #include <cmath>
@@ -15,13 +15,7 @@ namespace ite {
 namespace {
 
 constexpr int RT = 256;           // threads per reduction block
-constexpr int MAX_RED_BLOCKS = 1024;
-
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
+constexpr int MAX_RED_BLOCKS = 512;   // two a compute unit; every block of the next launch sums them
 
 // Block sum of v (every thread of the block gets the result).
 __device__ inline double block_sum(double v, double* sh) {
@@ -54,33 +48,27 @@ __global__ __launch_bounds__(RT) void dot_partials_kernel(const double* __restri
     dot_block(x, y, n, blockIdx.x, gridDim.x, partial + blockIdx.x, sh);
 }
 
-// Block vb of vg: partial[j * vg + vb] = its share of V_j . w for j < k.
-template <int KMAX>
-__device__ inline void mdot_block(const double* __restrict__ V, long ldv, int k, const double* __restrict__ w, size_t n,
-                                  int vb, int vg, double* __restrict__ partial, double* sh) {
-    double acc[KMAX];
+// partial[j*nb + b]: block b's share of V_j . w for j < k (k <= 16).
+__global__ __launch_bounds__(RT) void mdot_partials_kernel(const double* __restrict__ V, long ldv, int k,
+                                                           const double* __restrict__ w, size_t n,
+                                                           double* __restrict__ partial) {
+    __shared__ double sh[RT / 64];
+    double acc[16];
 #pragma unroll
-    for (int j = 0; j < KMAX; ++j) acc[j] = 0.0;
-    const size_t stride = (size_t)vg * RT;
-    for (size_t i = (size_t)vb * RT + threadIdx.x; i < n; i += stride) {
+    for (int j = 0; j < 16; ++j) acc[j] = 0.0;
+    const size_t stride = (size_t)gridDim.x * RT;
+    for (size_t i = (size_t)blockIdx.x * RT + threadIdx.x; i < n; i += stride) {
         const double wi = w[i];
 #pragma unroll
-        for (int j = 0; j < KMAX; ++j)
+        for (int j = 0; j < 16; ++j)
             if (j < k) acc[j] += V[(size_t)j * ldv + i] * wi;
     }
-    for (int j = 0; j < k; ++j) {
-        const double s = block_sum(acc[j], sh);
-        if (threadIdx.x == 0) partial[(size_t)j * vg + vb] = s;
-    }
-}
-
-// partial[j*nb + b]: block b's share of V_j . w for j < k (k <= 64).
-template <int KMAX>
-__global__ __launch_bounds__(RT) void mdot_partials_kernel(const double* __restrict__ V, long ldv,
-                                                           int k, const double* __restrict__ w,
-                                                           size_t n, double* __restrict__ partial) {
-    __shared__ double sh[RT / 64];
-    mdot_block<KMAX>(V, ldv, k, w, n, blockIdx.x, gridDim.x, partial, sh);
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+        if (j < k) {
+            const double s = block_sum(acc[j], sh);
+            if (threadIdx.x == 0) partial[(size_t)j * gridDim.x + blockIdx.x] = s;
+        }
 }
 
 // *out (mode 0: =, 1: +=, 2: = sqrt) of the sum of nb partials.
@@ -127,173 +115,6 @@ __global__ void axpby_kernel(size_t n, double a, const double* __restrict__ x, d
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
         out[i] = y ? a * x[i] + b * y[i] : a * x[i];
-}
-
-// Both Gram-Schmidt passes of one Arnoldi step for short vectors, in one
-// workgroup: w <- w - V (V^T w) twice (V: k1 vectors of length n, leading
-// dimension ldv), the coefficients of the passes to col[0..k1) and
-// col[64..64+k1), ||w|| to col[128] and, when vnext is given,
-// vnext = w / ||w|| (0 for a zero norm, as scale_inv).  Thread t owns the
-// entries t, t + CGS_T, ... of w, kept in LDS between the passes; fixed
-// reduction order.
-constexpr int CGS_T = 256, CGS_E = 32;
-template <int KMAX>
-struct CgsLDS {
-    double xs[CGS_T * CGS_E];
-    double part[CGS_T / 64][KMAX];
-    double coef[KMAX];
-};
-template <int KMAX>
-__device__ inline void cgs2_small_body(const double* __restrict__ V, long ldv, int k1, double* __restrict__ w, int n,
-                                       double* __restrict__ col, double* __restrict__ vnext, CgsLDS<KMAX>& L) {
-    auto& xs = L.xs;
-    auto& part = L.part;
-    auto& coef = L.coef;
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    for (int i = t; i < n; i += CGS_T) xs[i] = w[i];
-    for (int pass = 0; pass < 2; ++pass) {
-        double acc[KMAX];
-#pragma unroll
-        for (int j = 0; j < KMAX; ++j) acc[j] = 0.0;
-        for (int i = t; i < n; i += CGS_T) {
-            const double xi = xs[i];
-#pragma unroll
-            for (int j = 0; j < KMAX; ++j)
-                if (j < k1) acc[j] += V[j * ldv + i] * xi;
-        }
-#pragma unroll
-        for (int j = 0; j < KMAX; ++j) {
-            if (j < k1) {
-                const double sj = wave_sum(acc[j]);
-                if (lane == 0) part[wv][j] = sj;
-            }
-        }
-        __syncthreads();
-        if (t < k1) {
-            double sj = 0.0;
-#pragma unroll
-            for (int ww = 0; ww < CGS_T / 64; ++ww) sj += part[ww][t];
-            coef[t] = sj;
-            col[64 * pass + t] = sj;
-        }
-        __syncthreads();
-        for (int i = t; i < n; i += CGS_T) {
-            double xi = xs[i];
-#pragma unroll
-            for (int j = 0; j < KMAX; ++j)
-                if (j < k1) xi -= coef[j] * V[j * ldv + i];
-            xs[i] = xi;
-        }
-        __syncthreads();
-    }
-    double ss = 0.0;
-    for (int i = t; i < n; i += CGS_T) ss += xs[i] * xs[i];
-    ss = wave_sum(ss);
-    if (lane == 0) part[wv][0] = ss;
-    __syncthreads();
-    double tot = 0.0;
-#pragma unroll
-    for (int ww = 0; ww < CGS_T / 64; ++ww) tot += part[ww][0];
-    const double nrm = sqrt(fmax(tot, 0.0));
-    if (t == 0) col[128] = nrm;
-    const double inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
-    for (int i = t; i < n; i += CGS_T) {
-        w[i] = xs[i];
-        if (vnext) vnext[i] = xs[i] * inv;
-    }
-}
-
-template <int KMAX>
-__global__ __launch_bounds__(CGS_T) void cgs2_small_kernel(const double* __restrict__ V, long ldv, int k1,
-                                                           double* __restrict__ w, int n, double* __restrict__ col,
-                                                           double* __restrict__ vnext) {
-    __shared__ CgsLDS<KMAX> sh;
-    cgs2_small_body<KMAX>(V, ldv, k1, w, n, col, vnext, sh);
-}
-
-// The small least-squares problem of one GMRES cycle, on the device (one
-// thread; the Hessenberg matrix in LDS): the columns of the cycle's Arnoldi
-// steps are hd[k * HESS_HC + i] (first Gram-Schmidt pass), + 64 (second
-// pass), + 128 (the norm of the next vector); hd[mm * HESS_HC] = ||b||,
-// hd[mm * HESS_HC + 1] = beta = ||r0||.  Givens rotations reduce H to upper
-// triangular form while the residual estimate |g_(k+1)| is tracked; an
-// Arnoldi step whose next norm is <= 1e-14 beta ends the cycle (invariant
-// subspace); y solves R y = g by back substitution (zero beyond the steps
-// used).  stats (per local solve, zeroed by the caller before the first
-// cycle): [0] relative residual estimate, [1] products whose results enter
-// the solution, [2] ITE_FLAG_* bits, [3] 1 once a cycle found an invariant
-// subspace or a zero residual (later cycles then change nothing).
-// LDS of one solve: H ((KMAX + 1) x KMAX), then cos, sin and g.
-constexpr int HESS_LDS = (HESS_KMAX + 1) * HESS_KMAX + 3 * HESS_KMAX + 1;
-__device__ void hess_solve_one(const double* __restrict__ hd, int mm, double* __restrict__ y,
-                               double* __restrict__ stats, int r_product, int last_cycle, double* Hs) {
-    if (stats[3] != 0.0) {
-        for (int i = 0; i < mm; ++i) y[i] = 0.0;
-        return;
-    }
-    if (r_product) {
-        stats[1] += 1.0;
-        stats[4] += 1.0;   // the residual products alone (FP64 even when the others are not)
-    }
-    const double bnorm = hd[(size_t)mm * HESS_HC], beta = hd[(size_t)mm * HESS_HC + 1];
-    stats[0] = bnorm > 0.0 ? beta / bnorm : 0.0;
-    if (!(beta > 0.0)) {
-        for (int i = 0; i < mm; ++i) y[i] = 0.0;
-        stats[3] = 1.0;
-        return;
-    }
-    double* cs = Hs + (HESS_KMAX + 1) * HESS_KMAX;
-    double* sn = cs + HESS_KMAX;
-    double* g = sn + HESS_KMAX;
-    for (int i = 0; i <= mm; ++i) g[i] = 0.0;
-    g[0] = beta;
-    int kused = 0;
-    bool breakdown = false;
-    for (int k = 0; k < mm; ++k) {
-        const double* col = hd + (size_t)k * HESS_HC;
-        for (int i = 0; i <= k; ++i) Hs[i * HESS_KMAX + k] = col[i] + col[64 + i];
-        const double hnext = col[128];
-        for (int i = 0; i < k; ++i) {
-            const double a = Hs[i * HESS_KMAX + k], bb = Hs[(i + 1) * HESS_KMAX + k];
-            Hs[i * HESS_KMAX + k] = cs[i] * a + sn[i] * bb;
-            Hs[(i + 1) * HESS_KMAX + k] = -sn[i] * a + cs[i] * bb;
-        }
-        const double a = Hs[k * HESS_KMAX + k];
-        const double rr = hypot(a, hnext);
-        cs[k] = rr > 0.0 ? a / rr : 1.0;
-        sn[k] = rr > 0.0 ? hnext / rr : 0.0;
-        Hs[k * HESS_KMAX + k] = rr;
-        g[k + 1] = -sn[k] * g[k];
-        g[k] = cs[k] * g[k];
-        kused = k + 1;
-        stats[0] = bnorm > 0.0 ? fabs(g[k + 1]) / bnorm : 0.0;
-        if (hnext <= 1e-14 * beta) {
-            breakdown = true;
-            break;
-        }
-    }
-    stats[1] += kused;
-    for (int i = kused - 1; i >= 0; --i) {
-        double sum = g[i];
-        for (int j = i + 1; j < kused; ++j) sum -= Hs[i * HESS_KMAX + j] * y[j];
-        const double dgn = Hs[i * HESS_KMAX + i];
-        y[i] = dgn != 0.0 ? sum / dgn : 0.0;
-    }
-    for (int i = kused; i < mm; ++i) y[i] = 0.0;
-    int flags = (int)stats[2];
-    if (breakdown) {
-        flags |= ITE_FLAG_BREAKDOWN;
-        stats[3] = 1.0;
-    } else if (last_cycle) {
-        flags |= ITE_FLAG_BUDGET_EXHAUSTED;
-    }
-    stats[2] = (double)flags;
-}
-
-__global__ __launch_bounds__(64) void hess_solve_kernel(const double* __restrict__ hd, int mm, double* __restrict__ y,
-                                                        double* __restrict__ stats, int r_product, int last_cycle) {
-    __shared__ double Hs[HESS_LDS];
-    if (threadIdx.x == 0) hess_solve_one(hd, mm, y, stats, r_product, last_cycle, Hs);
 }
 
 __global__ void scale_inv_kernel(const double* __restrict__ x, const double* __restrict__ den,
@@ -528,19 +349,10 @@ void dot_partials(const double* x, const double* y, size_t n, double* partial, h
 void mdot_partials(const double* V, long ldv, int k, const double* w, size_t n, double* partial,
                    hipStream_t s) {
     const int nb = reduce_blocks(n);
-    if (k <= 4)
-        hipLaunchKernelGGL((mdot_partials_kernel<4>), dim3(nb), dim3(RT), 0, s, V, ldv, k, w, n, partial);
-    else if (k <= 8)
-        hipLaunchKernelGGL((mdot_partials_kernel<8>), dim3(nb), dim3(RT), 0, s, V, ldv, k, w, n, partial);
-    else if (k <= 16)
-        hipLaunchKernelGGL((mdot_partials_kernel<16>), dim3(nb), dim3(RT), 0, s, V, ldv, k, w, n, partial);
-    else {
-        // wider bases: 16 at a time
-        for (int j0 = 0; j0 < k; j0 += 16) {
-            const int kk = k - j0 < 16 ? k - j0 : 16;
-            hipLaunchKernelGGL((mdot_partials_kernel<16>), dim3(nb), dim3(RT), 0, s, V + (size_t)j0 * ldv,
-                               ldv, kk, w, n, partial + (size_t)j0 * nb);
-        }
+    for (int j0 = 0; j0 < k; j0 += 16) {
+        const int kk = k - j0 < 16 ? k - j0 : 16;
+        hipLaunchKernelGGL(mdot_partials_kernel, dim3(nb), dim3(RT), 0, s, V + (size_t)j0 * ldv, ldv, kk, w, n,
+                           partial + (size_t)j0 * nb);
     }
     HIP_CHECK(hipGetLastError());
 }
@@ -580,21 +392,6 @@ void axpby(size_t n, double a, const double* x, double b, const double* y, doubl
     if (n == 0) return;
     hipLaunchKernelGGL(axpby_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, n, a, x, b, y, out);
     HIP_CHECK(hipGetLastError());
-}
-
-bool cgs2_small(const double* V, long ldv, int k1, double* w, size_t n, double* col, double* vnext, hipStream_t s) {
-    if (n == 0 || n > (size_t)CGS_T * CGS_E || k1 < 1 || k1 > 64) return false;
-    const int nn = (int)n;
-    if (k1 <= 8)
-        hipLaunchKernelGGL((cgs2_small_kernel<8>), dim3(1), dim3(CGS_T), 0, s, V, ldv, k1, w, nn, col, vnext);
-    else if (k1 <= 16)
-        hipLaunchKernelGGL((cgs2_small_kernel<16>), dim3(1), dim3(CGS_T), 0, s, V, ldv, k1, w, nn, col, vnext);
-    else if (k1 <= 32)
-        hipLaunchKernelGGL((cgs2_small_kernel<32>), dim3(1), dim3(CGS_T), 0, s, V, ldv, k1, w, nn, col, vnext);
-    else
-        hipLaunchKernelGGL((cgs2_small_kernel<64>), dim3(1), dim3(CGS_T), 0, s, V, ldv, k1, w, nn, col, vnext);
-    HIP_CHECK(hipGetLastError());
-    return true;
 }
 
 // One site of the conditional sampling of an MPS in the product basis, one
@@ -787,12 +584,6 @@ void lanczos_eig(const double* hd, int mm, double* y, double* rec, hipStream_t s
     HIP_CHECK(hipGetLastError());
 }
 
-void hess_solve(const double* hd, int mm, double* y, double* stats, bool r_product, bool last_cycle, hipStream_t s) {
-    if (mm < 1 || mm > HESS_KMAX) ITE_FAIL(ITE_EINVAL, "hess_solve: Krylov dimension outside 1..64");
-    hipLaunchKernelGGL(hess_solve_kernel, dim3(1), dim3(64), 0, s, hd, mm, y, stats, (int)r_product, (int)last_cycle);
-    HIP_CHECK(hipGetLastError());
-}
-
 void scale(double* x, double a, size_t n, hipStream_t s) {
     if (n == 0) return;
     hipLaunchKernelGGL(scale_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, x, a, n);
@@ -888,64 +679,16 @@ void stage_f64(const Stage& st, hipStream_t s) {
 // ---------------------------------------------------------------------------
 namespace {
 
-// Problem of unit u in a range split by the per-problem first units
-// (start(g) increasing; G small): the last g with start(g) <= u.
-template <typename F>
-__device__ inline int unit_problem(int u, int G, F start) {
-    int g = 0;
-    while (g + 1 < G && start(g + 1) <= u) ++g;
-    return g;
-}
-
-template <int KMAX>
-__global__ __launch_bounds__(RT) void batch_reduce_kernel(const BatchVec* __restrict__ d, int G,
-                                                          const int* __restrict__ tot, int mode, int k1) {
-    __shared__ double sh[RT / 64];
-    const int total = tot[BT_RED];
-    for (int u = blockIdx.x; u < total; u += gridDim.x) {
-        const int g = unit_problem(u, G, [&](int q) { return d[q].red_start; });
-        const BatchVec& p = d[g];
-        const int vb = u - p.red_start;
-        if (vb >= p.nb) continue;
-        if (mode <= 1 && p.small) continue;
-        if (mode == 0) {
-            mdot_block<KMAX>(p.V, p.n, k1, p.w, p.n, vb, p.nb, p.part, sh);
-        } else {
-            const double* x = mode == 1 ? p.w : (mode == 2 ? p.V : p.b);
-            dot_block(x, x, p.n, vb, p.nb, p.part + vb, sh);
-        }
-    }
-}
-
-__global__ __launch_bounds__(RT) void batch_finish_kernel(const BatchVec* __restrict__ d, int G, int k, int k1,
-                                                          int target) {
-    __shared__ double sh[RT / 64];
-    const int total = G * k1;
-    for (int u = blockIdx.x; u < total; u += gridDim.x) {
-        const int g = u / k1, j = u % k1;
-        const BatchVec& p = d[g];
-        if (target <= 2 && p.small) continue;
-        double* col = p.hd + (size_t)k * HESS_HC;
-        double* out;
-        int mode = 2;
-        if (target == 0) { out = col + j; mode = 0; }
-        else if (target == 1) { out = col + 64 + j; mode = 0; }
-        else if (target == 2) out = col + 128;
-        else out = p.hd + (size_t)k * HESS_HC + (target == 3 ? 0 : 1);   // k = mm here: ||b||, ||r0||
-        finish_one(p.part + (size_t)j * p.nb, p.nb, out, mode, sh);
-    }
-}
-
-// w -= sum_(j < k1) c_j V_j, in chunks of 16 basis vectors as gemv_launch does.
-__device__ inline double gemv_elem(const double* __restrict__ V, long ldv, int k1, const double* __restrict__ c,
-                                   double wi, size_t i, bool sub) {
-    for (int j0 = 0; j0 < k1; j0 += 16) {
-        const int kk = k1 - j0 < 16 ? k1 - j0 : 16;
+// x += sum_j c_j V_j at entry i, in chunks of 16 basis vectors as gemv_launch does.
+__device__ inline double gemv_elem(const double* __restrict__ V, long ldv, int k, const double* __restrict__ c,
+                                   double x, size_t i) {
+    for (int j0 = 0; j0 < k; j0 += 16) {
+        const int kk = k - j0 < 16 ? k - j0 : 16;
         double s = 0.0;
         for (int j = 0; j < kk; ++j) s += c[j0 + j] * V[(size_t)(j0 + j) * ldv + i];
-        wi = sub ? wi - s : wi + s;
+        x += s;
     }
-    return wi;
+    return x;
 }
 
 __global__ __launch_bounds__(RT) void batch_vec_kernel(const BatchVec* __restrict__ d, int G,
@@ -954,53 +697,14 @@ __global__ __launch_bounds__(RT) void batch_vec_kernel(const BatchVec* __restric
     for (int u = blockIdx.x; u < total; u += gridDim.x) {
         const int g = unit_problem(u, G, [&](int q) { return d[q].ew_start; });
         const BatchVec& p = d[g];
-        if (op <= 2 && p.small) continue;
         const size_t i0 = (size_t)(u - p.ew_start) * BATCH_EW;
         const size_t i1 = min((size_t)p.n, i0 + BATCH_EW);
-        const double* col = p.hd + (size_t)k * HESS_HC;
-        if (op == 0 || op == 1) {
-            const double* cf = op == 0 ? col : col + 64;
-            for (size_t i = i0 + threadIdx.x; i < i1; i += RT) p.w[i] = gemv_elem(p.V, p.n, k + 1, cf, p.w[i], i, true);
-        } else if (op == 2) {
-            const double dd = col[128];
-            const double inv = dd > 0.0 ? 1.0 / dd : 0.0;
-            double* vn = p.V + (size_t)(k + 1) * p.n;
-            for (size_t i = i0 + threadIdx.x; i < i1; i += RT) vn[i] = p.w[i] * inv;
-        } else if (op == 3) {
-            for (size_t i = i0 + threadIdx.x; i < i1; i += RT) p.V[i] = 1.0 * p.b[i] + -1.0 * p.V[i];
-        } else if (op == 4) {
-            const double dd = p.hd[(size_t)k * HESS_HC + 1];
-            const double inv = dd > 0.0 ? 1.0 / dd : 0.0;
-            for (size_t i = i0 + threadIdx.x; i < i1; i += RT) p.V[i] = p.V[i] * inv;
-        } else if (op == 6) {
+        if (op == 0) {
+            for (size_t i = i0 + threadIdx.x; i < i1; i += RT) p.x[i] = gemv_elem(p.V, p.n, k, p.y, p.x[i], i);
+        } else {
             const double* vk = p.V + (size_t)k * p.n;
             for (size_t i = i0 + threadIdx.x; i < i1; i += RT) p.tlo[i] = (float)vk[i];
-        } else {
-            for (size_t i = i0 + threadIdx.x; i < i1; i += RT) p.x[i] = gemv_elem(p.V, p.n, k, p.y, p.x[i], i, false);
         }
-    }
-}
-
-template <int KMAX>
-__global__ __launch_bounds__(CGS_T) void batch_cgs2_small_kernel(const BatchVec* __restrict__ d, int G, int k,
-                                                                 int mm) {
-    __shared__ CgsLDS<KMAX> sh;
-    for (int g = blockIdx.x; g < G; g += gridDim.x) {
-        const BatchVec& p = d[g];
-        if (!p.small) continue;
-        double* vnext = k + 1 < mm ? p.V + (size_t)(k + 1) * p.n : nullptr;
-        cgs2_small_body<KMAX>(p.V, p.n, k + 1, p.w, (int)p.n, p.hd + (size_t)k * HESS_HC, vnext, sh);
-        __syncthreads();
-    }
-}
-
-__global__ __launch_bounds__(64) void batch_hess_kernel(const BatchVec* __restrict__ d, int G, int mm, int r_product,
-                                                        int last_cycle) {
-    __shared__ double Hs[HESS_LDS];
-    for (int g = blockIdx.x; g < G; g += gridDim.x) {
-        const BatchVec& p = d[g];
-        if (threadIdx.x == 0) hess_solve_one(p.hd, mm, p.y, p.stats, r_product, last_cycle, Hs);
-        __syncthreads();
     }
 }
 
@@ -1022,59 +726,11 @@ __global__ __launch_bounds__(STAGE_NT) void batch_stage_kernel(const BatchVec* _
     }
 }
 
-__global__ __launch_bounds__(64) void batch_zero_stats_kernel(const BatchVec* __restrict__ d, int G) {
-    for (int g = blockIdx.x; g < G; g += gridDim.x)
-        if (threadIdx.x < 8) d[g].stats[threadIdx.x] = 0.0;
-}
-
 }  // namespace
-
-void batch_zero_stats(const BatchVec* d, int G, hipStream_t s) {
-    if (G <= 0) return;
-    hipLaunchKernelGGL(batch_zero_stats_kernel, dim3(std::min(G, BATCH_GRID)), dim3(64), 0, s, d, G);
-    HIP_CHECK(hipGetLastError());
-}
-
-void batch_reduce(const BatchVec* d, int G, const int* tot, int mode, int k1, hipStream_t s) {
-    if (G <= 0) return;
-    if (mode == 0 && k1 > 16) ITE_FAIL(ITE_EINVAL, "batch_reduce: at most 16 basis vectors per launch");
-    if (mode != 0 || k1 <= 4)
-        hipLaunchKernelGGL((batch_reduce_kernel<4>), dim3(BATCH_GRID), dim3(RT), 0, s, d, G, tot, mode, k1);
-    else if (k1 <= 8)
-        hipLaunchKernelGGL((batch_reduce_kernel<8>), dim3(BATCH_GRID), dim3(RT), 0, s, d, G, tot, mode, k1);
-    else
-        hipLaunchKernelGGL((batch_reduce_kernel<16>), dim3(BATCH_GRID), dim3(RT), 0, s, d, G, tot, mode, k1);
-    HIP_CHECK(hipGetLastError());
-}
-
-void batch_finish(const BatchVec* d, int G, int k, int k1, int target, hipStream_t s) {
-    if (G <= 0) return;
-    hipLaunchKernelGGL(batch_finish_kernel, dim3(std::min(BATCH_GRID, G * k1)), dim3(RT), 0, s, d, G, k, k1, target);
-    HIP_CHECK(hipGetLastError());
-}
 
 void batch_vec(const BatchVec* d, int G, const int* tot, int op, int k, hipStream_t s) {
     if (G <= 0) return;
     hipLaunchKernelGGL(batch_vec_kernel, dim3(BATCH_GRID), dim3(RT), 0, s, d, G, tot, op, k);
-    HIP_CHECK(hipGetLastError());
-}
-
-void batch_cgs2_small(const BatchVec* d, int G, int k, int mm, hipStream_t s) {
-    if (G <= 0) return;
-    const int k1 = k + 1;
-    const dim3 grid(std::min(G, BATCH_GRID));
-    if (k1 <= 8) hipLaunchKernelGGL((batch_cgs2_small_kernel<8>), grid, dim3(CGS_T), 0, s, d, G, k, mm);
-    else if (k1 <= 16) hipLaunchKernelGGL((batch_cgs2_small_kernel<16>), grid, dim3(CGS_T), 0, s, d, G, k, mm);
-    else if (k1 <= 32) hipLaunchKernelGGL((batch_cgs2_small_kernel<32>), grid, dim3(CGS_T), 0, s, d, G, k, mm);
-    else hipLaunchKernelGGL((batch_cgs2_small_kernel<64>), grid, dim3(CGS_T), 0, s, d, G, k, mm);
-    HIP_CHECK(hipGetLastError());
-}
-
-void batch_hess(const BatchVec* d, int G, int mm, bool r_product, bool last_cycle, hipStream_t s) {
-    if (G <= 0) return;
-    if (mm < 1 || mm > HESS_KMAX) ITE_FAIL(ITE_EINVAL, "batch_hess: Krylov dimension outside 1..64");
-    hipLaunchKernelGGL(batch_hess_kernel, dim3(std::min(G, BATCH_GRID)), dim3(64), 0, s, d, G, mm, (int)r_product,
-                       (int)last_cycle);
     HIP_CHECK(hipGetLastError());
 }
 
