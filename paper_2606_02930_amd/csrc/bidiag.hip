@@ -7,9 +7,10 @@
 // the superdiagonal.  While more than 192 rows are left a step is one pass over
 // the trailing block (bd_step_kernel: both reflectors applied to a row while it
 // is in a wavefront's registers, and its share of the next step's column
-// products taken) and one sum over the workgroups (bd_sum_kernel); the rest is
+// products taken) and one sum over the workgroups (bd_sum_kernel), or both in
+// one launch from 512 rows and columns on (bd_step1_kernel); the rest is
 // done by one workgroup in its registers (bd_tail_kernel).  Bound by the
-// latency of a step: about 7 us with two launches at 200 to 512 columns,
+// latency of a step: 5 to 7 us at 200 to 512 columns,
 // 18 us at 2048 (38 MB read and written by it on average there), 1.3 to 1.9 us
 // inside one workgroup.  Two launches a step that each read and wrote the
 // block (columns, then rows) took 9 us and 31 us.
@@ -242,6 +243,134 @@ __global__ __launch_bounds__(1024) void bd_sum_kernel(BdWork b, int c, int q0, i
 #pragma unroll
         for (int q = 1; q < 16; ++q) s += sh[q][tx];
         b.p[j] = s;
+    }
+}
+
+// The same step in one launch, for up to 64 CPL columns from c on and few
+// workgroups: NW wavefronts of R rows each, so that every workgroup can sum
+// the products of all (src, workgroups q0 .. ns - 1) by itself.  That sum is
+// all loads in flight at once; it and the redundant reflectors grow with the
+// rows a workgroup has less, the row work with those it has more: 8
+// wavefronts of 2 rows take 5.3 us at 256 rows and columns and 7.2 at 512
+// (8 x 1: 5.1 and 8.0, 8 x 4: 6.2 and 8.1, 16 x 2: 6.3 and 8.4; step and sum as
+// two launches 7.1 and 8.0).
+template <int CPL, int R, int NW>
+__global__ __launch_bounds__(64 * NW) void bd_step1_kernel(BdWork b, int c, const double* __restrict__ src, int q0, int ns,
+                                                        double* __restrict__ part) {
+    constexpr int NT = 64 * NW, W = 64 * CPL, PARTS = NT / W;
+    static_assert(NT % W == 0, "a thread a column");
+    __shared__ double buf[NW][W];
+    __shared__ double z[W + 1], u[W + 1], sh[CPL];
+    const int P = b.P, N = b.N, c1 = c + 1, len = N - c1;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int blk0 = c1 / (NW * R);
+    if ((int)blockIdx.x < blk0) return;
+    const double* rowc = b.A + (long)c * N;
+    double* Ai[R];
+    bool in[R];
+    double a[R][CPL], x[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = (blockIdx.x * R + r) * NW + w;
+        in[r] = i >= c1 && i < P;
+        Ai[r] = b.A + (long)i * N + c1;
+        x[r] = in[r] ? Ai[r][-1] : 0.0;
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) a[r][q] = in[r] && lane + 64 * q < len ? Ai[r][lane + 64 * q] : 0.0;
+    }
+    // column c + tj of the products and of row c
+    const int tj = t % W;
+    const double alpha = rowc[c], rj = tj <= len ? rowc[c + tj] : 0.0;
+    double s = 0.0;
+    if (tj <= len)
+        for (int q = q0 + t / W; q < ns; q += 16 * PARTS) {
+            double v[16];       // in flight together
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = q + e * PARTS < ns ? src[(long)(q + e * PARTS) * N + c + tj] : 0.0;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s += v[e];
+        }
+    buf[t / W][tj] = s;
+    __syncthreads();
+    double pc = buf[0][0], pj = buf[0][tj];
+#pragma unroll
+    for (int q = 1; q < PARTS; ++q) {
+        pc += buf[q][0];
+        pj += buf[q][tj];
+    }
+    const Refl h = reflector(alpha, pc);
+    const double zj = h.tau * (rj + h.scale * pj), uj = rj - zj;
+    if (t < W) {
+        if (t > 0) {
+            z[t - 1] = zj;
+            u[t - 1] = uj;
+        }
+        const double n2 = wave_sum(t > 1 && t <= len ? uj * uj : 0.0);
+        if (lane == 0) sh[w] = n2;
+    }
+    __syncthreads();
+    double n2 = sh[0];
+#pragma unroll
+    for (int q = 1; q < CPL; ++q) n2 += sh[q];
+    const Refl k = reflector(len > 0 ? u[0] : 0.0, n2);
+    const int ldq = pad16(P), ldp = pad16(N);
+    if ((int)blockIdx.x == blk0) {
+        double* vq = b.VQ + (long)c * ldq;
+        for (int q = t; q <= c; q += NT) vq[q] = q == c ? 1.0 : 0.0;
+        for (int q = P + t; q < ldq; q += NT) vq[q] = 0.0;
+        if (len > 0) {
+            double* vp = b.VP + (long)c * ldp;
+            for (int q = t; q < ldp; q += NT)
+                vp[q] = q < c1 || q >= N ? 0.0 : q == c1 ? 1.0 : u[q - c1] * k.scale;
+        }
+        if (t == 0) {
+            b.tauq[c] = h.tau;
+            b.d[c] = h.beta;
+            b.taup[c] = k.tau;
+            b.e[c] = k.beta;
+        }
+    }
+    double acc[CPL];
+    {
+        double zl[CPL], ul[CPL];
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) {
+            const int j = lane + 64 * q;
+            acc[q] = 0.0;
+            zl[q] = j < len ? z[j] : 0.0;
+            ul[q] = j == 0 ? 1.0 : j < len ? u[j] * k.scale : 0.0;
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const double v = x[r] * h.scale;
+            const int i = (blockIdx.x * R + r) * NW + w;
+            if (in[r] && lane == 0) b.VQ[(long)c * ldq + i] = v;
+            double d = 0.0;
+#pragma unroll
+            for (int q = 0; q < CPL; ++q) {
+                a[r][q] -= v * zl[q];
+                d += a[r][q] * ul[q];
+            }
+            d = k.tau * wave_sum(d);
+#pragma unroll
+            for (int q = 0; q < CPL; ++q) {
+                a[r][q] -= d * ul[q];
+                if (in[r] && lane + 64 * q < len) Ai[r][lane + 64 * q] = a[r][q];
+            }
+            // the next step's column products: rows below its own row
+            const double xn = i == c1 || !in[r] ? 0.0 : lane_value(a[r][0], 0);
+#pragma unroll
+            for (int q = 0; q < CPL; ++q) acc[q] += xn * a[r][q];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) buf[w][lane + 64 * q] = acc[q];
+    __syncthreads();
+    if (t < len) {
+        double v = buf[0][t];
+#pragma unroll
+        for (int q = 1; q < NW; ++q) v += buf[q][t];
+        part[(long)blockIdx.x * N + c1 + t] = v;
     }
 }
 
@@ -675,6 +804,7 @@ __global__ __launch_bounds__(64 * NW) void wy_apply_kernel(WySide s0, WySide s1,
 }
 
 constexpr int BD_TAIL = 192;                // rows of the block that one workgroup finishes
+constexpr int BD_ONE = 512;                 // rows and columns from which on a step is one launch
 constexpr int WY_MAX = 8 * WYB * 16;     // longest vector held in registers
 
 }  // namespace
@@ -682,7 +812,7 @@ constexpr int WY_MAX = 8 * WYB * 16;     // longest vector held in registers
 size_t bd_workspace(int P, int N) {
     const size_t nb = (size_t)(N + WYB - 1) / WYB, np = pad16(N);
     return (size_t)P * N + np * pad16(P) + np * np + 2 * nb * WYB * WYB +
-           (size_t)((P + BS_NW - 1) / BS_NW) * N + 5 * (size_t)N + 64;
+           2 * (size_t)((P + 15) / 16) * N + 5 * (size_t)N + 64;
 }
 
 BdWork bd_carve(double* ws, int P, int N) {
@@ -696,7 +826,7 @@ BdWork bd_carve(double* ws, int P, int N) {
     w.TQ = w.VP + (size_t)pad16(N) * pad16(N);
     w.TP = w.TQ + nb * WYB * WYB;
     w.part = w.TP + nb * WYB * WYB;
-    w.p = w.part + (size_t)((P + BS_NW - 1) / BS_NW) * N;
+    w.p = w.part + 2 * (size_t)((P + 15) / 16) * N;
     w.tauq = w.p + N;
     w.taup = w.tauq + N;
     w.d = w.taup + N;
@@ -719,6 +849,26 @@ void bidiagonalise(const BdWork& w, const double* theta, bool tr, hipStream_t s,
                                         (c + 1) / BS_NW, g);
         if (timed) probe->end(PK_BIDIAG, s);
     };
+    // the products of the column the next step clears: in p (ns = 1), or a row
+    // per workgroup in one half of part while the steps take one launch each
+    const double* src = w.p;
+    int q0 = 0, ns = 1;
+    double* const half[2] = {w.part, w.part + (size_t)((P + 15) / 16) * N};
+    auto step1 = [&](int c) {
+        const bool timed = probe && probe->begin(PK_BIDIAG, s);
+        double* out = half[c & 1];
+        constexpr int NW = 8, R = 2;
+        const int g = (P + NW * R - 1) / (NW * R);
+#define ITE_S1(CPL) \
+    hipLaunchKernelGGL((bd_step1_kernel<CPL, R, NW>), dim3(g), dim3(64 * NW), 0, s, w, c, src, q0, ns, out)
+        if (N - c <= 256) ITE_S1(4);
+        else ITE_S1(8);
+#undef ITE_S1
+        src = out;
+        q0 = (c + 1) / (NW * R);
+        ns = g;
+        if (timed) probe->end(PK_BIDIAG, s);
+    };
     const bool whole = P <= BD_TAIL;
     if (!whole) {
         hipLaunchKernelGGL(bd_load_kernel, dim3((N + 31) / 32, (P + 31) / 32), dim3(256), 0, s, theta, P, N, (int)tr,
@@ -728,7 +878,8 @@ void bidiagonalise(const BdWork& w, const double* theta, bool tr, hipStream_t s,
     for (int c = 0; c < N; ++c) {
         const int len = P - c;
         if (len > BD_TAIL) {
-            step(c, false);
+            if (N - c <= BD_ONE && len <= BD_ONE) step1(c);
+            else step(c, false);
             continue;
         }
         const bool timed = probe && probe->begin(PK_BIDIAG, s);
