@@ -154,6 +154,7 @@ int ite_ctx_destroy(ite_ctx* c) {
     if (c->side) (void)hipStreamDestroy(c->side);
     for (int s = 0; s < SL_NSLOTS; ++s) dev_free(c, c->slot_ptr[s]);
     if (c->pinned) (void)hipHostFree(c->pinned);
+    if (c->mail) (void)hipHostFree(c->mail);
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->prof_events) (void)hipEventDestroy(e);
     delete c;
@@ -773,6 +774,7 @@ int ite_debug_svd_split(ite_ctx* c, int dir, int Dl, int d1, int d2, int Dr, con
         ITE_REQUIRE(dir == 0 || dir == 1, "debug_svd_split: dir must be 0 or 1");
         std::vector<double> s;
         SplitResult r = split(c, dir, Dl, d1, d2, Dr, theta, chi_max, cutoff, tie_rel, A1, A2, &s);
+        sync(c);
         if (sigma_out) std::memcpy(sigma_out, s.data(), s.size() * sizeof(double));
         if (k_out) *k_out = r.k;
         if (disc_out) *disc_out = r.disc;

@@ -982,6 +982,40 @@ int dc_depth(int n) {
     return depth;
 }
 
+// Rank of every singular value by counting those before it (16 lanes a
+// value, a pass over all n each): one launch for the order and the way to the
+// host, where a copy, a sort there and a copy back took three and a wait.  The
+// bits of the magnitudes order everything, NaN first.
+__global__ __launch_bounds__(1024) void dc_sorted_kernel(const double* __restrict__ sg, int n,
+                                                         const double* __restrict__ scale, int* __restrict__ perm,
+                                                         HostPost post) {
+    __shared__ double sorted[DC_POST];
+    const int t = threadIdx.x, part = t & 15;
+    const double f = *scale;
+    auto key = [&](int i) { return (unsigned long long)__double_as_longlong(sg[i]) & 0x7fffffffffffffffull; };
+    for (int i = blockIdx.x * 64 + (t >> 4); i < n; i += gridDim.x * 64) {
+        const unsigned long long mine = key(i);
+        int rank = 0;
+        for (int j = part; j < n; j += 16) {
+            const unsigned long long k = key(j);
+            rank += k > mine || (k == mine && j < i);
+        }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) rank += __shfl_xor(rank, o, 16);
+        if (part == 0) {
+            perm[rank] = i;
+            if (post.flag) sorted[rank] = sg[i] * f;
+            else post.data[rank] = sg[i] * f;
+        }
+    }
+    if (!post.flag) return;
+    __syncthreads();
+    if (t < 64) {
+        for (int i = t; i < n; i += 64) post.data[i] = sorted[i];
+        if (t == 0) post_flag(post);
+    }
+}
+
 }  // namespace
 
 size_t dc_workspace(int n) {
@@ -1036,6 +1070,12 @@ DcWork dc_carve(double* ws, int n, const double* d, const double* e) {
     w.i1 = itake(n);
     w.K = itake(nodes);
     return w;
+}
+
+void dc_sorted(const DcWork& w, int cur, int* perm, const HostPost& post, hipStream_t s) {
+    const int blocks = w.n <= DC_POST ? 1 : (w.n + 63) / 64;
+    hipLaunchKernelGGL(dc_sorted_kernel, dim3(blocks), dim3(1024), 0, s, w.sg[cur], w.n, w.scale, perm, post);
+    HIP_CHECK(hipGetLastError());
 }
 
 int bidiagonal_svd(const DcWork& w, hipStream_t s, LaunchProbe* probe) {

@@ -83,6 +83,37 @@ double* pinned(ite_ctx* c, size_t doubles) {
     return c->pinned;
 }
 
+HostPost mail_post(ite_ctx* c, int area) {
+    if (!c->mail) {
+        void* p = nullptr;
+        HIP_CHECK(hipHostMalloc(&p, MAIL_DOUBLES * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent));
+        c->mail = static_cast<unsigned long long*>(p);
+        *c->mail = 0;
+    }
+    HostPost post;
+    post.flag = c->mail;
+    post.data = reinterpret_cast<double*>(c->mail) + area;
+    post.seq = ++c->mail_seq;
+    return post;
+}
+
+// Posts arrive in stream order.  A wait on the stream costs the host 11 us
+// and a copy 3 more; the sequence number is there about 2 us after the kernel
+// wrote it.  The stream is asked now and then, so that the wait also ends when
+// it has drained or failed.
+void mail_wait(ite_ctx* c, const HostPost& post) {
+    for (unsigned n = 1;; ++n) {
+        if (__atomic_load_n(post.flag, __ATOMIC_ACQUIRE) >= post.seq) return;
+        if (n % 4096 == 0) {
+            const hipError_t q = hipStreamQuery(c->stream);
+            if (q == hipSuccess) return;
+            if (q != hipErrorNotReady) HIP_CHECK(q);
+            (void)hipGetLastError();   // not ready is no error
+        }
+        __builtin_ia32_pause();
+    }
+}
+
 void sync(ite_ctx* c) { HIP_CHECK(hipStreamSynchronize(c->stream)); }
 
 void d2h(ite_ctx* c, double* host, const double* dev, size_t n) {
@@ -386,11 +417,10 @@ double dot(ite_ctx* c, const double* x, const double* y, size_t n) {
     double* part = slot_t<double>(c, SL_PART, (size_t)nb * 64 + 64);
     double* sm = slot_t<double>(c, SL_SMALL, 512);
     dot_partials(x, y, n, part, c->stream);
-    finish_partials(part, 1, nb, sm + 256, 0, c->stream);
-    double* h = pinned(c, 64);
-    d2h(c, h, sm + 256, 1);
-    sync(c);
-    return h[0];
+    const HostPost post = mail_post(c, MAIL_ONE);
+    finish_partials(part, 1, nb, sm + 256, 0, c->stream, post);
+    mail_wait(c, post);
+    return post.data[0];
 }
 
 // ---------------------------------------------------------------------------
@@ -417,20 +447,17 @@ int truncation_rank(const std::vector<double>& s, double cutoff, int chi_max, do
     return k;
 }
 
-// Truncation of the singular values nv (any order): idx their order from the
-// largest down, the kept count and the discarded weight.
-static SplitResult truncate(const std::vector<double>& nv, int r, double cutoff, int chi_max, double tie_rel,
-                            std::vector<int>& idx, std::vector<double>* sigma) {
-    idx.resize(nv.size());
-    std::iota(idx.begin(), idx.end(), 0);
-    std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return nv[a] > nv[b]; });
-    std::vector<double> s(r);
-    for (int i = 0; i < r; ++i) s[i] = nv[idx[i]];
+// Truncation of the singular values s (descending): the kept count and the
+// discarded weight.
+static SplitResult truncate(const std::vector<double>& s, double cutoff, int chi_max, double tie_rel,
+                            std::vector<double>* sigma) {
     SplitResult res;
     res.k = truncation_rank(s, cutoff, chi_max, tie_rel);
     double total = 0.0, dropped = 0.0;
-    for (int i = 0; i < r; ++i) total += s[i] * s[i];
-    for (int i = res.k; i < r; ++i) dropped += s[i] * s[i];
+    for (size_t i = 0; i < s.size(); ++i) {
+        total += s[i] * s[i];
+        if ((int)i >= res.k) dropped += s[i] * s[i];
+    }
     res.disc = total > 0.0 ? dropped / total : 0.0;
     if (sigma) *sigma = s;
     return res;
@@ -451,24 +478,22 @@ SplitResult split(ite_ctx* c, int dir, int Dl, int d1, int d2, int Dr, const dou
     int* perm = slot_t<int>(c, SL_PERM, (size_t)N + 16);
     bidiagonalise(bd, theta, tr, c->stream, pr);
     const int w = bidiagonal_svd(dc, c->stream, pr);
-    double* host = pinned(c, (size_t)N + 64);
-    d2h(c, host, dc.sg[w], N);
-    d2h(c, host + N, dc.scale, 1);
-    sync(c);
-    std::vector<double> nv(host, host + N);
-    for (double& v : nv) v *= host[N];
-    std::vector<int> idx;
-    const SplitResult res = truncate(nv, N, cutoff, chi_max, tie_rel, idx, sigma);
-    int* hp = reinterpret_cast<int*>(host);
-    std::memcpy(hp, idx.data(), sizeof(int) * res.k);
-    h2d(c, perm, hp, sizeof(int) * res.k);
+    // the order and the values: few through the mailbox, many through the
+    // staging buffer
+    HostPost post;
+    if (N <= DC_POST) post = mail_post(c, MAIL_SIGMA);
+    else post.data = pinned(c, (size_t)N + 64);
+    dc_sorted(dc, w, perm, post, c->stream);
+    if (N <= DC_POST) mail_wait(c, post);
+    else sync(c);
+    const std::vector<double> nv(post.data, post.data + N);
+    const SplitResult res = truncate(nv, cutoff, chi_max, tie_rel, sigma);
     const size_t nt = bd_vectors_tmp(P, N, res.k);
     double* tmp = nt ? slot_t<double>(c, SL_VECS, nt) : nullptr;
     // U to A1 [m][k], V^T to A2 [k][n]; the singular values go to the factor
     // that is not orthonormal
     const BdOut u{A1, 1, dir == 1}, v{A2, 0, dir == 0};
     bd_vectors(bd, dc.UT[w], dc.VT[w], perm, res.k, dc.sg[w], dc.scale, tr ? v : u, tr ? u : v, tmp, c->stream, pr);
-    sync(c);   // the pinned staging buffer is reused by the next call
     return res;
 }
 
@@ -498,9 +523,12 @@ SplitResult split_jacobi(ite_ctx* c, int dir, int m, int n, const double* theta,
     row_norms(Z, p, q, ld, norms, c->stream);
     d2h(c, host, norms, p);
     sync(c);
-    const std::vector<double> nv(host, host + p);
-    std::vector<int> idx;
-    const SplitResult res = truncate(nv, std::min(m, n), cutoff, chi_max, tie_rel, idx, sigma);
+    std::vector<int> idx(p);
+    std::iota(idx.begin(), idx.end(), 0);
+    std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return host[a] > host[b]; });
+    std::vector<double> nv(std::min(m, n));
+    for (size_t i = 0; i < nv.size(); ++i) nv[i] = host[idx[i]];
+    const SplitResult res = truncate(nv, cutoff, chi_max, tie_rel, sigma);
     int* hp = reinterpret_cast<int*>(host);
     std::memcpy(hp, idx.data(), sizeof(int) * res.k);
     h2d(c, perm, hp, sizeof(int) * res.k);
@@ -570,7 +598,7 @@ static SolveStats gmres_budget(ite_ctx* c, const LocalOp& op, const double* b, d
             op_apply(c, op, V + (size_t)k * n, w);
             gram_schmidt(V, (long)n, k + 1, w, n, col, vnext, part, c->stream);
         }
-        hess_solve(hd, mm, ydev, stats, r_product, cyc + 1 == max_cycles, c->stream);
+        hess_solve(hd, norms, mm, ydev, stats, r_product, cyc + 1 == max_cycles, c->stream);
         gemv_add(V, (long)n, mm, ydev, x, n, c->stream);
     }
     SolveStats st;
@@ -585,9 +613,15 @@ static SolveStats gmres_budget(ite_ctx* c, const LocalOp& op, const double* b, d
 
 // GMRES(m) (Saad and Schultz) with classical Gram-Schmidt applied twice; the
 // Hessenberg column comes to the host once per Arnoldi step, where Givens
-// rotations keep the least-squares residual.  Vectors, Gram-Schmidt and the
-// Hessenberg problem are FP64 whatever the precision of the products.  With
-// x_is_zero the first residual is b itself (no product).
+// rotations keep the least-squares residual; the combination is solved on the
+// device as in gmres_budget.  Vectors, Gram-Schmidt and the Hessenberg problem
+// are FP64 whatever the precision of the products.  With x_is_zero the first
+// residual is b itself (no product).
+//
+// The next step is issued before a column has arrived unless this one is
+// expected to end the cycle (the residual falling once more as it last did):
+// the device would wait for the host about as long as a step at bond 32
+// takes.  A step that turns out not to be needed leaves nothing that is read.
 static SolveStats gmres(ite_ctx* c, const LocalOp& op, const double* b, double* x, int m, int max_cycles,
                         double tol, bool x_is_zero = false) {
     if (tol <= 0) return gmres_budget(c, op, b, x, m, max_cycles, x_is_zero);
@@ -596,13 +630,16 @@ static SolveStats gmres(ite_ctx* c, const LocalOp& op, const double* b, double* 
     int& mv = lo ? st.matvecs_lo : st.matvecs64;
     const size_t n = op.n();
     const int mm = (int)std::min<size_t>((size_t)m, n);
+    constexpr int HC = HESS_HC;
     double* V = slot_t<double>(c, SL_V, (size_t)(mm + 1) * n);
     double* w = slot_t<double>(c, SL_W, n);
     const int nb = reduce_blocks(n);
     double* part = slot_t<double>(c, SL_PART, (size_t)nb * 64 + 64);
-    double* sm = slot_t<double>(c, SL_SMALL, 512);   // [0,64) h1, [64,128) h2, 128 norm, [192,256) y
-    double* host = pinned(c, 512);
-    std::vector<double> H((size_t)(mm + 1) * mm), cs(mm), sn(mm), g(mm + 1), y(mm);
+    double* hd = slot_t<double>(c, SL_HESS, (size_t)mm * HC + 8 + 64 + 8);
+    double* norms = hd + (size_t)mm * HC;
+    double* ydev = norms + 8;
+    double* rec = ydev + 64;        // record of the device's least squares, not read
+    std::vector<double> H((size_t)(mm + 1) * mm), cs(mm), sn(mm), g(mm + 1);
     for (int cyc = 0; cyc < max_cycles; ++cyc) {
         // r0 = b - A x
         const bool ax = !(x_is_zero && cyc == 0);
@@ -610,23 +647,31 @@ static SolveStats gmres(ite_ctx* c, const LocalOp& op, const double* b, double* 
             op_apply(c, op, x, V);
             mv++;
         }
-        krylov_start(b, V, ax, n, sm + 128, part, nullptr, c->stream);
-        d2h(c, host, sm + 128, 2);
-        sync(c);
-        const double bnorm = host[0], beta = host[1];
+        const HostPost np = mail_post(c, MAIL_NORMS);
+        krylov_start(b, V, ax, n, norms, part, rec, c->stream, np);
+        HostPost post[2];
+        auto issue = [&](int k) {
+            op_apply(c, op, V + (size_t)k * n, w);
+            post[k & 1] = mail_post(c, MAIL_COLS + HC * (k & 1));
+            gram_schmidt(V, (long)n, k + 1, w, n, hd + (size_t)k * HC, k + 1 < mm ? V + (size_t)(k + 1) * n : nullptr,
+                         part, c->stream, post[k & 1]);
+        };
+        mail_wait(c, np);
+        const double bnorm = np.data[0], beta = np.data[1];
         st.res_rel = bnorm > 0 ? beta / bnorm : 0.0;
-        if (!(beta > 0.0) || (tol > 0 && beta <= tol * bnorm)) return st;
+        if (!(beta > 0.0) || beta <= tol * bnorm) return st;
         std::fill(H.begin(), H.end(), 0.0);
         std::fill(g.begin(), g.end(), 0.0);
         g[0] = beta;
-        int kused = 0;
+        int kused = 0, issued = 0;
         bool converged = false;
+        double before = beta, last = beta;      // residuals of the last two steps
         for (int k = 0; k < mm; ++k) {
-            op_apply(c, op, V + (size_t)k * n, w);
+            if (issued == k) issue(issued++);
+            if (k + 1 < mm && (k == 0 || last * (last / before) > tol * bnorm)) issue(issued++);
             mv++;
-            gram_schmidt(V, (long)n, k + 1, w, n, sm, nullptr, part, c->stream);
-            d2h(c, host, sm, 129);
-            sync(c);
+            mail_wait(c, post[k & 1]);
+            const double* host = post[k & 1].data;
             for (int i = 0; i <= k; ++i) H[(size_t)i * mm + k] = host[i] + host[64 + i];
             const double hnext = host[128];
             // apply the previous rotations to column k
@@ -645,33 +690,21 @@ static SolveStats gmres(ite_ctx* c, const LocalOp& op, const double* b, double* 
             kused = k + 1;
             const double res = std::fabs(g[k + 1]);
             st.res_rel = bnorm > 0 ? res / bnorm : 0.0;
+            before = last;
+            last = res;
             if (hnext <= 1e-14 * beta) {
                 st.flags |= ITE_FLAG_BREAKDOWN;
                 converged = true;
                 break;
             }
-            if (tol > 0 && res <= tol * bnorm) {
+            if (res <= tol * bnorm) {
                 converged = true;
                 break;
             }
-            scale_inv(w, sm + 128, V + (size_t)(k + 1) * n, n, c->stream);
         }
-        // back substitution R y = g
-        for (int i = kused - 1; i >= 0; --i) {
-            double s = g[i];
-            for (int j = i + 1; j < kused; ++j) s -= H[(size_t)i * mm + j] * y[j];
-            const double dgn = H[(size_t)i * mm + i];
-            y[i] = dgn != 0.0 ? s / dgn : 0.0;
-        }
-        for (int i = 0; i < kused; ++i) host[256 + i] = y[i];
-        h2d(c, sm + 192, host + 256, sizeof(double) * kused);
-        gemv_add(V, (long)n, kused, sm + 192, x, n, c->stream);
-        sync(c);
+        hess_solve(hd, norms, kused, ydev, rec, false, false, c->stream);
+        gemv_add(V, (long)n, kused, ydev, x, n, c->stream);
         if (converged) return st;
-        if (tol <= 0) {
-            if (cyc + 1 == max_cycles) st.flags |= ITE_FLAG_BUDGET_EXHAUSTED;
-            continue;
-        }
         if (cyc + 1 == max_cycles) st.flags |= ITE_FLAG_BUDGET_EXHAUSTED;
     }
     return st;
@@ -1024,13 +1057,20 @@ struct Timer {
         }
         return c->events[c->events_used++];
     }
+    // A record costs the host as much as two launches: a phase starts at the
+    // end of the one before it on this context.
     int open(int phase) {
-        hipEvent_t a = ev(), b = ev();
-        HIP_CHECK(hipEventRecord(a, c->stream));
-        spans.push_back({phase, {a, b}});
+        if (!c->phase_end) mark();
+        spans.push_back({phase, {c->phase_end, c->phase_end}});
         return (int)spans.size() - 1;
     }
-    void close(int idx) { HIP_CHECK(hipEventRecord(spans[idx].second.second, c->stream)); }
+    hipEvent_t mark() {
+        c->phase_end = ev();
+        HIP_CHECK(hipEventRecord(c->phase_end, c->stream));
+        return c->phase_end;
+    }
+    void close(int idx) { spans[idx].second.second = mark(); }
+    void close(int idx, hipEvent_t at) { spans[idx].second.second = at; }
     void collect(double* ms) {
         sync(c);
         for (auto& s : spans) {
@@ -1347,6 +1387,7 @@ void imag_step_sweep(ite_mps* psi, const ite_mpo* H, double h, const ite_step_op
     ite_ctx* c = psi->ctx;
     check_step(psi, H, h, o);
     c->events_used = 0;
+    c->phase_end = nullptr;
     const int nblocks = 2 * (psi->L - 1) * o.nsweeps;
     StepRun run(psi, H, h, o, slot_t<double>(c, SL_STATS, (size_t)8 * nblocks + 8));
     for (int slot = 0; slot < run.nblocks; ++slot) {
@@ -1422,6 +1463,7 @@ void step_batch(int n, ite_mps* const* psi, const ite_mpo* const* H, const doubl
         return;
     }
     c->events_used = 0;
+    c->phase_end = nullptr;
     // per-state records and b / guess buffers
     std::vector<size_t> soff(n), boff(n), bmax(n);
     size_t stot = 0, btot = 0;
@@ -1465,7 +1507,8 @@ void step_batch(int n, ite_mps* const* psi, const ite_mpo* const* H, const doubl
                 spans.push_back(r.tm.open(PH_SOLVE));
             }
             gmres_batch(c, items, std::get<0>(grp.first), std::get<1>(grp.first), std::get<2>(grp.first));
-            for (size_t q = 0; q < grp.second.size(); ++q) runs[grp.second[q]]->tm.close(spans[q]);
+            const hipEvent_t end = runs[grp.second[0]]->tm.mark();
+            for (size_t q = 0; q < grp.second.size(); ++q) runs[grp.second[q]]->tm.close(spans[q], end);
         }
         for (int j = 0; j < n; ++j)
             if (slot < runs[j]->nblocks) runs[j]->split_env();

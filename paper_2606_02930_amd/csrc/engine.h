@@ -40,8 +40,13 @@ struct ite_ctx {
     size_t slot_bytes[SL_NSLOTS] = {};
     double* pinned = nullptr;      // host staging (hipHostMalloc)
     size_t pinned_bytes = 0;
+    // mailbox of the kernels' posts: coherent pinned memory, the sequence
+    // number of the last post first, the data from MAIL_DATA on
+    unsigned long long* mail = nullptr;
+    unsigned long long mail_seq = 0;
     std::vector<hipEvent_t> events;
     size_t events_used = 0;
+    hipEvent_t phase_end = nullptr;     // the last phase boundary recorded by the running call
     // launch profiler (observability): FP64 GEMM launches are all timed,
     // split launches every `split_period`-th of a kind; see LaunchProbe
     bool prof_on = false;
@@ -132,6 +137,12 @@ template <typename T> inline T* slot_t(ite_ctx* c, SlotId s, size_t count) {
     return static_cast<T*>(slot(c, s, count * sizeof(T)));
 }
 double* pinned(ite_ctx* c, size_t doubles);
+// A few values a kernel leaves for the host (HostPost), without a copy and
+// without draining the stream.  Areas of the mailbox in doubles: one value, the
+// norms of a Krylov cycle, two Hessenberg columns, singular values.
+enum { MAIL_ONE = 16, MAIL_NORMS = 24, MAIL_COLS = 64, MAIL_SIGMA = 512, MAIL_DOUBLES = 1024 };
+HostPost mail_post(ite_ctx* c, int area);
+void mail_wait(ite_ctx* c, const HostPost& post);
 void sync(ite_ctx* c);
 void prof_collect(ite_ctx* c);
 

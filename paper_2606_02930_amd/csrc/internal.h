@@ -115,6 +115,15 @@ void stage_f64(const Stage& st, hipStream_t s);
 void convert_f32(const double* x, float* y, size_t n, hipStream_t s);
 void convert_bf16(const double* x, uint16_t* y, size_t n, hipStream_t s);
 
+// A few values a kernel leaves for the host in coherent pinned memory: data,
+// then the sequence number in *flag (mail_wait in engine.cpp).  The wavefront
+// that writes the data writes the flag.  No flag: nothing is posted.
+struct HostPost {
+    double* data = nullptr;
+    unsigned long long* flag = nullptr;
+    unsigned long long seq = 0;
+};
+
 // Vector kernels.  Reductions are two-pass with a fixed grid so results do not
 // depend on timing (bitwise reproducible for a given n).
 int  reduce_blocks(size_t n);
@@ -124,7 +133,8 @@ void dot_partials(const double* x, const double* y, size_t n, double* partial, h
 void mdot_partials(const double* V, long ldv, int k, const double* w, size_t n, double* partial,
                    hipStream_t s);
 // out[j] (+)= sum_b partial[j*nb + b]; mode 0: store, 1: add, 2: store sqrt
-void finish_partials(const double* partial, int k, int nb, double* out, int mode, hipStream_t s);
+// (post: out[0] for the host, k = 1)
+void finish_partials(const double* partial, int k, int nb, double* out, int mode, hipStream_t s, HostPost post = {});
 // w -= sum_j coef[j] V_j   (coef on device)
 void gemv_sub(const double* V, long ldv, int k, const double* coef, double* w, size_t n,
               hipStream_t s);
@@ -149,21 +159,23 @@ void sample_site(const double* T, int nsamples, int d, int Dr, const double* u, 
 // shapes, or many (3).
 int krylov_class(size_t n);
 // Start of a cycle: r = b - v0 (ax: v0 holds A x) or r = b, norms[0] = ||b||,
-// norms[1] = ||r||, v0 = r / ||r||; zeroes stats (8 doubles) unless null.
+// norms[1] = ||r||, v0 = r / ||r||; zeroes stats (8 doubles) unless null; post:
+// the norms.
 void krylov_start(const double* b, double* v0, bool ax, size_t n, double* norms, double* part, double* stats,
-                  hipStream_t s);
+                  hipStream_t s, HostPost post = {});
 // Both classical Gram-Schmidt passes of one Arnoldi step (k1 <= 64 basis
 // vectors): coefficients to col[0..k1) and col[64..64+k1), ||w|| to col[128],
-// vnext = w / ||w|| when not null.
+// vnext = w / ||w|| when not null; post: the same values at the same places
+// (129 doubles).
 void gram_schmidt(const double* V, long ldv, int k1, double* w, size_t n, double* col, double* vnext, double* part,
-                  hipStream_t s);
+                  hipStream_t s, HostPost post = {});
 // Device least-squares solve of one GMRES cycle (see hess_solve_one in
 // krylov.hip): hd holds the cycle's Hessenberg columns, HESS_HC doubles each,
-// then ||b|| and ||r0||; y gets the mm combination coefficients; stats (8
+// norms ||b|| and ||r0||; y gets the mm combination coefficients; stats (8
 // doubles per local solve, zeroed before the first cycle) accumulate the
 // residual estimate, the product count and the flags.
 constexpr int HESS_HC = 192, HESS_KMAX = 64;
-void hess_solve(const double* hd, int mm, double* y, double* stats, bool r_product, bool last_cycle, hipStream_t s);
+void hess_solve(const double* hd, const double* norms, int mm, double* y, double* stats, bool r_product, bool last_cycle, hipStream_t s);
 // Device eigensolve of a Lanczos cycle's projected matrix (lanczos_eig_kernel
 // in vec.hip): y = the eigenvector of the lowest eigenvalue; rec: [0] the
 // eigenvalue, [1] relative residual estimate, [2] += steps used, [3] steps used.
@@ -304,6 +316,11 @@ struct DcWork {
 size_t dc_workspace(int n);                   // doubles
 DcWork dc_carve(double* ws, int n, const double* d, const double* e);
 int bidiagonal_svd(const DcWork& w, hipStream_t s, LaunchProbe* probe = nullptr);
+// The singular values of buffer cur in descending order to post.data (host
+// memory the device can write), perm[r] the index of the r-th.  Up to DC_POST
+// values are posted (post.flag), more are there once the stream has drained.
+constexpr int DC_POST = 512;
+void dc_sorted(const DcWork& w, int cur, int* perm, const HostPost& post, hipStream_t s);
 
 // MFMA lane-layout probe (tests only).
 void mfma_probe_f64(double* out, hipStream_t s);

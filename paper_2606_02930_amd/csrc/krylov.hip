@@ -74,6 +74,13 @@ __device__ inline double sum8(double (&v)[8], int lane) {
 // One workgroup
 // ---------------------------------------------------------------------------
 
+__device__ inline void post_norms(const HostPost& post, double bn, double rn) {
+    if (!post.flag) return;
+    post.data[0] = bn;
+    post.data[1] = rn;
+    post_flag(post);
+}
+
 struct GsLDS {
     double part[GS_T / 64][GS_KMAX];
     double coef[GS_KMAX];
@@ -102,7 +109,8 @@ __device__ inline double group_sum(double v, double (*part)[GS_KMAX]) {
 // second to fourth time are the vectors beyond (n = 4096: 8 stay).
 template <int NT, int E, int KR>
 __device__ inline void gs_small(const double* __restrict__ V, long ldv, int k1, double* __restrict__ w, int n,
-                                double* __restrict__ col, double* __restrict__ vnext, GsLDS& L) {
+                                double* __restrict__ col, double* __restrict__ vnext, const HostPost& post,
+                                GsLDS& L) {
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int id = sum8_index(lane);
     // entries outside the vector are read from its last entry and kept zero
@@ -151,6 +159,7 @@ __device__ inline void gs_small(const double* __restrict__ V, long ldv, int k1, 
             for (int ww = 0; ww < NT / 64; ++ww) s += L.part[ww][t];
             L.coef[t] = s;
             col[64 * pass + t] = s;
+            if (post.flag) post.data[64 * pass + t] = s;
         }
         __syncthreads();
 #pragma unroll
@@ -176,8 +185,12 @@ __device__ inline void gs_small(const double* __restrict__ V, long ldv, int k1, 
 #pragma unroll
     for (int e = 0; e < E; ++e) ss += x[e] * x[e];
     const double nrm = sqrt(fmax(group_sum<NT>(ss, L.part), 0.0));
-    if (t == 0) col[128] = nrm;
+    if (t == 0) {
+        col[128] = nrm;
+        if (post.flag) post.data[128] = nrm;
+    }
     const double inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
+    if (post.flag && t == 0) post_flag(post);   // the coefficients are this wavefront's too (k1 <= 64)
 #pragma unroll
     for (int e = 0; e < E; ++e)
         if (in[e]) {
@@ -201,17 +214,18 @@ template <> struct GsShape<GS_8K> { static constexpr int NT = 1024, E = 8, KR = 
 
 template <int CLASS>
 __global__ __launch_bounds__(GsShape<CLASS>::NT) void gs_small_kernel(const double* V, long ldv, int k1, double* w,
-                                                                      int n, double* col, double* vnext) {
+                                                                      int n, double* col, double* vnext,
+                                                                      HostPost post) {
     typedef GsShape<CLASS> S;
     __shared__ GsLDS L;
-    gs_small<S::NT, S::E, S::KR>(V, ldv, k1, w, n, col, vnext, L);
+    gs_small<S::NT, S::E, S::KR>(V, ldv, k1, w, n, col, vnext, post, L);
 }
 
 // The start of a cycle: r = b - V_0 (V_0 holds A x) or r = b, norms[0] =
 // ||b||, norms[1] = ||r||, V_0 = r / ||r|| (0 for a zero norm).
 template <int NT>
 __device__ inline void start_small(const double* __restrict__ b, double* __restrict__ v0, bool ax, int n,
-                                   double* __restrict__ norms, GsLDS& L) {
+                                   double* __restrict__ norms, const HostPost& post, GsLDS& L) {
     const int t = threadIdx.x;
     double r[8];
     double bb = 0.0, rr = 0.0;
@@ -230,6 +244,7 @@ __device__ inline void start_small(const double* __restrict__ b, double* __restr
     if (t == 0) {
         norms[0] = bn;
         norms[1] = rn;
+        post_norms(post, bn, rn);
     }
     const double inv = rn > 0.0 ? 1.0 / rn : 0.0;
 #pragma unroll
@@ -238,15 +253,16 @@ __device__ inline void start_small(const double* __restrict__ b, double* __restr
         if (t < NT && i < n) v0[i] = r[e] * inv;
     }
 }
-__device__ inline void start_small_any(const double* b, double* v0, bool ax, int n, double* norms, GsLDS& L) {
-    if (n <= 2048) start_small<256>(b, v0, ax, n, norms, L);
-    else start_small<1024>(b, v0, ax, n, norms, L);
+__device__ inline void start_small_any(const double* b, double* v0, bool ax, int n, double* norms,
+                                       const HostPost& post, GsLDS& L) {
+    if (n <= 2048) start_small<256>(b, v0, ax, n, norms, post, L);
+    else start_small<1024>(b, v0, ax, n, norms, post, L);
 }
 __global__ __launch_bounds__(GS_T) void start_small_kernel(const double* b, double* v0, bool ax, int n, double* norms,
-                                                           double* stats) {
+                                                           double* stats, HostPost post) {
     __shared__ GsLDS L;
     if (stats && threadIdx.x < 8) stats[threadIdx.x] = 0.0;
-    start_small_any(b, v0, ax, n, norms, L);
+    start_small_any(b, v0, ax, n, norms, post, L);
 }
 
 // ---------------------------------------------------------------------------
@@ -342,20 +358,33 @@ __global__ __launch_bounds__(RT) void gs_kernel(const double* __restrict__ V, lo
 
 // vnext = w / ||w|| and the norm itself, from the blocks' partials.
 __device__ inline void scale_block(const double* __restrict__ w, size_t n, int vb, int vg,
-                                   const double* __restrict__ part, double* __restrict__ norm,
-                                   double* __restrict__ vnext, BlockLDS& L) {
+                                   const double* __restrict__ part, double* __restrict__ col, int k1,
+                                   double* __restrict__ vnext, const HostPost& post, BlockLDS& L) {
     sum_partials(part, 1, vg, L);
     const double nrm = sqrt(fmax(L.coef[0], 0.0));
-    if (vb == 0 && threadIdx.x == 0) *norm = nrm;
+    if (vb == 0 && threadIdx.x < 64) {
+        const int t = threadIdx.x;
+        if (t == 0) col[128] = nrm;
+        if (post.flag) {
+            if (t < k1) {
+                post.data[t] = col[t];
+                post.data[64 + t] = col[64 + t];
+            }
+            if (t == 0) {
+                post.data[128] = nrm;
+                post_flag(post);
+            }
+        }
+    }
     if (!vnext) return;
     const double inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
     for (size_t i = (size_t)vb * RT + threadIdx.x; i < n; i += (size_t)vg * RT) vnext[i] = w[i] * inv;
 }
 __global__ __launch_bounds__(RT) void gs_scale_kernel(const double* __restrict__ w, size_t n, int vg,
-                                                      const double* __restrict__ part, double* __restrict__ norm,
-                                                      double* __restrict__ vnext) {
+                                                      const double* __restrict__ part, double* __restrict__ col,
+                                                      int k1, double* __restrict__ vnext, HostPost post) {
     __shared__ BlockLDS L;
-    scale_block(w, n, blockIdx.x, vg, part + (size_t)32 * vg, norm, vnext, L);
+    scale_block(w, n, blockIdx.x, vg, part + (size_t)32 * vg, col, k1, vnext, post, L);
 }
 
 __device__ inline void start_block(const double* __restrict__ b, double* __restrict__ v0, bool ax, size_t n, int vb,
@@ -371,12 +400,14 @@ __device__ inline void start_block(const double* __restrict__ b, double* __restr
     put_partials<8>(acc, 2, vb, vg, part, L);
 }
 __device__ inline void start_scale_block(double* __restrict__ v0, size_t n, int vb, int vg,
-                                         const double* __restrict__ part, double* __restrict__ norms, BlockLDS& L) {
+                                         const double* __restrict__ part, double* __restrict__ norms,
+                                         const HostPost& post, BlockLDS& L) {
     sum_partials(part, 2, vg, L);
     const double bn = sqrt(fmax(L.coef[0], 0.0)), rn = sqrt(fmax(L.coef[1], 0.0));
     if (vb == 0 && threadIdx.x == 0) {
         norms[0] = bn;
         norms[1] = rn;
+        post_norms(post, bn, rn);
     }
     const double inv = rn > 0.0 ? 1.0 / rn : 0.0;
     for (size_t i = (size_t)vb * RT + threadIdx.x; i < n; i += (size_t)vg * RT) v0[i] *= inv;
@@ -388,9 +419,10 @@ __global__ __launch_bounds__(RT) void start_kernel(const double* __restrict__ b,
     start_block(b, v0, ax, n, blockIdx.x, gridDim.x, part, L);
 }
 __global__ __launch_bounds__(RT) void start_scale_kernel(double* __restrict__ v0, size_t n,
-                                                         const double* __restrict__ part, double* __restrict__ norms) {
+                                                         const double* __restrict__ part, double* __restrict__ norms,
+                                                         HostPost post) {
     __shared__ BlockLDS L;
-    start_scale_block(v0, n, blockIdx.x, gridDim.x, part, norms, L);
+    start_scale_block(v0, n, blockIdx.x, gridDim.x, part, norms, post, L);
 }
 
 // ---------------------------------------------------------------------------
@@ -400,8 +432,8 @@ __global__ __launch_bounds__(RT) void start_scale_kernel(double* __restrict__ v0
 // The small least-squares problem of one GMRES cycle in one wavefront, lane k
 // holding column k of the Hessenberg matrix: the columns of the cycle's
 // Arnoldi steps are hd[k * HESS_HC + i] (first Gram-Schmidt pass), + 64
-// (second pass), + 128 (the norm of the next vector); hd[mm * HESS_HC] =
-// ||b||, hd[mm * HESS_HC + 1] = beta = ||r0||.  Givens rotation i comes from
+// (second pass), + 128 (the norm of the next vector); norms: ||b|| and
+// beta = ||r0||.  Givens rotation i comes from
 // column i and is applied to all later columns at once (they would wait for
 // it one by one otherwise: 16.5 us a cycle of ten, now 6.5), and the residual
 // estimate |g_(k+1)| is tracked; an Arnoldi step whose next norm is <= 1e-14
@@ -414,7 +446,7 @@ __global__ __launch_bounds__(RT) void start_scale_kernel(double* __restrict__ v0
 // Hs: LDS of R, rows padded so that a row's lanes and a column's spread over
 // the banks.
 constexpr int HESS_LD = HESS_KMAX + 1;
-__device__ void hess_solve_one(const double* __restrict__ hd, int mm, double* __restrict__ y,
+__device__ void hess_solve_one(const double* __restrict__ hd, const double* __restrict__ norms, int mm, double* __restrict__ y,
                                double* __restrict__ stats, int r_product, int last_cycle,
                                double (*Hs)[HESS_LD]) {
     const int k = threadIdx.x;
@@ -425,7 +457,7 @@ __device__ void hess_solve_one(const double* __restrict__ hd, int mm, double* __
     double products = stats[1] + (r_product ? 1.0 : 0.0);
     const double rproducts = stats[4] + (r_product ? 1.0 : 0.0);   // FP64 even when the others are not
     const int flags0 = (int)stats[2];
-    const double bnorm = hd[(size_t)mm * HESS_HC], beta = hd[(size_t)mm * HESS_HC + 1];
+    const double bnorm = norms[0], beta = norms[1];
     if (!(beta > 0.0)) {
         if (k < mm) y[k] = 0.0;
         if (k == 0) {
@@ -490,10 +522,11 @@ __device__ void hess_solve_one(const double* __restrict__ hd, int mm, double* __
     }
 }
 
-__global__ __launch_bounds__(64) void hess_solve_kernel(const double* __restrict__ hd, int mm, double* __restrict__ y,
-                                                        double* __restrict__ stats, int r_product, int last_cycle) {
+__global__ __launch_bounds__(64) void hess_solve_kernel(const double* __restrict__ hd, const double* __restrict__ norms,
+                                                        int mm, double* __restrict__ y, double* __restrict__ stats,
+                                                        int r_product, int last_cycle) {
     __shared__ double Hs[HESS_KMAX][HESS_LD];
-    hess_solve_one(hd, mm, y, stats, r_product, last_cycle, Hs);
+    hess_solve_one(hd, norms, mm, y, stats, r_product, last_cycle, Hs);
 }
 
 // ---------------------------------------------------------------------------
@@ -509,7 +542,8 @@ __global__ __launch_bounds__(GsShape<CLASS>::NT) void batch_gs_small_kernel(cons
         const BatchVec& p = d[g];
         if (gs_class(p.n) != CLASS) continue;
         double* vnext = k + 1 < mm ? p.V + (size_t)(k + 1) * p.n : nullptr;
-        gs_small<S::NT, S::E, S::KR>(p.V, p.n, k + 1, p.w, (int)p.n, p.hd + (size_t)k * HESS_HC, vnext, L);
+        gs_small<S::NT, S::E, S::KR>(p.V, p.n, k + 1, p.w, (int)p.n, p.hd + (size_t)k * HESS_HC, vnext,
+                                     HostPost{}, L);
         __syncthreads();
     }
 }
@@ -521,7 +555,7 @@ __global__ __launch_bounds__(GS_T) void batch_start_small_kernel(const BatchVec*
         const BatchVec& p = d[g];
         if (gs_class(p.n) == GS_LONG) continue;
         if (first && threadIdx.x < 8) p.stats[threadIdx.x] = 0.0;
-        start_small_any(p.b, p.V, true, (int)p.n, p.hd + (size_t)mm * HESS_HC, L);
+        start_small_any(p.b, p.V, true, (int)p.n, p.hd + (size_t)mm * HESS_HC, HostPost{}, L);
         __syncthreads();
     }
 }
@@ -542,13 +576,13 @@ __global__ __launch_bounds__(RT) void batch_gs_kernel(const BatchVec* __restrict
         if constexpr (PASS < 3) {
             gs_block<KMAX, PASS>(p.V, p.n, k + 1, p.w, p.n, vb, p.nb, p.part, col, L);
         } else if constexpr (PASS == 3) {
-            scale_block(p.w, p.n, vb, p.nb, p.part + (size_t)32 * p.nb, col + 128,
-                        k + 1 < mm ? p.V + (size_t)(k + 1) * p.n : nullptr, L);
+            scale_block(p.w, p.n, vb, p.nb, p.part + (size_t)32 * p.nb, col, k + 1,
+                        k + 1 < mm ? p.V + (size_t)(k + 1) * p.n : nullptr, HostPost{}, L);
         } else if constexpr (PASS == 4) {
             if (first && vb == 0 && threadIdx.x < 8) p.stats[threadIdx.x] = 0.0;
             start_block(p.b, p.V, true, p.n, vb, p.nb, p.part, L);
         } else {
-            start_scale_block(p.V, p.n, vb, p.nb, p.part, p.hd + (size_t)mm * HESS_HC, L);
+            start_scale_block(p.V, p.n, vb, p.nb, p.part, p.hd + (size_t)mm * HESS_HC, HostPost{}, L);
         }
         __syncthreads();   // the LDS is the next unit's
     }
@@ -559,7 +593,7 @@ __global__ __launch_bounds__(64) void batch_hess_kernel(const BatchVec* __restri
     __shared__ double Hs[HESS_KMAX][HESS_LD];
     for (int g = blockIdx.x; g < G; g += gridDim.x) {
         const BatchVec& p = d[g];
-        hess_solve_one(p.hd, mm, p.y, p.stats, r_product, last_cycle, Hs);
+        hess_solve_one(p.hd, p.hd + (size_t)mm * HESS_HC, mm, p.y, p.stats, r_product, last_cycle, Hs);
         __syncthreads();
     }
 }
@@ -569,15 +603,15 @@ __global__ __launch_bounds__(64) void batch_hess_kernel(const BatchVec* __restri
 int krylov_class(size_t n) { return gs_class((long)n); }
 
 void krylov_start(const double* b, double* v0, bool ax, size_t n, double* norms, double* part, double* stats,
-                  hipStream_t s) {
+                  hipStream_t s, HostPost post) {
     if (n == 0) return;
     if (gs_class((long)n) != GS_LONG) {
         hipLaunchKernelGGL(start_small_kernel, dim3(1), dim3(n <= 2048 ? 256 : GS_T), 0, s, b, v0, ax, (int)n, norms,
-                           stats);
+                           stats, post);
     } else {
         const dim3 grid(reduce_blocks(n));
         hipLaunchKernelGGL(start_kernel, grid, dim3(RT), 0, s, b, v0, ax, n, part, stats);
-        hipLaunchKernelGGL(start_scale_kernel, grid, dim3(RT), 0, s, v0, n, part, norms);
+        hipLaunchKernelGGL(start_scale_kernel, grid, dim3(RT), 0, s, v0, n, part, norms, post);
     }
     HIP_CHECK(hipGetLastError());
 }
@@ -592,13 +626,13 @@ static void gs_launch(const double* V, long ldv, int k1, double* w, size_t n, do
 }
 
 void gram_schmidt(const double* V, long ldv, int k1, double* w, size_t n, double* col, double* vnext, double* part,
-                  hipStream_t s) {
+                  hipStream_t s, HostPost post) {
     if (n == 0) return;
     if (k1 < 1 || k1 > GS_KMAX) ITE_FAIL(ITE_EINVAL, "gram_schmidt: basis outside 1..64 vectors");
     const int cls = gs_class((long)n);
     if (cls != GS_LONG) {
 #define ITE_GS(C) \
-    hipLaunchKernelGGL((gs_small_kernel<C>), dim3(1), dim3(GsShape<C>::NT), 0, s, V, ldv, k1, w, (int)n, col, vnext)
+    hipLaunchKernelGGL((gs_small_kernel<C>), dim3(1), dim3(GsShape<C>::NT), 0, s, V, ldv, k1, w, (int)n, col, vnext, post)
         if (cls == GS_1K) ITE_GS(GS_1K);
         else if (cls == GS_4K) ITE_GS(GS_4K);
         else ITE_GS(GS_8K);
@@ -611,7 +645,7 @@ void gram_schmidt(const double* V, long ldv, int k1, double* w, size_t n, double
         if (k1 <= 4) gs_launch<4>(V, ldv, k1, w, n, col, part, s);
         else if (k1 <= 8) gs_launch<8>(V, ldv, k1, w, n, col, part, s);
         else gs_launch<16>(V, ldv, k1, w, n, col, part, s);
-        hipLaunchKernelGGL(gs_scale_kernel, dim3(vnext ? nb : 1), dim3(RT), 0, s, w, n, nb, part, col + 128, vnext);
+        hipLaunchKernelGGL(gs_scale_kernel, dim3(vnext ? nb : 1), dim3(RT), 0, s, w, n, nb, part, col, k1, vnext, post);
         HIP_CHECK(hipGetLastError());
         return;
     }
@@ -622,14 +656,15 @@ void gram_schmidt(const double* V, long ldv, int k1, double* w, size_t n, double
         finish_partials(part, k1, nb, col + 64 * pass, 0, s);
         gemv_sub(V, ldv, k1, col + 64 * pass, w, n, s);
     }
-    dot_partials(w, w, n, part, s);
-    finish_partials(part, 1, nb, col + 128, 2, s);
-    if (vnext) scale_inv(w, col + 128, vnext, n, s);
+    dot_partials(w, w, n, part + (size_t)32 * nb, s);
+    hipLaunchKernelGGL(gs_scale_kernel, dim3(vnext ? nb : 1), dim3(RT), 0, s, w, n, nb, part, col, k1, vnext, post);
+    HIP_CHECK(hipGetLastError());
 }
 
-void hess_solve(const double* hd, int mm, double* y, double* stats, bool r_product, bool last_cycle, hipStream_t s) {
+void hess_solve(const double* hd, const double* norms, int mm, double* y, double* stats, bool r_product, bool last_cycle, hipStream_t s) {
     if (mm < 1 || mm > HESS_KMAX) ITE_FAIL(ITE_EINVAL, "hess_solve: Krylov dimension outside 1..64");
-    hipLaunchKernelGGL(hess_solve_kernel, dim3(1), dim3(64), 0, s, hd, mm, y, stats, (int)r_product, (int)last_cycle);
+    hipLaunchKernelGGL(hess_solve_kernel, dim3(1), dim3(64), 0, s, hd, norms, mm, y, stats, (int)r_product,
+                       (int)last_cycle);
     HIP_CHECK(hipGetLastError());
 }
 

@@ -87,10 +87,14 @@ __device__ inline void finish_one(const double* __restrict__ partial, int nb, do
 
 __global__ __launch_bounds__(RT) void finish_partials_kernel(const double* __restrict__ partial,
                                                              int nb, double* __restrict__ out,
-                                                             int mode) {
+                                                             int mode, HostPost post) {
     __shared__ double sh[RT / 64];
     const int j = blockIdx.x;
     finish_one(partial + (size_t)j * nb, nb, out + j, mode, sh);
+    if (post.flag && j == 0 && threadIdx.x == 0) {
+        post.data[0] = out[0];
+        post_flag(post);
+    }
 }
 
 template <int KMAX, bool SUB>
@@ -357,8 +361,9 @@ void mdot_partials(const double* V, long ldv, int k, const double* w, size_t n, 
     HIP_CHECK(hipGetLastError());
 }
 
-void finish_partials(const double* partial, int k, int nb, double* out, int mode, hipStream_t s) {
-    hipLaunchKernelGGL(finish_partials_kernel, dim3(k), dim3(RT), 0, s, partial, nb, out, mode);
+void finish_partials(const double* partial, int k, int nb, double* out, int mode, hipStream_t s,
+                     HostPost post) {
+    hipLaunchKernelGGL(finish_partials_kernel, dim3(k), dim3(RT), 0, s, partial, nb, out, mode, post);
     HIP_CHECK(hipGetLastError());
 }
 

@@ -69,4 +69,9 @@ __device__ inline double recip_sqrt(double x) {
     return fma(0.5 * r, fma(-x * r, r, 1.0), r);
 }
 
+// The sequence number of a HostPost, after everything this wavefront wrote.
+template <typename Post> __device__ inline void post_flag(const Post& p) {
+    __hip_atomic_store(p.flag, p.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 }  // namespace ite
