@@ -192,17 +192,6 @@ struct CtxProbe final : LaunchProbe {
 
 }  // namespace
 
-// Concurrent workgroups of the GEMM kernels on the context's device (two per
-// compute unit).
-static int gemm_slots(ite_ctx* c) {
-    if (c->gemm_slots == 0) {
-        int cus = 0;
-        HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
-        c->gemm_slots = 2 * std::max(cus, 1);
-    }
-    return c->gemm_slots;
-}
-
 void gemm(ite_ctx* c, bool tA, bool tB, int M, int N, int K, double alpha, const double* A, long lda,
           const double* B, long ldb, double beta, const double* C, long ldc, double* D, long ldd) {
     Gemm g;
@@ -211,7 +200,7 @@ void gemm(ite_ctx* c, bool tA, bool tB, int M, int N, int K, double alpha, const
     g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc; g.D = D; g.ldd = ldd;
     // an output too small to fill the chip but with a long K: K parts as one
     // batch, summed in a fixed order
-    const int parts = M > 0 && N > 0 ? splitk_parts_f64(M, N, K) : 1;
+    const int parts = M > 0 && N > 0 ? splitk_parts(M, N, K) : 1;
     double* work = parts > 1 ? slot_t<double>(c, SL_SPLITK, (size_t)parts * M * N) : nullptr;
     if (c->prof_on && M > 0 && N > 0) {
         CtxProbe pr(c);
@@ -264,7 +253,7 @@ static void gemm_lo(ite_ctx* c, Prec p, bool tA, bool tB, int M, int N, int K, d
     if (p == Prec::F32) {
         // an FP64 output too small to fill the chip with a long K: K parts,
         // as for the FP64 products
-        const int parts = !Df && M > 0 && N > 0 ? splitk_parts(M, N, K, gemm_slots(c)) : 1;
+        const int parts = !Df && M > 0 && N > 0 ? splitk_parts(M, N, K) : 1;
         if (parts > 1) gemm_f32_splitk(g, parts, slot_t<double>(c, SL_SPLITK, (size_t)parts * M * N), c->stream);
         else gemm_f32(g, c->stream);
     } else {

@@ -75,7 +75,6 @@ struct ite_ctx {
     long long graph_captures = 0, graph_replays = 0, batch_solves = 0;
     long long graph_fallbacks = 0;   // batched solves issued directly after a capture was invalidated
     std::vector<char> batch_host;   // host image of the batch descriptors (kept until the next batch)
-    int gemm_slots = 0;             // concurrent GEMM workgroups (two per compute unit), queried once
 };
 
 // Sparse small matrix in CSR form on the device.

@@ -5,7 +5,7 @@
 //
 // FP64 and FP32 operands: gemm_direct.h (memory -> registers -> matrix cores,
 // no barrier in the K loop), with the wavefront and workgroup tiles chosen by
-// launch_direct.  BF16 operands: a 128 x 128 tile staged through LDS, below.
+// tile_kind.  BF16 operands: the same, or a 128 x 128 tile staged through LDS.
 //
 // Workgroup -> tile mapping is XCD-aware: the hardware deals workgroups to the
 // 8 XCDs round-robin, so consecutive workgroup ids are remapped to give each
@@ -61,23 +61,25 @@ void launch_tiles(const Gemm& g, Params p, hipStream_t s) {
 // short (160 x 128 x 32: 2.9 and 3.4) and slower when it is long (64 x 64 x
 // 4000: 18.1 and 13.4); they meet near 500.
 //
-// FP32 keeps one K order whatever the tile, so its products have the same
-// bits alone and in a batch: no K parts, 32 x 32 with a matrix-core tile a
-// wavefront or 64 x 64 with four:
-//      1532 x 401 x 2005 (NT) 53.5 (32)    79.6 (64)     201 (LDS)
-//      1280 x 1024 x 256      14.6         18.1           46        320 64-tiles
-//      1920 x 1536 x 384      39.9         33.1           64        720 64-tiles
-//      5120 x 4096 x 1024      695          441          551
+// FP32 (us; the 32 tile with 4 K parts):
+//      480 x 120 x 600 (NT)    4.6     7.7    16.5    67.2
+//      600 x 480 x 120         5.6     5.5     7.9    26.3     285 32-tiles
+//      1024 x 256 x 1280 (NT) 12.8    12.1    29.1     126     256 32-tiles
+//      1532 x 401 x 2005 (NT) 53.7    39.1    46.3     201     168 64-tiles
+//      1920 x 1536 x 384      49.4    31.0    31.7    61.4     720 64-tiles
+//      2560 x 2048 x 512       110    66.9    62.7     106    1280 64-tiles
+//      5120 x 4096 x 1024      938     562     458     561
+// the same, with 64 from 1024 of its tiles on.
 //
 // A side-contiguous operand (A transposed, B not) needs a side of at least
 // one wavefront tile, which only the 16-wide tiles guarantee.
+template <typename T> constexpr int K32 = sizeof(T) == 8 ? 8 : 4;   // K parts of the 32 tile
 enum TileKind { TILE_64, TILE_32, TILE_16_LONG, TILE_16 };
 template <typename T>
 TileKind tile_kind(const Gemm& g) {
     auto tiles = [&](int side) { return (long)((g.M + side - 1) / side) * ((g.N + side - 1) / side) * g.batch; };
     const bool wide = (!g.tA || g.M >= 32) && (g.tB || g.N >= 32);
-    if (wide && tiles(64) >= 512) return TILE_64;
-    if (std::is_same<T, float>::value) return TILE_32;
+    if (wide && tiles(64) >= (std::is_same<T, double>::value ? 512 : 1024)) return TILE_64;
     if (wide && tiles(32) >= 192) return TILE_32;
     return g.K >= 512 ? TILE_16_LONG : TILE_16;
 }
@@ -101,15 +103,10 @@ void launch(const Gemm& g, hipStream_t s) {
     Params p = params(g);
     if (std::is_same<T, double>::value) p.Df = nullptr;
     const TileKind kind = tile_kind<T>(g);
-    if constexpr (std::is_same<T, double>::value) {
-        if (kind == TILE_64) launch_tiles<T, 2, 2, 2, 2, 2, 1>(g, p, s);
-        else if (kind == TILE_32) launch_tiles<T, 2, 2, 1, 1, 8, 1>(g, p, s);
-        else if (kind == TILE_16_LONG) launch_tiles<T, 1, 1, 1, 1, 8, 2>(g, p, s);
-        else launch_tiles<T, 1, 1, 1, 1, 4, 2>(g, p, s);
-    } else {
-        if (kind == TILE_64) launch_tiles<T, 2, 2, 2, 2, 1, 1>(g, p, s);
-        else launch_tiles<T, 1, 1, 2, 2, 1, 4>(g, p, s);
-    }
+    if (kind == TILE_64) launch_tiles<T, 2, 2, 2, 2, 2, 1>(g, p, s);
+    else if (kind == TILE_32) launch_tiles<T, 2, 2, 1, 1, K32<T>, 1>(g, p, s);
+    else if (kind == TILE_16_LONG) launch_tiles<T, 1, 1, 1, 1, 8, 2>(g, p, s);
+    else launch_tiles<T, 1, 1, 1, 1, 4, 2>(g, p, s);
 }
 
 // Many independent problems in one persistent launch (the products of the
@@ -118,22 +115,22 @@ void launch(const Gemm& g, hipStream_t s) {
 // output; every workgroup walks that range with a stride of the grid, so the
 // grid can stay fixed (graph capture) while the problems change.  The
 // descriptors live in device memory.  Each problem has the tile of its shape;
-// a 16 x 16 one of four K parts takes two neighbours for the eight wavefronts.
+// one of four K parts takes two neighbours for the eight wavefronts.
 struct GroupDesc {
     Params p;
     int tile_start;
     int kind;
 };
 int group_rows(TileKind k) { return k == TILE_64 ? 64 : k == TILE_32 ? 32 : 16; }
-int group_cols(TileKind k) { return k == TILE_64 ? 64 : k == TILE_16_LONG ? 16 : 32; }
+int group_cols(TileKind k, bool f32) {
+    return k == TILE_64 ? 64 : k == TILE_32 ? (f32 ? 64 : 32) : k == TILE_16_LONG ? 16 : 32;
+}
 
 template <typename T, bool TB>
-__global__ __launch_bounds__(sizeof(T) == 8 ? 512 : 256) void gemm_grouped_kernel(
-    const GroupDesc* __restrict__ desc, const int* __restrict__ count) {
-    constexpr bool F64 = std::is_same<T, double>::value;
-    constexpr int KS64 = F64 ? 2 : 1, KS32 = F64 ? 8 : 1;
-    constexpr int L64 = direct_lds<T, false, TB, 2, 2, 2, 2, KS64>();
-    constexpr int L32 = F64 ? direct_lds<T, false, TB, 2, 2, 1, 1, KS32>() : direct_lds<T, false, TB, 1, 1, 2, 2, 1>();
+__global__ __launch_bounds__(512) void gemm_grouped_kernel(const GroupDesc* __restrict__ desc,
+                                                           const int* __restrict__ count) {
+    constexpr int W32 = 8 / K32<T>;
+    constexpr int L64 = direct_lds<T, false, TB, 2, 2, 2, 2, 2>(), L32 = direct_lds<T, false, TB, 2, 2, 1, W32, K32<T>>();
     __shared__ __attribute__((aligned(16))) T lds[L64 > L32 ? L64 : L32];
     const int G = count[0], ntiles = count[1];
     int g = 0;
@@ -142,14 +139,10 @@ __global__ __launch_bounds__(sizeof(T) == 8 ? 512 : 256) void gemm_grouped_kerne
         const Params p = desc[g].p;
         const int kind = desc[g].kind;
         const int lt = tile - desc[g].tile_start, m = lt / p.nt, n = lt % p.nt;
-        if (kind == TILE_64) direct_tile<T, false, TB, 2, 2, 2, 2, KS64, 1>(p, m * 64, n * 64, 0, lds);
-        else if constexpr (F64) {
-            if (kind == TILE_32) direct_tile<T, false, TB, 2, 2, 1, 1, 8, 1>(p, m * 32, n * 32, 0, lds);
-            else if (kind == TILE_16_LONG) direct_tile<T, false, TB, 1, 1, 1, 1, 8, 2>(p, m * 16, n * 16, 0, lds);
-            else direct_tile<T, false, TB, 1, 1, 1, 2, 4, 2>(p, m * 16, n * 32, 0, lds);
-        } else {
-            direct_tile<T, false, TB, 1, 1, 2, 2, 1, 4>(p, m * 32, n * 32, 0, lds);
-        }
+        if (kind == TILE_64) direct_tile<T, false, TB, 2, 2, 2, 2, 2, 1>(p, m * 64, n * 64, 0, lds);
+        else if (kind == TILE_32) direct_tile<T, false, TB, 2, 2, 1, W32, K32<T>, 1>(p, m * 32, n * 32 * W32, 0, lds);
+        else if (kind == TILE_16_LONG) direct_tile<T, false, TB, 1, 1, 1, 1, 8, 2>(p, m * 16, n * 16, 0, lds);
+        else direct_tile<T, false, TB, 1, 1, 1, 2, 4, 2>(p, m * 16, n * 32, 0, lds);
         __syncthreads();   // the LDS is the next tile's
     }
 }
@@ -177,7 +170,6 @@ __global__ void mfma_probe_kernel(double* out) {
 // the banks without padding.  Lane group g = lane / 16 supplies K values
 // 8 g .. 8 g + 7 of each 32-wide step; A and B use the same mapping.
 // ---------------------------------------------------------------------------
-typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 constexpr int BK16 = 64;
 
 // u16 offset of chunk c (8 K values) of LDS row r
@@ -380,20 +372,11 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const double* __restric
 }  // namespace
 
 // Eight K parts of a workgroup are enough until each is 16 slices of 32 long;
-// beyond that more workgroups share K (FP64 64 x 64 x 16384 is 8 parts, 45 us
-// as one).
-int splitk_parts_f64(int M, int N, int K) {
+// beyond that more workgroups share K.
+int splitk_parts(int M, int N, int K) {
     const long tiles = (long)((M + 15) / 16) * ((N + 15) / 16);
     if (tiles > 128 || K < 4096) return 1;
     int s = (int)std::min<long>(256 / tiles, K / 2048);
-    while (s > 1 && K % (s * BK) != 0) --s;
-    return std::max(s, 1);
-}
-
-int splitk_parts(int M, int N, int K, int slots) {
-    const long tiles = (long)((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-    if (tiles * 2 > slots || K < 2048) return 1;
-    int s = (int)std::min<long>(slots / tiles, K / 1024);
     while (s > 1 && K % (s * BK) != 0) --s;
     return std::max(s, 1);
 }
@@ -447,7 +430,7 @@ int grouped_desc_fill(const Gemm& g, bool f32, int tile_start, void* out) {
     d.p = params(g);
     d.p.sA = d.p.sB = d.p.sC = d.p.sD = 0;
     d.p.mt = g.M > 0 ? (g.M + group_rows(k) - 1) / group_rows(k) : 0;
-    d.p.nt = g.N > 0 ? (g.N + group_cols(k) - 1) / group_cols(k) : 0;
+    d.p.nt = g.N > 0 ? (g.N + group_cols(k, f32) - 1) / group_cols(k, f32) : 0;
     d.tile_start = tile_start;
     d.kind = k;
     std::memcpy(out, &d, sizeof(d));
@@ -458,8 +441,8 @@ void gemm_grouped(const void* desc, const int* count, bool f32, bool tB, hipStre
     const auto* d = static_cast<const GroupDesc*>(desc);
     const dim3 grid(512);
     if (f32) {
-        if (tB) hipLaunchKernelGGL((gemm_grouped_kernel<float, true>), grid, dim3(256), 0, s, d, count);
-        else hipLaunchKernelGGL((gemm_grouped_kernel<float, false>), grid, dim3(256), 0, s, d, count);
+        if (tB) hipLaunchKernelGGL((gemm_grouped_kernel<float, true>), grid, dim3(512), 0, s, d, count);
+        else hipLaunchKernelGGL((gemm_grouped_kernel<float, false>), grid, dim3(512), 0, s, d, count);
     } else {
         if (tB) hipLaunchKernelGGL((gemm_grouped_kernel<double, true>), grid, dim3(512), 0, s, d, count);
         else hipLaunchKernelGGL((gemm_grouped_kernel<double, false>), grid, dim3(512), 0, s, d, count);
@@ -469,23 +452,33 @@ void gemm_grouped(const void* desc, const int* count, bool f32, bool tB, hipStre
 
 void gemm_f32(const Gemm& g, hipStream_t s) { launch<float>(g, s); }
 
+// BF16 tiles: straight to registers (32 x 32 or 16 x 16, four K parts) while the
+// 128 x 128 tiles through LDS leave compute units idle; those read each operand
+// a quarter as often and win once they fill the chip, from 256 of them on with
+// K contiguous in both operands and from 512 on where they transpose on the way
+// into LDS (us: 16, 32, LDS 128):
+//      128 x 32 x 160 (NT)       4.1   6.5  13.7
+//      2048 x 128 x 768 (NT)     4.9   5.2  24.2     256 32-tiles
+//      4096 x 256 x 1536 (NT)   19.6  14.3  38.5      64 128-tiles
+//      1536 x 4096 x 256        47.0  30.7  34.9     384
+//      8192 x 512 x 3072 (NT)    121  74.6  68.5     256
+//      5120 x 4096 x 1024        596   283   199    1280
 void gemm_bf16(const Gemm& g, hipStream_t s) {
     if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return;
-    Params p;
-    p.M = g.M; p.N = g.N; p.K = g.K;
-    p.alpha = g.alpha; p.beta = g.beta;
-    p.A = g.A; p.lda = g.lda; p.sA = g.sA;
-    p.B = g.B; p.ldb = g.ldb; p.sB = g.sB;
-    p.C = g.C; p.ldc = g.ldc; p.sC = g.sC;
-    p.D = g.D; p.ldd = g.ldd; p.sD = g.sD;
-    p.Df = g.Df;
     if (g.Df && g.C) ITE_FAIL(ITE_EINVAL, "gemm: an FP32 output takes no C");
-    p.mt = (g.M + BM - 1) / BM;
-    p.nt = (g.N + BN - 1) / BN;
-    dim3 grid(p.mt * p.nt, 1, g.batch);
+    Params p = params(g);
+    auto tiles = [&](int side) { return (long)((g.M + side - 1) / side) * ((g.N + side - 1) / side) * g.batch; };
+    const bool wide = (!g.tA || g.M >= 32) && (g.tB || g.N >= 32);
+    const int side = tiles(128) >= (!g.tA && g.tB ? 256 : 512) ? 128 : wide && tiles(32) >= 192 ? 32 : 16;
+    p.mt = (g.M + side - 1) / side;
+    p.nt = (g.N + side - 1) / side;
+    const dim3 grid(p.mt * p.nt, 1, g.batch);
     const bool v = vec16(g, sizeof(uint16_t));
-#define ITE_GB(TA, TB)                                                                               \
-    if (v) hipLaunchKernelGGL((gemm_bf16_kernel<TA, TB, true>), grid, dim3(NTHREADS), 0, s, p);      \
+#define ITE_GB(TA, TB)                                                                                          \
+    if (side == 16) hipLaunchKernelGGL((direct_bf16_kernel<TA, TB, 1, 1, 1, 1, 4>), grid, dim3(256), 0, s, p);  \
+    else if (side == 32)                                                                                        \
+        hipLaunchKernelGGL((direct_bf16_kernel<TA, TB, 2, 2, 1, 1, 4>), grid, dim3(256), 0, s, p);              \
+    else if (v) hipLaunchKernelGGL((gemm_bf16_kernel<TA, TB, true>), grid, dim3(NTHREADS), 0, s, p);            \
     else hipLaunchKernelGGL((gemm_bf16_kernel<TA, TB, false>), grid, dim3(NTHREADS), 0, s, p)
     if (!g.tA && !g.tB) { ITE_GB(false, false); }
     else if (!g.tA && g.tB) { ITE_GB(false, true); }

@@ -127,10 +127,73 @@ template <typename T, int S> struct Side<T, false, S> {
     }
 };
 
+// The end of a tile: the K parts summed in order and in FP64 through LDS (KS
+// parts of WM WN MI NI 256 values; unused for one part), alpha, beta and the
+// store of the rows and columns from (ms, ns) on that are inside.  row(i, r),
+// col(j): the matrix row and column of this lane's accumulator element r of
+// tile (i, j).  out: nothing of the wavefront's tile is inside.
+template <int MI, int NI, int WM, int WN, int KS, typename T, typename Acc, typename Row, typename Col>
+__device__ __forceinline__ void finish_tile(const Params& p, long bz, int ms, int ns, bool out,
+                                            const Acc (&acc)[MI][NI], Row row, Col col, T* lds) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ks = wave / (WM * WN), wmn = wave % (WM * WN);
+    const double* C = p.C ? p.C + bz * p.sC : nullptr;
+    double* D = p.Df ? nullptr : p.D + bz * p.sD;
+    float* Df = p.Df ? p.Df + bz * p.sD : nullptr;
+    auto store = [&](int i, int j, int r, double sum) {
+        const int m = row(i, r), n = col(j);
+        if (m >= ms && m < p.M && n >= ns && n < p.N) {
+            double v = p.alpha * sum;
+            if (Df) {
+                Df[(long)m * p.ldd + n] = (float)v;
+            } else {
+                if (C) v += p.beta * C[(long)m * p.ldc + n];
+                D[(long)m * p.ldd + n] = v;
+            }
+        }
+    };
+    if constexpr (KS == 1) {
+        if (out) return;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) store(i, j, r, (double)acc[i][j][r]);
+    } else {
+        constexpr int E = MI * NI * 4;               // values of a lane
+        constexpr int PART = WM * WN * E * 64;
+        __syncthreads();
+        T* mine = lds + ks * PART + wmn * E * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) mine[((i * NI + j) * 4 + r) * 64] = acc[i][j][r];
+        __syncthreads();
+        if (!out) {
+            const T* sum0 = lds + wmn * E * 64 + lane;
+            // values ks, ks + KS, ... of this wavefront's tile
+#pragma unroll
+            for (int e0 = 0; e0 < E; e0 += KS) {
+                const int e = e0 + ks;
+                if (E % KS == 0 || e < E) {
+                    double v = (double)sum0[e * 64];
+#pragma unroll
+                    for (int q = 1; q < KS; ++q) v += (double)sum0[q * PART + e * 64];
+                    store(e / (4 * NI), (e / 4) % NI, e % 4, v);
+                }
+            }
+        }
+    }
+}
+
 // A (16 MI WM) x (16 NI WN) output tile at (m0, n0): WM x WN wavefronts of
 // MI x NI matrix-core tiles, and KS such groups that take a part of the K
-// slices each; the parts are summed in order through LDS (lds: direct_lds
-// values).  PD slices are in flight per wavefront.  A side of more than one tile per wavefront that is
+// slices each; the parts are summed in order and in FP64 through LDS (lds:
+// direct_lds values).  PD slices are in flight per wavefront.  A side of more than one tile per wavefront that is
 // side-contiguous (A transposed, B not) must be at least 16 MI (16 NI) long.
 template <typename T, bool TA, bool TB, int MI, int NI, int WM, int WN, int KS>
 constexpr int direct_lds() {
@@ -225,57 +288,9 @@ __device__ __forceinline__ void direct_tile(const Params& p, int m0, int n0, lon
         }
     }
 
-    const double* C = p.C ? p.C + bz * p.sC : nullptr;
-    double* D = p.Df ? nullptr : p.D + bz * p.sD;
-    float* Df = p.Df ? p.Df + bz * p.sD : nullptr;
-    auto store = [&](int i, int j, int r, T sum) {
-        const int row = mt + SideA::index(i, MfmaOp<T>::row(lane >> 4, r));
-        const int col = nt + SideB::index(j, lane & 15);
-        if (row >= ms && row < p.M && col >= ns && col < p.N) {
-            double v = p.alpha * (double)sum;
-            if (Df) {
-                Df[(long)row * p.ldd + col] = (float)v;
-            } else {
-                if (C) v += p.beta * C[(long)row * p.ldc + col];
-                D[(long)row * p.ldd + col] = v;
-            }
-        }
-    };
-    if constexpr (KS == 1) {
-        if (out) return;
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NI; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) store(i, j, r, acc[i][j][r]);
-    } else {
-        constexpr int E = MI * NI * 4;               // values of a lane
-        constexpr int PART = WM * WN * E * 64;
-        __syncthreads();
-        T* mine = lds + ks * PART + wmn * E * 64 + lane;
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NI; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) mine[((i * NI + j) * 4 + r) * 64] = acc[i][j][r];
-        __syncthreads();
-        if (!out) {
-            const T* sum0 = lds + wmn * E * 64 + lane;
-            // values ks, ks + KS, ... of this wavefront's tile
-#pragma unroll
-            for (int e0 = 0; e0 < E; e0 += KS) {
-                const int e = e0 + ks;
-                if (E % KS == 0 || e < E) {
-                    T v = sum0[e * 64];
-#pragma unroll
-                    for (int q = 1; q < KS; ++q) v += sum0[q * PART + e * 64];
-                    store(e / (4 * NI), (e / 4) % NI, e % 4, v);
-                }
-            }
-        }
-    }
+    finish_tile<MI, NI, WM, WN, KS>(
+        p, bz, ms, ns, out, acc, [&](int i, int r) { return mt + SideA::index(i, MfmaOp<T>::row(lane >> 4, r)); },
+        [&](int j) { return nt + SideB::index(j, lane & 15); }, lds);
 }
 
 template <typename T, bool TA, bool TB, int MI, int NI, int WM, int WN, int KS, int PD>
@@ -284,6 +299,168 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void direct_kernel(Params p) {
     const int tile = xcd_band_tile(blockIdx.x, p.mt * p.nt);
     direct_tile<T, TA, TB, MI, NI, WM, WN, KS, PD>(p, (tile / p.nt) * 16 * MI * WM, (tile % p.nt) * 16 * NI * WN,
                                                    (long)blockIdx.z, lds);
+}
+
+// ---------------------------------------------------------------------------
+// BF16 operands, FP32 accumulation: the same with slices of 64 (two
+// v_mfma_f32_16x16x32_bf16 steps), lane group g supplying K values 8 g .. 8 g +
+// 7 of a step.  Side-contiguous operands are packed from eight K rows in
+// registers.
+// ---------------------------------------------------------------------------
+typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+constexpr int BKB = 64;
+
+template <bool KC, int S> struct SideB16;
+
+template <int S> struct SideB16<true, S> {
+    static constexpr int LDK = BKB + 8, LDS = 16 * S * LDK;   // in 16-bit words
+    struct Slice { uint4 v[2 * S]; };
+    const uint16_t* ptr[2 * S];
+    uint16_t* lds;
+    int lane;
+    __device__ void init(const uint16_t* src, long ld, int side0, int sideN, int lane_, uint16_t* lds_) {
+        lane = lane_;
+        lds = lds_;
+#pragma unroll
+        for (int n = 0; n < 2 * S; ++n)
+            ptr[n] = src + (long)min(side0 + 8 * n + (lane >> 3), sideN - 1) * ld + (lane & 7) * 8;
+    }
+    __device__ static int index(int t, int pos) { return 16 * t + pos; }
+    __device__ static uint4 pack(const uint16_t (&h)[8]) {
+        return uint4{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16),
+                     (uint32_t)h[4] | ((uint32_t)h[5] << 16), (uint32_t)h[6] | ((uint32_t)h[7] << 16)};
+    }
+    __device__ void load(int k0, Slice& r) const {
+#pragma unroll
+        for (int n = 0; n < 2 * S; ++n) {
+            uint16_t h[8];
+            load_elems<uint16_t, 8>(ptr[n] + k0, h);
+            r.v[n] = pack(h);
+        }
+    }
+    __device__ void load_tail(int k0, int K, Slice& r) const {
+#pragma unroll
+        for (int n = 0; n < 2 * S; ++n) {
+            uint16_t h[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) h[e] = k0 + (lane & 7) * 8 + e < K ? ptr[n][k0 + e] : (uint16_t)0;
+            r.v[n] = pack(h);
+        }
+    }
+    __device__ void values(const Slice& r, bf8_t (&v)[S][2]) const {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int n = 0; n < 2 * S; ++n)
+            *reinterpret_cast<uint4*>(&lds[(8 * n + (lane >> 3)) * LDK + (lane & 7) * 8]) = r.v[n];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                v[i][h] = *reinterpret_cast<const bf8_t*>(&lds[(16 * i + (lane & 15)) * LDK + 32 * h + 8 * (lane >> 4)]);
+    }
+};
+
+template <int S> struct SideB16<false, S> {
+    static constexpr int LDS = 0;
+    struct Slice { uint16_t v[16][S]; };
+    const uint16_t* ptr;
+    long ld;
+    int kg;
+    __device__ void init(const uint16_t* src, long ld_, int side0, int sideN, int lane, uint16_t*) {
+        ld = ld_;
+        kg = lane >> 4;
+        const int l16 = lane & 15;
+        ptr = src + (S == 1 ? min(side0 + l16, sideN - 1) : side0 + S * l16) + (long)(8 * kg) * ld;
+    }
+    __device__ static int index(int t, int pos) { return S * pos + t; }
+    __device__ void load(int k0, Slice& r) const {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) load_elems<uint16_t, S>(ptr + (long)(k0 + 32 * (e >> 3) + (e & 7)) * ld, r.v[e]);
+    }
+    __device__ void load_tail(int k0, int K, Slice& r) const {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int k = k0 + 32 * (e >> 3) + (e & 7);
+#pragma unroll
+            for (int i = 0; i < S; ++i) r.v[e][i] = k + 8 * kg < K ? ptr[(long)k * ld + i] : (uint16_t)0;
+        }
+    }
+    __device__ void values(const Slice& r, bf8_t (&v)[S][2]) const {
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint4 x;
+                uint32_t* w = &x.x;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    w[e] = (uint32_t)r.v[8 * h + 2 * e][i] | ((uint32_t)r.v[8 * h + 2 * e + 1][i] << 16);
+                v[i][h] = *reinterpret_cast<const bf8_t*>(&x);
+            }
+    }
+};
+
+template <bool TA, bool TB, int MI, int NI, int WM, int WN, int KS>
+__global__ __launch_bounds__(64 * WM * WN * KS) void direct_bf16_kernel(Params p) {
+    typedef SideB16<!TA, MI> SideA;
+    typedef SideB16<TB, NI> SideB;
+    constexpr int STAGE = WM * WN * KS * (SideA::LDS + SideB::LDS) / 2, PARTS = KS == 1 ? 1 : KS * WM * WN * MI * NI * 256;
+    __shared__ __attribute__((aligned(16))) float lds[STAGE > PARTS ? STAGE : PARTS];
+    const int tile = xcd_band_tile(blockIdx.x, p.mt * p.nt);
+    const long bz = blockIdx.z;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ks = wave / (WM * WN), wmn = wave % (WM * WN);
+    const int ms = ((tile / p.nt) * WM + wmn / WN) * 16 * MI, ns = ((tile % p.nt) * WN + wmn % WN) * 16 * NI;
+    const bool out = ms >= p.M || ns >= p.N;
+    const int mt = TA && MI > 1 ? min(ms, p.M - 16 * MI) : ms;
+    const int nt = !TB && NI > 1 ? min(ns, p.N - 16 * NI) : ns;
+    f4_t acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) acc[i][j] = f4_t{0, 0, 0, 0};
+    if (!out) {
+        SideA sa;
+        SideB sb;
+        uint16_t* mine = reinterpret_cast<uint16_t*>(lds) + wave * (SideA::LDS + SideB::LDS);
+        sa.init(static_cast<const uint16_t*>(p.A) + bz * p.sA, p.lda, mt, p.M, lane, mine);
+        sb.init(static_cast<const uint16_t*>(p.B) + bz * p.sB, p.ldb, nt, p.N, lane, mine + SideA::LDS);
+        const int nk = (p.K + BKB - 1) / BKB;
+        const int kb = (int)((long)nk * ks / KS), ke = (int)((long)nk * (ks + 1) / KS);
+        typename SideA::Slice a;
+        typename SideB::Slice b;
+        auto load = [&](int kt) {
+            if ((kt + 1) * BKB <= p.K) {
+                sa.load(kt * BKB, a);
+                sb.load(kt * BKB, b);
+            } else {
+                sa.load_tail(kt * BKB, p.K, a);
+                sb.load_tail(kt * BKB, p.K, b);
+            }
+        };
+        if (kb < ke) load(kb);
+        for (int kt = kb; kt < ke; ++kt) {
+            bf8_t x[MI][2], y[NI][2];
+            sa.values(a, x);
+            sb.values(b, y);
+            if (kt + 1 < ke) load(kt + 1);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NI; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i][h], y[j][h], acc[i][j], 0, 0, 0);
+        }
+    }
+    finish_tile<MI, NI, WM, WN, KS>(
+        p, bz, ms, ns, out, acc, [&](int i, int r) { return mt + SideA::index(i, 4 * (lane >> 4) + r); },
+        [&](int j) { return nt + SideB::index(j, lane & 15); }, lds);
 }
 
 }  // namespace

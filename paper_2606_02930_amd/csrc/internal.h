@@ -65,11 +65,8 @@ void gemm_f64(const Gemm& g, hipStream_t s);
 // split) when the output leaves the chip idle and K is long; the parts
 // (K / parts each, a multiple of the K slice) run as one batched launch into
 // `work` (parts M N doubles) and are summed in a fixed order with alpha, beta,
-// C.  splitk_parts: FP32 operands, counted in 128 x 128 output tiles that fill
-// at most half of `slots` concurrent workgroups (FP32 sums no longer than
-// needed).
-int splitk_parts_f64(int M, int N, int K);
-int splitk_parts(int M, int N, int K, int slots);
+// C.
+int splitk_parts(int M, int N, int K);
 void gemm_f64_splitk(const Gemm& g, int parts, double* work, hipStream_t s);
 // The same with FP32 operands (FP32 accumulation within a part, the parts
 // summed in FP64); FP64 output only.

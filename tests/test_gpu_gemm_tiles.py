@@ -4,8 +4,9 @@ tile, K shorter than a slice, and K split over workgroups.  The operands sit in
 wider buffers filled with NaN, so a value read from outside the matrix shows.
 
 Tolerances: FP64 sums of K products differ from numpy's by at most a few
-sqrt(K) eps of the largest entry (K = 8192: 2e-14 x 4); FP32 accumulation by
-sqrt(K) 2^-24 (K = 500: 1.4e-6 x 4).
+sqrt(K) eps of the largest entry (K = 8192: 2e-14 x 4); FP32 accumulation (FP32
+operands, or BF16 operands rounded beforehand) by sqrt(K) 2^-24 for K terms in
+a row (K = 500, or K = 8192 in eight parts or more: below 2e-6 x 3).
 """
 import numpy as np
 import pytest
@@ -19,7 +20,10 @@ F64 = [(1, 1, 1), (16, 16, 16), (17, 31, 15), (33, 16, 511), (15, 33, 513),     
        (700, 300, 500), (500, 417, 33), (6200, 31, 40), (31, 6200, 40),         # 32 wide, sides below 32
        (2100, 1100, 77), (1472, 1537, 128),                                     # 64 wide
        (40, 33, 8192), (17, 5, 8192), (33, 17, 4112)]                           # K over workgroups
-F32 = [(1, 1, 1), (33, 31, 15), (65, 129, 500), (1600, 1500, 50), (1472, 1537, 16)]
+F32 = [(1, 1, 1), (33, 31, 15), (65, 129, 500), (700, 300, 500), (500, 417, 33), (6200, 31, 40), (31, 6200, 40),
+       (2100, 2050, 50), (40, 33, 8192)]
+BF16 = [(1, 1, 1), (17, 33, 63), (33, 17, 64), (65, 129, 500), (700, 300, 500), (500, 417, 65), (6200, 31, 40),
+        (31, 6200, 40), (2050, 2040, 130), (2900, 2950, 33)]
 
 
 @pytest.fixture(scope="module")
@@ -38,8 +42,11 @@ def _run(env, shape, tA, tB, prec, tol):
 
     def operand(rows, cols, pad):
         x = rng.standard_normal((rows, cols))
-        if prec:
+        if prec == 1:
             x = x.astype(np.float32).astype(np.float64)
+        elif prec == 2:
+            m, e = np.frexp(x)
+            x = np.ldexp(np.round(m * 256.0) / 256.0, e)
         buf = np.full((rows, cols + pad), np.nan)
         buf[:, :cols] = x
         return x, torch.from_numpy(buf).cuda(), cols + pad
@@ -66,3 +73,9 @@ def test_fp64_product_at_tile_edges(env, shape, tA, tB):
 @pytest.mark.parametrize("shape", F32)
 def test_fp32_product_at_tile_edges(env, shape, tA, tB):
     _run(env, shape, tA, tB, 1, 6e-6)
+
+
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("shape", BF16)
+def test_bf16_product_at_tile_edges(env, shape, tA, tB):
+    _run(env, shape, tA, tB, 2, 6e-6)
