@@ -62,6 +62,19 @@ __device__ inline Refl reflector(double alpha, double sg) {
     }
     return r;
 }
+// The part of a row entry r that the left reflector takes away (p: the product
+// of its column with the pivot column), and what it leaves.  Rounded the same way
+// wherever they are formed: of a row that is almost finished only rounding is
+// left, and the reflector that is applied has to be the one that is kept.
+__device__ inline double left_part(const Refl& h, double r, double p) {
+#pragma clang fp contract(off)
+    const double sp = h.scale * p;
+    return h.tau * (r + sp);
+}
+__device__ inline double left_rest(double r, double z) {
+#pragma clang fp contract(off)
+    return r - z;
+}
 // The rows past the last reflector of either side.
 __device__ inline void clear_padding(int P, int N, double* VQ, double* VP, long id, long all) {
     for (long i = (long)N * pad16(P) + id; i < (long)pad16(N) * pad16(P); i += all) VQ[i] = 0.0;
@@ -125,10 +138,10 @@ __global__ __launch_bounds__(64 * BS_NW) void bd_step_kernel(BdWork b, int c, bo
         const double* rowc = b.A + (long)c * N;
         const double x = in ? Ai[-1] : 0.0;
         const Refl h = reflector(rowc[c], b.p[c]);
-        auto left = [&](int j) { return h.tau * (rowc[c1 + j] + h.scale * b.p[c1 + j]); };
+        auto left = [&](int j) { return left_part(h, rowc[c1 + j], b.p[c1 + j]); };
         double n2 = 0.0;
         for (int j = t; j < len; j += NT) {
-            const double zj = left(j), r = rowc[c1 + j] - zj;
+            const double zj = left(j), r = left_rest(rowc[c1 + j], zj);
             if (CPL > 0) {
                 z[j] = zj;
                 u[j] = r;
@@ -141,14 +154,14 @@ __global__ __launch_bounds__(64 * BS_NW) void bd_step_kernel(BdWork b, int c, bo
         n2 = sh[0];
 #pragma unroll
         for (int q = 1; q < BS_NW; ++q) n2 += sh[q];
-        const Refl k = reflector(len > 0 ? rowc[c1] - left(0) : 0.0, n2);
+        const Refl k = reflector(len > 0 ? left_rest(rowc[c1], left(0)) : 0.0, n2);
         if (CPL > 0) {
             for (int j = t; j < len; j += NT) u[j] = j == 0 ? 1.0 : u[j] * k.scale;
             __syncthreads();
         }
         auto uat = [&](int j) {
             if (CPL > 0) return u[j];
-            return j == 0 ? 1.0 : (rowc[c1 + j] - left(j)) * k.scale;
+            return j == 0 ? 1.0 : left_rest(rowc[c1 + j], left(j)) * k.scale;
         };
         const int ldq = pad16(P), ldp = pad16(N);
         if ((int)blockIdx.x == blk0) {
@@ -251,21 +264,46 @@ __global__ __launch_bounds__(1024) void bd_sum_kernel(BdWork b, int c, int q0, i
 // the products of all (src, workgroups q0 .. ns - 1) by itself.  That sum is
 // all loads in flight at once; it and the redundant reflectors grow with the
 // rows a workgroup has less, the row work with those it has more: 8
-// wavefronts of 2 rows take 5.3 us at 256 rows and columns and 7.2 at 512
-// (8 x 1: 5.1 and 8.0, 8 x 4: 6.2 and 8.1, 16 x 2: 6.3 and 8.4; step and sum as
+// wavefronts of 2 rows take 5.1 us at 256 rows and columns and 6.7 at 512
+// (8 x 1: 5.4 and 7.2, 8 x 4: 6.1 and 8.1, 16 x 2: 6.9 and 8.7; step and sum as
 // two launches 7.1 and 8.0).
 template <int CPL, int R, int NW>
 __global__ __launch_bounds__(64 * NW) void bd_step1_kernel(BdWork b, int c, const double* __restrict__ src, int q0, int ns,
                                                         double* __restrict__ part) {
-    constexpr int NT = 64 * NW, W = 64 * CPL, PARTS = NT / W;
+    constexpr int NT = 64 * NW, W = 64 * CPL, PARTS = 2 * NT / W;
+    constexpr int U = W / (NW * R * PARTS);   // products of W rows at once
     static_assert(NT % W == 0, "a thread a column");
+    typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));
     __shared__ double buf[NW][W];
     __shared__ double z[W + 1], u[W + 1], sh[CPL];
     const int P = b.P, N = b.N, c1 = c + 1, len = N - c1;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int blk0 = c1 / (NW * R);
     if ((int)blockIdx.x < blk0) return;
+    // the products first: all loads in flight, two columns each, in the order
+    // they are needed (the rows are waited for only after the reflectors)
+    const int jp = 2 * (t % (W / 2));
+    double s0 = 0.0, s1 = 0.0;
+    for (int q = q0 + t / (W / 2); q < ns; q += U * PARTS) {
+        pair_t v[U];
+#pragma unroll
+        for (int e = 0; e < U; ++e) {
+            const double* from = src + (long)(q + e * PARTS) * N + c + jp;
+            const bool row = q + e * PARTS < ns;
+            v[e] = pair_t{0.0, 0.0};
+            if (row && jp < len) v[e] = *reinterpret_cast<const pair_t*>(from);
+            else if (row && jp == len) v[e].x = *from;
+        }
+#pragma unroll
+        for (int e = 0; e < U; ++e) {
+            s0 += v[e].x;
+            s1 += v[e].y;
+        }
+    }
+    // column c + tj of row c
     const double* rowc = b.A + (long)c * N;
+    const int tj = t % W;
+    const double alpha = rowc[c], rj = tj <= len ? rowc[c + tj] : 0.0;
     double* Ai[R];
     bool in[R];
     double a[R][CPL], x[R];
@@ -278,19 +316,8 @@ __global__ __launch_bounds__(64 * NW) void bd_step1_kernel(BdWork b, int c, cons
 #pragma unroll
         for (int q = 0; q < CPL; ++q) a[r][q] = in[r] && lane + 64 * q < len ? Ai[r][lane + 64 * q] : 0.0;
     }
-    // column c + tj of the products and of row c
-    const int tj = t % W;
-    const double alpha = rowc[c], rj = tj <= len ? rowc[c + tj] : 0.0;
-    double s = 0.0;
-    if (tj <= len)
-        for (int q = q0 + t / W; q < ns; q += 16 * PARTS) {
-            double v[16];       // in flight together
-#pragma unroll
-            for (int e = 0; e < 16; ++e) v[e] = q + e * PARTS < ns ? src[(long)(q + e * PARTS) * N + c + tj] : 0.0;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) s += v[e];
-        }
-    buf[t / W][tj] = s;
+    buf[t / (W / 2)][jp] = s0;
+    buf[t / (W / 2)][jp + 1] = s1;
     __syncthreads();
     double pc = buf[0][0], pj = buf[0][tj];
 #pragma unroll
@@ -299,7 +326,7 @@ __global__ __launch_bounds__(64 * NW) void bd_step1_kernel(BdWork b, int c, cons
         pj += buf[q][tj];
     }
     const Refl h = reflector(alpha, pc);
-    const double zj = h.tau * (rj + h.scale * pj), uj = rj - zj;
+    const double zj = left_part(h, rj, pj), uj = left_rest(rj, zj);
     if (t < W) {
         if (t > 0) {
             z[t - 1] = zj;
@@ -414,18 +441,18 @@ struct TailLDS {
     double part[NW][16 * CS], psum[16 * CS], rowc[2][16 * CS], colc[2][4 * NW * RS];
 };
 
-// Columns 16 U0 .. 16 U0 + 15 of it; true when the block is finished.
+// Columns 16 U0 .. 16 U0 + 15 of it.
 template <int NW, int RS, int CS, int U0>
-__device__ __forceinline__ bool bd_tail_columns(const BdWork& b, int c0, double (&a)[RS][CS],
+__device__ __forceinline__ void bd_tail_columns(const BdWork& b, int c0, double (&a)[RS][CS],
                                                 TailLDS<NW, RS, CS>& L) {
     constexpr int RW = 4 * NW, NC = 16 * CS;         // rows and columns a register slot covers in all
     constexpr int s0 = U0 * 16 / RW;                 // row slots before it are finished
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, cx = lane & 15, g = lane >> 4, ry = 4 * w + g;
     const int P = b.P, N = b.N, C = N - c0;
     const int sel = ((g & 1) << 1) | (g >> 1);       // the slot of four whose sum this row of lanes gets
-    for (int cc = 0; cc < 16; ++cc) {
+    const int cols = min(16, C - 16 * U0);
+    for (int cc = 0; cc < cols; ++cc) {
         const int c = 16 * U0 + cc;
-        if (c >= C) return true;
         double* rowc = L.rowc[c & 1];
         double* colc = L.colc[c & 1];
         // column c below row c, to every lane of a row (and to LDS)
@@ -475,8 +502,8 @@ __device__ __forceinline__ bool bd_tail_columns(const BdWork& b, int c0, double 
 #pragma unroll
         for (int u = U0; u < CS; ++u) {
             const int j = cx + 16 * u;
-            const double rc = rowc[j], z = h.tau * (rc + h.scale * L.psum[j]);
-            r[u] = rc - z;
+            const double rc = rowc[j], z = left_part(h, rc, L.psum[j]);
+            r[u] = left_rest(rc, z);
 #pragma unroll
             for (int s = s0; s < RS; ++s) a[s][u] -= x[s] * z;
         }
@@ -490,7 +517,7 @@ __device__ __forceinline__ bool bd_tail_columns(const BdWork& b, int c0, double 
             b.tauq[c0 + c] = h.tau;
             b.d[c0 + c] = h.beta;
         }
-        if (c + 1 >= C) return true;
+        if (c + 1 >= C) return;
         // right reflector from the updated row c
         double n2 = 0.0;
 #pragma unroll
@@ -513,33 +540,35 @@ __device__ __forceinline__ bool bd_tail_columns(const BdWork& b, int c0, double 
 #pragma unroll
             for (int u = U0; u < CS; ++u) a[s][u] -= q * r[u];
         }
-        for (int j = t; j < ldp; j += 64 * NW) {
-            const int l = j - c0;
-            double v = l == c + 1 ? 1.0 : 0.0;
-            if (l > c + 1 && j < N) {
-                const double rc = rowc[l];
-                v = k.scale * (rc - h.tau * (rc + h.scale * L.psum[l]));
-            }
-            b.VP[(long)(c0 + c) * ldp + j] = v;
+        // the row of VP, from the registers of one row of lanes (formed anew it
+        // would have to round alike: next to nothing is left of a row that is
+        // almost finished)
+        double* vp = b.VP + (long)(c0 + c) * ldp;
+        if (ry == c % RW) {
+#pragma unroll
+            for (int u = U0; u < CS; ++u)
+                if (c0 + cx + 16 * u < ldp) vp[c0 + cx + 16 * u] = r[u];
         }
+        for (int j = t; j < c0 + 16 * U0; j += 64 * NW) vp[j] = 0.0;
+        for (int j = c0 + NC + t; j < ldp; j += 64 * NW) vp[j] = 0.0;
         if (t == 0) {
             b.taup[c0 + c] = k.tau;
             b.e[c0 + c] = k.beta;
         }
     }
-    return false;
 }
 
 template <int NW, int RS, int CS, int U0>
-__device__ __forceinline__ void bd_tail_from(const BdWork& b, int c0, double (&a)[RS][CS], TailLDS<NW, RS, CS>& L) {
+__device__ __forceinline__ void bd_tail_from(const BdWork& b, int c0, double (&a)[RS][CS],
+                                             TailLDS<NW, RS, CS>& L) {
     if constexpr (U0 < CS) {
-        if (bd_tail_columns<NW, RS, CS, U0>(b, c0, a, L)) return;
+        bd_tail_columns<NW, RS, CS, U0>(b, c0, a, L);
         bd_tail_from<NW, RS, CS, U0 + 1>(b, c0, a, L);
     }
 }
 
-// c0 = 0: the block is theta itself (tr: its transpose), and the padding rows of
-// the reflectors are cleared here.
+// c0 = 0: the block may be theta itself (tr: its transpose), and the padding
+// rows of the reflectors are cleared here.
 template <int NW, int RS, int CS>
 __global__ __launch_bounds__(64 * NW) void bd_tail_kernel(BdWork b, int c0, const double* __restrict__ theta, int tr) {
     constexpr int RW = 4 * NW;
