@@ -32,7 +32,7 @@ FLAGS = [
     f"-I{CSRC}",
 ]
 
-SOURCES = ["gemm.hip", "vec.hip", "krylov.hip", "svd.hip", "qr.hip", "bidiag.hip", "dcsvd.hip", "engine.cpp", "capi.cpp", "server.cpp", "noalloc.hip", "batch.cpp", "panel.cpp"]
+SOURCES = ["gemm.hip", "vec.hip", "krylov.hip", "heff.hip", "svd.hip", "qr.hip", "bidiag.hip", "dcsvd.hip", "engine.cpp", "capi.cpp", "server.cpp", "noalloc.hip", "batch.cpp", "panel.cpp"]
 
 
 def _compile(src: str, build_dir: str) -> str:

@@ -30,11 +30,13 @@ namespace {
 
 // The products of one batch: for product p (0: the residual's product with
 // x, k + 1: the Arnoldi product with V_k) and each of the two GEMMs, the
-// descriptors; counts[p][gemm] = {problems, tiles}.
+// descriptors; counts[p][gemm] = {problems, tiles}; or, for blocks that take it
+// in one launch, hd[p] and hc[p] = {problems, units}.
 // With FP32 products (lo): for product p >= 1 and each GEMM one more
 // descriptor set, counts_lo[p][gemm] = {problems, tiles}.
 struct BatchLayout {
-    size_t vec_off = 0, tot_off = 0, desc_off = 0, cnt_off = 0, dlo_off = 0, clo_off = 0, bytes = 0;
+    size_t vec_off = 0, tot_off = 0, desc_off = 0, cnt_off = 0, hd_off = 0, hc_off = 0, dlo_off = 0, clo_off = 0,
+           bytes = 0;
     int G = 0, np = 0;
     bool lo = false;
 };
@@ -49,11 +51,16 @@ BatchLayout layout(int G, int np, bool lo) {
     l.tot_off = al(sizeof(BatchVec) * G);
     l.desc_off = al(l.tot_off + sizeof(int) * BT_N);
     l.cnt_off = al(l.desc_off + grouped_desc_bytes() * (size_t)np * 2 * G);
-    l.dlo_off = al(l.cnt_off + sizeof(int) * 2 * (size_t)np * 2);
+    l.hd_off = al(l.cnt_off + sizeof(int) * 2 * (size_t)np * 2);
+    l.hc_off = al(l.hd_off + heff_desc_bytes() * (size_t)np * G);
+    l.dlo_off = al(l.hc_off + sizeof(int) * 2 * (size_t)np);
     l.clo_off = al(l.dlo_off + (lo ? grouped_desc_bytes() * (size_t)np * 2 * G : 0));
     l.bytes = al(l.clo_off + sizeof(int) * 2 * (size_t)np * 2);
     return l;
 }
+
+// Kinds of launches a batch needs: the krylov_class bits, then the forms of H_eff.
+constexpr unsigned BATCH_HEFF_SMALL = 16, BATCH_HEFF_LARGE = 32;
 
 // The launch sequence of the batched solve on stream s; every argument is
 // either fixed for the batch's size and budget or read from `dev`.
@@ -74,7 +81,10 @@ void issue(char* dev, const BatchLayout& l, unsigned classes, int mm, int max_cy
             }
             return;
         }
-        for (int gm = 0; gm < 2; ++gm) {
+        if (classes & BATCH_HEFF_SMALL)
+            heff_grouped(dev + l.hd_off + heff_desc_bytes() * (size_t)p * G,
+                         reinterpret_cast<const int*>(dev + l.hc_off) + 2 * p, s);
+        for (int gm = 0; gm < 2 && (classes & BATCH_HEFF_LARGE); ++gm) {
             const int q = p * 2 + gm;
             const void* desc = dev + l.desc_off + grouped_desc_bytes() * (size_t)q * G;
             const int* cnt = reinterpret_cast<const int*>(dev + l.cnt_off) + 2 * q;
@@ -137,7 +147,8 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
     int* hcnt = reinterpret_cast<int*>(host.data() + lay.cnt_off);
     std::vector<double*> X1(G), X3(G);
     std::vector<float*> Llo(G), Rlo(G), X1lo(G), X3lo(G);
-    int red = 0, ew = 0, stg = 0;
+    int red = 0, ew = 0, stg = 0, stg_lo = 0;
+    std::vector<char> small(G);
     unsigned classes = 0;
     for (int g = 0; g < G; ++g) {
         const LocalOp& op = items[g].op;
@@ -211,13 +222,19 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
         v.red_start = red;
         v.ew_start = ew;
         v.stage_start = stg;
+        v.stage_lo_start = stg_lo;
         red += v.nb;
         ew += (int)((n + BATCH_EW - 1) / BATCH_EW);
-        stg += op.s.Dxl * ((op.s.Dyr + (1 << BATCH_STAGE_LC) - 1) >> BATCH_STAGE_LC);
+        const int units = op.s.Dxl * ((op.s.Dyr + (1 << BATCH_STAGE_LC) - 1) >> BATCH_STAGE_LC);
+        stg_lo += units;
+        small[g] = heff_small_ok(heff_small_of(op.s, op.L, *op.ww, op.R, nullptr, 0.0, 0.0, nullptr, nullptr));
+        if (!small[g]) stg += units;
+        classes |= small[g] ? BATCH_HEFF_SMALL : BATCH_HEFF_LARGE;
     }
     htot[BT_RED] = red;
     htot[BT_EW] = ew;
     htot[BT_STAGE] = stg;
+    htot[BT_STAGE_LO] = stg_lo;
     // grouped products: theta = x (p = 0) or V_(p-1), into V_0 or w
     std::vector<Gemm> g1(G), g2(G);
     for (int g = 0; g < G; ++g) {
@@ -248,24 +265,39 @@ void gmres_batch(ite_ctx* c, const std::vector<BatchItem>& items, int m, int max
         b.ldc = s.Dxr;
         b.ldd = s.Dxr;
     }
+    int* hhc = reinterpret_cast<int*>(host.data() + lay.hc_off);
     for (int p = 0; p < np; ++p) {
+        auto theta = [&](int g) -> const double* {
+            return p == 0 ? items[g].x : hv[g].V + (size_t)(p - 1) * hv[g].n;
+        };
+        auto out = [&](int g) { return p == 0 ? hv[g].V : hv[g].w; };
         for (int gm = 0; gm < 2; ++gm) {
             const int q = p * 2 + gm;
             char* desc = host.data() + lay.desc_off + grouped_desc_bytes() * (size_t)q * G;
-            int tiles = 0;
+            int cnt = 0, tiles = 0;
             for (int g = 0; g < G; ++g) {
+                if (small[g]) continue;
                 Gemm e = gm == 0 ? g1[g] : g2[g];
-                const double* theta = p == 0 ? items[g].x : hv[g].V + (size_t)(p - 1) * hv[g].n;
-                if (gm == 0) e.B = theta;
+                if (gm == 0) e.B = theta(g);
                 else {
-                    e.C = theta;
-                    e.D = p == 0 ? hv[g].V : hv[g].w;
+                    e.C = theta(g);
+                    e.D = out(g);
                 }
-                tiles += grouped_desc_fill(e, false, tiles, desc + grouped_desc_bytes() * g);
+                tiles += grouped_desc_fill(e, false, tiles, desc + grouped_desc_bytes() * cnt++);
             }
-            hcnt[2 * q] = G;
+            hcnt[2 * q] = cnt;
             hcnt[2 * q + 1] = tiles;
         }
+        char* desc = host.data() + lay.hd_off + heff_desc_bytes() * (size_t)p * G;
+        int cnt = 0, units = 0;
+        for (int g = 0; g < G; ++g) {
+            if (!small[g]) continue;
+            const LocalOp& op = items[g].op;
+            const HeffSmall h = heff_small_of(op.s, op.L, *op.ww, op.R, theta(g), op.beta, op.alpha, theta(g), out(g));
+            units += heff_desc_fill(h, units, desc + heff_desc_bytes() * cnt++);
+        }
+        hhc[2 * p] = cnt;
+        hhc[2 * p + 1] = units;
     }
     if (lo) {
         // FP32 products p >= 1: L_lo tlo -> X1lo (FP32), X3lo R_lo^T + (1 - h s) V_(p-1) -> w

@@ -273,6 +273,17 @@ void lo_shadows(ite_ctx* c, const HeffShape& s, Prec prec, const double* L, cons
     *Rlo = r;
 }
 
+HeffSmall heff_small_of(const HeffShape& s, const double* L, const CsrDev& ww, const double* R, const double* theta,
+                        double beta, double alpha, const double* Cadd, double* y) {
+    HeffSmall h;
+    h.L = L; h.theta = theta; h.R = R; h.C = Cadd; h.y = y;
+    h.alpha = alpha; h.beta = beta;
+    h.Dxl = s.Dxl; h.Dyl = s.Dyl; h.Dxr = s.Dxr; h.Dyr = s.Dyr;
+    h.w0 = s.w0; h.w2 = s.w2; h.dd = s.d1 * s.d2;
+    h.rowptr = ww.rowptr; h.col = ww.col; h.val = ww.val; h.nnz = ww.nnz;
+    return h;
+}
+
 void heff_apply(ite_ctx* c, const HeffShape& s, const double* L, const CsrDev& ww, const double* R,
                 const double* theta, double beta, double alpha, const double* Cadd, double* y, Prec prec,
                 const void* Llo, const void* Rlo) {
@@ -301,6 +312,22 @@ void heff_apply(ite_ctx* c, const HeffShape& s, const double* L, const CsrDev& w
         stage(c, ww, st);
         gemm_lo(c, prec, false, true, s.Dxl * s.d1 * s.d2, s.Dxr, s.w2 * s.Dyr, beta, x3lo, (long)s.w2 * s.Dyr,
                 Rlo, (long)s.w2 * s.Dyr, alpha, Cadd, s.Dxr, y, s.Dxr);
+        return;
+    }
+    const HeffSmall hs = heff_small_of(s, L, ww, R, theta, beta, alpha, Cadd, y);
+    const double* y1 = y + (size_t)s.Dxl * s.d1 * s.d2 * s.Dxr;
+    const double* t1 = theta + (size_t)s.Dyl * s.d1 * s.d2 * s.Dyr;
+    if (heff_small_ok(hs) && (y1 <= theta || t1 <= y)) {
+        CtxProbe pr(c);
+        if (c->prof_on) pr.begin(PK_GEMM, c->stream);
+        heff_small(hs, c->stream);
+        if (c->prof_on) {
+            pr.end(PK_GEMM, c->stream);
+            const double m1 = (double)s.Dxl * s.w0, n1 = (double)s.d1 * s.d2 * s.Dyr, k1 = s.Dyl;
+            const double m3 = (double)s.Dxl * s.d1 * s.d2, n3 = s.Dxr, k3 = (double)s.w2 * s.Dyr;
+            pr.work(PK_GEMM, 2.0 * (m1 * n1 * k1 + m3 * n3 * k3),
+                    8.0 * (m1 * k1 + k1 * n1 + n3 * k3 + (Cadd ? 2.0 : 1.0) * m3 * n3));
+        }
         return;
     }
     double* X1 = slot_t<double>(c, SL_X1, nx);

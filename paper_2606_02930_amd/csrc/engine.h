@@ -156,6 +156,8 @@ struct HeffShape {
 // buffers, valid until the next call), as a local solve makes them once.
 void lo_shadows(ite_ctx* c, const HeffShape& s, Prec prec, const double* L, const double* R, const void** Llo,
                 const void** Rlo);
+HeffSmall heff_small_of(const HeffShape& s, const double* L, const CsrDev& ww, const double* R, const double* theta,
+                        double beta, double alpha, const double* Cadd, double* y);
 void heff_apply(ite_ctx* c, const HeffShape& s, const double* L, const CsrDev& ww, const double* R,
                 const double* theta, double beta, double alpha, const double* Cadd, double* y,
                 Prec prec, const void* Llo = nullptr, const void* Rlo = nullptr);

@@ -188,6 +188,25 @@ void nonfinite_any(const double* x, size_t n, int* flag, hipStream_t s);
 // out[j][i] = in[i][j]  (rows x cols -> cols x rows)
 void transpose(const double* in, int rows, int cols, double* out, hipStream_t s);
 
+// H_eff of a small block in one launch (heff.hip): y = beta H theta + alpha C (C
+// may be null or y itself, theta may not overlap y), WW in CSR form.
+struct HeffSmall {
+    const double *L = nullptr, *theta = nullptr, *R = nullptr, *C = nullptr;
+    double* y = nullptr;
+    double alpha = 0.0, beta = 1.0;
+    int Dxl = 0, Dyl = 0, Dxr = 0, Dyr = 0, w0 = 0, w2 = 0, dd = 0;   // dd = d1 d2
+    const int* rowptr = nullptr; const int* col = nullptr; const double* val = nullptr;
+    int nnz = -1;
+};
+constexpr int HEFF_STEPS = 32;
+bool heff_small_ok(const HeffSmall& h);        // by the shape alone
+void heff_small(const HeffSmall& h, hipStream_t s);
+// The same for many problems: descriptors in device memory, count = {problems,
+// their units}; heff_desc_fill returns the problem's units.
+size_t heff_desc_bytes();
+int heff_desc_fill(const HeffSmall& h, int start, void* out);
+void heff_grouped(const void* desc, const int* count, hipStream_t s);
+
 // ---------------------------------------------------------------------------
 // Batched fixed-budget GMRES: the local solves of several independent states
 // advanced together, one launch per operation for all of them (persistent
@@ -214,10 +233,10 @@ struct BatchVec {
     // from FP32 X1 to FP32 X3
     float* tlo;
     Stage st_lo;
-    int red_start, ew_start, stage_start;   // first unit of this problem in each unit range
+    int red_start, ew_start, stage_start, stage_lo_start;   // first unit of this problem in each unit range
 };
-// Unit totals of a batch (device ints): reductions, elementwise, stage.
-enum { BT_RED = 0, BT_EW = 1, BT_STAGE = 2, BT_N = 4 };
+// Unit totals of a batch (device ints): reductions, elementwise, stage, FP32 stage.
+enum { BT_RED = 0, BT_EW = 1, BT_STAGE = 2, BT_STAGE_LO = 3, BT_N = 4 };
 constexpr int BATCH_GRID = 1024;      // workgroups of every batched vector launch
 constexpr int BGRAPH_CACHE = 12;      // captured batched solves kept per context
 constexpr long BATCH_EW = 4096;       // elements per elementwise unit
@@ -231,7 +250,8 @@ void batch_gram_schmidt(const BatchVec* d, int G, const int* tot, unsigned class
 void batch_vec(const BatchVec* d, int G, const int* tot, int op, int k, hipStream_t s);
 // The cycle's least-squares solve of every problem.
 void batch_hess(const BatchVec* d, int G, int mm, bool r_product, bool last_cycle, hipStream_t s);
-// The MPO stage of every problem (inputs per column at most 128).
+// The MPO stage of every problem that has stage units (inputs per column at
+// most 128).
 void batch_stage(const BatchVec* d, int G, const int* tot, hipStream_t s);
 // The FP32 stage st_lo of every problem (FP32 in, FP32 out).
 void batch_stage_lo(const BatchVec* d, int G, const int* tot, hipStream_t s);

@@ -718,12 +718,12 @@ template <bool LO>
 __global__ __launch_bounds__(STAGE_NT) void batch_stage_kernel(const BatchVec* __restrict__ d, int G,
                                                                const int* __restrict__ tot) {
     __shared__ double lds[(BATCH_STAGE_I << BATCH_STAGE_LC) + BATCH_STAGE_CSR / 8];
-    const int total = tot[BT_STAGE];
+    const int total = tot[LO ? BT_STAGE_LO : BT_STAGE];
     for (int u = blockIdx.x; u < total; u += gridDim.x) {
-        const int g = unit_problem(u, G, [&](int q) { return d[q].stage_start; });
+        const int g = unit_problem(u, G, [&](int q) { return LO ? d[q].stage_lo_start : d[q].stage_start; });
         const Stage& st = LO ? d[g].st_lo : d[g].st;
         const int nc = (st.C + (1 << BATCH_STAGE_LC) - 1) >> BATCH_STAGE_LC;
-        const int lu = u - d[g].stage_start;
+        const int lu = u - (LO ? d[g].stage_lo_start : d[g].stage_start);
         const int cb = (lu % nc) << BATCH_STAGE_LC;
         if (LO) stage_tile<1, 1, float>(st, lu / nc, cb, BATCH_STAGE_LC, reinterpret_cast<float*>(lds));
         else stage_tile<0, 1, double>(st, lu / nc, cb, BATCH_STAGE_LC, lds);
