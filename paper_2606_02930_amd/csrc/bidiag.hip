@@ -111,12 +111,13 @@ __global__ __launch_bounds__(256) void bd_load_kernel(const double* __restrict__
 // step, only the products for the first column (c = -1).  CPL = 0: rows of any
 // length, in memory, with z and u formed again where they are used.
 constexpr int BS_NW = 8;            // rows (wavefronts) a workgroup
-constexpr int BS_CH = 512;          // columns of a row of products in LDS
+// columns of a row of products in LDS at a time
+template <int CPL> constexpr int BS_CH = CPL == 0 ? 512 : CPL > 16 ? 1024 : 64 * CPL;
 template <int CPL>
 __global__ __launch_bounds__(64 * BS_NW) void bd_step_kernel(BdWork b, int c, bool start) {
-    constexpr int NT = 64 * BS_NW;
+    constexpr int NT = 64 * BS_NW, CH = BS_CH<CPL>;
     extern __shared__ double zu[];                  // z and u, the columns from c + 1 on
-    __shared__ double buf[BS_NW][BS_CH];
+    __shared__ double buf[BS_NW][CH];
     __shared__ double sh[BS_NW];
     const int P = b.P, N = b.N, c1 = c + 1, len = N - c1;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
@@ -128,6 +129,29 @@ __global__ __launch_bounds__(64 * BS_NW) void bd_step_kernel(BdWork b, int c, bo
     double* u = zu + len;
     double* Ai = b.A + (long)i * N + c1;
     constexpr int CR = CPL > 0 ? CPL : 1;
+    // row c and the products are needed first, so they are asked for first; the
+    // rows arrive while the reflectors are formed
+    constexpr int CT = CPL > 8 ? CPL / 8 : 1;      // columns of row c a thread
+    const double* rowc = b.A + (long)c * N;
+    double rc[CT], pc[CT], alpha = 0.0, sg = 0.0;
+    if (CPL > 0 && !start) {
+#pragma unroll
+        for (int q = 0; q < CT; ++q) {
+            const int j = t + NT * q;
+            rc[q] = j < len ? rowc[c1 + j] : 0.0;
+            pc[q] = j < len ? b.p[c1 + j] : 0.0;
+        }
+    }
+    double first = 0.0, pfirst = 0.0;
+    if (!start) {
+        alpha = rowc[c];
+        sg = b.p[c];
+        if (len > 0) {
+            first = rowc[c1];
+            pfirst = b.p[c1];
+        }
+    }
+    const double x = in && !start ? Ai[-1] : 0.0;
     double a[CR];
     if (CPL > 0) {
 #pragma unroll
@@ -135,18 +159,25 @@ __global__ __launch_bounds__(64 * BS_NW) void bd_step_kernel(BdWork b, int c, bo
     }
     double xn;       // the row's entry in the next step's column
     if (!start) {
-        const double* rowc = b.A + (long)c * N;
-        const double x = in ? Ai[-1] : 0.0;
-        const Refl h = reflector(rowc[c], b.p[c]);
+        const Refl h = reflector(alpha, sg);
         auto left = [&](int j) { return left_part(h, rowc[c1 + j], b.p[c1 + j]); };
         double n2 = 0.0;
-        for (int j = t; j < len; j += NT) {
-            const double zj = left(j), r = left_rest(rowc[c1 + j], zj);
-            if (CPL > 0) {
-                z[j] = zj;
-                u[j] = r;
+        if (CPL > 0) {
+#pragma unroll
+            for (int q = 0; q < CT; ++q) {
+                const int j = t + NT * q;
+                if (j < len) {
+                    const double zj = left_part(h, rc[q], pc[q]), r = left_rest(rc[q], zj);
+                    z[j] = zj;
+                    u[j] = r;
+                    if (j > 0) n2 += r * r;
+                }
             }
-            if (j > 0) n2 += r * r;
+        } else {
+            for (int j = 1 + t; j < len; j += NT) {
+                const double r = left_rest(rowc[c1 + j], left(j));
+                n2 += r * r;
+            }
         }
         n2 = wave_sum(n2);
         if (lane == 0) sh[w] = n2;
@@ -154,13 +185,9 @@ __global__ __launch_bounds__(64 * BS_NW) void bd_step_kernel(BdWork b, int c, bo
         n2 = sh[0];
 #pragma unroll
         for (int q = 1; q < BS_NW; ++q) n2 += sh[q];
-        const Refl k = reflector(len > 0 ? left_rest(rowc[c1], left(0)) : 0.0, n2);
-        if (CPL > 0) {
-            for (int j = t; j < len; j += NT) u[j] = j == 0 ? 1.0 : u[j] * k.scale;
-            __syncthreads();
-        }
+        const Refl k = reflector(len > 0 ? left_rest(first, left_part(h, first, pfirst)) : 0.0, n2);
         auto uat = [&](int j) {
-            if (CPL > 0) return u[j];
+            if (CPL > 0) return j == 0 ? 1.0 : u[j] * k.scale;
             return j == 0 ? 1.0 : left_rest(rowc[c1 + j], left(j)) * k.scale;
         };
         const int ldq = pad16(P), ldp = pad16(N);
@@ -184,34 +211,35 @@ __global__ __launch_bounds__(64 * BS_NW) void bd_step_kernel(BdWork b, int c, bo
         if (len == 0) return;
         double d = 0.0;
         if (CPL > 0) {
+            double ur[CR];
 #pragma unroll
             for (int q = 0; q < CR; ++q) {
                 const int j = lane + 64 * q;
+                ur[q] = 0.0;
                 if (j < len) {
+                    ur[q] = uat(j);
                     a[q] -= v * z[j];
-                    d += a[q] * u[j];
+                    d += a[q] * ur[q];
                 }
             }
             d = k.tau * wave_sum(d);
 #pragma unroll
             for (int q = 0; q < CR; ++q) {
                 const int j = lane + 64 * q;
-                if (j < len) {
-                    a[q] -= d * u[j];
-                    if (in) Ai[j] = a[q];
-                }
+                a[q] -= d * ur[q];
+                if (in && j < len) Ai[j] = a[q];
             }
             xn = lane_value(a[0], 0);
         } else {
             for (int j = lane; in && j < len; j += 64) d += (Ai[j] - v * left(j)) * uat(j);
             d = k.tau * wave_sum(d);
-            double first = 0.0;
+            double head = 0.0;
             for (int j = lane; in && j < len; j += 64) {
                 const double r = Ai[j] - v * left(j) - d * uat(j);
                 Ai[j] = r;
-                if (j == 0) first = r;
+                if (j == 0) head = r;
             }
-            xn = lane_value(first, 0);
+            xn = lane_value(head, 0);
         }
     } else {
         xn = in ? Ai[0] : 0.0;
@@ -219,19 +247,19 @@ __global__ __launch_bounds__(64 * BS_NW) void bd_step_kernel(BdWork b, int c, bo
     // the next step's column products: rows below its own row
     if (i == c1 || !in) xn = 0.0;
     double* part = b.part + (long)blockIdx.x * N + c1;
-    for (int c0 = 0; c0 < len; c0 += BS_CH) {
+    for (int c0 = 0; c0 < len; c0 += CH) {
         if (c0 > 0) __syncthreads();
         if (CPL > 0) {
 #pragma unroll
             for (int q = 0; q < CR; ++q) {
                 const int j = lane + 64 * q - c0;
-                if (j >= 0 && j < BS_CH) buf[w][j] = xn * a[q];
+                if (j >= 0 && j < CH) buf[w][j] = xn * a[q];
             }
         } else {
-            for (int j = lane; j < BS_CH; j += 64) buf[w][j] = (in && c0 + j < len) ? xn * Ai[c0 + j] : 0.0;
+            for (int j = lane; j < CH; j += 64) buf[w][j] = (in && c0 + j < len) ? xn * Ai[c0 + j] : 0.0;
         }
         __syncthreads();
-        for (int j = t; j < BS_CH && c0 + j < len; j += NT) {
+        for (int j = t; j < CH && c0 + j < len; j += NT) {
             double s = buf[0][j];
 #pragma unroll
             for (int q = 1; q < BS_NW; ++q) s += buf[q][j];
