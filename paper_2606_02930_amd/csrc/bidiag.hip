@@ -11,7 +11,7 @@
 // one launch from 512 rows and columns on (bd_step1_kernel); the rest is
 // done by one workgroup in its registers (bd_tail_kernel).  Bound by the
 // latency of a step: 5 to 7 us at 200 to 512 columns,
-// 18 us at 2048 (38 MB read and written by it on average there), 1.3 to 1.9 us
+// 14 us at 2048 (38 MB read and written by it on average there), 1.2 to 2 us
 // inside one workgroup.  Two launches a step that each read and wrote the
 // block (columns, then rows) took 9 us and 31 us.
 //
@@ -102,47 +102,35 @@ __global__ __launch_bounds__(256) void bd_load_kernel(const double* __restrict__
     }
 }
 
-// Step c in one pass over the rows below it, a wavefront a row (in registers,
-// 64 CPL columns at most).  p[j] = sum_(i > c) A[i][c] A[i][j] (j >= c) is all
-// that is needed from the other rows: with it every workgroup has the left
-// reflector and the updated row c, and from that the right reflector.  Each row
-// takes both reflectors, and its share of the next step's p follows while it
-// is in registers: part[workgroup][j], summed by bd_sum_kernel.  start: no
-// step, only the products for the first column (c = -1).  CPL = 0: rows of any
-// length, in memory, with z and u formed again where they are used.
-constexpr int BS_NW = 8;            // rows (wavefronts) a workgroup
-// columns of a row of products in LDS at a time
-template <int CPL> constexpr int BS_CH = CPL == 0 ? 512 : CPL > 16 ? 1024 : 64 * CPL;
-template <int CPL>
-__global__ __launch_bounds__(64 * BS_NW) void bd_step_kernel(BdWork b, int c, bool start) {
-    constexpr int NT = 64 * BS_NW, CH = BS_CH<CPL>;
-    extern __shared__ double zu[];                  // z and u, the columns from c + 1 on
-    __shared__ double buf[BS_NW][CH];
-    __shared__ double sh[BS_NW];
+// Step c in one pass over the rows below it.  p[j] = sum_(i > c) A[i][c] A[i][j]
+// (j >= c) is all that is needed from the other rows: with it every workgroup has
+// the left reflector and the updated row c, and from that the right reflector.
+// Each row takes both reflectors, and its share of the next step's p follows
+// while it is in registers: part[workgroup][j], summed by bd_sum_kernel.  start:
+// no step, only the products for the first column (c = -1).
+//
+// A thread has Q columns of all the workgroup's rows, so its parts of row c, of
+// the reflectors and of the products stay in its registers, and what crosses
+// wavefronts is a norm and a number a row.  (With a wavefront a row the
+// reflectors were read from LDS by every row and the products summed through it:
+// 13.2 us a step over 2048 to 1024 columns, now 11.4; 7.4 over 1024 to 512, now
+// 7.2.  16 rows a workgroup leave half the compute units idle: 16.1 and 11.9.)
+constexpr int BS_NW = 8;            // rows and wavefronts of a workgroup
+constexpr int BS_NT = 64 * BS_NW;
+template <int Q>
+__global__ __launch_bounds__(BS_NT) void bd_step_kernel(BdWork b, int c, bool start) {
+    constexpr int R = BS_NW;
+    __shared__ double sh[BS_NW], dots[BS_NW][R];
     const int P = b.P, N = b.N, c1 = c + 1, len = N - c1;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     // a row has the same workgroup number in every step; the first ones finish
-    const int blk0 = c1 / BS_NW, i = blockIdx.x * BS_NW + w;
+    const int blk0 = c1 / R, i0 = blockIdx.x * R;
     if ((int)blockIdx.x < blk0) return;
-    const bool in = i >= c1 && i < P;
-    double* z = zu;
-    double* u = zu + len;
-    double* Ai = b.A + (long)i * N + c1;
-    constexpr int CR = CPL > 0 ? CPL : 1;
     // row c and the products are needed first, so they are asked for first; the
     // rows arrive while the reflectors are formed
-    constexpr int CT = CPL > 8 ? CPL / 8 : 1;      // columns of row c a thread
-    const double* rowc = b.A + (long)c * N;
-    double rc[CT], pc[CT], alpha = 0.0, sg = 0.0;
-    if (CPL > 0 && !start) {
-#pragma unroll
-        for (int q = 0; q < CT; ++q) {
-            const int j = t + NT * q;
-            rc[q] = j < len ? rowc[c1 + j] : 0.0;
-            pc[q] = j < len ? b.p[c1 + j] : 0.0;
-        }
-    }
-    double first = 0.0, pfirst = 0.0;
+    const double* rowc = b.A + (long)max(c, 0) * N;
+    double rc[Q], pc[Q], a[R][Q], x[R], xn[R];
+    double alpha = 0.0, sg = 0.0, first = 0.0, pfirst = 0.0;
     if (!start) {
         alpha = rowc[c];
         sg = b.p[c];
@@ -150,34 +138,34 @@ __global__ __launch_bounds__(64 * BS_NW) void bd_step_kernel(BdWork b, int c, bo
             first = rowc[c1];
             pfirst = b.p[c1];
         }
-    }
-    const double x = in && !start ? Ai[-1] : 0.0;
-    double a[CR];
-    if (CPL > 0) {
 #pragma unroll
-        for (int q = 0; q < CR; ++q) a[q] = (in && lane + 64 * q < len) ? Ai[lane + 64 * q] : 0.0;
+        for (int q = 0; q < Q; ++q) {
+            const int j = t + BS_NT * q;
+            rc[q] = j < len ? rowc[c1 + j] : 0.0;
+            pc[q] = j < len ? b.p[c1 + j] : 0.0;
+        }
     }
-    double xn;       // the row's entry in the next step's column
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = i0 + r;
+        const bool in = i >= c1 && i < P;
+        const double* Ai = b.A + (long)i * N;
+        x[r] = in && !start ? Ai[c] : 0.0;
+        xn[r] = in && len > 0 ? Ai[c1] : 0.0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int j = t + BS_NT * q;
+            a[r][q] = in && j < len ? Ai[c1 + j] : 0.0;
+        }
+    }
     if (!start) {
         const Refl h = reflector(alpha, sg);
-        auto left = [&](int j) { return left_part(h, rowc[c1 + j], b.p[c1 + j]); };
-        double n2 = 0.0;
-        if (CPL > 0) {
+        double z[Q], u[Q], n2 = 0.0;
 #pragma unroll
-            for (int q = 0; q < CT; ++q) {
-                const int j = t + NT * q;
-                if (j < len) {
-                    const double zj = left_part(h, rc[q], pc[q]), r = left_rest(rc[q], zj);
-                    z[j] = zj;
-                    u[j] = r;
-                    if (j > 0) n2 += r * r;
-                }
-            }
-        } else {
-            for (int j = 1 + t; j < len; j += NT) {
-                const double r = left_rest(rowc[c1 + j], left(j));
-                n2 += r * r;
-            }
+        for (int q = 0; q < Q; ++q) {
+            z[q] = left_part(h, rc[q], pc[q]);
+            u[q] = left_rest(rc[q], z[q]);
+            if (t + BS_NT * q > 0) n2 += u[q] * u[q];
         }
         n2 = wave_sum(n2);
         if (lane == 0) sh[w] = n2;
@@ -185,11 +173,115 @@ __global__ __launch_bounds__(64 * BS_NW) void bd_step_kernel(BdWork b, int c, bo
         n2 = sh[0];
 #pragma unroll
         for (int q = 1; q < BS_NW; ++q) n2 += sh[q];
-        const Refl k = reflector(len > 0 ? left_rest(first, left_part(h, first, pfirst)) : 0.0, n2);
-        auto uat = [&](int j) {
-            if (CPL > 0) return j == 0 ? 1.0 : u[j] * k.scale;
-            return j == 0 ? 1.0 : left_rest(rowc[c1 + j], left(j)) * k.scale;
-        };
+        const double z0 = left_part(h, first, pfirst);
+        const Refl k = reflector(len > 0 ? left_rest(first, z0) : 0.0, n2);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) u[q] = t + BS_NT * q == 0 ? 1.0 : u[q] * k.scale;
+        const int ldq = pad16(P), ldp = pad16(N);
+        if ((int)blockIdx.x == blk0) {
+            double* vq = b.VQ + (long)c * ldq;
+            for (int q = t; q <= c; q += BS_NT) vq[q] = q == c ? 1.0 : 0.0;
+            for (int q = P + t; q < ldq; q += BS_NT) vq[q] = 0.0;
+            if (len > 0) {
+                double* vp = b.VP + (long)c * ldp;
+                for (int q = t; q < c1; q += BS_NT) vp[q] = 0.0;
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+                    if (c1 + t + BS_NT * q < N) vp[c1 + t + BS_NT * q] = u[q];
+                for (int q = N + t; q < ldp; q += BS_NT) vp[q] = 0.0;
+            }
+            if (t == 0) {
+                b.tauq[c] = h.tau;
+                b.d[c] = h.beta;
+                b.taup[c] = k.tau;
+                b.e[c] = k.beta;
+            }
+        }
+        double v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = x[r] * h.scale;
+        if (t < R && i0 + t >= c1 && i0 + t < P) {
+            double mine = v[0];
+#pragma unroll
+            for (int r = 1; r < R; ++r) mine = t == r ? v[r] : mine;
+            b.VQ[(long)c * ldq + i0 + t] = mine;
+        }
+        if (len == 0) return;
+        double d[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            d[r] = 0.0;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                a[r][q] -= v[r] * z[q];
+                d[r] += a[r][q] * u[q];
+            }
+        }
+        const double mine = sum8(d, lane);
+        if ((lane & 7) == 0) dots[w][sum8_index(lane)] = mine;
+        __syncthreads();
+        // lane 8 s + r: wavefront s's part of row r
+        double dr = dots[lane >> 3][lane & 7];
+        dr += dpp_move<0x128, 0xf>(dr);                 // row_ror:8
+        dr = swap_add16(dr, dr);
+        dr = k.tau * swap_add32(dr, dr);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const double e = lane_value(dr, r);
+            const int i = i0 + r;
+            const bool in = i >= c1 && i < P;
+            double* Ai = b.A + (long)i * N + c1;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                a[r][q] -= e * u[q];
+                if (in && t + BS_NT * q < len) Ai[t + BS_NT * q] = a[r][q];
+            }
+            xn[r] = xn[r] - v[r] * z0 - e;
+        }
+    }
+    // the next step's column products: rows below its own row
+    double* part = b.part + (long)blockIdx.x * N + c1;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        double s = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) s += (i0 + r > c1 && i0 + r < P ? xn[r] : 0.0) * a[r][q];
+        if (t + BS_NT * q < len) part[t + BS_NT * q] = s;
+    }
+}
+
+// The same for rows of any length, in memory, with z and u formed again where they
+// are used; a wavefront a row.
+constexpr int BS_CH = 512;          // columns of a row of products in LDS
+__global__ __launch_bounds__(BS_NT) void bd_step_long_kernel(BdWork b, int c, bool start) {
+    constexpr int NT = BS_NT;
+    __shared__ double buf[BS_NW][BS_CH];
+    __shared__ double sh[BS_NW];
+    const int P = b.P, N = b.N, c1 = c + 1, len = N - c1;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int blk0 = c1 / BS_NW, i = blockIdx.x * BS_NW + w;
+    if ((int)blockIdx.x < blk0) return;
+    const bool in = i >= c1 && i < P;
+    double* Ai = b.A + (long)i * N + c1;
+    const double* rowc = b.A + (long)max(c, 0) * N;
+    double xn;       // the row's entry in the next step's column
+    if (!start) {
+        const double x = in ? Ai[-1] : 0.0;
+        const Refl h = reflector(rowc[c], b.p[c]);
+        auto left = [&](int j) { return left_part(h, rowc[c1 + j], b.p[c1 + j]); };
+        double n2 = 0.0;
+        for (int j = 1 + t; j < len; j += NT) {
+            const double r = left_rest(rowc[c1 + j], left(j));
+            n2 += r * r;
+        }
+        n2 = wave_sum(n2);
+        if (lane == 0) sh[w] = n2;
+        __syncthreads();
+        n2 = sh[0];
+#pragma unroll
+        for (int q = 1; q < BS_NW; ++q) n2 += sh[q];
+        const Refl k = reflector(len > 0 ? left_rest(rowc[c1], left(0)) : 0.0, n2);
+        auto uat = [&](int j) { return j == 0 ? 1.0 : left_rest(rowc[c1 + j], left(j)) * k.scale; };
         const int ldq = pad16(P), ldp = pad16(N);
         if ((int)blockIdx.x == blk0) {
             double* vq = b.VQ + (long)c * ldq;
@@ -210,56 +302,26 @@ __global__ __launch_bounds__(64 * BS_NW) void bd_step_kernel(BdWork b, int c, bo
         if (in && lane == 0) b.VQ[(long)c * ldq + i] = v;
         if (len == 0) return;
         double d = 0.0;
-        if (CPL > 0) {
-            double ur[CR];
-#pragma unroll
-            for (int q = 0; q < CR; ++q) {
-                const int j = lane + 64 * q;
-                ur[q] = 0.0;
-                if (j < len) {
-                    ur[q] = uat(j);
-                    a[q] -= v * z[j];
-                    d += a[q] * ur[q];
-                }
-            }
-            d = k.tau * wave_sum(d);
-#pragma unroll
-            for (int q = 0; q < CR; ++q) {
-                const int j = lane + 64 * q;
-                a[q] -= d * ur[q];
-                if (in && j < len) Ai[j] = a[q];
-            }
-            xn = lane_value(a[0], 0);
-        } else {
-            for (int j = lane; in && j < len; j += 64) d += (Ai[j] - v * left(j)) * uat(j);
-            d = k.tau * wave_sum(d);
-            double head = 0.0;
-            for (int j = lane; in && j < len; j += 64) {
-                const double r = Ai[j] - v * left(j) - d * uat(j);
-                Ai[j] = r;
-                if (j == 0) head = r;
-            }
-            xn = lane_value(head, 0);
+        for (int j = lane; in && j < len; j += 64) d += (Ai[j] - v * left(j)) * uat(j);
+        d = k.tau * wave_sum(d);
+        double head = 0.0;
+        for (int j = lane; in && j < len; j += 64) {
+            const double r = Ai[j] - v * left(j) - d * uat(j);
+            Ai[j] = r;
+            if (j == 0) head = r;
         }
+        xn = lane_value(head, 0);
     } else {
         xn = in ? Ai[0] : 0.0;
     }
     // the next step's column products: rows below its own row
     if (i == c1 || !in) xn = 0.0;
     double* part = b.part + (long)blockIdx.x * N + c1;
-    for (int c0 = 0; c0 < len; c0 += CH) {
+    for (int c0 = 0; c0 < len; c0 += BS_CH) {
         if (c0 > 0) __syncthreads();
-        if (CPL > 0) {
-#pragma unroll
-            for (int q = 0; q < CR; ++q) {
-                const int j = lane + 64 * q - c0;
-                if (j >= 0 && j < CH) buf[w][j] = xn * a[q];
-            }
-        } else {
-            for (int j = lane; j < CH; j += 64) buf[w][j] = (in && c0 + j < len) ? xn * Ai[c0 + j] : 0.0;
-        }
+        for (int j = lane; j < BS_CH; j += 64) buf[w][j] = (in && c0 + j < len) ? xn * Ai[c0 + j] : 0.0;
         __syncthreads();
-        for (int j = t; j < CH && c0 + j < len; j += NT) {
+        for (int j = t; j < BS_CH && c0 + j < len; j += NT) {
             double s = buf[0][j];
 #pragma unroll
             for (int q = 1; q < BS_NW; ++q) s += buf[q][j];
@@ -432,18 +494,6 @@ __global__ __launch_bounds__(64 * NW) void bd_step1_kernel(BdWork b, int c, cons
 // The sum over the four 16-lane rows of the wavefront for four values at a
 // time, scattered: row g ends with the sum of v[{0, 2, 1, 3}[g]] (the swaps
 // pair the halves and then the rows of two values, so an addition serves both).
-__device__ inline double swap_add32(double a, double b) {
-    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
-    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
-    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
-}
-__device__ inline double swap_add16(double a, double b) {
-    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
-    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
-    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
-}
 __device__ inline double rows_sum4(double v0, double v1, double v2, double v3) {
     return swap_add16(swap_add32(v0, v1), swap_add32(v2, v3));
 }
@@ -896,12 +946,11 @@ void bidiagonalise(const BdWork& w, const double* theta, bool tr, hipStream_t s,
     auto step = [&](int c, bool start) {
         const bool timed = probe && probe->begin(PK_BIDIAG, s);
         const int len = N - c - 1, g = (P + BS_NW - 1) / BS_NW;
-        const size_t lds = start || len > 2048 ? 0 : 2 * sizeof(double) * (size_t)std::max(len, 1);
-        if (len <= 256) hipLaunchKernelGGL((bd_step_kernel<4>), dim3(g), dim3(64 * BS_NW), lds, s, w, c, start);
-        else if (len <= 512) hipLaunchKernelGGL((bd_step_kernel<8>), dim3(g), dim3(64 * BS_NW), lds, s, w, c, start);
-        else if (len <= 1024) hipLaunchKernelGGL((bd_step_kernel<16>), dim3(g), dim3(64 * BS_NW), lds, s, w, c, start);
-        else if (len <= 2048) hipLaunchKernelGGL((bd_step_kernel<32>), dim3(g), dim3(64 * BS_NW), lds, s, w, c, start);
-        else hipLaunchKernelGGL((bd_step_kernel<0>), dim3(g), dim3(64 * BS_NW), lds, s, w, c, start);
+        const dim3 grid(g), block(BS_NT);
+        if (len <= 512) hipLaunchKernelGGL((bd_step_kernel<1>), grid, block, 0, s, w, c, start);
+        else if (len <= 1024) hipLaunchKernelGGL((bd_step_kernel<2>), grid, block, 0, s, w, c, start);
+        else if (len <= 2048) hipLaunchKernelGGL((bd_step_kernel<4>), grid, block, 0, s, w, c, start);
+        else hipLaunchKernelGGL(bd_step_long_kernel, grid, block, 0, s, w, c, start);
         if (len > 0) hipLaunchKernelGGL(bd_sum_kernel, dim3((len + 15) / 16), dim3(1024), 0, s, w, c + 1,
                                         (c + 1) / BS_NW, g);
         if (timed) probe->end(PK_BIDIAG, s);

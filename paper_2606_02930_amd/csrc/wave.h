@@ -55,6 +55,66 @@ __device__ inline double wave_max_nonneg(double v) {
     return lane_value(v, 63);
 }
 
+// Exchange of the upper 32 (16 of each half) lanes of a with the lower ones of
+// b, both halves of the doubles.
+__device__ inline void swap32(double& a, double& b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __longlong_as_double(((long long)hi[0] << 32) | lo[0]);
+    b = __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+__device__ inline void swap16(double& a, double& b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __longlong_as_double(((long long)hi[0] << 32) | lo[0]);
+    b = __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+
+// Sums over the wavefront of eight values at once: lane l returns the sum of
+// value sum8_index(l).  Halving the values with every exchange takes 34
+// instructions where eight separate sums take 160.
+__device__ inline int sum8_index(int lane) { return (lane >> 5) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1); }
+__device__ inline double sum8(double (&v)[8], int lane) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        swap32(v[j], v[j + 4]);
+        v[j] += v[j + 4];
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        swap16(v[j], v[j + 2]);
+        v[j] += v[j + 2];
+    }
+    const bool up = lane & 8;
+    const double keep = up ? v[1] : v[0], give = up ? v[0] : v[1];
+    double s = keep + dpp_move<0x128, 0xf>(give);   // row_ror:8
+    s += dpp_move<0x141, 0xf>(s);                   // row_half_mirror
+    s += dpp_move<0x4E, 0xf>(s);                    // quad_perm [2, 3, 0, 1]
+    s += dpp_move<0xB1, 0xf>(s);                    // quad_perm [1, 0, 3, 2]
+    return s;
+}
+
+// ---------------------------------------------------------------------------
+// One workgroup
+// ---------------------------------------------------------------------------
+
+// Exchange and add: lanes 0..31 (of each half 0..15) end with the sum of a over
+// the halves, the others with that of b.
+__device__ inline double swap_add32(double a, double b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+__device__ inline double swap_add16(double a, double b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) + __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+}
+
 // 1 / x and 1 / sqrt(x) to rounding for normal x away from the ends of the
 // range: the hardware estimate (relative error below 1e-7) and two Newton
 // steps.
