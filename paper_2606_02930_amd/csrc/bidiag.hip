@@ -113,8 +113,8 @@ __global__ __launch_bounds__(256) void bd_load_kernel(const double* __restrict__
 // the reflectors and of the products stay in its registers, and what crosses
 // wavefronts is a norm and a number a row.  (With a wavefront a row the
 // reflectors were read from LDS by every row and the products summed through it:
-// 13.2 us a step over 2048 to 1024 columns, now 11.4; 7.4 over 1024 to 512, now
-// 7.2.  16 rows a workgroup leave half the compute units idle: 16.1 and 11.9.)
+// 13.2 us a step over 2048 to 1024 columns, now 11.0; 7.4 over 1024 to 512, now
+// 6.5.)
 constexpr int BS_NW = 8;            // rows and wavefronts of a workgroup
 constexpr int BS_NT = 64 * BS_NW;
 template <int Q>
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(BS_NT) void bd_step_kernel(BdWork b, int c, bool st
     // row c and the products are needed first, so they are asked for first; the
     // rows arrive while the reflectors are formed
     const double* rowc = b.A + (long)max(c, 0) * N;
-    double rc[Q], pc[Q], a[R][Q], x[R], xn[R];
+    double rc[Q], pc[Q], a[R][Q];
     double alpha = 0.0, sg = 0.0, first = 0.0, pfirst = 0.0;
     if (!start) {
         alpha = rowc[c];
@@ -145,17 +145,21 @@ __global__ __launch_bounds__(BS_NT) void bd_step_kernel(BdWork b, int c, bool st
             pc[q] = j < len ? b.p[c1 + j] : 0.0;
         }
     }
+    // lane r: the entries of row i0 + r in columns c and c + 1
+    double xl = 0.0, xnl = 0.0;
+    const int il = i0 + (lane & (R - 1));
+    if (il >= c1 && il < P) {
+        if (!start) xl = b.A[(long)il * N + c];
+        if (len > 0) xnl = b.A[(long)il * N + c1];
+    }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int i = i0 + r;
-        const bool in = i >= c1 && i < P;
-        const double* Ai = b.A + (long)i * N;
-        x[r] = in && !start ? Ai[c] : 0.0;
-        xn[r] = in && len > 0 ? Ai[c1] : 0.0;
+        const double* Ai = b.A + (long)i * N + c1;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const int j = t + BS_NT * q;
-            a[r][q] = in && j < len ? Ai[c1 + j] : 0.0;
+            a[r][q] = i >= c1 && i < P && j < len ? Ai[j] : 0.0;
         }
     }
     if (!start) {
@@ -197,15 +201,11 @@ __global__ __launch_bounds__(BS_NT) void bd_step_kernel(BdWork b, int c, bool st
                 b.e[c] = k.beta;
             }
         }
+        const double vl = xl * h.scale;
+        if (t < R && il >= c1 && il < P) b.VQ[(long)c * ldq + il] = vl;
         double v[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = x[r] * h.scale;
-        if (t < R && i0 + t >= c1 && i0 + t < P) {
-            double mine = v[0];
-#pragma unroll
-            for (int r = 1; r < R; ++r) mine = t == r ? v[r] : mine;
-            b.VQ[(long)c * ldq + i0 + t] = mine;
-        }
+        for (int r = 0; r < R; ++r) v[r] = lane_value(vl, r);
         if (len == 0) return;
         double d[R];
 #pragma unroll
@@ -236,16 +236,20 @@ __global__ __launch_bounds__(BS_NT) void bd_step_kernel(BdWork b, int c, bool st
                 a[r][q] -= e * u[q];
                 if (in && t + BS_NT * q < len) Ai[t + BS_NT * q] = a[r][q];
             }
-            xn[r] = xn[r] - v[r] * z0 - e;
         }
+        xnl = xnl - vl * z0 - dr;
     }
     // the next step's column products: rows below its own row
+    if (il <= c1 || il >= P) xnl = 0.0;
+    double xn[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) xn[r] = lane_value(xnl, r);
     double* part = b.part + (long)blockIdx.x * N + c1;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         double s = 0.0;
 #pragma unroll
-        for (int r = 0; r < R; ++r) s += (i0 + r > c1 && i0 + r < P ? xn[r] : 0.0) * a[r][q];
+        for (int r = 0; r < R; ++r) s += xn[r] * a[r][q];
         if (t + BS_NT * q < len) part[t + BS_NT * q] = s;
     }
 }
