@@ -16,6 +16,7 @@
 #include "internal.h"
 
 #include <algorithm>
+#include <climits>
 #include <cstdint>
 #include <cstring>
 #include <type_traits>
@@ -57,7 +58,11 @@ void launch_tiles(const Gemm& g, Params p, hipStream_t s) {
 //      1920 x 1536 x 384        74    56.5    47.7      87     720 64-tiles
 //      5120 x 4096 x 1024     1550     895     694     829
 // so 64 from 512 of its tiles on (two workgroups a compute unit), 32 from 192
-// of its tiles on.  With 16, four K parts are as fast as eight while K is
+// of its tiles on.  A few tiles more than 512 are a second round that leaves most
+// of the chip idle, which costs more the longer K is (H_eff, us, its second product in
+// 32 and 64: 576 tiles, K 3840 730 and 858; 676, K 4160 927 and 993; 756, K 4320 1029 and
+// 1068; 784, K 4480 1148 and 1156; 900, K 4800 1412 and 1367): with a long K 64 from
+// 800 on.  With 16, four K parts are as fast as eight while K is
 // short (160 x 128 x 32: 2.9 and 3.4) and slower when it is long (64 x 64 x
 // 4000: 18.1 and 13.4); they meet near 500.
 //
@@ -79,9 +84,30 @@ template <typename T>
 TileKind tile_kind(const Gemm& g) {
     auto tiles = [&](int side) { return (long)((g.M + side - 1) / side) * ((g.N + side - 1) / side) * g.batch; };
     const bool wide = (!g.tA || g.M >= 32) && (g.tB || g.N >= 32);
-    if (wide && tiles(64) >= (std::is_same<T, double>::value ? 512 : 1024)) return TILE_64;
+    if (wide && tiles(64) >= (!std::is_same<T, double>::value ? 1024 : g.K >= 1024 ? 800 : 512)) return TILE_64;
     if (wide && tiles(32) >= 192) return TILE_32;
     return g.K >= 512 ? TILE_16_LONG : TILE_16;
+}
+
+// Large TILE_64 products take larger tiles of the same two K parts (the same
+// bits, so a grouped launch need not): wavefronts of 32 x 64 (FP64) or 64 x 64
+// (FP32) read 3/4 or half of what those of 32 x 32 do, and one workgroup fills
+// a compute unit.
+//
+// H_eff products, us of both of their products and the stage (none / 2048 tiles on / 1024 on):
+//      d 2, bond 512, FP64 (1280 tiles, K 512)              224     224     241
+//      d 4, bond 384, FP64 (3456 tiles, K 384)              553     570     568
+//      d 2, bond 1024, FP64 (5120, K 1024; 1024, K 5120)   1608    1577    1508
+//      d 2, bond 512, FP32                                  127     128     132
+//      d 2, bond 768, FP32 (2880 tiles, K 768)              412     385     385
+//      d 4, bond 512, FP32 (6144, K 512; 1024, K 3072)      584     542     526
+// so a long K pays from 1024 tiles on in either type, a short one in FP32 from
+// 2048 on.
+template <typename T>
+bool large_tile(const Gemm& g) {
+    const long tiles = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
+    if ((g.tA && g.M < 64) || (!g.tB && g.N < 64)) return false;
+    return tiles >= (g.K >= 1024 ? 1024 : std::is_same<T, double>::value ? LONG_MAX : 2048);
 }
 
 Params params(const Gemm& g) {
@@ -103,7 +129,10 @@ void launch(const Gemm& g, hipStream_t s) {
     Params p = params(g);
     if (std::is_same<T, double>::value) p.Df = nullptr;
     const TileKind kind = tile_kind<T>(g);
-    if (kind == TILE_64) launch_tiles<T, 2, 2, 2, 2, 2, 1>(g, p, s);
+    if (kind == TILE_64 && large_tile<T>(g)) {
+        if constexpr (std::is_same<T, double>::value) launch_tiles<T, 2, 4, 2, 2, 2, 1>(g, p, s);
+        else launch_tiles<T, 4, 4, 2, 1, 2, 1>(g, p, s);
+    } else if (kind == TILE_64) launch_tiles<T, 2, 2, 2, 2, 2, 1>(g, p, s);
     else if (kind == TILE_32) launch_tiles<T, 2, 2, 1, 1, K32<T>, 1>(g, p, s);
     else if (kind == TILE_16_LONG) launch_tiles<T, 1, 1, 1, 1, 8, 2>(g, p, s);
     else launch_tiles<T, 1, 1, 1, 1, 4, 2>(g, p, s);

@@ -79,3 +79,17 @@ def test_fp32_product_at_tile_edges(env, shape, tA, tB):
 @pytest.mark.parametrize("shape", BF16)
 def test_bf16_product_at_tile_edges(env, shape, tA, tB):
     _run(env, shape, tA, tB, 2, 6e-6)
+
+
+# tiles larger than 64 x 64, from 1024 of those on with a K of 1024 or more, or 2048 in
+# FP32: their remainders in both directions and in K, and sides shorter than one
+# wavefront tile, which keep the 64 x 64
+LARGE = [(2100, 2020, 1024), (1985, 2113, 1031), (3000, 2800, 77), (65600, 33, 1025), (33, 65600, 1025),
+         (131100, 64, 33), (65, 66000, 1040)]
+
+
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("shape", LARGE)
+def test_large_tiles(env, shape, tA, tB):
+    _run(env, shape, tA, tB, 0, 1e-13)
+    _run(env, shape, tA, tB, 1, 6e-6)
