@@ -102,11 +102,12 @@ TileKind tile_kind(const Gemm& g) {
 //      d 2, bond 768, FP32 (2880 tiles, K 768)              412     385     385
 //      d 4, bond 512, FP32 (6144, K 512; 1024, K 3072)      584     542     526
 // so a long K pays from 1024 tiles on in either type, a short one in FP32 from
-// 2048 on.
+// 2048 on.  Not in FP64 with A transposed (environment updates up to bond 1024,
+// on average 391 and 457 us).
 template <typename T>
 bool large_tile(const Gemm& g) {
     const long tiles = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
-    if ((g.tA && g.M < 64) || (!g.tB && g.N < 64)) return false;
+    if ((g.tA && (std::is_same<T, double>::value || g.M < 64)) || (!g.tB && g.N < 64)) return false;
     return tiles >= (g.K >= 1024 ? 1024 : std::is_same<T, double>::value ? LONG_MAX : 2048);
 }
 
