@@ -269,11 +269,11 @@ int ite_imag_step(ite_mps* psi, const ite_mpo* H, double h,
  * as a batch: the sweeps advance in lockstep block by block, and the
  * fixed-budget GMRES local solves of a block slot run together -- one
  * grouped launch per contraction stage for the H_eff products of all states
- * (uneven bond dimensions, tile size per GEMM shape from the library's
- * autotuner), one batched launch per Krylov vector operation, the small
+ * (uneven bond dimensions, tile by each product's shape), one batched
+ * launch per Krylov vector operation, the small
  * least-squares solves on the device -- captured as a HIP graph on a
  * private stream (ordered after ctx's stream) and replayed while the batch
- * keeps its size, budget and precision (the last four such graphs are kept;
+ * keeps its size, budget and precision (the last twelve such graphs are kept;
  * a capture that another thread's call invalidates is issued directly).
  * FP64 solves and FP32 refinement with a fixed number of corrections
  * (tol_refine = 0, max_cycles = 1: one cycle per correction, the Arnoldi

@@ -5,8 +5,8 @@
 // and Kahan): in step c a reflector on the rows from c on clears column c
 // below the diagonal, one on the columns from c + 1 on clears row c right of
 // the superdiagonal.  While more than 192 rows are left a step is one pass over
-// the trailing block (bd_step_kernel: both reflectors applied to a row while it
-// is in a wavefront's registers, and its share of the next step's column
+// the trailing block (bd_step_kernel: both reflectors applied to a row while its
+// entries are in registers, and its share of the next step's column
 // products taken) and one sum over the workgroups (bd_sum_kernel), or both in
 // one launch from 512 rows and columns on (bd_step1_kernel); the rest is
 // done by one workgroup in its registers (bd_tail_kernel).  Bound by the
@@ -1007,9 +1007,12 @@ void bidiagonalise(const BdWork& w, const double* theta, bool tr, hipStream_t s,
                        w.TQ, w.TP);
     HIP_CHECK(hipGetLastError());
     if (probe) {
-        // 4 P N^2 - 4 N^3 / 3 flops over the block read and the reflectors written
+        // 4 P N^2 - 4 N^3 / 3 flops; the block read and the reflectors written,
+        // and the trailing block read and written by every step before the tail
         const double p = P, n = N;
-        probe->work(PK_BIDIAG, 4.0 * n * n * (p - n / 3.0), 8.0 * (2.0 * p * n + n * n));
+        double bytes = 8.0 * (2.0 * p * n + n * n);
+        for (int c = 0; c < N && P - c > BD_TAIL; ++c) bytes += 16.0 * (P - c) * (N - c - 1);
+        probe->work(PK_BIDIAG, 4.0 * n * n * (p - n / 3.0), bytes);
     }
 }
 
