@@ -72,6 +72,8 @@ __device__ inline Node node_of(int n, int depth, int g, int& q) {
     return Node{a, a + (b - a) / 2, b};
 }
 
+// NaN as zero, so that orders and counts stay those of a finite matrix (the
+// scale, and with it every singular value, is NaN where an entry is not finite).
 __device__ inline double clean(double v) { return v == v ? v : 0.0; }
 
 // r = sqrt(x^2 + y^2), c = x / r, s = y / r for values scaled to at most about 1
@@ -497,8 +499,11 @@ __device__ inline double pow2_scale(double mx, bool inverse) {
 __global__ __launch_bounds__(LNT) void dc_leaf_kernel(DcWork w, int depth) {
     __shared__ LeafLDS L;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6, n = w.n;
-    double mx = 0.0;
-    for (int i = t; i < n; i += LNT) mx = fmax(mx, fmax(fabs(w.d[i]), i + 1 < n ? fabs(w.e[i]) : 0.0));
+    double mx = 0.0;       // infinite for entries that are not finite (fmax passes NaN by)
+    for (int i = t; i < n; i += LNT) {
+        const double d = fabs(w.d[i]), e = i + 1 < n ? fabs(w.e[i]) : 0.0;
+        mx = d < INFINITY && e < INFINITY ? fmax(mx, fmax(d, e)) : INFINITY;
+    }
     mx = wave_max_nonneg(mx);
     if (lane == 0) L.red[wv] = mx;
     __syncthreads();
@@ -506,7 +511,7 @@ __global__ __launch_bounds__(LNT) void dc_leaf_kernel(DcWork w, int depth) {
     for (int q = 1; q < LNW; ++q) mx = fmax(mx, L.red[q]);
     const double inv = pow2_scale(mx, true);
     if (blockIdx.x == 0 && t == 0) {
-        *w.scale = pow2_scale(mx, false);
+        *w.scale = mx < INFINITY ? pow2_scale(mx, false) : NAN;
         *w.inv = inv;
     }
     const Node root = node_at(0, n, depth, blockIdx.x);
@@ -985,7 +990,7 @@ int dc_depth(int n) {
 // Rank of every singular value by counting those before it (16 lanes a
 // value, a pass over all n each): one launch for the order and the way to the
 // host, where a copy, a sort there and a copy back took three and a wait.  The
-// bits of the magnitudes order everything, NaN first.
+// bits of the magnitudes order everything, NaN first (all values are NaN or none is).
 __global__ __launch_bounds__(1024) void dc_sorted_kernel(const double* __restrict__ sg, int n,
                                                          const double* __restrict__ scale, int* __restrict__ perm,
                                                          HostPost post) {
