@@ -7,8 +7,8 @@
 // column m and beta = e_m in column m + 1; the rows before and after m are its
 // children.  With the children's singular values and vectors, and their null
 // vectors (a child has one column more than rows), the node's matrix becomes
-// orthogonally equivalent to diag(0, d) with a first row z.  Entries with
-// |z_j| below a few eps times the norm, and all but one of a group of equal
+// orthogonally equivalent to diag(0, d) with a first row z.  Entries with a
+// small |z_j| (deflation_limit), and all but one of a group of equal
 // d_j (after a rotation that leaves one of their z_j), are singular values as
 // they stand (deflation).  The other singular values are the roots of
 //   1 + sum_j z_j^2 / (d_j^2 - sigma^2) = 0,
@@ -37,7 +37,14 @@ namespace {
 
 constexpr int LEAF = 32;
 constexpr double EPS = 2.220446049250313e-16;
-constexpr double DEFLATE = 8.0 * EPS;
+
+// What counts as zero, and as equal, at a value d of a node with norm nrm: 8 eps
+// of the norm at the norm itself, where that saves work on equal values, falling
+// to eps for small d.  (With 8 eps throughout a vanishing value came back as
+// 1.8e-15 of the largest and values up to that as zero, so that a cutoff of 1e-30
+// kept 6 to 9 vectors of a block of rank 3; with eps throughout a block of equal
+// values of 33 rows took 208 us instead of 130.)
+__device__ inline double deflation_limit(double nrm, double d) { return EPS * fma(7.0, d, nrm); }
 
 struct Node {
     int a, m, b;
@@ -253,7 +260,7 @@ __device__ __forceinline__ void leaf_deflate(LeafLDS& L, int cur, int a, int m, 
         U[m][a + lane] = a + lane == m ? 1.0 : 0.0;
     }
     const double nrm = fmax(wave_max_nonneg(dv), fmax(fabs(clean(alpha)), fabs(clean(beta))));
-    const double tol = DEFLATE * nrm;
+    const double tol = deflation_limit(nrm, 0.0);
     wave_fence();
     const int lm = m - a;
     int rank = lane == lm ? 0 : 1;
@@ -275,7 +282,8 @@ __device__ __forceinline__ void leaf_deflate(LeafLDS& L, int cur, int a, int m, 
         row = srow[lane];
         if (lane == 0 && !(fabs(zs) > tol)) zs = zs < 0.0 ? -tol : tol;
     }
-    const bool surv = lane > 0 && lane < N && fabs(zs) > tol;
+    const double lim = deflation_limit(nrm, ds);
+    const bool surv = lane > 0 && lane < N && fabs(zs) > lim;
     const bool tiny = surv && ds <= tol;
     const unsigned long long below = (1ull << lane) - 1;
     const unsigned long long ms = __ballot(surv && !tiny);
@@ -283,7 +291,7 @@ __device__ __forceinline__ void leaf_deflate(LeafLDS& L, int cur, int a, int m, 
     if (surv && !tiny) {
         const unsigned long long q = ms & below;
         pv = q ? 63 - __clzll(q) : -1;
-        act = pv >= 0 && ds - sd[pv] <= tol ? 2 : 0;
+        act = pv >= 0 && ds - sd[pv] <= lim ? 2 : 0;
     } else if (tiny) {
         act = 3;
     } else if (lane == 0) {
@@ -627,7 +635,7 @@ __global__ __launch_bounds__(PREP_NT) void dc_prep_kernel(DcWork w, int depth, i
     if (lane == 0) red[wv] = mx;
     __syncthreads();
     for (int q = 0; q < PREP_NT / 64; ++q) mx = fmax(mx, red[q]);
-    const double tol = DEFLATE * fmax(mx, fmax(fabs(alpha), fabs(beta)));
+    const double nrm = fmax(mx, fmax(fabs(alpha), fabs(beta))), tol = deflation_limit(nrm, 0.0);
     // ascending order, the middle row first: a bitonic network over the keys in
     // LDS (row numbers break ties; pairs up to 64 apart stay in a wavefront)
     auto zof = [&](int r) {
@@ -687,7 +695,7 @@ __global__ __launch_bounds__(PREP_NT) void dc_prep_kernel(DcWork w, int depth, i
     int total = 0;
     for (int base = 0; base < N; base += PREP_NT) {
         const int s = base + t;
-        const bool surv = s > 0 && s < N && fabs(sz[s]) > tol, tiny = surv && sd[s] <= tol;
+        const bool surv = s > 0 && s < N && fabs(sz[s]) > deflation_limit(nrm, sd[s]), tiny = surv && sd[s] <= tol;
         if (s < N) act[s] = tiny ? 3 : (s == 0 ? 0 : 1);
         const unsigned long long bal = __ballot(surv && !tiny);
         if (lane == 0) cnt[wv] = __popcll(bal);
@@ -700,7 +708,7 @@ __global__ __launch_bounds__(PREP_NT) void dc_prep_kernel(DcWork w, int depth, i
     }
     for (int ci = t; ci < total; ci += PREP_NT) {
         const int s = cl[ci];
-        act[s] = ci > 0 && sd[s] - sd[cl[ci - 1]] <= tol ? 2 : 0;
+        act[s] = ci > 0 && sd[s] - sd[cl[ci - 1]] <= deflation_limit(nrm, sd[s]) ? 2 : 0;
     }
     __syncthreads();
     // destinations: starts by their order, then the deflated entries
