@@ -36,15 +36,18 @@ __host__ __device__ inline int pad16(int n) { return (n + 15) & ~15; }
 
 // The reflector of x[0..len) (LAPACK's convention: beta = -sign(alpha) ||x||,
 // tau = (beta - alpha) / beta, v = x / (alpha - beta) with v_0 = 1; tau = 0
-// when x_1.. = 0) from alpha = x_0 and sg = x_1^2 + ...
+// when x_1.. = 0) from alpha = x_0 and sg = x_1^2 + ...  Below ||x|| = 1e-140 the
+// squares lose digits or vanish, and a reflector formed from them would not be
+// orthogonal: such an x counts as zero (split scales blocks that are that small
+// altogether).
 struct Refl {
     double beta, tau, scale;
 };
 __device__ inline Refl reflector(double alpha, double sg) {
     Refl r{alpha, 0.0, 0.0};
-    if (sg > 0.0) {
-        const double s2 = alpha * alpha + sg;
-        if (s2 > 1e-280 && s2 < 1e280) {
+    const double s2 = alpha * alpha + sg;
+    if (sg > 0.0 && s2 > 1e-280) {
+        if (s2 < 1e280) {
             // the two reciprocals side by side instead of a square root and
             // two divisions in a chain
             const double y = recip_sqrt(s2), nrm = s2 * y;
@@ -57,8 +60,8 @@ __device__ inline Refl reflector(double alpha, double sg) {
             r.tau = (r.beta - alpha) / r.beta;
             r.scale = 1.0 / (alpha - r.beta);
         }
-    } else if (!(sg == 0.0)) {
-        r.beta = r.tau = sg;     // NaN stays visible in the result
+    } else if (!(sg >= 0.0)) {
+        r.beta = r.tau = sg;     // NaN stays NaN (dc_leaf_kernel looks for it)
     }
     return r;
 }

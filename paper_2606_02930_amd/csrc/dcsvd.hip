@@ -44,7 +44,13 @@ constexpr double EPS = 2.220446049250313e-16;
 // 1.8e-15 of the largest and values up to that as zero, so that a cutoff of 1e-30
 // kept 6 to 9 vectors of a block of rank 3; with eps throughout a block of equal
 // values of 33 rows took 208 us instead of 130.)
-__device__ inline double deflation_limit(double nrm, double d) { return EPS * fma(7.0, d, nrm); }
+//
+// Never below FLOOR, so that the squares of what is left, and what is divided by
+// them, stay numbers (the matrix is scaled to a largest entry of one).
+constexpr double FLOOR = 1e-120;
+__device__ inline double deflation_limit(double nrm, double d) { return fmax(EPS * fma(7.0, d, nrm), FLOOR); }
+// The one singular value left of a node.
+__device__ inline double lone_value(double z) { return fabs(z) > FLOOR ? fabs(z) : 0.0; }
 
 struct Node {
     int a, m, b;
@@ -440,7 +446,7 @@ __device__ __forceinline__ void leaf_vectors(LeafLDS& L, int cur, int len, int r
                 L.dc[r] = dc;
             }
         } else if (j0 == 0) {
-            L.sg[cur ^ 1][r] = fabs(z[0]);
+            L.sg[cur ^ 1][r] = lone_value(z[0]);
         }
     }
     __syncthreads();
@@ -496,11 +502,12 @@ __device__ __forceinline__ void leaf_vectors(LeafLDS& L, int cur, int len, int r
     __syncthreads();
 }
 
-// A power of two near the largest |d|, |e|.
+// A power of two near the largest |d|, |e| (2^-1000 at least).
 __device__ inline double pow2_scale(double mx, bool inverse) {
     if (!(mx > 0.0) || !(mx < 1e300)) return 1.0;
     int ex;
     (void)frexp(mx, &ex);
+    ex = max(ex, -1000);
     return ldexp(1.0, inverse ? -ex : ex);
 }
 
@@ -794,7 +801,7 @@ __global__ __launch_bounds__(256) void dc_roots_kernel(DcWork w, int depth, int 
         double* sgo = w.sg[cur ^ 1];
         if (K == 1) {
             if (lane == 0) {
-                sgo[g] = fabs(zz[0]);
+                sgo[g] = lone_value(zz[0]);
                 w.x[g] = zz[0] * zz[0];
                 w.dc[g] = 0.0;
             }

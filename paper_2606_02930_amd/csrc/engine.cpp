@@ -482,6 +482,11 @@ static SplitResult truncate(const std::vector<double>& s, double cutoff, int chi
 // The split by bidiagonalisation and divide and conquer: the singular values
 // come to the host for the truncation, then only the kept vectors are
 // transformed back, straight into the two site tensors.
+//
+// The reflectors square the block's entries.  A block whose largest singular
+// value comes out below SPLIT_TINY (or as nothing at all) is therefore done once
+// more, scaled to entries near one.
+constexpr double SPLIT_TINY = 1e-120;
 SplitResult split(ite_ctx* c, int dir, int Dl, int d1, int d2, int Dr, const double* theta, int chi_max,
                   double cutoff, double tie_rel, double* A1, double* A2, std::vector<double>* sigma) {
     const int m = Dl * d1, n = d2 * Dr;
@@ -492,24 +497,45 @@ SplitResult split(ite_ctx* c, int dir, int Dl, int d1, int d2, int Dr, const dou
     const BdWork bd = bd_carve(slot_t<double>(c, SL_Z, bd_workspace(P, N)), P, N);
     const DcWork dc = dc_carve(slot_t<double>(c, SL_DC, dc_workspace(N)), N, bd.d, bd.e);
     int* perm = slot_t<int>(c, SL_PERM, (size_t)N + 16);
-    bidiagonalise(bd, theta, tr, c->stream, pr);
-    const int w = bidiagonal_svd(dc, c->stream, pr);
-    // the order and the values: few through the mailbox, many through the
-    // staging buffer
-    HostPost post;
-    if (N <= DC_POST) post = mail_post(c, MAIL_SIGMA);
-    else post.data = pinned(c, (size_t)N + 64);
-    dc_sorted(dc, w, perm, post, c->stream);
-    if (N <= DC_POST) mail_wait(c, post);
-    else sync(c);
-    const std::vector<double> nv(post.data, post.data + N);
+    auto values = [&](const double* block, std::vector<double>& s) {
+        bidiagonalise(bd, block, tr, c->stream, pr);
+        const int w = bidiagonal_svd(dc, c->stream, pr);
+        // the order and the values: few through the mailbox, many through the
+        // staging buffer
+        HostPost post;
+        if (N <= DC_POST) post = mail_post(c, MAIL_SIGMA);
+        else post.data = pinned(c, (size_t)N + 64);
+        dc_sorted(dc, w, perm, post, c->stream);
+        if (N <= DC_POST) mail_wait(c, post);
+        else sync(c);
+        s.assign(post.data, post.data + N);
+        return w;
+    };
+    std::vector<double> nv;
+    int w = values(theta, nv);
+    double unit = 1.0;       // of the values that were found
+    if (nv[0] < SPLIT_TINY) {
+        const size_t all = (size_t)m * n;
+        const HostPost post = mail_post(c, MAIL_ONE);
+        max_abs(theta, all, post, c->stream);
+        mail_wait(c, post);
+        if (post.data[0] > 0.0) {
+            unit = std::ldexp(1.0, std::max(std::ilogb(post.data[0]), -1000));
+            double* scaled = slot_t<double>(c, SL_VECS, all);
+            axpby(all, 1.0 / unit, theta, 0.0, nullptr, scaled, c->stream);
+            w = values(scaled, nv);
+        }
+    }
     const SplitResult res = truncate(nv, cutoff, chi_max, tie_rel, sigma);
+    if (sigma && unit != 1.0)
+        for (double& v : *sigma) v *= unit;
     const size_t nt = bd_vectors_tmp(P, N, res.k);
     double* tmp = nt ? slot_t<double>(c, SL_VECS, nt) : nullptr;
     // U to A1 [m][k], V^T to A2 [k][n]; the singular values go to the factor
     // that is not orthonormal
     const BdOut u{A1, 1, dir == 1}, v{A2, 0, dir == 0};
     bd_vectors(bd, dc.UT[w], dc.VT[w], perm, res.k, dc.sg[w], dc.scale, tr ? v : u, tr ? u : v, tmp, c->stream, pr);
+    if (unit != 1.0) scale(dir == 0 ? A2 : A1, unit, (size_t)res.k * (dir == 0 ? n : m), c->stream);
     return res;
 }
 

@@ -15,7 +15,7 @@ enum SlotId {
     SL_TPSI, SL_B, SL_TH,          // theta_psi, right-hand side, solution
     SL_V, SL_W,                    // Krylov basis, work vector
     SL_PART, SL_SMALL,             // reduction partials, small device scalars
-    SL_Z, SL_DC, SL_VECS, SL_PERM,   // split: block, divide and conquer, long vectors
+    SL_Z, SL_DC, SL_VECS, SL_PERM,   // split: block, divide and conquer, long vectors (or a scaled block)
     SL_GRAM, SL_ROT, SL_OFF, SL_NORM,      // Jacobi of the density matrices
     SL_QR,                         // Householder preconditioning
     SL_TMPA, SL_TMPB,              // scratch environments (overlap, energy)

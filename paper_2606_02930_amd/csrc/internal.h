@@ -179,6 +179,8 @@ void hess_solve(const double* hd, const double* norms, int mm, double* y, double
 void lanczos_eig(const double* hd, int mm, double* y, double* rec, hipStream_t s);
 // x *= a
 void scale(double* x, double a, size_t n, hipStream_t s);
+// The largest |x_i| (infinite when one is not finite) to the host.
+void max_abs(const double* x, size_t n, const HostPost& post, hipStream_t s);
 // y[i] = x[i*inc] for i < n (strided gather)
 void fill(double* x, double v, size_t n, hipStream_t s);
 // identity matrix D x D (row-major) into x

@@ -140,6 +140,19 @@ __global__ void fill_kernel(double* __restrict__ x, double v, size_t n) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) x[i] = v;
 }
 
+__global__ __launch_bounds__(1024) void max_abs_kernel(const double* __restrict__ x, size_t n, HostPost post) {
+    __shared__ double sh[16];
+    double m = 0.0;
+    for (size_t i = threadIdx.x; i < n; i += 1024) m = isfinite(x[i]) ? fmax(m, fabs(x[i])) : INFINITY;
+    m = wave_max_nonneg(m);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x > 0) return;
+    for (int q = 1; q < 16; ++q) m = fmax(m, sh[q]);
+    post.data[0] = m;
+    post_flag(post);
+}
+
 __global__ void eye_kernel(double* __restrict__ x, int D) {
     const size_t n = (size_t)D * D;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -592,6 +605,11 @@ void lanczos_eig(const double* hd, int mm, double* y, double* rec, hipStream_t s
 void scale(double* x, double a, size_t n, hipStream_t s) {
     if (n == 0) return;
     hipLaunchKernelGGL(scale_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, x, a, n);
+    HIP_CHECK(hipGetLastError());
+}
+
+void max_abs(const double* x, size_t n, const HostPost& post, hipStream_t s) {
+    hipLaunchKernelGGL(max_abs_kernel, dim3(1), dim3(1024), 0, s, x, n, post);
     HIP_CHECK(hipGetLastError());
 }
 
