@@ -484,26 +484,41 @@ void gemm_f32(const Gemm& g, hipStream_t s) { launch<float>(g, s); }
 
 // BF16 tiles: straight to registers (32 x 32 or 16 x 16, four K parts) while the
 // 128 x 128 tiles through LDS leave compute units idle; those read each operand
-// a quarter as often and win once they fill the chip, from 256 of them on with
-// K contiguous in both operands and from 512 on where they transpose on the way
-// into LDS (us: 16, 32, LDS 128):
+// a quarter as often and win once they fill the chip, from 256 of them on:
+// 16 x 16, 32 x 32 and LDS 128, us on the device
 //      128 x 32 x 160 (NT)       4.1   6.5  13.7
 //      2048 x 128 x 768 (NT)     4.9   5.2  24.2     256 32-tiles
 //      4096 x 256 x 1536 (NT)   19.6  14.3  38.5      64 128-tiles
-//      1536 x 4096 x 256        47.0  30.7  34.9     384
-//      8192 x 512 x 3072 (NT)    121  74.6  68.5     256
-//      5120 x 4096 x 1024        596   283   199    1280
+// and the latter two with the call and its wait, some 20 us (NN, NT, TN):
+//      1024 x 1024 x 512         27 33   27 33   28 34      64
+//      2048 x 1024 x 512         34 37   33 37   36 38     128
+//      1920 x 1536 x 512         38 37   36 36   40 37     180
+//      1920 x 1536 x 2048        82 65   71 63   93 66     180
+//      2048 x 2048 x 256         35 32   35 31   36 32     256
+//      2048 x 2048 x 2048       115 68  104 66  126 69     256
+//      6361 x 704 x 1024         62 67   57 62      --     300
+//      1536 x 4096 x 256         43 36   43 36   46 37     384
+//      3000 x 2400 x 512         55 49   54 46   66 52     456
+// From 160 on they win when K is long, and from 128 on when it is shorter than a
+// slice of the 32 x 32 tile (2048 x 1024 x 32: 32 29  39 29  28 28).  Their loads
+// are single values where an operand does not allow 16 bytes at a time, which
+// takes longer the longer K is: such products go to LDS from 512 of these tiles
+// on only, or 256 with K contiguous in both operands (2300 x 1840 x 512, TN, rows
+// of 2300: 53 and 91; x 32: 36 and 31).
 void gemm_bf16(const Gemm& g, hipStream_t s) {
     if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return;
     if (g.Df && g.C) ITE_FAIL(ITE_EINVAL, "gemm: an FP32 output takes no C");
     Params p = params(g);
     auto tiles = [&](int side) { return (long)((g.M + side - 1) / side) * ((g.N + side - 1) / side) * g.batch; };
     const bool wide = (!g.tA || g.M >= 32) && (g.tB || g.N >= 32);
-    const int side = tiles(128) >= (!g.tA && g.tB ? 256 : 512) ? 128 : wide && tiles(32) >= 192 ? 32 : 16;
+    const bool v = vec16(g, sizeof(uint16_t));
+    const long t128 = tiles(128);
+    const bool lds = t128 >= (v || (!g.tA && g.tB) ? 256 : 512) || (t128 >= 160 && v && g.K >= 2048) ||
+                     (t128 >= 128 && g.K < BKB);
+    const int side = lds ? 128 : wide && tiles(32) >= 192 ? 32 : 16;
     p.mt = (g.M + side - 1) / side;
     p.nt = (g.N + side - 1) / side;
     const dim3 grid(p.mt * p.nt, 1, g.batch);
-    const bool v = vec16(g, sizeof(uint16_t));
 #define ITE_GB(TA, TB)                                                                                          \
     if (side == 16) hipLaunchKernelGGL((direct_bf16_kernel<TA, TB, 1, 1, 1, 1, 4>), grid, dim3(256), 0, s, p);  \
     else if (side == 32)                                                                                        \
