@@ -76,15 +76,28 @@ void launch_tiles(const Gemm& g, Params p, hipStream_t s) {
 //      5120 x 4096 x 1024      938     562     458     561
 // the same, with 64 from 1024 of its tiles on.
 //
+// Up to a K of 128 the exchange of the two K parts costs a 64 tile more than they
+// save: it has one part there (us with the call and its wait, some 20: two parts,
+// one, and LDS as above; NN):
+//      4336 x 1880 x 16       34  30  29    FP32  34  33  33
+//      2500 x 7500 x 32       69  62  61          56  53  53
+//      4000 x 4000 x 100     108  94  95          76  72  86
+//      6850 x 2468 x 128     114 105 124          79  74  97
+//      2048 x 2048 x 256      56  57  61          48  46  53
+//      4000 x 4000 x 512     307 324 316         204 187 234
+// (FP32 keeps two parts beyond 128 as well, for the shorter chains of additions.)
+//
 // A side-contiguous operand (A transposed, B not) needs a side of at least
 // one wavefront tile, which only the 16-wide tiles guarantee.
 template <typename T> constexpr int K32 = sizeof(T) == 8 ? 8 : 4;   // K parts of the 32 tile
-enum TileKind { TILE_64, TILE_32, TILE_16_LONG, TILE_16 };
+constexpr int K_SHORT = 128;
+enum TileKind { TILE_64, TILE_64_SHORT, TILE_32, TILE_16_LONG, TILE_16 };
 template <typename T>
 TileKind tile_kind(const Gemm& g) {
     auto tiles = [&](int side) { return (long)((g.M + side - 1) / side) * ((g.N + side - 1) / side) * g.batch; };
     const bool wide = (!g.tA || g.M >= 32) && (g.tB || g.N >= 32);
-    if (wide && tiles(64) >= (!std::is_same<T, double>::value ? 1024 : g.K >= 1024 ? 800 : 512)) return TILE_64;
+    if (wide && tiles(64) >= (!std::is_same<T, double>::value ? 1024 : g.K >= 1024 ? 800 : 512))
+        return g.K <= K_SHORT ? TILE_64_SHORT : TILE_64;
     if (wide && tiles(32) >= 192) return TILE_32;
     return g.K >= 512 ? TILE_16_LONG : TILE_16;
 }
@@ -101,14 +114,16 @@ TileKind tile_kind(const Gemm& g) {
 //      d 2, bond 512, FP32                                  127     128     132
 //      d 2, bond 768, FP32 (2880 tiles, K 768)              412     385     385
 //      d 4, bond 512, FP32 (6144, K 512; 1024, K 3072)      584     542     526
-// so a long K pays from 1024 tiles on in either type, a short one in FP32 from
-// 2048 on.  Not in FP64 with A transposed (environment updates up to bond 1024,
+// so a long K pays from 1024 tiles on in either type, one of 512 or more in FP32
+// from 2048 on (below 512 the 64 x 64 tile is faster, FP32, NN, us with the call:
+// 2500 x 7500 x 32 82 and 56, x 128 115 and 91, x 256 156 and 140, x 384 195 and 190,
+// x 512 230 and 239).  Not in FP64 with A transposed (environment updates up to bond 1024,
 // on average 391 and 457 us).
 template <typename T>
 bool large_tile(const Gemm& g) {
     const long tiles = (long)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
     if ((g.tA && (std::is_same<T, double>::value || g.M < 64)) || (!g.tB && g.N < 64)) return false;
-    return tiles >= (g.K >= 1024 ? 1024 : std::is_same<T, double>::value ? LONG_MAX : 2048);
+    return tiles >= (g.K >= 1024 ? 1024 : std::is_same<T, double>::value || g.K < 512 ? LONG_MAX : 2048);
 }
 
 Params params(const Gemm& g) {
@@ -134,6 +149,7 @@ void launch(const Gemm& g, hipStream_t s) {
         if constexpr (std::is_same<T, double>::value) launch_tiles<T, 2, 4, 2, 2, 2, 1>(g, p, s);
         else launch_tiles<T, 4, 4, 2, 1, 2, 1>(g, p, s);
     } else if (kind == TILE_64) launch_tiles<T, 2, 2, 2, 2, 2, 1>(g, p, s);
+    else if (kind == TILE_64_SHORT) launch_tiles<T, 2, 2, 2, 2, 1, 1>(g, p, s);
     else if (kind == TILE_32) launch_tiles<T, 2, 2, 1, 1, K32<T>, 1>(g, p, s);
     else if (kind == TILE_16_LONG) launch_tiles<T, 1, 1, 1, 1, 8, 2>(g, p, s);
     else launch_tiles<T, 1, 1, 1, 1, 4, 2>(g, p, s);
@@ -145,15 +161,15 @@ void launch(const Gemm& g, hipStream_t s) {
 // output; every workgroup walks that range with a stride of the grid, so the
 // grid can stay fixed (graph capture) while the problems change.  The
 // descriptors live in device memory.  Each problem has the tile of its shape;
-// one of four K parts takes two neighbours for the eight wavefronts.
+// one of four wavefronts takes two neighbours for the eight.
 struct GroupDesc {
     Params p;
     int tile_start;
     int kind;
 };
-int group_rows(TileKind k) { return k == TILE_64 ? 64 : k == TILE_32 ? 32 : 16; }
+int group_rows(TileKind k) { return k == TILE_64 || k == TILE_64_SHORT ? 64 : k == TILE_32 ? 32 : 16; }
 int group_cols(TileKind k, bool f32) {
-    return k == TILE_64 ? 64 : k == TILE_32 ? (f32 ? 64 : 32) : k == TILE_16_LONG ? 16 : 32;
+    return k == TILE_64 ? 64 : k == TILE_64_SHORT ? 128 : k == TILE_32 ? (f32 ? 64 : 32) : k == TILE_16_LONG ? 16 : 32;
 }
 
 template <typename T, bool TB>
@@ -170,6 +186,7 @@ __global__ __launch_bounds__(512) void gemm_grouped_kernel(const GroupDesc* __re
         const int kind = desc[g].kind;
         const int lt = tile - desc[g].tile_start, m = lt / p.nt, n = lt % p.nt;
         if (kind == TILE_64) direct_tile<T, false, TB, 2, 2, 2, 2, 2, 1>(p, m * 64, n * 64, 0, lds);
+        else if (kind == TILE_64_SHORT) direct_tile<T, false, TB, 2, 2, 2, 4, 1, 1>(p, m * 64, n * 128, 0, lds);
         else if (kind == TILE_32) direct_tile<T, false, TB, 2, 2, 1, W32, K32<T>, 1>(p, m * 32, n * 32 * W32, 0, lds);
         else if (kind == TILE_16_LONG) direct_tile<T, false, TB, 1, 1, 1, 1, 8, 2>(p, m * 16, n * 16, 0, lds);
         else direct_tile<T, false, TB, 1, 1, 1, 2, 4, 2>(p, m * 16, n * 32, 0, lds);
