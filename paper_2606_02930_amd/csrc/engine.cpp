@@ -539,6 +539,13 @@ SplitResult split(ite_ctx* c, int dir, int Dl, int d1, int d2, int Dr, const dou
     return res;
 }
 
+double split_workspace(double m, double n, double k) {
+    const double P = std::max(m, n), N = std::min(m, n);
+    if (P > 1e6) return 10.0 * P * N;      // (the sizes below are ints)
+    return (double)bd_workspace((int)P, (int)N) + (double)dc_workspace((int)N) +
+           (double)bd_vectors_tmp((int)P, (int)N, (int)std::min(k, N)) + 0.5 * N;
+}
+
 SplitResult split_jacobi(ite_ctx* c, int dir, int m, int n, const double* theta, int chi_max, double cutoff,
                          double tie_rel, double* A1, double* A2, std::vector<double>* sigma) {
     const int p = dir == 0 ? m : n, q = dir == 0 ? n : m, ld = p + q;

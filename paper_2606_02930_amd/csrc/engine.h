@@ -183,6 +183,8 @@ struct SplitResult {
 };
 SplitResult split(ite_ctx* c, int dir, int Dl, int d1, int d2, int Dr, const double* theta, int chi_max,
                   double cutoff, double tie_rel, double* A1, double* A2, std::vector<double>* sigma);
+// Doubles a split of an m x n block into k vectors takes in the context's buffers.
+double split_workspace(double m, double n, double k);
 // The same by one-sided Jacobi, for matrices whose small rows carry information
 // below the rounding of the large ones (density matrices).
 SplitResult split_jacobi(ite_ctx* c, int dir, int m, int n, const double* theta, int chi_max, double cutoff,

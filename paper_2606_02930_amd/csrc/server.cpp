@@ -290,15 +290,13 @@ double ite_request_footprint(int L, const int* d, const int* w, int chi_max, int
         nmax = std::max(nmax, n);
         const double I = (double)std::max(w[i], w[i + 2]) * d[i] * d[i + 1];
         xmax = std::max(xmax, (double)D[i] * I * D[i + 2]);
-        const double rows = (double)D[i] * d[i], cols = (double)d[i + 1] * D[i + 2];
-        const double p = std::min(rows, cols);
-        zmax = std::max(zmax, p * (2.0 * std::max(rows, cols) + 7.0 * p));
+        zmax = std::max(zmax, split_workspace((double)D[i] * d[i], (double)d[i + 1] * D[i + 2], D[i + 1]));
     }
-    // psi and its working copy, three environment kinds, Krylov basis and
-    // solve vectors, the two contraction intermediates, the split (the block and
-    // its reflectors, six square vector buffers of the divide and conquer),
-    // low-precision shadows (at most half of FP64)
-    const double doubles = 2.0 * mps + envs + (krylov_dim + 8.0) * nmax + 2.0 * xmax + zmax +
+    // psi and its working copy, three environment kinds; in the context's
+    // buffers, which are taken an eighth larger than asked for: Krylov basis and
+    // solve vectors, the two contraction intermediates, the split; low-precision
+    // shadows (at most half of FP64)
+    const double doubles = 2.0 * mps + envs + 1.125 * ((krylov_dim + 8.0) * nmax + 2.0 * xmax + zmax) +
                            0.5 * (envs + xmax + nmax);
     return 8.0 * doubles + (double)(64 << 20);
 }
