@@ -591,6 +591,12 @@ int ite_debug_svd_split(ite_ctx* ctx, int dir, int Dl, int d1, int d2, int Dr,
                         const double* theta, int chi_max, double cutoff, double tie_rel,
                         double* A1, double* A2, double* sigma_out, int* k_out, double* disc_out);
 
+/* Eigendecomposition of a density matrix rho [n][n] (device; symmetric, positive
+ * semidefinite) as ite_mpo_apply takes it, by one-sided Jacobi: V [k][n] (device)
+ * receives the eigenvectors of the k largest eigenvalues as rows, lambda_out
+ * (host, nullable, capacity n) all eigenvalues in descending order. */
+int ite_debug_density_split(ite_ctx* ctx, int n, const double* rho, int k, double* V, double* lambda_out);
+
 /* One local solve: GMRES on (alpha I + beta H_eff) x = b with x0 as the
  * initial guess (shapes as ite_debug_heff_apply with Dyl = Dxl, Dyr = Dxr).
  * precision, max_refine, tol_refine as in ite_step_opts (mixed precision:

@@ -138,6 +138,7 @@ _SIGNATURES = {
                                  _D, _D, _P, _I, _I, _PD]),
     "ite_debug_env_update": (_I, [_P, _I, _I, _I, _I, _I, _I, _I, _I, _P, _P, _PD, _P, _P]),
     "ite_debug_svd_split": (_I, [_P, _I, _I, _I, _I, _I, _P, _I, _D, _D, _P, _P, _PD, _PI, _PD]),
+    "ite_debug_density_split": (_I, [_P, _I, _P, _I, _P, _PD]),
     "ite_debug_local_solve": (_I, [_P, _I, _I, _I, _I, _I, _I, _I, _P, _PD, _PD, _P, _D, _D, _P, _P,
                                    _I, _I, _D, _I, _I, _D, _P, _PI, _PD]),
     "ite_debug_mfma_probe": (_I, [_P, _I, _PD]),
@@ -607,6 +608,15 @@ def ite_debug_svd_split(ctx: Ctx, direction, theta, chi_max, cutoff, tie_rel, A1
                                               float(cutoff), float(tie_rel), _tp(A1), _tp(A2), _dptr(sig),
                                               C.byref(k), C.byref(disc)), ctx.handle)
     return k.value, sig, disc.value
+
+
+def ite_debug_density_split(ctx: Ctx, rho, k, V):
+    """All eigenvalues (descending); the rows of V [k][n] are the eigenvectors of
+    the k largest."""
+    n = rho.shape[0]
+    lam = np.zeros(n)
+    _check(load_library().ite_debug_density_split(ctx.handle, n, _tp(rho), int(k), _tp(V), _dptr(lam)), ctx.handle)
+    return lam
 
 
 def ite_debug_local_solve(ctx: Ctx, L, W1, W2, R, alpha, beta, b, x0, x, krylov_dim=10, max_cycles=1, tol=0.0,

@@ -781,6 +781,18 @@ int ite_debug_svd_split(ite_ctx* c, int dir, int Dl, int d1, int d2, int Dr, con
     });
 }
 
+int ite_debug_density_split(ite_ctx* c, int n, const double* rho, int k, double* V, double* lambda_out) {
+    if (!c) return ITE_EINVAL;
+    return guarded(c, [&] {
+        set_device(c);
+        ITE_REQUIRE(rho && V, "debug_density_split: NULL pointer");
+        ITE_REQUIRE(n > 0 && k >= 1 && k <= n, "debug_density_split: bad shape");
+        std::vector<double> lam;
+        density_split(c, n, rho, k, V, &lam);
+        if (lambda_out) std::memcpy(lambda_out, lam.data(), lam.size() * sizeof(double));
+    });
+}
+
 int ite_debug_local_solve(ite_ctx* c, int Dl, int Dr, int d1, int d2, int w0, int w1, int w2, const double* L,
                           const double* W1h, const double* W2h, const double* R, double alpha, double beta,
                           const double* b, const double* x0, int krylov_dim, int max_cycles, double tol,

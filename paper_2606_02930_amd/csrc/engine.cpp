@@ -546,45 +546,38 @@ double split_workspace(double m, double n, double k) {
            (double)bd_vectors_tmp((int)P, (int)N, (int)std::min(k, N)) + 0.5 * N;
 }
 
-SplitResult split_jacobi(ite_ctx* c, int dir, int m, int n, const double* theta, int chi_max, double cutoff,
-                         double tie_rel, double* A1, double* A2, std::vector<double>* sigma) {
-    const int p = dir == 0 ? m : n, q = dir == 0 ? n : m, ld = p + q;
-    double* Z = slot_t<double>(c, SL_Z, (size_t)p * ld);
+void density_split(ite_ctx* c, int n, const double* rho, int k, double* V, std::vector<double>* lambda) {
+    const int ld = 2 * n;
+    double* Z = slot_t<double>(c, SL_Z, (size_t)n * ld);
     size_t ngram = 0, nrot = 0, noff = 0;
-    jacobi_workspace(p, q, &ngram, &nrot, &noff);
+    jacobi_workspace(n, n, &ngram, &nrot, &noff);
     double* gram = slot_t<double>(c, SL_GRAM, ngram);
     double* rot = slot_t<double>(c, SL_ROT, nrot);
     double* off = slot_t<double>(c, SL_OFF, noff);
-    double* norms = slot_t<double>(c, SL_NORM, (size_t)p + 16);
-    int* perm = slot_t<int>(c, SL_PERM, (size_t)p + 16);
-    jacobi_input(theta, m, n, dir, Z, c->stream);
-    // Householder preconditioning: the Jacobi then works on the rows of R,
-    // of which only the first min(p, q) can be non-zero
-    int pj = p;
-    if (householder_applies(p, q)) {
-        double* qws = slot_t<double>(c, SL_QR, householder_workspace(p, q, ld));
-        householder_rows(Z, p, q, ld, qws, c->stream);
-        pj = std::min(p, q);
+    double* norms = slot_t<double>(c, SL_NORM, (size_t)n + 16);
+    int* perm = slot_t<int>(c, SL_PERM, (size_t)n + 16);
+    jacobi_input(rho, n, n, Z, c->stream);
+    // Householder preconditioning: the Jacobi then works on the rows of R
+    if (householder_applies(n, n)) {
+        double* qws = slot_t<double>(c, SL_QR, householder_workspace(n, n, ld));
+        householder_rows(Z, n, n, ld, qws, c->stream);
     }
-    double* host = pinned(c, (size_t)p + 64);
-    const double tol = 8.0 * std::sqrt((double)std::max(q, 1)) * 2.220446049250313e-16;
-    jacobi_rows(Z, pj, q, ld, tol, 60, gram, rot, off, host, c->stream);
-    row_norms(Z, p, q, ld, norms, c->stream);
-    d2h(c, host, norms, p);
+    double* host = pinned(c, (size_t)n + 64);
+    const double tol = 8.0 * std::sqrt((double)n) * 2.220446049250313e-16;
+    jacobi_rows(Z, n, n, ld, tol, 60, gram, rot, off, host, c->stream);
+    row_norms(Z, n, n, ld, norms, c->stream);
+    d2h(c, host, norms, n);
     sync(c);
-    std::vector<int> idx(p);
+    std::vector<int> idx(n);
     std::iota(idx.begin(), idx.end(), 0);
     std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return host[a] > host[b]; });
-    std::vector<double> nv(std::min(m, n));
-    for (size_t i = 0; i < nv.size(); ++i) nv[i] = host[idx[i]];
-    const SplitResult res = truncate(nv, cutoff, chi_max, tie_rel, sigma);
+    lambda->resize(n);
+    for (int i = 0; i < n; ++i) (*lambda)[i] = host[idx[i]];
     int* hp = reinterpret_cast<int*>(host);
-    std::memcpy(hp, idx.data(), sizeof(int) * res.k);
-    h2d(c, perm, hp, sizeof(int) * res.k);
-    if (dir == 0) gather_split(Z, ld, perm, res.k, 0, q, A2, q, p, A1, c->stream);
-    else gather_split(Z, ld, perm, res.k, q, p, A2, 0, q, A1, c->stream);
+    std::memcpy(hp, idx.data(), sizeof(int) * k);
+    h2d(c, perm, hp, sizeof(int) * k);
+    gather_rows(Z, ld, perm, k, n, n, V, c->stream);
     sync(c);   // the pinned staging buffer is reused by the next call
-    return res;
 }
 
 // ---------------------------------------------------------------------------

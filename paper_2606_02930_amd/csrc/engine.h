@@ -25,7 +25,7 @@ enum SlotId {
     SL_STATS,                      // per-block device records of the local solves of a step
     SL_BATCH, SL_BDESC, SL_BATCHB, // batched solves: workspaces, descriptors, per-state b and guess
     SL_DMF, SL_DM1, SL_DM2, SL_DM3, SL_DMC,   // density-matrix MPO-MPS product: environments,
-    SL_DMR, SL_DMV, SL_DMU,                   // intermediates, kept part, density matrix and its split
+    SL_DMR, SL_DMV,                           // intermediates, kept part, density matrix and its vectors
     SL_SPLITK,                     // K parts of under-filled FP64 products
     SL_NSLOTS
 };
@@ -185,10 +185,11 @@ SplitResult split(ite_ctx* c, int dir, int Dl, int d1, int d2, int Dr, const dou
                   double cutoff, double tie_rel, double* A1, double* A2, std::vector<double>* sigma);
 // Doubles a split of an m x n block into k vectors takes in the context's buffers.
 double split_workspace(double m, double n, double k);
-// The same by one-sided Jacobi, for matrices whose small rows carry information
-// below the rounding of the large ones (density matrices).
-SplitResult split_jacobi(ite_ctx* c, int dir, int m, int n, const double* theta, int chi_max, double cutoff,
-                         double tie_rel, double* A1, double* A2, std::vector<double>* sigma);
+// Eigenvalues (descending) of a density matrix rho (n x n, symmetric, positive
+// semidefinite) and the eigenvectors of the k largest as rows of V [k][n], by
+// one-sided Jacobi: the small eigenvalues carry information below the rounding of
+// the large ones.
+void density_split(ite_ctx* c, int n, const double* rho, int k, double* V, std::vector<double>* lambda);
 // Truncation rule on sigma sorted descending (host).
 int truncation_rank(const std::vector<double>& s, double cutoff, int chi_max, double tie_rel);
 

@@ -274,22 +274,17 @@ struct LaunchProbe {
 
 // One-sided Jacobi on the rows of Z[p][ld] (the first q columns are the
 // matrix whose rows are orthogonalised; all ld columns are rotated).
-struct JacobiResult { int sweeps = 0; double last_off = 0.0; };
-JacobiResult jacobi_rows(double* Z, int p, int q, int ld, double tol, int max_sweeps,
-                         double* gram_ws, double* rot_ws, double* off_ws, double* host_off,
-                         hipStream_t s);
-// Build the Jacobi work matrix [theta | I_m] (dir 0) or [theta^T | I_n]
-// (dir 1) for theta m x n; leading dimension m + n.
-void jacobi_input(const double* theta, int m, int n, int dir, double* Z, hipStream_t s);
+void jacobi_rows(double* Z, int p, int q, int ld, double tol, int max_sweeps,
+                 double* gram_ws, double* rot_ws, double* off_ws, double* host_off,
+                 hipStream_t s);
+// The Jacobi work matrix [theta^T | I_n] for theta m x n; leading dimension m + n.
+void jacobi_input(const double* theta, int m, int n, double* Z, hipStream_t s);
 // Workspace sizes (doubles) of jacobi_rows for p rows of length q.
 void jacobi_workspace(int p, int q, size_t* gram, size_t* rot, size_t* off);
 // norms[i] = || Z[i][0:q] ||
 void row_norms(const double* Z, int p, int q, int ld, double* norms, hipStream_t s);
-// Gather kept rows: for t < k, r = perm[t]:
-//   rowdst[t][0:nr] = Z[r][roff : roff + nr]
-//   coldst[i][t]    = Z[r][coff + i] for i < nc   (a transposed write, ldc = k)
-void gather_split(const double* Z, int ld, const int* perm, int k, int roff, int nr,
-                  double* rowdst, int coff, int nc, double* coldst, hipStream_t s);
+// dst[t][0:nr] = Z[perm[t]][off : off + nr] for t < k
+void gather_rows(const double* Z, int ld, const int* perm, int k, int off, int nr, double* dst, hipStream_t s);
 
 // Householder QR of the first q columns of Z (p <= 2048 rows, leading dimension
 // ld): Z <- Q^T Z, the rows q..p-1 of the first part zero when p > q; ws holds

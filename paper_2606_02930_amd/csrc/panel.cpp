@@ -241,7 +241,7 @@ void widen_augmented(ite_ctx* c, ite_mps* a, int chi) {
             ITE_REQUIRE(pz <= 2048, "gl panel: bond widening beyond 2048 rows");
             double* Z = slot_t<double>(c, SL_Z, (size_t)pz * ldz);
             double* ws = slot_t<double>(c, SL_QR, householder_workspace(pz, qz, ldz));
-            jacobi_input(w, Dl, pz, 1, Z, c->stream);
+            jacobi_input(w, Dl, pz, Z, c->stream);
             householder_rows(Z, pz, qz, ldz, ws, c->stream);
             HIP_CHECK(hipMemcpy2DAsync(w + (size_t)Dl * ncol, sizeof(double) * ncol, Z + (size_t)Dl * ldz + qz,
                                        sizeof(double) * ldz, sizeof(double) * ncol, (size_t)(Tl - Dl),
@@ -525,12 +525,11 @@ double mpo_apply_dm(ite_mps* psi, const ite_mpo* O, int chi_max, double cutoff, 
         // rho[(s' k'), (s k)] = T[(a' w'), (s' k')]^T G1[(a' w'), (s k)]
         double* rho = slot_t<double>(c, SL_DMR, (size_t)nk * nk);
         gemm(c, true, false, nk, nk, Dj * wj, 1.0, T, nk, G1, nk, 0.0, nullptr, 0, rho, nk);
-        // eigenvectors: rows of V^T from the split of rho (no truncation there)
+        // eigenvectors as rows (no truncation there)
         const int kcap = std::min(chi, caps[j]);
         const int kall = std::min(nk, kcap);
         double* Vt = slot_t<double>(c, SL_DMV, (size_t)kall * nk);
-        double* US = slot_t<double>(c, SL_DMU, (size_t)kall * nk);
-        split_jacobi(c, 1, nk, nk, rho, kall, 0.0, 0.0, US, Vt, &lam);
+        density_split(c, nk, rho, kall, Vt, &lam);
         std::vector<double> sq(lam.size());
         double total = 0.0;
         for (size_t i = 0; i < lam.size(); ++i) {

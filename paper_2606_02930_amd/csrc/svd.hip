@@ -1,10 +1,12 @@
 // One-sided (Hestenes) block-Jacobi SVD for the reduced density matrices of the
 // MPO-MPS product (Appendix B).  Their eigenvalues are squares, so the part of
-// a state with amplitude 1e-9 sits at 1e-18 of the largest: Jacobi rotations
-// keep the small rows of a graded matrix accurate to their own size, where the
-// bidiagonalisation of the bond splits (bidiag.hip) leaves an absolute error of
-// 1e-16 of the largest value (a step at complete bonds: 6e-9 in the energy
-// against the full-vector step instead of below 1e-9).
+// a state with amplitude 1e-9 sits at 1e-18 of the largest.  The rows of such a
+// matrix fall with its eigenvalues, and a rotation changes a small row by rounding
+// of its own size: what limits it is the tolerance at which rows count as
+// orthogonal (off_den), about 1e-17 of the largest value, where the
+// bidiagonalisation of the bond splits (bidiag.hip) leaves 1e-16 (a step at
+// complete bonds: 6e-9 in the energy against the full-vector step instead of
+// below 1e-9).
 //
 // The rows of the first q columns of a work matrix Z[p][ld] are made mutually
 // orthogonal by orthogonal row rotations, and the same rotations are applied
@@ -175,11 +177,11 @@ __device__ inline void atomic_max_pos(double* addr, double v) {
 
 // Orthogonality measure of rows i, j with Gram entries g_ii, g_jj, g_ij:
 //   |g_ij| / (d_i d_j + kappa s1 (d_i + d_j)),   d = sqrt(g), s1 ~ sigma_max.
-// The second term is the rounding floor: rotations with large rows leave an
-// absolute error of order eps s1 in every row, so small rows cannot be made
-// orthogonal relative to their own length (their singular values and
-// vectors are then accurate in absolute terms, as for any backward-stable
-// SVD).
+// The second term is a floor: rows of general matrices carry rounding of order
+// eps s1 from rotations with large rows and would never be orthogonal relative to
+// their own length, so a component of kappa tol s1 along another row is let
+// be.  Singular values below that, and their vectors, are accurate in absolute
+// terms only.
 __device__ inline double off_den(double gi, double gj, double kappa_s1) {
     const double di = sqrt(fmax(gi, 0.0)), dj = sqrt(fmax(gj, 0.0));
     return di * dj + kappa_s1 * (di + dj);
@@ -766,21 +768,18 @@ __global__ __launch_bounds__(Blk<RB>::NTI) void inner_kernel(const double* __res
 // MFMA straight from memory, tiles on and above the diagonal), pair_sweep,
 // and the rotation of the rows over all ld columns; until the rows are
 // orthogonal to the tolerance, the measure stagnates at the rounding floor
-// (as in the multi-pair driver), or max_sweeps.  res[0]: the last measure,
-// res[1]: the number of sweeps.
+// (as in the multi-pair driver), or max_sweeps.
 template <int RB>
 __global__ __launch_bounds__(Blk<RB>::NTI) void single_pair_jacobi_kernel(double* __restrict__ Z, int p, int q,
                                                                           int ld, double tol, double kappa,
-                                                                          int max_sweeps, double* __restrict__ res) {
+                                                                          int max_sweeps) {
     constexpr int PR = Blk<RB>::PR, NT = Blk<RB>::NT, NW = NT / 64;
     constexpr int NTL = PR / 16, NTILE = NTL * (NTL + 1) / 2;
     __shared__ PairLDS<RB> sh;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int l16 = lane & 15, kg = lane >> 4;
     double prev = 1e300, off = 0.0;
-    int sweeps = 0;
     for (int sw = 0; sw < max_sweeps; ++sw) {
-        sweeps = sw + 1;
         if (t < NT) {
             for (int tile = w; tile < NTILE; tile += NW) {
                 int I = 0, J = tile;
@@ -813,10 +812,6 @@ __global__ __launch_bounds__(Blk<RB>::NTI) void single_pair_jacobi_kernel(double
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "agent");
         if (sw >= 3 && off > 0.5 * prev && off < 1e3 * tol) break;
         prev = off;
-    }
-    if (t == 0) {
-        res[0] = off;
-        res[1] = sweeps;
     }
 }
 
@@ -1081,44 +1076,22 @@ __global__ void gather_rows_kernel(const double* __restrict__ Z, int ld, const i
         dst[(long)t * nr + c] = Z[(long)r * ld + roff + c];
 }
 
-// coldst[i][t] = Z[perm[t]][coff + i] through a 32 x 32 tile
-__global__ void gather_cols_kernel(const double* __restrict__ Z, int ld, const int* __restrict__ perm,
-                                   int k, int coff, int nc, double* __restrict__ dst) {
-    __shared__ double tile[32][33];
-    const int i0 = blockIdx.x * 32, t0 = blockIdx.y * 32;
-    for (int yy = threadIdx.y; yy < 32; yy += blockDim.y) {
-        const int t = t0 + yy, i = i0 + threadIdx.x;
-        tile[yy][threadIdx.x] = (t < k && i < nc) ? Z[(long)perm[t] * ld + coff + i] : 0.0;
-    }
-    __syncthreads();
-    for (int yy = threadIdx.y; yy < 32; yy += blockDim.y) {
-        const int i = i0 + yy, t = t0 + threadIdx.x;
-        if (i < nc && t < k) dst[(long)i * k + t] = tile[threadIdx.x][yy];
-    }
-}
-
-// Z[i][c] = X[i][c] for c < q and the identity in columns q..q+p, where X is
-// theta (dir 0, p = m rows) or theta^T (dir 1, p = n rows) for theta m x n.
-__global__ void jacobi_input_kernel(const double* __restrict__ theta, int m, int n, int dir,
-                                    double* __restrict__ Z, int p, int q, int ld) {
-    const long total = (long)p * ld;
+// Z[i][c] = theta[c][i] for c < m and the identity behind, theta m x n.
+__global__ void jacobi_input_kernel(const double* __restrict__ theta, int m, int n, double* __restrict__ Z) {
+    const int ld = m + n;
+    const long total = (long)n * ld;
     for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (long)gridDim.x * blockDim.x) {
         const int i = (int)(e / ld), c = (int)(e % ld);
-        double v;
-        if (c < q) v = dir == 0 ? theta[(long)i * n + c] : theta[(long)c * n + i];
-        else v = (c - q == i) ? 1.0 : 0.0;
-        Z[e] = v;
+        Z[e] = c < m ? theta[(long)c * n + i] : (c - m == i ? 1.0 : 0.0);
     }
 }
 
 }  // namespace
 
-void jacobi_input(const double* theta, int m, int n, int dir, double* Z, hipStream_t s) {
-    const int p = dir == 0 ? m : n, q = dir == 0 ? n : m, ld = p + q;
-    const long total = (long)p * ld;
-    int blocks = (int)std::min<long>(8192, (total + 255) / 256);
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(jacobi_input_kernel, dim3(blocks), dim3(256), 0, s, theta, m, n, dir, Z, p, q, ld);
+void jacobi_input(const double* theta, int m, int n, double* Z, hipStream_t s) {
+    const long total = (long)n * (m + n);
+    const int blocks = (int)std::max<long>(1, std::min<long>(8192, (total + 255) / 256));
+    hipLaunchKernelGGL(jacobi_input_kernel, dim3(blocks), dim3(256), 0, s, theta, m, n, Z);
     HIP_CHECK(hipGetLastError());
 }
 
@@ -1146,10 +1119,9 @@ inline int rotate_width(int npairs, int ncols) {
 }
 
 template <int RB>
-JacobiResult run_jacobi(double* Z, int p, int q, int ld, double tol, int max_sweeps, double* gram_ws,
-                        double* rot_ws, double* off_ws, double* host_off, hipStream_t s) {
-    constexpr int GC = Blk<RB>::GC, NT = Blk<RB>::NT, PR = Blk<RB>::PR, UW = Blk<RB>::UW;
-    JacobiResult res;
+void run_jacobi(double* Z, int p, int q, int ld, double tol, int max_sweeps, double* gram_ws,
+                double* rot_ws, double* off_ws, double* host_off, hipStream_t s) {
+    constexpr int GC = Blk<RB>::GC, PR = Blk<RB>::PR, UW = Blk<RB>::UW;
     int nb = (p + RB - 1) / RB;
     if (nb < 2) nb = 2;
     if (nb & 1) ++nb;
@@ -1213,8 +1185,6 @@ JacobiResult run_jacobi(double* Z, int p, int q, int ld, double tol, int max_swe
         HIP_CHECK(hipStreamSynchronize(s));
         const double soff = host_off[0];
         sigma1sq = host_off[1];
-        res.sweeps = sw + 1;
-        res.last_off = soff;
         if (soff <= tol) break;
         // In the quadratic phase the next sweep would most likely only
         // confirm convergence: check all row pairs at once instead, with the
@@ -1247,10 +1217,7 @@ JacobiResult run_jacobi(double* Z, int p, int q, int ld, double tol, int max_swe
             HIP_CHECK(hipGetLastError());
             HIP_CHECK(hipMemcpyAsync(host_off, chk, sizeof(double), hipMemcpyDeviceToHost, s));
             HIP_CHECK(hipStreamSynchronize(s));
-            if (*host_off <= tol) {
-                res.last_off = *host_off;
-                break;
-            }
+            if (*host_off <= tol) break;
         }
         // stagnation at the rounding floor: stop once the measure no longer drops
         if (sw >= 3 && soff > 0.5 * prev && soff < 1e3 * tol) break;
@@ -1271,7 +1238,6 @@ JacobiResult run_jacobi(double* Z, int p, int q, int ld, double tol, int max_swe
                            nb, rot_ws + (long)cur * npairs * PR * PR, rotated + cur * npairs, q, ld, uw);
         HIP_CHECK(hipGetLastError());
     }
-    return res;
 }
 
 }  // namespace
@@ -1280,27 +1246,22 @@ void jacobi_workspace(int p, int q, size_t* gram, size_t* rot, size_t* off) {
     ws_sizes<32>(p, q, gram, rot, off);
 }
 
-JacobiResult jacobi_rows(double* Z, int p, int q, int ld, double tol, int max_sweeps, double* gram_ws,
-                         double* rot_ws, double* off_ws, double* host_off, hipStream_t s) {
-    if (p <= 1) return JacobiResult{};
+void jacobi_rows(double* Z, int p, int q, int ld, double tol, int max_sweeps, double* gram_ws,
+                 double* rot_ws, double* off_ws, double* host_off, hipStream_t s) {
+    if (p <= 1) return;
     ITE_REQUIRE((long)p * ld < 2147483647L, "svd: work matrix too large for 32-bit element offsets");
     if (p <= Blk<32>::PR) {
-        // one block pair: the whole Jacobi in one launch and one host read
+        // one block pair: the whole Jacobi in one launch
         if (p <= Blk<16>::PR)
             hipLaunchKernelGGL((single_pair_jacobi_kernel<16>), dim3(1), dim3(Blk<16>::NTI), 0, s, Z, p, q, ld, tol,
-                               1e-3, max_sweeps, off_ws);
+                               1e-3, max_sweeps);
         else
             hipLaunchKernelGGL((single_pair_jacobi_kernel<32>), dim3(1), dim3(Blk<32>::NTI), 0, s, Z, p, q, ld, tol,
-                               1e-3, max_sweeps, off_ws);
+                               1e-3, max_sweeps);
         HIP_CHECK(hipGetLastError());
-        HIP_CHECK(hipMemcpyAsync(host_off, off_ws, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-        HIP_CHECK(hipStreamSynchronize(s));
-        JacobiResult res;
-        res.last_off = host_off[0];
-        res.sweeps = (int)host_off[1];
-        return res;
+        return;
     }
-    return run_jacobi<32>(Z, p, q, ld, tol, max_sweeps, gram_ws, rot_ws, off_ws, host_off, s);
+    run_jacobi<32>(Z, p, q, ld, tol, max_sweeps, gram_ws, rot_ws, off_ws, host_off, s);
 }
 
 void row_norms(const double* Z, int p, int q, int ld, double* norms, hipStream_t s) {
@@ -1309,17 +1270,10 @@ void row_norms(const double* Z, int p, int q, int ld, double* norms, hipStream_t
     HIP_CHECK(hipGetLastError());
 }
 
-void gather_split(const double* Z, int ld, const int* perm, int k, int roff, int nr, double* rowdst,
-                  int coff, int nc, double* coldst, hipStream_t s) {
-    if (k <= 0) return;
-    if (nr > 0) {
-        dim3 grid(std::min(64, (nr + 255) / 256), k);
-        hipLaunchKernelGGL(gather_rows_kernel, grid, dim3(256), 0, s, Z, ld, perm, k, roff, nr, rowdst);
-    }
-    if (nc > 0) {
-        dim3 grid((nc + 31) / 32, (k + 31) / 32);
-        hipLaunchKernelGGL(gather_cols_kernel, grid, dim3(32, 8), 0, s, Z, ld, perm, k, coff, nc, coldst);
-    }
+void gather_rows(const double* Z, int ld, const int* perm, int k, int off, int nr, double* dst, hipStream_t s) {
+    if (k <= 0 || nr <= 0) return;
+    hipLaunchKernelGGL(gather_rows_kernel, dim3(std::min(64, (nr + 255) / 256), k), dim3(256), 0, s, Z, ld, perm, k, off,
+                       nr, dst);
     HIP_CHECK(hipGetLastError());
 }
 
