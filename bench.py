@@ -58,7 +58,7 @@ PREC = {"fp64": 0, "fp32": 1, "bf16": 2}
 DTYPE = {"fp64": "f64", "fp32": "f64+f32", "bf16": "f64+bf16"}
 # kernel kinds of the context's launch profile
 KERNELS = {0: ("direct_kernel<double> (FP64 MFMA contraction)", "mfma"),
-           1: ("bidiagonalisation (bd_step_kernel, bd_tail_kernel: Householder reflectors of a split's block)", "hbm"),
+           1: ("bidiagonalisation (bd_step_kernel, bd_step1_kernel, bd_tail_kernel: Householder reflectors of a split's block)", "hbm"),
            2: ("divide and conquer (dc_*_kernel: merges of a split's bidiagonal SVD, FP64 MFMA products)", "mfma"),
            3: ("wy_apply_kernel (reflectors applied to a split's kept singular vectors, FP64 MFMA)", "mfma")}
 

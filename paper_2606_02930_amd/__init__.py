@@ -282,7 +282,12 @@ def ite_ctx_profile_read(ctx: Ctx) -> tuple[int, float, float]:
     return n.value, ms.value, fl.value
 
 
-PROBE_GEMM, PROBE_GRAM, PROBE_INNER, PROBE_ROTATE = 0, 1, 2, 3
+# Kernel kinds of the launch profile: contractions; of the splits the
+# bidiagonalisation, the divide and conquer's merges, and the vectors transformed
+# back.
+PROBE_GEMM, PROBE_BIDIAG, PROBE_MERGE, PROBE_VECTORS = 0, 1, 2, 3
+# the same numbers under the names they had when the splits ran a Jacobi
+PROBE_GRAM, PROBE_INNER, PROBE_ROTATE = PROBE_BIDIAG, PROBE_MERGE, PROBE_VECTORS
 
 
 def ite_ctx_profile_kernel(ctx: Ctx, kind: int) -> dict:

@@ -977,23 +977,9 @@ __global__ __launch_bounds__(NTHREADS, 2) void dc_gemm_kernel(DcWork w, int dept
     const int nt = (cols + BS - 1) / BS, mt = (K + BS - 1) / BS;
     if ((int)blockIdx.x >= mt * nt) return;
     const long at = (long)nd.a * n + nd.a;
-    Params p;
-    p.M = K;
-    p.N = cols;
-    p.K = K;
-    p.alpha = 1.0;
-    p.beta = 0.0;
-    p.A = (side ? w.VT[cur] : w.UT[cur]) + at;
-    p.B = (side ? w.GV : w.GU) + at;
-    p.C = nullptr;
-    p.D = (side ? w.VT[cur ^ 1] : w.UT[cur ^ 1]) + at;
-    p.Df = nullptr;
-    p.lda = p.ldb = p.ldc = p.ldd = n;
-    p.sA = p.sB = p.sC = p.sD = 0;
-    p.mt = mt;
-    p.nt = nt;
     const int tile = blockIdx.x;
-    gemm_tile<double, false, false, BS>(p, (tile / nt) * BS, (tile % nt) * BS, 0, As, Bs);
+    lds_tile<BS>((side ? w.VT[cur] : w.UT[cur]) + at, n, (side ? w.GV : w.GU) + at, n,
+                 (side ? w.VT[cur ^ 1] : w.UT[cur ^ 1]) + at, n, K, cols, K, (tile / nt) * BS, (tile % nt) * BS, As, Bs);
 }
 
 int dc_depth(int n) {

@@ -418,7 +418,7 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const double* __restric
 }
 }  // namespace
 
-// Eight K parts of a workgroup are enough until each is 16 slices of 32 long;
+// Eight K parts of a workgroup are enough until each is 32 slices of 16 long;
 // beyond that more workgroups share K.
 int splitk_parts(int M, int N, int K) {
     const long tiles = (long)((M + 15) / 16) * ((N + 15) / 16);

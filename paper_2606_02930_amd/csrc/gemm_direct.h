@@ -25,7 +25,7 @@ __device__ inline void load_elems(const T* __restrict__ src, T (&v)[N]) {
 
 // One operand of a wavefront's 16 S-wide tile side: the values of a K slice
 // of 16 as v[tile][step], lane group g = lane / 16 supplying K index
-// 4 g + step (the order of gemm_tile).  `load` fetches a slice into registers,
+// 4 g + step.  `load` fetches a slice into registers,
 // `values` turns it into v.
 //
 // KC: K is the contiguous index.  A lane's values are four of one row, so

@@ -1,6 +1,5 @@
-// The MFMA tile of the library's FP64 and FP32 products: operand staging through
-// LDS, the K loop and the epilogue of one BS x BS output tile (gemm.hip says
-// how the tiles are chosen and mapped).
+// What the products share (matrix-core operations, parameters, the order of tiles),
+// and the FP64 tile through LDS of the divide and conquer's merges (dcsvd.hip).
 #pragma once
 
 #include "internal.h"
@@ -55,106 +54,74 @@ __device__ inline int xcd_band_tile(int bid, int T) {
     return base + idx;
 }
 
-// Stage one K slice of an operand into registers (BS = 128 or 64 rows of the
-// tile side, E = BS * 16 / 256 values per thread).  KC: the source is stored
-// with K contiguous (rows of the tile side are strided by ld); otherwise K is
-// the slow index (rows are K, the tile side is contiguous).
-template <typename T, bool KC, int BS>
-__device__ inline void fetch_slice(const T* __restrict__ src, long ld, int side0, int sideN, int k0,
-                                   int K, int t, T (&r)[BS / 16]) {
-    constexpr int E = BS / 16;
-    if (KC) {
-        const int kk = t & 15;
-        const int k = k0 + kk;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int row = side0 + (t >> 4) + 16 * e;
-            r[e] = (row < sideN && k < K) ? src[(long)row * ld + k] : T(0);
-        }
-    } else {
-        const int col = side0 + (t % BS);
-        const int kh = (t / BS) * E;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int k = k0 + kh + e;
-            r[e] = (col < sideN && k < K) ? src[(long)k * ld + col] : T(0);
-        }
-    }
-}
-
-template <typename T, bool KC, int BS>
-__device__ inline void store_slice(T* __restrict__ lds, int t, const T (&r)[BS / 16]) {
-    constexpr int LDK = MfmaOp<T>::LDK, E = BS / 16;
-    if (KC) {
-        const int kk = t & 15;
-#pragma unroll
-        for (int e = 0; e < E; ++e) lds[((t >> 4) + 16 * e) * LDK + kk] = r[e];
-    } else {
-        const int row = t % BS;
-        const int kh = (t / BS) * E;
-#pragma unroll
-        for (int e = 0; e < E; ++e) lds[row * LDK + kh + e] = r[e];
-    }
-}
-
-// One BS x BS output tile at (m0, n0) of problem p (batch index bz): four
-// wavefronts in a 2 x 2 arrangement, each owning (BS / 2)^2 outputs as
-// (BS / 32)^2 MFMA tiles of 16 x 16.  The K order of every output element
-// (slices of 16, four sub-steps, lane group g supplying K index 4 g + step)
-// does not depend on BS, so the 128 and 64 tiles give the same bits.  As, Bs:
-// LDS of two slices of each operand.  Ends with a barrier after the last LDS
-// read, so the caller may start another tile.
-template <typename T, bool TA, bool TB, int BS>
-__device__ __forceinline__ void gemm_tile(const Params& p, int m0, int n0, long bz, T* As, T* Bs) {
-    typedef typename MfmaOp<T>::acc_t acc_t;
-    constexpr int LDK = MfmaOp<T>::LDK, IT = BS / 32, E = BS / 16;
-    const T* __restrict__ A = static_cast<const T*>(p.A) + bz * p.sA;
-    const T* __restrict__ B = static_cast<const T*>(p.B) + bz * p.sB;
-
+// D = A B for one BS x BS output tile at (m0, n0) (A M x K, B K x N, row-major; BS
+// 128, 64 or 32): a K slice of 16 of each operand through LDS (As, Bs: two
+// slices), four wavefronts in a 2 x 2 arrangement, each owning (BS / 2)^2 outputs
+// as (BS / 32)^2 MFMA tiles of 16 x 16.  The K order of every output element
+// (slices of 16, four sub-steps, lane group g supplying K index 4 g + step) does
+// not depend on BS.  Ends with a barrier after the last LDS read.
+template <int BS>
+__device__ __forceinline__ void lds_tile(const double* __restrict__ A, long lda, const double* __restrict__ B, long ldb,
+                                         double* __restrict__ D, long ldd, int M, int N, int K, int m0, int n0, double* As,
+                                         double* Bs) {
+    constexpr int LDK = MfmaOp<double>::LDK, IT = BS / 32, E = BS / 16;
     const int t = threadIdx.x;
     const int lane = t & 63;
     const int wave = t >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int l16 = lane & 15, kg = lane >> 4;
 
-    acc_t acc[IT][IT];
+    d4_t acc[IT][IT];
 #pragma unroll
     for (int i = 0; i < IT; ++i)
 #pragma unroll
-        for (int j = 0; j < IT; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
+        for (int j = 0; j < IT; ++j) acc[i][j] = d4_t{0, 0, 0, 0};
 
-    // A: K-contiguous unless transposed.  B: K-contiguous only when transposed.
-    T ra[E], rb[E];
-    const int nk = (p.K + BK - 1) / BK;
-    fetch_slice<T, !TA, BS>(A, p.lda, m0, p.M, 0, p.K, t, ra);
-    fetch_slice<T, TB, BS>(B, p.ldb, n0, p.N, 0, p.K, t, rb);
-    store_slice<T, !TA, BS>(As, t, ra);
-    store_slice<T, TB, BS>(Bs, t, rb);
+    // a thread's share of a slice: one K index of E rows of A, E K indices of
+    // one column of B
+    double ra[E], rb[E];
+    const int ak = t & 15, arow = t >> 4, bcol = t % BS, bk = (t / BS) * E;
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int row = m0 + arow + 16 * e;
+            ra[e] = (row < M && k0 + ak < K) ? A[(long)row * lda + k0 + ak] : 0.0;
+            const int k = k0 + bk + e;
+            rb[e] = (n0 + bcol < N && k < K) ? B[(long)k * ldb + n0 + bcol] : 0.0;
+        }
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            As[(buf * BS + arow + 16 * e) * LDK + ak] = ra[e];
+            Bs[(buf * BS + bcol) * LDK + bk + e] = rb[e];
+        }
+    };
+    const int nk = (K + BK - 1) / BK;
+    fetch(0);
+    store(0);
     __syncthreads();
 
     for (int kt = 0; kt < nk; ++kt) {
         const int cur = kt & 1;
         const bool more = kt + 1 < nk;
-        const T* Ac = As + cur * BS * LDK;
-        const T* Bc = Bs + cur * BS * LDK;
-        if (more) {
-            fetch_slice<T, !TA, BS>(A, p.lda, m0, p.M, (kt + 1) * BK, p.K, t, ra);
-            fetch_slice<T, TB, BS>(B, p.ldb, n0, p.N, (kt + 1) * BK, p.K, t, rb);
-        }
+        const double* Ac = As + cur * BS * LDK;
+        const double* Bc = Bs + cur * BS * LDK;
+        if (more) fetch((kt + 1) * BK);
         // two sub-steps of the slice at a time: 16 operand values live
         // instead of 32, which leaves room for two workgroups per CU
 #pragma unroll
         for (int s2 = 0; s2 < 4; s2 += 2) {
-            T a[IT][2], b[IT][2];
+            double a[IT][2], b[IT][2];
 #pragma unroll
             for (int i = 0; i < IT; ++i) {
-                const T* src = &Ac[(wm * (BS / 2) + i * 16 + l16) * LDK + 4 * kg + s2];
+                const double* src = &Ac[(wm * (BS / 2) + i * 16 + l16) * LDK + 4 * kg + s2];
                 a[i][0] = src[0];
                 a[i][1] = src[1];
             }
 #pragma unroll
             for (int j = 0; j < IT; ++j) {
-                const T* src = &Bc[(wn * (BS / 2) + j * 16 + l16) * LDK + 4 * kg + s2];
+                const double* src = &Bc[(wn * (BS / 2) + j * 16 + l16) * LDK + 4 * kg + s2];
                 b[j][0] = src[0];
                 b[j][1] = src[1];
             }
@@ -163,20 +130,13 @@ __device__ __forceinline__ void gemm_tile(const Params& p, int m0, int n0, long 
 #pragma unroll
                 for (int i = 0; i < IT; ++i)
 #pragma unroll
-                    for (int j = 0; j < IT; ++j) acc[i][j] = MfmaOp<T>::mma(a[i][s], b[j][s], acc[i][j]);
+                    for (int j = 0; j < IT; ++j) acc[i][j] = MfmaOp<double>::mma(a[i][s], b[j][s], acc[i][j]);
         }
-        if (more) {
-            store_slice<T, !TA, BS>(As + (cur ^ 1) * BS * LDK, t, ra);
-            store_slice<T, TB, BS>(Bs + (cur ^ 1) * BS * LDK, t, rb);
-        }
+        if (more) store(cur ^ 1);
         __syncthreads();
     }
 
-    // Epilogue.  Accumulator element r of lane l holds column l % 16 of its
-    // 16 x 16 tile and row 4 r + l / 16 (FP64 MFMA) or 4 (l / 16) + r (FP32).
-    const double* __restrict__ C = p.C ? p.C + bz * p.sC : nullptr;
-    double* __restrict__ D = p.Df ? nullptr : p.D + bz * p.sD;
-    float* __restrict__ Df = p.Df ? p.Df + bz * p.sD : nullptr;
+    // accumulator element r of lane l holds column l % 16 and row 4 r + l / 16
 #pragma unroll
     for (int i = 0; i < IT; ++i)
 #pragma unroll
@@ -184,16 +144,8 @@ __device__ __forceinline__ void gemm_tile(const Params& p, int m0, int n0, long 
             const int col = n0 + wn * (BS / 2) + j * 16 + l16;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int row = m0 + wm * (BS / 2) + i * 16 + MfmaOp<T>::row(kg, r);
-                if (row < p.M && col < p.N) {
-                    double v = p.alpha * (double)acc[i][j][r];
-                    if (Df) {
-                        Df[(long)row * p.ldd + col] = (float)v;
-                    } else {
-                        if (C) v += p.beta * C[(long)row * p.ldc + col];
-                        D[(long)row * p.ldd + col] = v;
-                    }
-                }
+                const int row = m0 + wm * (BS / 2) + i * 16 + MfmaOp<double>::row(kg, r);
+                if (row < M && col < N) D[(long)row * ldd + col] = acc[i][j][r];
             }
         }
 }
