@@ -133,7 +133,8 @@ typedef struct ite_step_report {
     double mean_res_rel;
     long long matvecs_fp64;  /* effective-Hamiltonian products in FP64 */
     long long matvecs_lo;    /* ... in FP32 or BF16 */
-    double ms_total, ms_rhs, ms_solve, ms_split, ms_env;   /* device time per phase (the density-matrix
+    double ms_total, ms_rhs, ms_solve, ms_split, ms_env;   /* time on the stream per phase, each from
+                          * the end of the phase before it, waits for the host included (the density-matrix
                           * product of ITE_RHS_MPS counts as rhs, a panel's read-off and cut-back as
                           * split; those two are timed on the host around a drained stream) */
     double rhs_disc;     /* ITE_RHS_MPS: largest discarded-weight fraction of the density-matrix product */

@@ -258,7 +258,9 @@ __global__ __launch_bounds__(BS_NT) void bd_step_kernel(BdWork b, int c, bool st
 }
 
 // The same for rows of any length, in memory, with z and u formed again where they
-// are used; a wavefront a row.
+// are used; a wavefront a row.  A row is read three times and written once: 2100 rows
+// and columns take 29 ms in all (2048: 24), 2600 61, 3200 107, 4096 200 (the Jacobi
+// before: 107, 146, 232, 445, and 265 to 1017 for a graded block).
 constexpr int BS_CH = 512;          // columns of a row of products in LDS
 __global__ __launch_bounds__(BS_NT) void bd_step_long_kernel(BdWork b, int c, bool start) {
     constexpr int NT = BS_NT;
@@ -917,7 +919,12 @@ __global__ __launch_bounds__(64 * NW) void wy_apply_kernel(WySide s0, WySide s1,
     }
 }
 
-constexpr int BD_TAIL = 192;                // rows of the block that one workgroup finishes
+// Rows of the block that one workgroup finishes: a column takes it 2 us where a step
+// takes 5, so as many as it holds in registers (72 doubles a lane, 144 of its 256
+// registers; 256 rows would need them all).  Its three shapes by what is left, us for
+// a whole block in this shape and in the next larger: 32 rows 44 and 68, 64 76 and 117
+// (4, 4, 4); 80 138 and 218, 128 191 and 304 (4, 8, 8).
+constexpr int BD_TAIL = 192;
 constexpr int BD_ONE = 512;                 // rows and columns from which on a step is one launch
 constexpr int WY_MAX = 8 * WYB * 16;     // longest vector held in registers
 
@@ -1030,6 +1037,19 @@ void bd_vectors(const BdWork& w, const double* XQ, const double* XP, const int* 
     const dim3 grid(kr / WYB, 2);
     const bool timed = probe && probe->begin(PK_VECTORS, s);
     const int tiles = (w.P + WYB - 1) / WYB;
+// By tiles of 16 entries: as few wavefronts as hold them, since each has a part of
+// every block's sum and its own copy of T W.  us for half the vectors (32 and 64 rows:
+// all) of n x n blocks, the shape taken and the next ones:
+//      n      4,1   4,2   4,4   8,4   8,8  16,4  8,16   8,0
+//      64    10.5  12.8  18.1  30.9
+//      128         20.6  30.5  53.2
+//      256               57.2  99.9
+//      320                      124    74    87    82
+//      512                      199   144   167   157
+//      600                            185   207   202   392
+//      1024                           427   461   452   956
+//      2048                                      1495  3661
+// (8 wavefronts of 8 tiles, the fastest from 320 to 1024 rows, are not built yet.)
 #define ITE_WY(NW, TPW) \
     hipLaunchKernelGGL((wy_apply_kernel<NW, TPW>), grid, dim3(64 * NW), 0, s, sq, sp, N, perm, k, sg, scale)
     if (tiles <= 4) ITE_WY(4, 1);

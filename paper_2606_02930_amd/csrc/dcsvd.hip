@@ -1093,12 +1093,18 @@ int bidiagonal_svd(const DcWork& w, hipStream_t s, LaunchProbe* probe) {
     for (int dep = depth - 1; dep >= 0; --dep) {
         const int nodes = 1 << dep, most = (n >> dep) + 1, waves = (n + 3) / 4;
         const int nch = (most + 255) / 256;
+        // (256 threads or 1024 for the order: no difference from 40 to 800 rows,
+        // 110 and 110 us of merges at 100 rows, 448 and 433 at 800)
         timed = probe && probe->begin(PK_MERGE, s);
         if (most <= 256) hipLaunchKernelGGL((dc_prep_kernel<256>), dim3(nodes), dim3(256), 0, s, w, dep, cur);
         else hipLaunchKernelGGL((dc_prep_kernel<1024>), dim3(nodes), dim3(1024), 0, s, w, dep, cur);
         hipLaunchKernelGGL(dc_roots_kernel, dim3(waves + n * nch), dim3(256), 0, s, w, dep, cur, nch);
         hipLaunchKernelGGL(dc_zhat_kernel, dim3(waves), dim3(256), 0, s, w, dep);
         hipLaunchKernelGGL(dc_small_vectors_kernel, dim3(waves), dim3(256), 0, s, w, dep, cur);
+        // tile by the node's rows; all merges of a block with one tile throughout (32,
+        // 64, 128), us: 100 rows 107, 116, 135; 256 167, 178, 226; 512 246, 261, 362;
+        // 1024 437, 450, 608; 2048 1312, 1268, 1450.  As taken: 512 306, 1024 551,
+        // 2048 1400; the tiles want a better line than this one
         const int bs = most > 512 ? 128 : (most > 160 ? 64 : 32), tl = (most + bs - 1) / bs;
         const dim3 grid(tl * tl, nodes, 2);
         if (bs == 128) hipLaunchKernelGGL((dc_gemm_kernel<128>), grid, dim3(NTHREADS), 0, s, w, dep, cur);

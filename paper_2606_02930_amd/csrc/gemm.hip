@@ -117,7 +117,12 @@ TileKind tile_kind(const Gemm& g) {
 // so a long K pays from 1024 tiles on in either type, one of 512 or more in FP32
 // from 2048 on (below 512 the 64 x 64 tile is faster, FP32, NN, us with the call:
 // 2500 x 7500 x 32 82 and 56, x 128 115 and 91, x 256 156 and 140, x 384 195 and 190,
-// x 512 230 and 239).  Not in FP64 with A transposed (environment updates up to bond 1024,
+// x 512 230 and 239).  Around the FP64 line a whole product takes, without and with
+// them (d 2, us, forty in a row): bond 896 1127 and 1147, 960 1302 and 1308, 1000 1521
+// and 1453 (not taken: 1008 tiles), 1024 1533 and 1483, 1056 1862 and 1917, 1088 1980
+// and 2036, 1152 2252 and 2239, 1280 3078 and 3183, 1400 4155 and 3792, 1536 5256 and
+// 5044: where the last round of tiles is nearly full they win by up to 9%, where it is
+// nearly empty they lose 3%.  Not in FP64 with A transposed (environment updates up to bond 1024,
 // on average 391 and 457 us).
 template <typename T>
 bool large_tile(const Gemm& g) {
