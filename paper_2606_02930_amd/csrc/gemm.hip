@@ -61,8 +61,9 @@ void launch_tiles(const Gemm& g, Params p, hipStream_t s) {
 // of its tiles on.  A few tiles more than 512 are a second round that leaves most
 // of the chip idle, which costs more the longer K is (H_eff, us, its second product in
 // 32 and 64: 576 tiles, K 3840 730 and 858; 676, K 4160 927 and 993; 756, K 4320 1029 and
-// 1068; 784, K 4480 1148 and 1156; 900, K 4800 1412 and 1367): with a long K 64 from
-// 800 on.  With 16, four K parts are as fast as eight while K is
+// 1068; 784, K 4480 1148 and 1156; 900, K 4800 1412 and 1367): with a long K 64 at
+// 512, where the one round is full, and from 800 on (NN, us with the call: 496 tiles, K
+// 2048 170 and 149; 512 212 and 149, K 1024 100 and 84; 528, K 2048 188 and 211).  With 16, four K parts are as fast as eight while K is
 // short (160 x 128 x 32: 2.9 and 3.4) and slower when it is long (64 x 64 x
 // 4000: 18.1 and 13.4); they meet near 500.
 //
@@ -96,7 +97,8 @@ template <typename T>
 TileKind tile_kind(const Gemm& g) {
     auto tiles = [&](int side) { return (long)((g.M + side - 1) / side) * ((g.N + side - 1) / side) * g.batch; };
     const bool wide = (!g.tA || g.M >= 32) && (g.tB || g.N >= 32);
-    if (wide && tiles(64) >= (!std::is_same<T, double>::value ? 1024 : g.K >= 1024 ? 800 : 512))
+    const long t64 = tiles(64);
+    if (wide && t64 >= (!std::is_same<T, double>::value ? 1024 : g.K >= 1024 && t64 > 512 ? 800 : 512))
         return g.K <= K_SHORT ? TILE_64_SHORT : TILE_64;
     if (wide && tiles(32) >= 192) return TILE_32;
     return g.K >= 512 ? TILE_16_LONG : TILE_16;

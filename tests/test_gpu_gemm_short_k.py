@@ -25,6 +25,13 @@ def test_short_products(env, shape, tA, tB):  # noqa: F811
     _run(env, shape, tA, tB, 1, 6e-6)
 
 
+# one full round of 64 x 64 tiles and a few tiles more, with a long K
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("shape", [(1024, 2048, 1024), (1000, 2040, 1503), (500, 4070, 1031), (1025, 2048, 1031)])
+def test_one_round_of_long_products(env, shape, tA, tB):  # noqa: F811
+    _run(env, shape, tA, tB, 0, 1e-13)
+
+
 @pytest.mark.parametrize("precision", [ite.PREC_FP64, ite.PREC_FP32_IR])
 def test_short_first_contraction_in_a_batch(env, precision):  # noqa: F811
     # d = 4: the block between bonds of 64 and 600 is 384 x 9600 with K = 64
