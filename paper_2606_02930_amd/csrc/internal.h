@@ -126,9 +126,6 @@ struct HostPost {
 int  reduce_blocks(size_t n);
 // partial[b] = sum over block b of x.y
 void dot_partials(const double* x, const double* y, size_t n, double* partial, hipStream_t s);
-// partial[j*nb + b] = block b of V_j . w for j < k (V_j = V + j*ldv)
-void mdot_partials(const double* V, long ldv, int k, const double* w, size_t n, double* partial,
-                   hipStream_t s);
 // out[j] (+)= sum_b partial[j*nb + b]; mode 0: store, 1: add, 2: store sqrt
 // (post: out[0] for the host, k = 1)
 void finish_partials(const double* partial, int k, int nb, double* out, int mode, hipStream_t s, HostPost post = {});

@@ -48,29 +48,6 @@ __global__ __launch_bounds__(RT) void dot_partials_kernel(const double* __restri
     dot_block(x, y, n, blockIdx.x, gridDim.x, partial + blockIdx.x, sh);
 }
 
-// partial[j*nb + b]: block b's share of V_j . w for j < k (k <= 16).
-__global__ __launch_bounds__(RT) void mdot_partials_kernel(const double* __restrict__ V, long ldv, int k,
-                                                           const double* __restrict__ w, size_t n,
-                                                           double* __restrict__ partial) {
-    __shared__ double sh[RT / 64];
-    double acc[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) acc[j] = 0.0;
-    const size_t stride = (size_t)gridDim.x * RT;
-    for (size_t i = (size_t)blockIdx.x * RT + threadIdx.x; i < n; i += stride) {
-        const double wi = w[i];
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-            if (j < k) acc[j] += V[(size_t)j * ldv + i] * wi;
-    }
-#pragma unroll
-    for (int j = 0; j < 16; ++j)
-        if (j < k) {
-            const double s = block_sum(acc[j], sh);
-            if (threadIdx.x == 0) partial[(size_t)j * gridDim.x + blockIdx.x] = s;
-        }
-}
-
 // *out (mode 0: =, 1: +=, 2: = sqrt) of the sum of nb partials.
 __device__ inline void finish_one(const double* __restrict__ partial, int nb, double* __restrict__ out, int mode,
                                   double* sh) {
@@ -360,17 +337,6 @@ int reduce_blocks(size_t n) {
 
 void dot_partials(const double* x, const double* y, size_t n, double* partial, hipStream_t s) {
     hipLaunchKernelGGL(dot_partials_kernel, dim3(reduce_blocks(n)), dim3(RT), 0, s, x, y, n, partial);
-    HIP_CHECK(hipGetLastError());
-}
-
-void mdot_partials(const double* V, long ldv, int k, const double* w, size_t n, double* partial,
-                   hipStream_t s) {
-    const int nb = reduce_blocks(n);
-    for (int j0 = 0; j0 < k; j0 += 16) {
-        const int kk = k - j0 < 16 ? k - j0 : 16;
-        hipLaunchKernelGGL(mdot_partials_kernel, dim3(nb), dim3(RT), 0, s, V + (size_t)j0 * ldv, ldv, kk, w, n,
-                           partial + (size_t)j0 * nb);
-    }
     HIP_CHECK(hipGetLastError());
 }
 
